@@ -180,6 +180,8 @@ struct ClaimScope {
 // Rows per M tile of the ragged-M schedule for this dtype (the tile map must be built with it).
 int gemm_ragged_tile_rows(int dtype, int tall_tile);
 int launch_gemm(const GemmDesc& g, hipStream_t s);
+int launch_gemm_f32(const GemmDesc& g, hipStream_t s);   // what launch_gemm does with fp32 operands
+int gemm_f32_tile_rows();
 // tile_map capacity in int32 for a ragged-M problem: header, the group order of the ragged-K
 // schedule (one int per group), then a (group, first row) pair per M tile
 inline size_t tile_map_ints(int total_rows, int groups, int tile_rows) {

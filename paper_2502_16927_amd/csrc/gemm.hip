@@ -9,7 +9,7 @@
 // its side (128 x 256) where only A is k-contiguous; 256 x 256 (eight wavefronts, one workgroup per
 // CU, 64-deep k tiles) for the per-expert row products with a long K; 128 x 64 and 128 x 128 with
 // 64-deep k tiles for products with few tiles.
-// fp32 storage: a plain tiled FMA kernel (only the tiny fp32 workload uses it).
+// fp32 storage: see gemm_f32.hip.
 #include "gemm_core.hpp"
 
 namespace bigmac {
@@ -560,70 +560,6 @@ void mfma_gemm_kernel(GemmDesc p) {
   }
 }
 
-// ------------------------------------------------------------------------ fp32 kernel ------
-
-template <bool AK, bool BKC, int EPI>
-__global__ __launch_bounds__(256) void fma_gemm_kernel(GemmDesc p) {
-  constexpr int BM = 64, BN = 64, BK = 16;
-  __shared__ float sa[BK][BM + 1];
-  __shared__ float sb[BK][BN + 1];
-  const TileSpace ts = tile_space<BM, BN>(p);
-  const int id = tile_at(ts, (int)(blockIdx.x >> 3));
-  if (id < 0) return;
-  TileCoord t = resolve_tile<BM, BN>(p, ts, id, 4);
-  const float* A = (const float*)p.A;
-  const float* B = (const float*)t.B;
-  const int tid = threadIdx.x, ty = tid / 16, tx = tid % 16;
-  float acc[4][4] = {};
-  for (int kt = t.kbeg; kt < t.kend; kt += BK) {
-    const int kb = p.kwrap_b ? kt % p.kwrap_b : kt;
-    for (int e = tid; e < BM * BK; e += 256) {
-      int m = AK ? e / BK : e % BM, kk = AK ? e % BK : e / BM;
-      int gm = t.m0 + m, gk = kt + kk;
-      float v = 0.0f;
-      if (gm < t.m_end && gk < t.kend) v = AK ? A[(size_t)gm * p.lda + gk] : A[(size_t)gk * p.lda + gm];
-      sa[kk][m] = v;
-    }
-    for (int e = tid; e < BN * BK; e += 256) {
-      int n = BKC ? e / BK : e % BN, kk = BKC ? e % BK : e / BN;
-      int gn = t.n0 + n, gk = kt + kk;
-      float v = 0.0f;
-      if (gn < p.N && gk < t.kend) v = BKC ? B[(size_t)gn * p.ldb + kb + kk] : B[(size_t)(kb + kk) * p.ldb + gn];
-      sb[kk][n] = v;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < BK; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = sa[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = sb[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = t.m0 + ty * 4 + i, col = t.n0 + tx * 4 + j;
-      if (row >= t.m_end || col >= p.N) continue;
-      const size_t off = (size_t)row * p.ldc + col;
-      const float a = acc[i][j] + ((EPI == EPI_STORE || EPI == EPI_GELU) && t.bias ? ((const float*)t.bias)[col] : 0.0f);
-      float* c = (float*)t.C + off;
-      if (EPI == EPI_STORE) *c = a;
-      else if (EPI == EPI_GELU) {
-        if (p.aux_out) ((float*)p.aux_out)[off] = a;
-        *c = gelu_f(a);
-      } else if (EPI == EPI_DGELU) *c = a * gelu_grad_f(((const float*)p.aux_in)[off]);
-      else *c = p.beta ? *c + a : a;
-    }
-}
-
 // ------------------------------------------------------------------------ helpers ----------
 
 __global__ __launch_bounds__(1024) void build_tile_map_kernel(const int* __restrict__ offsets, int groups, int tile_rows, int* __restrict__ tile_map) {
@@ -668,7 +604,7 @@ __global__ void reduce_partials_multi_kernel(ReduceJobs jobs, int beta) {
   reduce_slices(j.part, j.nslices, j.n, j.out, beta, ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * 4);
 }
 
-int gemm_ragged_tile_rows(int dtype, int tall_tile) { return dtype == BIGMAC_BF16 ? (tall_tile ? BIGMAC_TALL_BM : BIGMAC_TILE_BM) : 64; }
+int gemm_ragged_tile_rows(int dtype, int tall_tile) { return dtype == BIGMAC_BF16 ? (tall_tile ? BIGMAC_TALL_BM : BIGMAC_TILE_BM) : gemm_f32_tile_rows(); }
 
 int launch_build_tile_map(const int* offsets, int groups, int tile_rows, int* tile_map, hipStream_t s) {
   if (groups > 1024) return BIGMAC_ERR_UNSUPPORTED;
@@ -888,20 +824,6 @@ int launch_mfma_deep(const GemmDesc& g, hipStream_t s) {
   return BIGMAC_OK;
 }
 
-template <bool AK, bool BKC>
-int launch_fma(const GemmDesc& g, hipStream_t s) {
-  dim3 grid = grid_for<64, 64>(g, false), block(256);
-  switch (g.epilogue) {
-    case EPI_STORE: hipLaunchKernelGGL((fma_gemm_kernel<AK, BKC, EPI_STORE>), grid, block, 0, s, g); break;
-    case EPI_GELU: hipLaunchKernelGGL((fma_gemm_kernel<AK, BKC, EPI_GELU>), grid, block, 0, s, g); break;
-    case EPI_DGELU: hipLaunchKernelGGL((fma_gemm_kernel<AK, BKC, EPI_DGELU>), grid, block, 0, s, g); break;
-    case EPI_ACCUM: hipLaunchKernelGGL((fma_gemm_kernel<AK, BKC, EPI_ACCUM>), grid, block, 0, s, g); break;
-    default: return BIGMAC_ERR_INVALID_ARG;
-  }
-  BIGMAC_CHECK_LAUNCH();
-  return BIGMAC_OK;
-}
-
 }  // namespace
 
 // Matrix-core rate probe: every wavefront issues 32x32x16 bf16 MFMAs back to back on four
@@ -1052,12 +974,7 @@ int launch_gemm(const GemmDesc& desc, hipStream_t s) {
       default: return BIGMAC_ERR_UNSUPPORTED;
     }
   }
-  switch (combo) {
-    case 2: return launch_fma<true, false>(g, s);
-    case 3: return launch_fma<true, true>(g, s);
-    case 0: return launch_fma<false, false>(g, s);
-    default: return BIGMAC_ERR_UNSUPPORTED;
-  }
+  return launch_gemm_f32(g, s);
 }
 
 }  // namespace bigmac
