@@ -167,15 +167,15 @@ struct GemmDesc {
   size_t touch_bytes;        //   so that its first use in a k loop meets the caches and not the memory (0 = off)
 };
 // Tile counters for the MFMA kernels' dynamic tile order: one slot per launch, one counter per XCD
-// (64 bytes apart).  An entry point opens a scope over a piece of its workspace; the scope clears
-// the piece with a fill kernel on the stream, and every launch_gemm of this thread inside the scope
-// takes the next slot (launches beyond the last slot run in the static order).
-constexpr int CLAIM_SLOTS = 48, CLAIM_SLOT_INTS = 8 * 16;
-constexpr size_t CLAIM_BYTES = (size_t)CLAIM_SLOTS * CLAIM_SLOT_INTS * 4;
+// (64 bytes apart).  An entry point opens a scope over a piece of its workspace, and every launch_gemm of
+// this thread inside the scope takes the next slot (launches beyond the last slot run in the static
+// order).  The piece is zeroed on the stream by a kernel that runs in front of the first such
+// product anyway (the sort, the combine's backward, the tile map): a fill kernel of its own was 2 to 5 us per call.
+constexpr int CLAIM_SLOTS = 4, CLAIM_SLOT_INTS = 8 * 16, CLAIM_INTS = CLAIM_SLOTS * CLAIM_SLOT_INTS;
+constexpr size_t CLAIM_BYTES = (size_t)CLAIM_INTS * 4;
 struct ClaimScope {
-  ClaimScope(void* region, hipStream_t s);
+  explicit ClaimScope(void* region);
   ~ClaimScope();
-  int status;   // BIGMAC_OK, or the fill kernel's launch error
 };
 // Rows per M tile of the ragged-M schedule for this dtype (the tile map must be built with it).
 int gemm_ragged_tile_rows(int dtype, int tall_tile);
@@ -188,7 +188,8 @@ inline size_t tile_map_ints(int total_rows, int groups, int tile_rows) {
   return 16 + (size_t)groups + 2 * ((size_t)total_rows / tile_rows + groups + 1);
 }
 double launch_mfma_probe(int blocks, int iters, float* sink, hipStream_t s);   // returns the flops issued, < 0 on a launch error
-int launch_build_tile_map(const int* offsets, int groups, int tile_rows, int* tile_map, hipStream_t s);
+struct TileMapJobs;
+int launch_build_tile_map(const int* offsets, int groups, const TileMapJobs& maps, hipStream_t s);
 // out[i] = (beta ? out[i] : 0) + sum_z part[z*n + i]
 int launch_reduce_partials(const float* part, int nslices, size_t n, float* out, int beta, hipStream_t s);
 // the same for up to 3 independent reductions in one launch
@@ -205,7 +206,8 @@ int launch_reduce_partials_bf16(const float* part, int nslices, size_t n, void* 
 // ----------------------------------------------------------------------------- route ----
 int launch_router_logits(const bigmac_dims& D, const void* x, const float* w_gate, const float* bias,
                          float* logits, hipStream_t s);
-int launch_topk_gate(const bigmac_dims& D, const float* logits, int32_t* topk_idx, float* topk_w, hipStream_t s);
+// counts (optional): the pairs per part of a chunk and expert, for launch_build_permutation (D.T, D.k, D.N must have sort_chunks)
+int launch_topk_gate(const bigmac_dims& D, const float* logits, int32_t* topk_idx, float* topk_w, hipStream_t s, int32_t* counts = nullptr);
 // Gate backward (softmax over the k picked logits) and the router's share of dx:
 //   dlogit[t,j] = w[t,j] (dgate[t,j] - sum_m w[t,m] dgate[t,m])
 //   dL_out [T,N] (storage dtype) = dlogit scattered to its expert columns, zeros elsewhere
@@ -215,22 +217,39 @@ size_t route_backward_ws_bytes(const bigmac_dims& D);
 // With logits and share (the load-balance loss is on) the loss's gradient
 //   D.aux_alpha N / T * p[t,n] (share[n] - sum_e share[e] p[t,e]),  p = softmax(logits[t,:]),
 // is added to every entry of dL_out and takes part in dx_f32.
+// gate_done: dL_out and ws hold the gate's part already, from a combine backward that was given gate_backward_job's job.
 int launch_route_backward(const bigmac_dims& D, const float* w_gate, const int32_t* topk_idx,
                           const float* topk_w, const float* dgate, const float* logits, const float* share,
-                          float* dx_f32, void* dL_out, void* ws, hipStream_t s);
+                          float* dx_f32, void* dL_out, void* ws, hipStream_t s, bool gate_done = false);
+// The gate's backward as a job for the combine's backward, whose wavefront has a token's gate gradients
+// in registers (bf16, up to 128 experts); false: launch_route_backward does it.
+struct GateBackward {
+  const int32_t* topk_idx;
+  const float* logits;      // with the load-balance loss: logits and pair shares, else NULL
+  const float* share;
+  float aux_scale;
+  int N;
+  bf16_t* dL;
+  float* dl_picked;         // optional
+};
+bool gate_backward_job(const bigmac_dims& D, const int32_t* topk_idx, const float* logits, const float* share, void* dL_out, void* ws, GateBackward* out);
 // Load-balance loss  D.aux_alpha N sum_e f_e P_e:  f_e = share of the T k pairs routed to e (before
 // any capacity drop), P_e = mean over tokens of softmax(logits)[e].  share [N] and loss [1] are
 // written; dlogits ([T,N], may be NULL) receives the gradient with f held fixed.
 size_t aux_loss_ws_bytes(const bigmac_dims& D);
 int launch_aux_loss(const bigmac_dims& D, const float* logits, const int32_t* topk_idx, float* share, float* loss,
-                    float* dlogits, void* ws, hipStream_t s);
+                    float* dlogits, void* ws, hipStream_t s, const int32_t* counts = nullptr);   // counts: as above, instead of topk_idx
 
 // ----------------------------------------------------------------------------- permute --
 size_t permutation_ws_bytes(int T, int k, int N);
+struct SortChunks {
+  int threads, tokens, parts, count;   // threads per workgroup, tokens per part of a chunk, parts per chunk, chunks; threads == 0: sorted another way
+};
+SortChunks sort_chunks(int T, int k, int N);
 // tile_maps (optional): tile maps of the expert offsets, built by the same launch that finds them
-struct TileMapJobs;
 int launch_build_permutation(int T, int k, int N, int capacity, const int32_t* topk_idx, int32_t* expert_offsets,
-                             int32_t* slot_of, int32_t* src_of, void* ws, hipStream_t s, const TileMapJobs* tile_maps = nullptr);
+                             int32_t* slot_of, int32_t* src_of, void* ws, hipStream_t s, const TileMapJobs* tile_maps = nullptr,
+                             bool counted = false);
 int launch_gather_probe(const void* table, const int32_t* order, long rows, long row_bytes, int streaming, unsigned* sink, hipStream_t s);
 int launch_dispatch_rows(int dtype, int T, int k, int width, const void* x_low, const int32_t* slot_of,
                          void* x_perm, hipStream_t s);
@@ -240,10 +259,11 @@ enum CombineOut { COMBINE_F32 = 0, COMBINE_SPLIT_BF16 = 1 };  // fp32 [T,w]  |  
 int launch_combine_rows(int dtype, int T, int k, int width, const void* o_perm, const int32_t* slot_of,
                         const float* topk_w, void* y_low, int out_kind, hipStream_t s, const float* addend = nullptr, int stream_out = 0);
 // backward of the weighted combine: dgate[t,j] = <dy_low[t], o_perm[slot]>, do_perm[slot] = w[t,j]*dy_low[t]
-// (o_dtype: element type of o_perm; do_perm has the storage type `dtype`)
-int launch_combine_backward(int dtype, int o_dtype, int T, int k, int width, const float* dy_low, const void* o_perm,
-                            const int32_t* slot_of, const float* topk_w, float* dgate, void* do_perm,
-                            hipStream_t s);
+// (dy_dtype, o_dtype: element types of dy_low and o_perm; do_perm has the storage type `dtype`).  gate (optional, bf16): the
+// gate's backward in the same pass (dgate is not written then).  claims (optional): CLAIM_INTS tile counters to clear.
+int launch_combine_backward(int dtype, int dy_dtype, int o_dtype, int T, int k, int width, const void* dy_low, const void* o_perm,
+                            const int32_t* slot_of, const float* topk_w, float* dgate, void* do_perm, const GateBackward* gate,
+                            unsigned* claims, hipStream_t s);
 
 // out[g, :] (fp32, [groups, cols]) (+)= sum over the rows of group g (offsets [groups + 1]) of src[row, :cols]
 size_t ragged_colsum_ws_bytes(int groups, int cols);

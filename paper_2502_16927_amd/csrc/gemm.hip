@@ -562,8 +562,10 @@ void mfma_gemm_kernel(GemmDesc p) {
 
 // ------------------------------------------------------------------------ helpers ----------
 
-__global__ __launch_bounds__(1024) void build_tile_map_kernel(const int* __restrict__ offsets, int groups, int tile_rows, int* __restrict__ tile_map) {
-  build_tile_map_block(offsets, groups, tile_rows, tile_map);
+__global__ __launch_bounds__(1024) void build_tile_map_kernel(const int* __restrict__ offsets, int groups, TileMapJobs maps) {
+  for (int i = threadIdx.x; i < maps.clear_ints; i += 1024) maps.clear[i] = 0u;
+  if (maps.map[0]) build_tile_map_block(offsets, groups, maps.tile_rows[0], maps.map[0]);
+  if (maps.map[1]) build_tile_map_block(offsets, groups, maps.tile_rows[1], maps.map[1], maps.map[0]);
 }
 
 // out[i .. i+4) = (beta ? out : 0) + sum_z part[z*n + i ..]: one float4 of the output per thread;
@@ -606,9 +608,9 @@ __global__ void reduce_partials_multi_kernel(ReduceJobs jobs, int beta) {
 
 int gemm_ragged_tile_rows(int dtype, int tall_tile) { return dtype == BIGMAC_BF16 ? (tall_tile ? BIGMAC_TALL_BM : BIGMAC_TILE_BM) : gemm_f32_tile_rows(); }
 
-int launch_build_tile_map(const int* offsets, int groups, int tile_rows, int* tile_map, hipStream_t s) {
+int launch_build_tile_map(const int* offsets, int groups, const TileMapJobs& maps, hipStream_t s) {
   if (groups > 1024) return BIGMAC_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL(build_tile_map_kernel, dim3(1), dim3(1024), 0, s, offsets, groups, tile_rows, tile_map);
+  hipLaunchKernelGGL(build_tile_map_kernel, dim3(1), dim3(1024), 0, s, offsets, groups, maps);
   BIGMAC_CHECK_LAUNCH();
   return BIGMAC_OK;
 }
@@ -865,17 +867,8 @@ double launch_mfma_probe(int blocks, int iters, float* sink, hipStream_t s) {
 namespace {
 struct ClaimPool { unsigned* base; int next; };
 thread_local ClaimPool claim_pool = {nullptr, 0};
-__global__ void clear_claims_kernel(unsigned* p, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0u;
-}
 }  // namespace
-ClaimScope::ClaimScope(void* region, hipStream_t s) {
-  const int n = CLAIM_SLOTS * CLAIM_SLOT_INTS;
-  hipLaunchKernelGGL(clear_claims_kernel, dim3((n + 255) / 256), dim3(256), 0, s, (unsigned*)region, n);
-  status = hipGetLastError() == hipSuccess ? BIGMAC_OK : BIGMAC_ERR_HIP;
-  claim_pool = {status == BIGMAC_OK ? (unsigned*)region : nullptr, 0};
-}
+ClaimScope::ClaimScope(void* region) { claim_pool = {(unsigned*)region, 0}; }
 ClaimScope::~ClaimScope() { claim_pool = {nullptr, 0}; }
 
 int launch_gemm(const GemmDesc& desc, hipStream_t s) {

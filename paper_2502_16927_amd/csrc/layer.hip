@@ -178,6 +178,14 @@ inline bool any_tall_rows(const bigmac_dims& D) {   // a tile map of 256-row til
   return tall_rows(D, W.hid, W.win) || tall_rows(D, W.win, W.hid) || big_rows(D, W.hid, W.win) || big_rows(D, W.win, W.hid);
 }
 
+TileMapJobs tile_map_jobs(const bigmac_dims& D, int* tile_map, int* tile_map_tall, unsigned* claims) {
+  TileMapJobs maps = {};
+  maps.tile_rows[0] = gemm_ragged_tile_rows(D.dtype, 0); maps.map[0] = tile_map;
+  if (any_tall_rows(D)) { maps.tile_rows[1] = gemm_ragged_tile_rows(D.dtype, 1); maps.map[1] = tile_map_tall; }
+  maps.clear = claims; maps.clear_ints = CLAIM_INTS;
+  return maps;
+}
+
 SavedPlan plan_saved(const bigmac_dims& D) {
   const Widths W = widths(D);
   const size_t Tk = (size_t)D.T * D.k, es = esize(D.dtype);
@@ -301,12 +309,12 @@ BwdPlan plan_bwd(const bigmac_dims& D) {
   const bool dcca = D.order == BIGMAC_ORDER_DCCA;
   Carver c;
   BwdPlan p;
-  p.dy_low = c.take((size_t)D.T * W.win * 4);
+  p.dy_low = c.take(dcca ? (size_t)D.T * W.win * 4 : 0);
   p.dgate = c.take(Tk * 4);
   p.do_perm = c.take(Tk * W.win * es);
   p.dx_perm = wire_f32(D) ? c.take(Tk * W.win * 4) : p.do_perm;   // same width: do_perm is dead once the second matrix's gradients are done
   p.dact = c.take(Tk * wide_ld(D) * es);
-  p.dx_low = c.take(dcca ? low_bytes(D) : (size_t)D.T * D.d * 4);
+  p.dx_low = c.take(dcca ? low_bytes(D) : 0);
   p.dL = c.take((size_t)D.T * D.N * es);
   p.route = c.take(route_backward_ws_bytes(router_dims(D)));
   p.dx_f32 = c.take((bf(D) && (D.flags & BIGMAC_FLAG_OUT_BF16)) ? (size_t)D.T * D.d * 4 : 0);
@@ -336,18 +344,9 @@ size_t ffn_ws_bytes(const bigmac_dims& D) {
          align_up(CLAIM_BYTES);
 }
 
-template <typename ET>
-__global__ void to_f32_kernel(const ET* __restrict__ in, float* __restrict__ out, size_t n) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = Elem<ET>::load(in + i);
-}
 __global__ void f32_to_bf16_kernel(const float* __restrict__ in, bf16_t* __restrict__ out, size_t n) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) out[i] = f2bf(in[i]);
-}
-__global__ void add_f32_kernel(float* __restrict__ acc, const float* __restrict__ in, size_t n) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) acc[i] += in[i];
 }
 inline dim3 grid1d(size_t n) { return dim3((unsigned)((n + 255) / 256)); }
 
@@ -597,10 +596,9 @@ int bigmac_grouped_ffn(const bigmac_dims* D, const void* x_perm, const int32_t* 
   void* hact = ws;
   int* tile_map = (int*)((char*)ws + align_up(Tk * W.hid * esize(D->dtype)));
   int* tile_map_tall = (int*)((char*)tile_map + align_up(tile_map_ints((int)Tk, D->N, gemm_ragged_tile_rows(D->dtype, 0)) * 4));
-  ClaimScope claims((char*)tile_map_tall + align_up(tile_map_ints((int)Tk, D->N, gemm_ragged_tile_rows(D->dtype, 0)) * 4), s);
-  if (claims.status) return claims.status;
-  rc = launch_build_tile_map(expert_offsets, D->N, gemm_ragged_tile_rows(D->dtype, 0), tile_map, s);
-  if (!rc && any_tall_rows(*D)) rc = launch_build_tile_map(expert_offsets, D->N, gemm_ragged_tile_rows(D->dtype, 1), tile_map_tall, s);
+  unsigned* claim_counters = (unsigned*)((char*)tile_map_tall + align_up(tile_map_ints((int)Tk, D->N, gemm_ragged_tile_rows(D->dtype, 0)) * 4));
+  ClaimScope claims(claim_counters);
+  rc = launch_build_tile_map(expert_offsets, D->N, tile_map_jobs(*D, tile_map, tile_map_tall, claim_counters), s);
   if (rc) return rc;
   return run_experts_forward(*D, x_perm, expert_offsets, tile_map, tile_map_tall, w1, w2, b1, b2, act_saved, hact, W.hid, o_perm, 0, s);
 }
@@ -626,8 +624,7 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
   const SavedPlan S = plan_saved(*D);
   char* wsb = (char*)ws;
   char* sv = saved ? (char*)saved : wsb + F.total;  // inference keeps the same pieces in the workspace
-  ClaimScope claims(wsb + F.claims, s);
-  if (claims.status) return claims.status;
+  ClaimScope claims(wsb + F.claims);
   int32_t* topk_idx = (int32_t*)(sv + S.topk_idx);
   float* topk_w = (float*)(sv + S.topk_w);
   int32_t* offsets = (int32_t*)(sv + S.offsets);
@@ -644,6 +641,8 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
   const bool aux = D->aux_alpha > 0.0f;                       // the loss lives in the saved block
   float* logits = aux ? (float*)(sv + S.logits) : (float*)(wsb + F.logits);
 
+  // the top-k kernel counts the pairs of the sort's chunks on its way
+  int32_t* chunk_counts = sort_chunks(D->T, D->k, D->N).threads ? (int32_t*)(wsb + F.perm) : nullptr;
   const bool low_router = route_low(*D);
   // x' is the workspace's piece, or (router on x': the backward pass reads it again) the saved block's
   void* x_low_buf = (low_router && saved) ? (void*)(sv + S.x_low) : (void*)(wsb + F.x_low);
@@ -656,9 +655,9 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
     }
     if (rr) return rr;
     BIGMAC_STAGE(BIGMAC_STAGE_TOPK_GATE);
-    rr = launch_topk_gate(*D, logits, topk_idx, topk_w, s);
+    rr = launch_topk_gate(*D, logits, topk_idx, topk_w, s, chunk_counts);
     if (!rr && aux)
-      rr = launch_aux_loss(*D, logits, topk_idx, (float*)(sv + S.aux + 256), (float*)(sv + S.aux), nullptr, wsb + F.aux, s);
+      rr = launch_aux_loss(*D, logits, topk_idx, (float*)(sv + S.aux + 256), (float*)(sv + S.aux), nullptr, wsb + F.aux, s, chunk_counts);
     return rr;
   };
   if (!low_router) {   // Section 3.1's default: the router reads the full-width token
@@ -667,10 +666,8 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
   }
   auto permute = [&]() -> int {
     BIGMAC_STAGE(BIGMAC_STAGE_PERMUTATION);
-    TileMapJobs maps = {};
-    maps.tile_rows[0] = gemm_ragged_tile_rows(D->dtype, 0); maps.map[0] = tile_map;
-    if (any_tall_rows(*D)) { maps.tile_rows[1] = gemm_ragged_tile_rows(D->dtype, 1); maps.map[1] = tile_map_tall; }
-    return launch_build_permutation(D->T, D->k, D->N, D->capacity, topk_idx, offsets, slot_of, src_of, wsb + F.perm, s, &maps);
+    const TileMapJobs maps = tile_map_jobs(*D, tile_map, tile_map_tall, (unsigned*)(wsb + F.claims));
+    return launch_build_permutation(D->T, D->k, D->N, D->capacity, topk_idx, offsets, slot_of, src_of, wsb + F.perm, s, &maps, chunk_counts != nullptr);
   };
   // A training forward on bf16 storage whose router reads x folds the dispatch into the descending
   // projection: the permutation is built first, and the product's epilogue writes every token's
@@ -785,8 +782,7 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
   const BwdPlan B = plan_bwd(*D);
   const char* sv = (const char*)saved;
   char* wsb = (char*)ws;
-  ClaimScope claims(wsb + B.claims, s);
-  if (claims.status) return claims.status;
+  ClaimScope claims(wsb + B.claims);
   const int32_t* topk_idx = (const int32_t*)(sv + S.topk_idx);
   const float* topk_w = (const float*)(sv + S.topk_w);
   const int32_t* offsets = (const int32_t*)(sv + S.offsets);
@@ -838,16 +834,19 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
     BIGMAC_STAGE(BIGMAC_STAGE_BWD_ASCEND_WGRAD);
     rc = run_token_wgrad(*D, y_low, low_ld(*D), D->r, dy, D->d, D->d, d_w_up, (float*)(wsb + B.part_up), &jobs[njobs++], s);
     if (rc) return rc;
-  } else {
-    BIGMAC_STAGE(BIGMAC_STAGE_BWD_ASCEND_DGRAD);
-    if (bf(*D)) hipLaunchKernelGGL(to_f32_kernel<bf16_t>, grid1d(Td), dim3(256), 0, s, (const bf16_t*)dy, dy_low, Td);
-    else hipLaunchKernelGGL(to_f32_kernel<float>, grid1d(Td), dim3(256), 0, s, (const float*)dy, dy_low, Td);
-    BIGMAC_CHECK_LAUNCH();
   }
   // weighted-sum backward: gate gradients and the scaled scatter of dy' to the expert rows
+  // (the fine-grained layer's rows of dy' are dy itself)
+  const bool low_router = route_low(*D), aux = D->aux_alpha > 0.0f;
+  const bigmac_dims R = router_dims(*D);
+  const float* logits = aux ? (const float*)(sv + S.logits) : nullptr;
+  const float* share = aux ? (const float*)(sv + S.aux + 256) : nullptr;
+  GateBackward gate_job;
+  const bool gate_fused = gate_backward_job(R, topk_idx, logits, share, dL, wsb + B.route, &gate_job);
   {
     BIGMAC_STAGE(BIGMAC_STAGE_BWD_COMBINE);
-    rc = launch_combine_backward(D->dtype, wire_dtype(*D), D->T, D->k, W.win, dy_low, o_perm, slot_of, topk_w, dgate, do_perm, s);
+    rc = launch_combine_backward(D->dtype, dcca ? BIGMAC_F32 : D->dtype, wire_dtype(*D), D->T, D->k, W.win, dcca ? (const void*)dy_low : dy, o_perm, slot_of,
+                                 topk_w, dgate, do_perm, gate_fused ? &gate_job : nullptr, (unsigned*)(wsb + B.claims), s);
   }
   if (rc) return rc;
   if (d_b2) {  // the second bias adds to every expert output: its gradient is the column sum of do_perm over the expert's rows
@@ -920,21 +919,18 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
   }
   // Gate backward.  The router's share of the input gradient goes to dx (router on x) or, with the
   // router on x', into an fp32 [T, r] row that the sum of dx' below starts from.
-  const bool low_router = route_low(*D);
-  const bigmac_dims R = router_dims(*D);
   float* gate_low = low_router ? (float*)(wsb + B.gate_low) : nullptr;
   {
     BIGMAC_STAGE(BIGMAC_STAGE_BWD_GATE);
-    const bool aux = D->aux_alpha > 0.0f;
-    rc = launch_route_backward(R, P->w_gate, topk_idx, topk_w, dgate, aux ? (const float*)(sv + S.logits) : nullptr,
-                               aux ? (const float*)(sv + S.aux + 256) : nullptr, low_router ? gate_low : dx_f32, dL, wsb + B.route, s);
+    rc = launch_route_backward(R, P->w_gate, topk_idx, topk_w, dgate, logits, share, low_router ? gate_low : dx_f32, dL, wsb + B.route, s, gate_fused);
   }
   if (rc) return rc;
-  // dispatch backward: dx' = sum_j dx_perm[slot_of[t, j]] (+ the router's share)
+  // dispatch backward: dx' = sum_j dx_perm[slot_of[t, j]] (+ the router's share); the fine-grained
+  // layer's dx' is dx itself and starts from the router's share that lies there
   {
     BIGMAC_STAGE(BIGMAC_STAGE_BWD_DISPATCH);
-    rc = launch_combine_rows(wire_dtype(*D), D->T, D->k, W.win, dx_perm, slot_of, nullptr, dx_low,
-                             (dcca && bf(*D)) ? COMBINE_SPLIT_BF16 : COMBINE_F32, s, gate_low,
+    rc = launch_combine_rows(wire_dtype(*D), D->T, D->k, W.win, dx_perm, slot_of, nullptr, dcca ? dx_low : (void*)dx_f32,
+                             (dcca && bf(*D)) ? COMBINE_SPLIT_BF16 : COMBINE_F32, s, dcca ? gate_low : dx_f32,
                              /*stream_out=*/low_bytes(*D) >= (32u << 20));   // (smaller results are read back from the caches)
   }
   if (rc) return rc;
@@ -972,8 +968,6 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
     if (rc) return rc;
   } else {
     BIGMAC_STAGE(BIGMAC_STAGE_BWD_OUTPUT_CAST);
-    hipLaunchKernelGGL(add_f32_kernel, grid1d(Td), dim3(256), 0, s, dx_f32, (const float*)dx_low, Td);
-    BIGMAC_CHECK_LAUNCH();
     rc = launch_reduce_partials_multi(jobs, njobs, (D->flags & BIGMAC_FLAG_ACCUMULATE) ? 1 : 0, s);
     if (rc) return rc;
   }

@@ -5,6 +5,7 @@
 // from ballots inside one wavefront walking its chunk in order.
 #include "common.hpp"
 #include "tile_map.hpp"
+#include "wave.hpp"
 
 #include <atomic>
 
@@ -17,7 +18,10 @@ namespace bigmac {
 
 namespace {
 
-// Flat pairs per chunk of the counting sort: small chunks give the count and rank kernels more
+constexpr int PP_MAX_EXPERTS = 512;     // experts up to which the one-pass sort runs (32 KB of counters at 16 wavefronts)
+
+// The sort of many pairs or experts (see sort_chunks): count, one-workgroup scan, rank.
+// Flat pairs per chunk: small chunks give the count and rank kernels more
 // workgroups, but the one-workgroup scan walks chunks x experts counters; 256 while those stay
 // below 32768 (gpt_medium: permutation 26.6 -> 23.6 us), else 1024.
 constexpr int P_CHUNK_SMALL = 256, P_CHUNK_LARGE = 1024;
@@ -110,6 +114,7 @@ __global__ __launch_bounds__(1024) void perm_scan_kernel(int32_t* __restrict__ c
     }
   }
   __syncthreads();
+  for (int i = threadIdx.x; i < maps.clear_ints; i += 1024) maps.clear[i] = 0u;
   if (maps.map[0]) build_tile_map_block(first_slot, N, maps.tile_rows[0], maps.map[0]);
   if (maps.map[1]) build_tile_map_block(first_slot, N, maps.tile_rows[1], maps.map[1], maps.map[0]);
 }
@@ -163,73 +168,106 @@ __global__ __launch_bounds__(64) void perm_rank_kernel(const int32_t* __restrict
   }
 }
 
-// The whole counting sort for a few pairs (decode batches) in one workgroup of 1024 threads:
-// pair f = (round, wavefront, lane) in flat order; per (round, wavefront) the pairs of each expert
-// are counted by ballots (one writer per counter, no atomics), the counters are scanned per expert
-// in that same order, and a pair's slot is its expert's first slot + the pairs of the expert in
-// earlier (round, wavefront) groups + the earlier lanes of its own group with the same expert.
-// The same slots as the three-kernel form; also writes the offsets and the tile maps.
-constexpr int PS_MAX_ROUNDS = 4;            // up to 4096 pairs
-constexpr int PS_MAX_COUNTERS = 8192;       // rounds x 16 wavefronts x experts, 32 KB of LDS
-template <int ROUNDS>
-__global__ __launch_bounds__(1024) void perm_small_kernel(const int32_t* __restrict__ idx, int Tk, int N, int nbits, int capacity,
-                                                          int32_t* __restrict__ offsets, int32_t* __restrict__ slot_of,
-                                                          int32_t* __restrict__ src_of, TileMapJobs maps) {
-  __shared__ int cnt[PS_MAX_COUNTERS];   // [round][wavefront][expert]
-  __shared__ int wave_totals[16];
-  __shared__ int first_slot[1025];
-  __shared__ int range_end[1024];
+// The counting sort in one pass over chunks that are counted already (part by part, by the top-k kernel or by
+// perm_count_kernel): a workgroup per chunk of THREADS pairs, one pair per thread.  Every workgroup
+// reads all chunks' counters (at most 512 x N, from the L2) and adds up for itself each expert's total and what
+// lies in front of its own chunk, so no one-workgroup scan sits between the count and the ranks: at 65536
+// pairs and 64 experts count + scan + rank took 5.1 + 10.7 + 5.1 us, this takes 8.0 with the
+// tile map (the counters come with the top-k kernel).  A pair's slot is its expert's first slot + the
+// expert's pairs in earlier chunks, in earlier wavefronts of its chunk (one counter per wavefront and
+// expert, one writer each) and in earlier lanes of its wavefront (ballots): no atomics, flat order.
+// A capacity drops a pair whose slot falls past its expert's range: slot_of = -1, no src_of entry.
+// One workgroup beyond the chunks writes the offsets and the tile maps and clears the tile counters.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void perm_place_kernel(const int32_t* __restrict__ idx, int Tk, int pairs_per_chunk, int nchunks, int parts, int N, int NP, int nbits,
+                                                             int capacity, const int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
+                                                             int32_t* __restrict__ slot_of, int32_t* __restrict__ src_of, TileMapJobs maps) {
+  constexpr int WAVES = THREADS / 64;
+  extern __shared__ int cnt[];           // [wavefront][expert]
+  __shared__ int totals[PP_MAX_EXPERTS], earlier[PP_MAX_EXPERTS];
+  __shared__ int group_total[THREADS], group_earlier[THREADS];
+  __shared__ int first_slot[PP_MAX_EXPERTS + 1];
+  __shared__ int wave_totals[WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int i = tid; i < ROUNDS * 16 * N; i += 1024) cnt[i] = 0;
-  __syncthreads();
-  const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  int mine[ROUNDS], rank[ROUNDS];
+  const int b = blockIdx.x;
+  const bool placing = b < nchunks;
+  const int f = b * pairs_per_chunk + tid;
+  const bool live = placing && tid < pairs_per_chunk && f < Tk;
+  const int e = live ? idx[f] : 0;
+  for (int i = tid; i < WAVES * N; i += THREADS) cnt[i] = 0;
+  // column sums of the counters: THREADS / width groups of chunks x width experts at a time
+  const int width = NP < THREADS ? NP : THREADS, G = THREADS / width, g = tid / width, rows = nchunks * parts;
+  for (int e0 = 0; e0 < N; e0 += width) {
+    const int ee = e0 + tid % width;
+    int total = 0, before = 0;
+    if (ee < N)
+      for (int c0 = g; c0 < rows; c0 += 8 * G) {
+        int v[8];
 #pragma unroll
-  for (int r = 0; r < ROUNDS; ++r) {
-    const int f = r * 1024 + tid;
-    mine[r] = f < Tk ? idx[f] : -1;
-    const bool live = mine[r] >= 0;
-    const int e = live ? mine[r] : 0;
-    unsigned long long same = __ballot(live);
-    for (int b = 0; b < nbits; ++b) {
-      const unsigned long long bal = __ballot((e >> b) & 1);
-      same &= ((e >> b) & 1) ? bal : ~bal;
-    }
-    rank[r] = __popcll(same & below);
-    if (live && (same >> lane) == 1ull) cnt[(r * 16 + wave) * N + e] = __popcll(same);   // highest lane of each expert group
-  }
-  __syncthreads();
-  int total = 0;
-  if (tid < N)
-    for (int g = 0; g < ROUNDS * 16; ++g) {      // counters -> pairs of the expert in earlier groups
-      const int c = cnt[g * N + tid];
-      cnt[g * N + tid] = total;
-      total += c;
-    }
-  const int held = capacity > 0 ? min(total, capacity) : total;
-  const int incl = block_scan_1024(tid < N ? held : 0, wave_totals);
-  if (tid < N) {
-    offsets[tid] = first_slot[tid] = incl - held;
-    range_end[tid] = incl;
-    if (tid == N - 1) offsets[N] = first_slot[N] = incl;
-  }
-  __syncthreads();
+        for (int u = 0; u < 8; ++u) v[u] = c0 + u * G < rows ? counts[(size_t)(c0 + u * G) * N + ee] : 0;
 #pragma unroll
-  for (int r = 0; r < ROUNDS; ++r) {
-    const int f = r * 1024 + tid;
-    if (mine[r] >= 0) {
-      const int e = mine[r];
-      const int slot = first_slot[e] + cnt[(r * 16 + wave) * N + e] + rank[r];
-      if (slot < range_end[e]) {
-        slot_of[f] = slot;
-        src_of[slot] = f;
-      } else {
-        slot_of[f] = -1;
+        for (int u = 0; u < 8; ++u) {
+          total += v[u];
+          before += c0 + u * G < b * parts ? v[u] : 0;
+        }
       }
+    group_total[tid] = total;
+    group_earlier[tid] = before;
+    __syncthreads();
+    if (tid < width && ee < N) {
+      int t = 0, w = 0;
+      for (int h = 0; h < G; ++h) { t += group_total[h * width + tid]; w += group_earlier[h * width + tid]; }
+      totals[ee] = t;
+      earlier[ee] = w;
     }
+    __syncthreads();
   }
-  if (maps.map[0]) build_tile_map_block(first_slot, N, maps.tile_rows[0], maps.map[0]);
-  if (maps.map[1]) build_tile_map_block(first_slot, N, maps.tile_rows[1], maps.map[1], maps.map[0]);
+  // first slots: exclusive scan of the experts' held pairs, THREADS experts at a time
+  int carry = 0;
+  for (int e0 = 0; e0 < N; e0 += THREADS) {
+    const int ee = e0 + tid;
+    const int held = ee < N ? (capacity > 0 ? min(totals[ee], capacity) : totals[ee]) : 0;
+    int v = held;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int o = __shfl_up(v, d, 64);
+      if (lane >= d) v += o;
+    }
+    if (lane == 63) wave_totals[wave] = v;
+    __syncthreads();
+    int before = carry;
+    for (int w = 0; w < WAVES; ++w) {
+      if (w < wave) before += wave_totals[w];
+      carry += wave_totals[w];
+    }
+    if (ee < N) {
+      first_slot[ee] = v - held + before;
+      if (ee == N - 1) first_slot[N] = v + before;
+    }
+    __syncthreads();
+  }
+  if (!placing) {
+    for (int i = tid; i <= N; i += THREADS) offsets[i] = first_slot[i];
+    for (int i = tid; i < maps.clear_ints; i += THREADS) maps.clear[i] = 0u;
+    if (maps.map[0]) build_tile_map_block(first_slot, N, maps.tile_rows[0], maps.map[0]);
+    if (maps.map[1]) build_tile_map_block(first_slot, N, maps.tile_rows[1], maps.map[1], maps.map[0]);
+    return;
+  }
+  unsigned long long same = __ballot(live);
+  for (int bit = 0; bit < nbits; ++bit) {
+    const unsigned long long bal = __ballot((e >> bit) & 1);
+    same &= ((e >> bit) & 1) ? bal : ~bal;
+  }
+  const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  if (live && (same >> lane) == 1ull) cnt[wave * N + e] = __popcll(same);   // highest lane of each expert group
+  __syncthreads();
+  if (live) {
+    int slot = first_slot[e] + earlier[e] + __popcll(same & below);
+    for (int w = 0; w < wave; ++w) slot += cnt[w * N + e];
+    const bool held = capacity == 0 || slot < first_slot[e] + capacity;
+    slot_of[f] = held ? slot : -1;
+    if (held) src_of[slot] = f;
+  }
 }
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
@@ -271,8 +309,8 @@ typedef const int32_t __attribute__((address_space(4))) * const_i32_ptr_t;
 typedef const float __attribute__((address_space(4))) * const_f32_ptr_t;
 template <typename ROW, int OUT, int KU, bool UNIFORM>
 __global__ __launch_bounds__(256) void combine_rows_kernel(const ROW* __restrict__ o_perm, const int32_t* __restrict__ slot_of,
-                                                           const float* __restrict__ w, const float* __restrict__ addend,
-                                                           void* __restrict__ y, int T, int k, int width, int stream_out) {
+                                                           const float* __restrict__ w, const float* addend,
+                                                           void* y, int T, int k, int width, int stream_out) {
   const int cpr = width / 8;
   const size_t g = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (g >= (size_t)T * cpr) return;
@@ -330,12 +368,17 @@ __global__ __launch_bounds__(256) void combine_rows_kernel(const ROW* __restrict
   }
 }
 
-// One wavefront per token: dgate[t,j] = <dy_low[t], o_perm[slot]>; do_perm[slot] = w[t,j] * dy_low[t].
-// OT: element type of the expert outputs, DT: of the scattered gradient rows.
-template <typename OT, typename DT>
-__global__ __launch_bounds__(256) void combine_backward_kernel(const float* __restrict__ dy_low, const OT* __restrict__ o_perm,
+__device__ __forceinline__ void clear_claims(unsigned* claims) {   // by the first workgroup
+  if (claims && blockIdx.x == 0)
+    for (int i = threadIdx.x; i < CLAIM_INTS; i += blockDim.x) claims[i] = 0u;
+}
+
+// One wavefront per token: dgate[t,j] = <dy_low[t], o_perm[slot]>; do_perm[slot] = w[t,j] * dy_low[t].  fp32 storage.
+__global__ __launch_bounds__(256) void combine_backward_kernel(const float* __restrict__ dy_low, const float* __restrict__ o_perm,
                                                                const int32_t* __restrict__ slot_of, const float* __restrict__ w,
-                                                               float* __restrict__ dgate, DT* __restrict__ do_perm, int T, int k, int width) {
+                                                               float* __restrict__ dgate, float* __restrict__ do_perm, int T, int k, int width,
+                                                               unsigned* __restrict__ claims) {
+  clear_claims(claims);
   const int lane = threadIdx.x & 63;
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= T) return;
@@ -351,31 +394,53 @@ __global__ __launch_bounds__(256) void combine_backward_kernel(const float* __re
     for (int c0 = 0; c0 < width; c0 += 256) {
       const int c = c0 + lane * 4;
       if (c < width) {
-        const float4 g = *(const float4*)(dy_low + (size_t)t * width + c);
-        const OT* o = o_perm + slot * width + c;
-        DT* q = do_perm + slot * width + c;
-        dot = fmaf(g.x, Elem<OT>::load(o + 0), dot); dot = fmaf(g.y, Elem<OT>::load(o + 1), dot);
-        dot = fmaf(g.z, Elem<OT>::load(o + 2), dot); dot = fmaf(g.w, Elem<OT>::load(o + 3), dot);
-        Elem<DT>::store(q + 0, wj * g.x); Elem<DT>::store(q + 1, wj * g.y);
-        Elem<DT>::store(q + 2, wj * g.z); Elem<DT>::store(q + 3, wj * g.w);
+        const float4 g = *(const float4*)(dy_low + (size_t)t * width + c), o = *(const float4*)(o_perm + slot * width + c);
+        dot = fmaf(g.x, o.x, dot); dot = fmaf(g.y, o.y, dot); dot = fmaf(g.z, o.z, dot); dot = fmaf(g.w, o.w, dot);
+        *(float4*)(do_perm + slot * width + c) = make_float4(wj * g.x, wj * g.y, wj * g.z, wj * g.w);
       }
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) dot += __shfl_xor(dot, off, 64);
+    dot = wave_sum(dot, lane);
     if (lane == 0) dgate[(size_t)t * k + j] = dot;
   }
 }
 
-// The same for bf16 gradient rows at least 512 wide: 16-byte accesses of 8 columns per lane, the
-// picks taken KU at a time (KU divides k) with all KU pieces of the expert outputs requested
-// before the first multiply-add; the token's dy' piece is read once per group of picks.
-template <typename OT, int KU>
-__global__ __launch_bounds__(256) void combine_backward_wide_kernel(const float* __restrict__ dy_low, const OT* __restrict__ o_perm,
+// C columns (4 or 8) of a row
+template <int C>
+__device__ __forceinline__ void load_cols(const float* p, float* f) {
+  if constexpr (C == 8) load_row8(p, f);
+  else {
+    const f32x4_t a = __builtin_nontemporal_load((const f32x4_t*)p);
+    f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w;
+  }
+}
+template <int C>
+__device__ __forceinline__ void load_cols(const bf16_t* p, float* f) {
+  if constexpr (C == 8) load_row8(p, f);
+  else {
+    typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+    const u32x2_t v = __builtin_nontemporal_load((const u32x2_t*)p);
+    f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xFFFF0000u);
+    f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xFFFF0000u);
+  }
+}
+
+// The same for bf16 gradient rows: C columns per lane (8, or 4 where 8 would leave lanes without a column),
+// the picks taken KU at a time (KU divides k) with all KU pieces of the expert outputs
+// requested before the first multiply-add; the token's dy' piece is read once per group of picks.  The rows'
+// bytes bound it: at width 256 the 8 + 4 bytes per element of the scalar form took 26.7 us at 65536 rows, 4 columns per lane 19.
+// With a gate job the token's gate gradients, which end up in this wavefront's registers, go through the
+// softmax's backward at once (a launch and a round trip through memory less); dy_bf16: dy_low is bf16, as
+// the fine-grained layer's dy is.
+template <typename OT, int KU, int C>
+__global__ __launch_bounds__(256) void combine_backward_wide_kernel(const void* __restrict__ dy_low, int dy_bf16, const OT* __restrict__ o_perm,
                                                                     const int32_t* __restrict__ slot_of, const float* __restrict__ w,
-                                                                    float* __restrict__ dgate, bf16_t* __restrict__ do_perm, int T, int k, int width) {
+                                                                    float* __restrict__ dgate, bf16_t* __restrict__ do_perm, int T, int k, int width,
+                                                                    GateBackward gate, unsigned* __restrict__ claims) {
+  clear_claims(claims);
   const int lane = threadIdx.x & 63;
   const int t = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
   if (t >= T) return;
+  float g_pick = 0.0f;                    // lane j: the gate gradient of pick j
   for (int j0 = 0; j0 < k; j0 += KU) {
     int slot[KU];
     float wj[KU], dot[KU];
@@ -385,36 +450,61 @@ __global__ __launch_bounds__(256) void combine_backward_wide_kernel(const float*
       wj[u] = ((const_f32_ptr_t)(unsigned long long)w)[(size_t)t * k + j0 + u];
       dot[u] = 0.0f;
     }
-    for (int c0 = 0; c0 < width; c0 += 512) {
-      const int c = c0 + lane * 8;
+    for (int c0 = 0; c0 < width; c0 += 64 * C) {
+      const int c = c0 + lane * C;
       if (c < width) {
-        float g[8];
-        const float4 g0 = *(const float4*)(dy_low + (size_t)t * width + c), g1 = *(const float4*)(dy_low + (size_t)t * width + c + 4);
-        g[0] = g0.x; g[1] = g0.y; g[2] = g0.z; g[3] = g0.w; g[4] = g1.x; g[5] = g1.y; g[6] = g1.z; g[7] = g1.w;
-        float o[KU][8];
+        float g[C];
+        const size_t at = (size_t)t * width + c;
+        if (dy_bf16) {
+          if constexpr (C == 8) unpack_bf16x8(*(const uint4*)((const bf16_t*)dy_low + at), g);
+          else {
+            const uint2 v = *(const uint2*)((const bf16_t*)dy_low + at);
+            g[0] = __uint_as_float(v.x << 16); g[1] = __uint_as_float(v.x & 0xFFFF0000u);
+            g[2] = __uint_as_float(v.y << 16); g[3] = __uint_as_float(v.y & 0xFFFF0000u);
+          }
+        } else {
 #pragma unroll
-        for (int u = 0; u < KU; ++u) load_row8(o_perm + (size_t)max(slot[u], 0) * width + c, o[u]);
+          for (int q = 0; q < C / 4; ++q) {
+            const float4 v = *((const float4*)((const float*)dy_low + at) + q);
+            g[q * 4 + 0] = v.x; g[q * 4 + 1] = v.y; g[q * 4 + 2] = v.z; g[q * 4 + 3] = v.w;
+          }
+        }
+        float o[KU][C];
+#pragma unroll
+        for (int u = 0; u < KU; ++u) load_cols<C>(o_perm + (size_t)max(slot[u], 0) * width + c, o[u]);
 #pragma unroll
         for (int u = 0; u < KU; ++u) {
           if (slot[u] < 0) continue;              // a dropped pair has no row; its dot stays 0
-          float q[8];
+          float q[C];
 #pragma unroll
-          for (int i = 0; i < 8; ++i) {
+          for (int i = 0; i < C; ++i) {
             dot[u] = fmaf(g[i], o[u][i], dot[u]);
             q[i] = wj[u] * g[i];
           }
-          *(uint4*)(do_perm + (size_t)slot[u] * width + c) = pack_bf16x8(q);
+          bf16_t* out = do_perm + (size_t)slot[u] * width + c;
+          if constexpr (C == 8) *(uint4*)out = pack_bf16x8(q);
+          else *(uint2*)out = make_uint2(f2bf_pair(q[0], q[1]), f2bf_pair(q[2], q[3]));
         }
       }
     }
 #pragma unroll
     for (int u = 0; u < KU; ++u) {
-      float d = dot[u];
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) d += __shfl_xor(d, off, 64);
-      if (lane == 0) dgate[(size_t)t * k + j0 + u] = d;
+      const float d = wave_sum(dot[u], lane);
+      if (lane == j0 + u) g_pick = d;
     }
   }
+  if (!gate.dL) {
+    if (lane < k) dgate[(size_t)t * k + lane] = g_pick;
+    return;
+  }
+  float w_pick = 0.0f, entry[2], dl;
+  int e_pick = 0;
+  if (lane < k) {
+    w_pick = w[(size_t)t * k + lane];
+    e_pick = gate.topk_idx[(size_t)t * k + lane];
+  }
+  gate_backward_row<bf16_t, 2>(w_pick, g_pick, e_pick, gate.logits ? gate.logits + (size_t)t * gate.N : nullptr, gate.share, gate.aux_scale, gate.N, k,
+                               lane, gate.dL + (size_t)t * gate.N, gate.dl_picked ? gate.dl_picked + (size_t)t * k : nullptr, entry, dl);
 }
 
 // Column sums over each group's rows (the gradients of the expert biases): part[(g * S + z), c] =
@@ -485,31 +575,60 @@ int launch_ragged_colsum(int dtype, const void* src, long ld, int cols, const in
   return BIGMAC_OK;
 }
 
+// Chunks of the one-pass sort: whole tokens, at most `threads` pairs.  Few pairs per chunk
+// give the sort more workgroups, few chunks give each of them less to add up.  A chunk is counted in up to four parts,
+// one row of counters each: the top-k kernel, which counts the tokens it picks for, is bound by its
+// arithmetic and wants every CU busy, so parts are added while there are at most 256 of them.
+// More than 64 experts: 1024 threads, which is what their tile maps are built by.  threads = 0: the three-kernel sort.
+SortChunks sort_chunks(int T, int k, int N) {
+  SortChunks c = {0, 0, 0, 0};
+  if (N > PP_MAX_EXPERTS) return c;
+  for (int threads = N > 64 ? 1024 : 256; threads <= 1024; threads *= 2) {
+    const int tokens = threads / k;
+    const long n = ((long)T + tokens - 1) / tokens;
+    if (n <= (threads == 1024 ? 512 : 160)) {
+      c.threads = threads;
+      c.parts = n * 4 <= 256 && tokens >= 16 ? 4 : (n * 2 <= 256 && tokens >= 8 ? 2 : 1);
+      c.tokens = tokens / c.parts;
+      c.count = (int)(((long)T + c.tokens * c.parts - 1) / (c.tokens * c.parts));
+      break;
+    }
+  }
+  return c;
+}
+
 size_t permutation_ws_bytes(int T, int k, int N) {
+  const SortChunks c = sort_chunks(T, k, N);
+  if (c.threads) return align_up((size_t)c.count * c.parts * N * sizeof(int32_t));
   const int chunk = perm_chunk(T * k, N);
   const size_t nchunks = ((size_t)T * k + chunk - 1) / chunk;
   return align_up(nchunks * N * sizeof(int32_t));
 }
 
+// counted: ws holds the chunks' counters (see sort_chunks) already
 int launch_build_permutation(int T, int k, int N, int capacity, const int32_t* topk_idx, int32_t* expert_offsets,
-                             int32_t* slot_of, int32_t* src_of, void* ws, hipStream_t s, const TileMapJobs* tile_maps) {
+                             int32_t* slot_of, int32_t* src_of, void* ws, hipStream_t s, const TileMapJobs* tile_maps, bool counted) {
   if (N > 1024) return BIGMAC_ERR_UNSUPPORTED;   // one thread of the scan per expert
   const TileMapJobs maps = tile_maps ? *tile_maps : TileMapJobs{};
-  {
-    const int need = (T * k + 1023) / 1024;
-    const int rounds = need <= 1 ? 1 : (need == 2 ? 2 : 4);           // the instantiated round counts
-    if (need <= PS_MAX_ROUNDS && rounds * 16 * N <= PS_MAX_COUNTERS) {
-      int bits = 0;
-      while ((1 << bits) < N) ++bits;
-#define BIGMAC_PERM_SMALL(R) \
-  hipLaunchKernelGGL(perm_small_kernel<R>, dim3(1), dim3(1024), 0, s, topk_idx, T * k, N, bits, capacity, expert_offsets, slot_of, src_of, maps)
-      if (rounds == 1) BIGMAC_PERM_SMALL(1);
-      else if (rounds == 2) BIGMAC_PERM_SMALL(2);
-      else BIGMAC_PERM_SMALL(4);
-#undef BIGMAC_PERM_SMALL
+  const SortChunks sc = sort_chunks(T, k, N);
+  if (sc.threads) {
+    const int part = sc.tokens * k, pairs = part * sc.parts, Tk = T * k;
+    int nbits = 0, NP = 1;
+    while ((1 << nbits) < N) ++nbits;
+    while (NP < N) NP <<= 1;
+    if (!counted) {
+      hipLaunchKernelGGL(perm_count_kernel, dim3(sc.count * sc.parts), dim3(256), N * sizeof(int), s, topk_idx, Tk, N, part, (int32_t*)ws);
       BIGMAC_CHECK_LAUNCH();
-      return BIGMAC_OK;
     }
+#define BIGMAC_PLACE(THREADS)                                                                                                        \
+  hipLaunchKernelGGL(perm_place_kernel<THREADS>, dim3(sc.count + 1), dim3(THREADS), THREADS / 64 * N * sizeof(int), s, topk_idx, Tk, pairs, \
+                     sc.count, sc.parts, N, NP, nbits, capacity, (const int32_t*)ws, expert_offsets, slot_of, src_of, maps)
+    if (sc.threads == 256) BIGMAC_PLACE(256);
+    else if (sc.threads == 512) BIGMAC_PLACE(512);
+    else BIGMAC_PLACE(1024);
+#undef BIGMAC_PLACE
+    BIGMAC_CHECK_LAUNCH();
+    return BIGMAC_OK;
   }
   const int Tk = T * k;
   const int chunk = perm_chunk(Tk, N);
@@ -630,13 +749,13 @@ int launch_combine_rows(int dtype, int T, int k, int width, const void* o_perm, 
 }
 
 namespace {
-template <typename OT>
-void launch_combine_backward_wide(int ku, dim3 grid, hipStream_t s, const float* dy_low, const OT* o_perm, const int32_t* slot_of,
-                                  const float* w, float* dgate, bf16_t* do_perm, int T, int k, int width) {
+template <typename OT, int C>
+void launch_combine_backward_wide(dim3 grid, hipStream_t s, const void* dy_low, int dy_bf16, const OT* o_perm, const int32_t* slot_of,
+                                  const float* w, float* dgate, bf16_t* do_perm, int T, int k, int width, const GateBackward& gate, unsigned* claims) {
   const dim3 block(256);
 #define BIGMAC_COMBINE_BWD(KU) \
-  hipLaunchKernelGGL((combine_backward_wide_kernel<OT, KU>), grid, block, 0, s, dy_low, o_perm, slot_of, w, dgate, do_perm, T, k, width)
-  switch (ku) {
+  hipLaunchKernelGGL((combine_backward_wide_kernel<OT, KU, C>), grid, block, 0, s, dy_low, dy_bf16, o_perm, slot_of, w, dgate, do_perm, T, k, width, gate, claims)
+  switch (combine_unroll(k)) {
     case 8: BIGMAC_COMBINE_BWD(8); break;
     case 7: BIGMAC_COMBINE_BWD(7); break;
     case 6: BIGMAC_COMBINE_BWD(6); break;
@@ -650,25 +769,28 @@ void launch_combine_backward_wide(int ku, dim3 grid, hipStream_t s, const float*
 }
 }  // namespace
 
-int launch_combine_backward(int dtype, int o_dtype, int T, int k, int width, const float* dy_low, const void* o_perm,
-                            const int32_t* slot_of, const float* topk_w, float* dgate, void* do_perm, hipStream_t s) {
+int launch_combine_backward(int dtype, int dy_dtype, int o_dtype, int T, int k, int width, const void* dy_low, const void* o_perm,
+                            const int32_t* slot_of, const float* topk_w, float* dgate, void* do_perm, const GateBackward* gate,
+                            unsigned* claims, hipStream_t s) {
   const dim3 grid((T + 3) / 4), block(256);
-  if (dtype == BIGMAC_BF16 && width % 8 == 0 && width >= 512) {   // narrower rows would leave lanes idle
-    const int ku = combine_unroll(k);
-    if (o_dtype == BIGMAC_BF16)
-      launch_combine_backward_wide<bf16_t>(ku, grid, s, dy_low, (const bf16_t*)o_perm, slot_of, topk_w, dgate, (bf16_t*)do_perm, T, k, width);
-    else
-      launch_combine_backward_wide<float>(ku, grid, s, dy_low, (const float*)o_perm, slot_of, topk_w, dgate, (bf16_t*)do_perm, T, k, width);
-  } else if (dtype == BIGMAC_BF16 && o_dtype == BIGMAC_BF16) {
-    hipLaunchKernelGGL((combine_backward_kernel<bf16_t, bf16_t>), grid, block, 0, s, dy_low, (const bf16_t*)o_perm, slot_of, topk_w, dgate,
-                       (bf16_t*)do_perm, T, k, width);
-  } else if (dtype == BIGMAC_BF16) {
-    hipLaunchKernelGGL((combine_backward_kernel<float, bf16_t>), grid, block, 0, s, dy_low, (const float*)o_perm, slot_of, topk_w, dgate,
-                       (bf16_t*)do_perm, T, k, width);
+  if (width % 8 || (gate && (dtype != BIGMAC_BF16 || gate->N > 128)) || k > 64) return BIGMAC_ERR_INVALID_ARG;
+  const GateBackward job = gate ? *gate : GateBackward{};
+  if (dtype == BIGMAC_BF16) {
+    const int dy_bf16 = dy_dtype == BIGMAC_BF16;
+#define BIGMAC_BWD_WIDE(OT, C) \
+  launch_combine_backward_wide<OT, C>(grid, s, dy_low, dy_bf16, (const OT*)o_perm, slot_of, topk_w, dgate, (bf16_t*)do_perm, T, k, width, job, claims)
+    if (width >= 512) {
+      if (o_dtype == BIGMAC_BF16) BIGMAC_BWD_WIDE(bf16_t, 8);
+      else BIGMAC_BWD_WIDE(float, 8);
+    } else {
+      if (o_dtype == BIGMAC_BF16) BIGMAC_BWD_WIDE(bf16_t, 4);
+      else BIGMAC_BWD_WIDE(float, 4);
+    }
+#undef BIGMAC_BWD_WIDE
   } else {
-    if (o_dtype != BIGMAC_F32) return BIGMAC_ERR_INVALID_ARG;
-    hipLaunchKernelGGL((combine_backward_kernel<float, float>), grid, block, 0, s, dy_low, (const float*)o_perm, slot_of, topk_w, dgate,
-                       (float*)do_perm, T, k, width);
+    if (o_dtype != BIGMAC_F32 || dy_dtype != BIGMAC_F32) return BIGMAC_ERR_INVALID_ARG;
+    hipLaunchKernelGGL(combine_backward_kernel, grid, block, 0, s, (const float*)dy_low, (const float*)o_perm, slot_of, topk_w, dgate,
+                       (float*)do_perm, T, k, width, claims);
   }
   BIGMAC_CHECK_LAUNCH();
   return BIGMAC_OK;

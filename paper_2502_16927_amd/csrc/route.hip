@@ -4,7 +4,7 @@
 //   p_l  = fma(x[t, 64q + l], W_g[64q + l, n], p_l),  q ascending, l = 0..63   (one lane each)
 //   tree = p_l + p_{l+off} for off = 32, 16, 8, 4, 2, 1;  logit = tree (+ bias[n], added last)
 // The tree is evaluated as a reduce-scatter over the wavefront: same pairs, 1/6 of the adds.
-#include "common.hpp"
+#include "wave.hpp"
 
 namespace bigmac {
 
@@ -372,100 +372,142 @@ __global__ __launch_bounds__(256) void router_logits_pipelined_kernel(const XT* 
   }
 }
 
-// One wavefront per token.  More than 128 experts: every lane ranks its logits against all N by broadcast (rank = how
-// many logits come first: greater, or equal with a lower index, which is the order k rounds of
-// arg-max with ties to the lowest index would pick them in); ranks below k are the selection, in
-// pick order.  Then the softmax over the k picked logits, summed in pick order.  PER = logits
-// held per lane.
+// (logit, expert) as one number: the greater key comes first, equal logits (-0 counts as 0) by lower index
+__device__ __forceinline__ unsigned long long pick_key(float logit, int expert) {
+  const unsigned u = __float_as_uint(logit + 0.0f);
+  return ((unsigned long long)((u & 0x80000000u) ? ~u : u | 0x80000000u) << 32) | (unsigned)~expert;
+}
+__device__ __forceinline__ float key_logit(unsigned long long key) {
+  const unsigned u = (unsigned)(key >> 32);
+  return __uint_as_float((u & 0x80000000u) ? u & 0x7FFFFFFFu : ~u);
+}
+// One compare-exchange step of a bitonic network over the wavefront, for U independent networks: partner lane
+// ^ J, the greater key of the pair goes to the lane for which greater_here holds.
+template <int J, int U>
+__device__ __forceinline__ void exchange_keys(unsigned long long (&key)[U], int lane, bool greater_here) {
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const unsigned long long other = ((unsigned long long)from_lane_xor<J>((unsigned)(key[u] >> 32), lane) << 32) | from_lane_xor<J>((unsigned)key[u], lane);
+    if ((key[u] > other) != greater_here) key[u] = other;
+  }
+}
+template <int SIZE, int J, int U>
+__device__ __forceinline__ void merge_keys(unsigned long long (&key)[U], int lane) {
+  exchange_keys<J>(key, lane, ((lane & J) == 0) == ((lane & SIZE) == 0));   // lower lane of a descending block
+  if constexpr (J > 1) merge_keys<SIZE, J / 2>(key, lane);
+}
+template <int SIZE, int U>
+__device__ __forceinline__ void sort_keys(unsigned long long (&key)[U], int lane) {   // lane 0 ends with the greatest
+  if constexpr (SIZE > 2) sort_keys<SIZE / 2>(key, lane);
+  merge_keys<SIZE, SIZE / 2>(key, lane);
+}
+
+// The k picks of each token in pick order (greater logit first, ties to the lower index) and the softmax over
+// their logits, summed in pick order.  One wavefront per token; a workgroup walks the `tokens` tokens of
+// its chunk and, if counts is given, counts their pairs per expert on the way (the sort's counters,
+// see launch_build_permutation).  PER = logits per lane.  Up to 64 experts: one key per lane, sorted across the wavefront by a
+// bitonic network (the order is strict and total, so the result is the unique sorted sequence);
+// lanes 0 .. k-1 then hold the picks.  Up to 128: two keys per lane, both halves sorted the same way;
+// the first 64 of their union are, lane by lane, the first of (half 0 at lane l, half 1 at lane
+// 63 - l), a bitonic sequence that six more steps sort: k <= 64 picks are all there.  More: every lane
+// ranks its logits against all N by broadcast (rank = how many logits come first); ranks below k
+// are the selection.
+// The network is a serial chain of 21 (27) exchanges and bound by its latency: keys of 64 bits cost one
+// comparison, partners are read by DPP moves and row swaps instead of through the LDS, and a
+// wavefront takes two tokens at a time (8192 tokens, 64 experts, counting included: 15.0 us by wavefronts
+// that take eight one by one, 6.3 us so).
 template <int PER>
-__global__ __launch_bounds__(256) void topk_gate_kernel(const float* __restrict__ logits, int T, int N, int k,
-                                                        int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
+__global__ __launch_bounds__(1024) void topk_gate_kernel(const float* __restrict__ logits, int T, int N, int k, int tokens,
+                                                         int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int32_t* __restrict__ counts) {
+  __shared__ int hist[1024];
   const int lane = threadIdx.x & 63;
-  const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (t >= T) return;
-  // "a comes first": greater logit, equal logits by lower index (a strict total order)
-  auto first = [](float av, int ai, float bv, int bi) { return av > bv || (av == bv && ai < bi); };
-  // one compare-exchange step of a bitonic network over the wavefront: partner lane ^ j, the pair's
-  // first element goes to the lane for which want_first holds
-  auto exchange = [&](float& mv, int& mi, int j, bool want_first) {
-    const float ov = __shfl_xor(mv, j, 64);
-    const int oi = __shfl_xor(mi, j, 64);
-    if (first(mv, mi, ov, oi) != want_first) { mv = ov; mi = oi; }
-  };
-  auto sort64 = [&](float& mv, int& mi) {   // lane 0 ends with the first element
-#pragma unroll
-    for (int size = 2; size <= 64; size <<= 1)
-#pragma unroll
-      for (int j = size >> 1; j > 0; j >>= 1) exchange(mv, mi, j, ((lane & j) == 0) == ((lane & size) == 0));   // lower lane of an ascending block
-  };
-  if constexpr (PER <= 2) {
-    // Up to 64 experts: one logit per lane, sorted across the wavefront by a bitonic network (the
-    // order is strict and total, so the result is the unique sorted sequence); lanes 0 .. k-1 then
-    // hold the picks in pick order.  Up to 128: two logits per lane, both halves sorted the same
-    // way; the first 64 of their union are, lane by lane, the first of (half 0 at lane l, half 1
-    // at lane 63 - l), a bitonic sequence that six more steps sort.  k <= 64 picks are all there.
-    float mv = lane < N ? logits[(size_t)t * N + lane] : -INFINITY;
-    int mi = lane;
-    sort64(mv, mi);
-    if constexpr (PER == 2) {
-      float uv = 64 + lane < N ? logits[(size_t)t * N + 64 + lane] : -INFINITY;
-      int ui = 64 + lane;
-      sort64(uv, ui);
-      const float rv = __shfl(uv, 63 - lane, 64);
-      const int ri = __shfl(ui, 63 - lane, 64);
-      if (!first(mv, mi, rv, ri)) { mv = rv; mi = ri; }
-#pragma unroll
-      for (int j = 32; j > 0; j >>= 1) exchange(mv, mi, j, (lane & j) == 0);
-    }
-    const float m = __shfl(mv, 0, 64);
-    const float e = lane < k ? expf(mv - m) : 0.0f;
+  if (counts) {
+    for (int e = threadIdx.x; e < N; e += blockDim.x) hist[e] = 0;
+    __syncthreads();
+  }
+  auto finish = [&](int t, float logit, int expert) {   // lane j < k holds pick j
+    const float m = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(logit), 0));
+    const float e = lane < k ? expf(logit - m) : 0.0f;
     float s = 0.0f;
-    for (int j = 0; j < k; ++j) s += __shfl(e, j, 64);
+    for (int j = 0; j < k; ++j) s += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(e), j));
     if (lane < k) {
-      topk_idx[(size_t)t * k + lane] = mi;
+      topk_idx[(size_t)t * k + lane] = expert;
       topk_w[(size_t)t * k + lane] = e / s;
+      if (counts) atomicAdd(&hist[expert], 1);
     }
-    return;
-  }
-  float v[PER];
-  int rank[PER];
+  };
+  const int t_end = min(T, (int)(blockIdx.x + 1) * tokens), step = blockDim.x >> 6;
+  constexpr int U = PER <= 2 ? 2 : 1;
+  for (int t = blockIdx.x * tokens + (threadIdx.x >> 6); t < t_end; t += U * step) {
+    if constexpr (PER <= 2) {
+      unsigned long long key[U];
 #pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int n = i * 64 + lane;
-    v[i] = n < N ? logits[(size_t)t * N + n] : -INFINITY;
-    rank[i] = 0;
-  }
-#pragma unroll
-  for (int io = 0; io < PER; ++io) {
-    const int live = min(64, N - io * 64);        // lanes of this register that hold a logit
-    for (int l = 0; l < live; ++l) {
-      const float o = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[io]), l));
-      const int on = io * 64 + l;
-#pragma unroll
-      for (int i = 0; i < PER; ++i) rank[i] += (o > v[i] || (o == v[i] && on < i * 64 + lane)) ? 1 : 0;
-    }
-  }
-  // lane j < k collects the j-th pick: its index and logit
-  float selv = 0.0f;
-  int seli = 0;
-  for (int j = 0; j < k; ++j) {
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const unsigned long long hit = __ballot(rank[i] == j && i * 64 + lane < N);
-      if (hit) {                                  // wave-uniform: exactly one (i, lane) has rank j
-        const int src = __ffsll((long long)hit) - 1;
-        const float pv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[i]), src));
-        if (lane == j) { selv = pv; seli = i * 64 + src; }
+      for (int u = 0; u < U; ++u) {     // (tokens past the chunk repeat the last one's loads and are not finished)
+        const float* row = logits + (size_t)min(t + u * step, t_end - 1) * N;
+        key[u] = pick_key(lane < N ? row[lane] : -INFINITY, lane);
       }
+      if constexpr (PER == 1) {
+        sort_keys<64>(key, lane);
+      } else {
+        unsigned long long upper[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const float* row = logits + (size_t)min(t + u * step, t_end - 1) * N;
+          upper[u] = pick_key(64 + lane < N ? row[64 + lane] : -INFINITY, 64 + lane);
+        }
+        sort_keys<64>(key, lane);
+        sort_keys<64>(upper, lane);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const unsigned hi = __shfl((unsigned)(upper[u] >> 32), 63 - lane, 64), lo = __shfl((unsigned)upper[u], 63 - lane, 64);
+          const unsigned long long mirrored = ((unsigned long long)hi << 32) | lo;
+          if (mirrored > key[u]) key[u] = mirrored;
+        }
+        merge_keys<64, 32>(key, lane);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (t + u * step < t_end) finish(t + u * step, key_logit(key[u]), (int)~(unsigned)key[u]);
+    } else {
+      const float* row = logits + (size_t)t * N;
+      float v[PER];
+      int rank[PER];
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        const int n = i * 64 + lane;
+        v[i] = n < N ? row[n] : -INFINITY;
+        rank[i] = 0;
+      }
+#pragma unroll
+      for (int io = 0; io < PER; ++io) {
+        const int live = min(64, N - io * 64);        // lanes of this register that hold a logit
+        for (int l = 0; l < live; ++l) {
+          const float o = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[io]), l));
+          const int on = io * 64 + l;
+#pragma unroll
+          for (int i = 0; i < PER; ++i) rank[i] += (o > v[i] || (o == v[i] && on < i * 64 + lane)) ? 1 : 0;
+        }
+      }
+      // lane j < k collects the j-th pick: its index and logit
+      float selv = 0.0f;
+      int seli = 0;
+      for (int j = 0; j < k; ++j) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+          const unsigned long long hit = __ballot(rank[i] == j && i * 64 + lane < N);
+          if (hit) {                                  // wave-uniform: exactly one (i, lane) has rank j
+            const int src = __ffsll((long long)hit) - 1;
+            const float pv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[i]), src));
+            if (lane == j) { selv = pv; seli = i * 64 + src; }
+          }
+        }
+      }
+      finish(t, selv, seli);
     }
   }
-  const float m = __shfl(selv, 0, 64);
-  const float e = lane < k ? expf(selv - m) : 0.0f;
-  float s = 0.0f;
-  for (int j = 0; j < k; ++j) s += __shfl(e, j, 64);
-  if (lane < k) {
-    topk_idx[(size_t)t * k + lane] = seli;
-    topk_w[(size_t)t * k + lane] = e / s;
+  if (counts) {
+    __syncthreads();
+    for (int e = threadIdx.x; e < N; e += blockDim.x) counts[(size_t)blockIdx.x * N + e] = hist[e];
   }
 }
 
@@ -478,51 +520,6 @@ __global__ void transpose_f32_kernel(const float* __restrict__ in, float* __rest
   int r = r0 + threadIdx.x, c0 = blockIdx.x * 32;
   for (int i = threadIdx.y; i < 32; i += 8)
     if (c0 + i < cols && r < rows) out[(size_t)(c0 + i) * rows + r] = tile[threadIdx.x][i];
-}
-
-// softmax over all N logits of one token by one wavefront: lane l holds experts l, l + 64, ...
-template <int PER>
-__device__ __forceinline__ void softmax_row(const float* __restrict__ row, int N, int lane, float (&p)[PER]) {
-  float m = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int n = i * 64 + lane;
-    p[i] = n < N ? row[n] : -INFINITY;
-    m = fmaxf(m, p[i]);
-  }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-  float sum = 0.0f;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    p[i] = i * 64 + lane < N ? expf(p[i] - m) : 0.0f;
-    sum += p[i];
-  }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
-  const float inv = 1.0f / sum;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) p[i] *= inv;
-}
-
-// Gradient of the load-balance loss  alpha N sum_e f_e P_e  with respect to one token's logits,
-// the pair shares f held fixed:  scale p_n (f_n - sum_e f_e p_e),  scale = alpha N / T.
-template <int PER>
-__device__ __forceinline__ void aux_grad_row(const float* __restrict__ row, const float* __restrict__ share, int N, int lane,
-                                             float scale, float (&g)[PER]) {
-  float f[PER];
-  softmax_row<PER>(row, N, lane, g);
-  float mix = 0.0f;
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int n = i * 64 + lane;
-    f[i] = n < N ? share[n] : 0.0f;
-    mix = fmaf(f[i], g[i], mix);
-  }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) mix += __shfl_xor(mix, off, 64);
-#pragma unroll
-  for (int i = 0; i < PER; ++i) g[i] = scale * g[i] * (f[i] - mix);
 }
 
 // Column sums of softmax(logits) over a strided share of the tokens: workgroup b, wavefront w
@@ -553,7 +550,9 @@ __global__ __launch_bounds__(256) void aux_colsum_kernel(const float* __restrict
 // threads are G groups x NP experts (NP = N rounded up to a power of two); group g adds its
 // contiguous range of partials in order, the G group sums are added in group order, and the N
 // terms f_e P_e go through a fixed tree.
-__global__ __launch_bounds__(1024) void aux_finish_kernel(const int32_t* __restrict__ topk_idx, const float* __restrict__ partial,
+// The counts come from the sort's counters of all chunks (chunk_counts [nchunks][N]) or, without them, from the picks.
+__global__ __launch_bounds__(1024) void aux_finish_kernel(const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ chunk_counts, int nchunks,
+                                                          const float* __restrict__ partial,
                                                           int nparts, int T, int N, int NP, int k, float alpha,
                                                           float* __restrict__ share, float* __restrict__ loss) {
   __shared__ int cnt[1024];
@@ -561,17 +560,27 @@ __global__ __launch_bounds__(1024) void aux_finish_kernel(const int32_t* __restr
   cnt[threadIdx.x] = 0;
   __syncthreads();
   const int Tk = T * k;
-  const int quads = Tk / 4;                        // 16-byte reads; the base pointer is 16-byte aligned
-  for (int q = threadIdx.x; q < quads; q += 1024) {
-    const int4 v = ((const int4*)topk_idx)[q];
-    atomicAdd(&cnt[v.x], 1); atomicAdd(&cnt[v.y], 1); atomicAdd(&cnt[v.z], 1); atomicAdd(&cnt[v.w], 1);
+  if (chunk_counts) {
+    const int n = threadIdx.x % NP;
+    int sum = 0;
+    if (n < N)
+#pragma unroll 8
+      for (int c = threadIdx.x / NP; c < nchunks; c += 1024 / NP) sum += chunk_counts[(size_t)c * N + n];
+    if (n < N) atomicAdd(&cnt[n], sum);
+  } else {
+    const int quads = Tk / 4;                      // 16-byte reads; the base pointer is 16-byte aligned
+    for (int q = threadIdx.x; q < quads; q += 1024) {
+      const int4 v = ((const int4*)topk_idx)[q];
+      atomicAdd(&cnt[v.x], 1); atomicAdd(&cnt[v.y], 1); atomicAdd(&cnt[v.z], 1); atomicAdd(&cnt[v.w], 1);
+    }
+    for (int f = quads * 4 + threadIdx.x; f < Tk; f += 1024) atomicAdd(&cnt[topk_idx[f]], 1);
   }
-  for (int f = quads * 4 + threadIdx.x; f < Tk; f += 1024) atomicAdd(&cnt[topk_idx[f]], 1);
   const int G = 1024 / NP, e = threadIdx.x % NP, g = threadIdx.x / NP;
   const int per = (nparts + G - 1) / G;
   const int b_beg = min(g * per, nparts), b_end = min(b_beg + per, nparts);
   float mine = 0.0f;
   if (e < N)
+#pragma unroll 8
     for (int b = b_beg; b < b_end; ++b) mine += partial[(size_t)b * N + e];
   psum[g * NP + e] = mine;
   __syncthreads();
@@ -621,10 +630,6 @@ __global__ __launch_bounds__(256) void gate_backward_kernel(const int32_t* __res
   const int lane = threadIdx.x & 63;
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= T) return;
-  float aux[PER];
-#pragma unroll
-  for (int i = 0; i < PER; ++i) aux[i] = 0.0f;
-  if (logits) aux_grad_row<PER>(logits + (size_t)t * N, share, N, lane, aux_scale, aux);
   float w = 0.0f, g = 0.0f;
   int e = 0;
   if (lane < k) {
@@ -632,23 +637,9 @@ __global__ __launch_bounds__(256) void gate_backward_kernel(const int32_t* __res
     g = dgate[(size_t)t * k + lane];
     e = topk_idx[(size_t)t * k + lane];
   }
-  float mix = 0.0f;
-  for (int j = 0; j < k; ++j) mix = fmaf(__shfl(w, j, 64), __shfl(g, j, 64), mix);
-  const float dl = w * (g - mix);
-  if (dl_picked && lane < k) dl_picked[(size_t)t * k + lane] = dl;
-  // every lane takes part in the shuffles (uniform trip counts); only loads and stores are guarded
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {        // dense row of dL: the k picked experts, zeros (or the loss term) elsewhere
-    if (i * 64 >= N) break;
-    const int n = i * 64 + lane;
-    float val = 0.0f;
-    for (int j = 0; j < k; ++j) {
-      const float dj = __shfl(dl, j, 64);
-      if (__shfl(e, j, 64) == n) val = dj;
-    }
-    aux[i] += val;                       // the whole dlogits entry from here on
-    if (n < N) Elem<DT>::store(dL + (size_t)t * N + n, logits ? aux[i] : val);
-  }
+  float aux[PER], dl;                     // aux: the whole row of dlogits
+  gate_backward_row<DT, PER>(w, g, e, logits ? logits + (size_t)t * N : nullptr, share, aux_scale, N, k, lane, dL + (size_t)t * N,
+                             dl_picked ? dl_picked + (size_t)t * k : nullptr, aux, dl);
   if (!dx) return;                        // the caller forms the router's share of dx as a product with dL
   for (int c0 = 0; c0 < d; c0 += 256) {
     const int c = c0 + lane * 4;
@@ -838,10 +829,14 @@ int launch_router_logits(const bigmac_dims& D, const void* x, const float* w_gat
   return BIGMAC_OK;
 }
 
-int launch_topk_gate(const bigmac_dims& D, const float* logits, int32_t* topk_idx, float* topk_w, hipStream_t s) {
-  const dim3 g2((D.T + 3) / 4), block(256);
+int launch_topk_gate(const bigmac_dims& D, const float* logits, int32_t* topk_idx, float* topk_w, hipStream_t s, int32_t* counts) {
+  const SortChunks sc = counts ? sort_chunks(D.T, D.k, D.N) : SortChunks{};
+  if (counts && !sc.threads) return BIGMAC_ERR_INVALID_ARG;
+  // two tokens per wavefront, up to 16 wavefronts: several wavefronts on a SIMD hide each other's latencies
+  const int tokens = counts ? sc.tokens : 4, threads = counts ? std::min(1024, std::max(256, (tokens + 1) / 2 * 64)) : 256;
+  const dim3 g2(counts ? sc.count * sc.parts : (D.T + tokens - 1) / tokens), block(threads);   // (a part past the end counts nothing)
   const int per = (D.N + 63) / 64;
-#define BIGMAC_TOPK(P) hipLaunchKernelGGL(topk_gate_kernel<P>, g2, block, 0, s, logits, D.T, D.N, D.k, topk_idx, topk_w)
+#define BIGMAC_TOPK(P) hipLaunchKernelGGL(topk_gate_kernel<P>, g2, block, 0, s, logits, D.T, D.N, D.k, tokens, topk_idx, topk_w, counts)
   if (per <= 1) BIGMAC_TOPK(1);
   else if (per <= 2) BIGMAC_TOPK(2);
   else if (per <= 4) BIGMAC_TOPK(4);
@@ -850,6 +845,18 @@ int launch_topk_gate(const bigmac_dims& D, const float* logits, int32_t* topk_id
 #undef BIGMAC_TOPK
   BIGMAC_CHECK_LAUNCH();
   return BIGMAC_OK;
+}
+
+// How the router's share of dx is formed (see launch_route_backward): on the matrix cores from the dense
+// dL (N is the product's K: whole k tiles), or from the picked entries with w_gate's rows in the LDS.
+static bool route_dx_by_product(const bigmac_dims& D, bool with_loss) { return with_loss && D.dtype == BIGMAC_BF16 && D.N % 32 == 0; }
+static bool route_dx_tiled(const bigmac_dims& D, bool with_loss) { return !with_loss && D.N <= 128 && D.k <= 64 && D.d % 4 == 0; }
+
+bool gate_backward_job(const bigmac_dims& D, const int32_t* topk_idx, const float* logits, const float* share, void* dL_out, void* ws, GateBackward* out) {
+  const bool tiled = route_dx_tiled(D, logits != nullptr);
+  if (D.dtype != BIGMAC_BF16 || D.N > 128 || !(tiled || route_dx_by_product(D, logits != nullptr))) return false;
+  *out = {topk_idx, logits, share, logits ? D.aux_alpha * (float)D.N / (float)D.T : 0.0f, D.N, (bf16_t*)dL_out, tiled ? (float*)ws : nullptr};
+  return true;
 }
 
 size_t route_backward_ws_bytes(const bigmac_dims& D) {
@@ -864,12 +871,12 @@ __global__ void router_to_bf16_kernel(const float* __restrict__ in, bf16_t* __re
 
 int launch_route_backward(const bigmac_dims& D, const float* w_gate, const int32_t* topk_idx,
                           const float* topk_w, const float* dgate, const float* logits, const float* share,
-                          float* dx_f32, void* dL_out, void* ws, hipStream_t s) {
+                          float* dx_f32, void* dL_out, void* ws, hipStream_t s, bool gate_done) {
   // With the loss every entry of a dL row is non-zero, and the router's share of dx is the dense
   // product dL w_gate^T: on bf16 runs it goes to the matrix cores (dL is stored in bf16 anyway,
   // w_gate is rounded to bf16 for this product only); otherwise the kernel walks all N rows.
-  const bool by_product = logits && D.dtype == BIGMAC_BF16 && D.N % 32 == 0;   // N is the product's K: whole k tiles
-  const bool tiled = !logits && D.N <= 128 && D.k <= 64 && D.d % 4 == 0;         // w_gate rows fit the LDS tile
+  const bool by_product = route_dx_by_product(D, logits != nullptr), tiled = route_dx_tiled(D, logits != nullptr);
+  if (gate_done && !by_product && !tiled) return BIGMAC_ERR_INVALID_ARG;
   float* wg_t = (float*)ws;
   if (tiled) {
     // nothing to prepare: the second kernel reads w_gate as it lies
@@ -894,7 +901,9 @@ int launch_route_backward(const bigmac_dims& D, const float* w_gate, const int32
   else if (per <= 4) BIGMAC_GATE_BWD(DT, 4); \
   else if (per <= 8) BIGMAC_GATE_BWD(DT, 8); \
   else BIGMAC_GATE_BWD(DT, 16)
-  if (D.dtype == BIGMAC_BF16) {
+  if (gate_done) {
+    // the combine's backward wrote dL and the picked entries
+  } else if (D.dtype == BIGMAC_BF16) {
     BIGMAC_GATE_BWD_PER(bf16_t);
   } else {
     BIGMAC_GATE_BWD_PER(float);
@@ -943,7 +952,7 @@ static int aux_parts(int T) {
 size_t aux_loss_ws_bytes(const bigmac_dims& D) { return align_up((size_t)aux_parts(D.T) * D.N * sizeof(float)); }
 
 int launch_aux_loss(const bigmac_dims& D, const float* logits, const int32_t* topk_idx, float* share, float* loss,
-                    float* dlogits, void* ws, hipStream_t s) {
+                    float* dlogits, void* ws, hipStream_t s, const int32_t* counts) {
   float* partial = (float*)ws;
   const int parts = aux_parts(D.T), per = (D.N + 63) / 64;
 #define BIGMAC_AUX_PER(KERNEL, GRID, ...)                                                         \
@@ -956,7 +965,7 @@ int launch_aux_loss(const bigmac_dims& D, const float* logits, const int32_t* to
   BIGMAC_CHECK_LAUNCH();
   int NP = 1;
   while (NP < D.N) NP <<= 1;
-  hipLaunchKernelGGL(aux_finish_kernel, dim3(1), dim3(1024), 0, s, topk_idx, partial, parts, D.T, D.N, NP, D.k, D.aux_alpha, share, loss);
+  hipLaunchKernelGGL(aux_finish_kernel, dim3(1), dim3(1024), 0, s, topk_idx, counts, counts ? sort_chunks(D.T, D.k, D.N).count * sort_chunks(D.T, D.k, D.N).parts : 0, partial, parts, D.T, D.N, NP, D.k, D.aux_alpha, share, loss);
   BIGMAC_CHECK_LAUNCH();
   if (dlogits) {
     const float scale = D.aux_alpha * (float)D.N / (float)D.T;

@@ -2,7 +2,7 @@
 // ragged-K one, built by one workgroup of 1024 threads: by the kernel of its own in gemm.hip, or at
 // the end of the counting sort's scan, which has the group offsets at hand.
 #pragma once
-#include <hip/hip_runtime.h>
+#include "wave.hpp"
 
 namespace bigmac {
 
@@ -13,6 +13,8 @@ constexpr int TILE_MAP_K_ROWS = 32;   // rows per k tile in the cost of a group 
 struct TileMapJobs {   // up to two maps (different tile heights) from one set of offsets; map == NULL: none
   int tile_rows[2];
   int* map[2];
+  unsigned* clear;     // optional: this many ints from here on are zeroed by the same launch (the products' tile counters)
+  int clear_ints;
 };
 
 // The map for at most 64 groups by one wavefront (lane = group): shuffles take the place of the
@@ -201,11 +203,9 @@ __device__ __forceinline__ void build_tile_map_block(const int* offsets, int gro
       for (int u = 0; u < 8; ++u) {
         if (r0 + u >= groups) break;
         unsigned key = (load << 3) | (unsigned)lane8;
-#pragma unroll
-        for (int off = 1; off < 8; off <<= 1) {
-          const unsigned o = (unsigned)__shfl_xor((int)key, off, 64);
-          key = o < key ? o : key;
-        }
+        key = min(key, from_lane_xor<1>(key, g));
+        key = min(key, from_lane_xor<2>(key, g));
+        key = min(key, from_lane_xor<4>(key, g));
         const int best = (int)(key & 7u);
         if (lane8 == best) {
           if (g < 8) {

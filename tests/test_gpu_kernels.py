@@ -46,3 +46,37 @@ def test_f32_expert_products(rows, r, h):
     # a sum of K fp32 products is off by about sqrt(K) 2^-24 of its norm (2.7e-6 at K = 2048); the activation adds 4e-7
     assert rel(act, ref_a) < 5e-6
     assert rel(o, ref_o) < 1e-5
+
+
+# the sort that follows the top-k kernel's counts: chunks of 256, 512 and 1024 pairs in one to four parts, a token past
+# a part or a chunk, picks that do not divide a chunk, dropped pairs, and (600 experts) the three-kernel sort
+@pytest.mark.parametrize("T,k,N,capacity", [(1, 1, 8, 0), (8, 8, 64, 0), (33, 8, 64, 9), (129, 5, 24, 0), (257, 64, 64, 0), (1025, 6, 40, 0),
+                                            (8193, 8, 64, 900), (700, 3, 72, 0), (5000, 8, 128, 0), (90, 2, 600, 0)])
+def test_sort_after_topk(oracle, T, k, N, capacity):
+    g = torch.Generator(device=DEV).manual_seed(T + N)
+    d = r = h = 64
+    dims = B.make_dims(T, d, r, N, k, h, B.BF16, capacity=capacity)
+    bf = dict(dtype=torch.bfloat16, device=DEV)
+    x = torch.randn((T, d), generator=g, device=DEV).to(torch.bfloat16)
+    w_gate = torch.randn((d, N), generator=g, device=DEV) * 0.1
+    bias = -1.2 * torch.log1p(torch.arange(N, device=DEV).float())
+    w = [torch.zeros(s, **bf) for s in ((d, r), (r, d), (N, r, h), (N, h, r))]
+    y = torch.empty((T, d), device=DEV)
+    saved = B.alloc_bytes(B.workspace_bytes(dims, B.WS_SAVED))
+    B.bigmac_layer_forward(dims, B.make_params(w[0], w[1], w_gate, bias, w[2], w[3]), x, y, saved,
+                           B.alloc_bytes(B.workspace_bytes(dims, B.WS_LAYER_TRAIN)))
+    at = B.saved_layout(dims)
+    part = lambda n, size: saved[at[n]:at[n] + 4 * size].view(torch.int32).cpu().numpy()
+    idx, off, slot = part("topk_idx", T * k).reshape(T, k), part("expert_offsets", N + 1), part("slot_of", T * k)
+    logits = oracle.router_logits(x.float().cpu().numpy(), w_gate.cpu().numpy(), bias.cpu().numpy())
+    order = (-logits.astype("f8")).argsort(axis=1, kind="stable")[:, :k]       # greater first, ties to the lower index
+    assert (idx == order).all()
+    r_off, r_slot, _ = oracle.permutation(idx, N)
+    if capacity:
+        held = (r_off[1:] - r_off[:-1]).clip(max=capacity)
+        first = held.cumsum() - held
+        rank = r_slot.reshape(T, k) - r_off[idx]
+        assert (off[1:] - off[:-1] == held).all()
+        assert (slot.reshape(T, k) == (rank < capacity) * (first[idx] + rank + 1) - 1).all()
+    else:
+        assert (off == r_off).all() and (slot == r_slot.reshape(-1)).all()
