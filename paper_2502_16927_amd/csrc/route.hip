@@ -372,9 +372,12 @@ __global__ __launch_bounds__(256) void router_logits_pipelined_kernel(const XT* 
   }
 }
 
-// (logit, expert) as one number: the greater key comes first, equal logits (-0 counts as 0) by lower index
-__device__ __forceinline__ unsigned long long pick_key(float logit, int expert) {
-  const unsigned u = __float_as_uint(logit + 0.0f);
+// (logit, expert) as one number: the greater key comes first, equal logits (-0 counts as 0) by lower index.  NaN logits
+// have a place in that order too (by their sign, past the infinities), and a lane past the N experts comes after every
+// expert, so that whatever the logits are the k <= N picks are k different experts: the sort writes to slots counted by them.
+__device__ __forceinline__ unsigned long long pick_key(const float* row, int expert, int N) {
+  if (expert >= N) return (unsigned)~expert;
+  const unsigned u = __float_as_uint(row[expert] + 0.0f);
   return ((unsigned long long)((u & 0x80000000u) ? ~u : u | 0x80000000u) << 32) | (unsigned)~expert;
 }
 __device__ __forceinline__ float key_logit(unsigned long long key) {
@@ -444,7 +447,7 @@ __global__ __launch_bounds__(1024) void topk_gate_kernel(const float* __restrict
 #pragma unroll
       for (int u = 0; u < U; ++u) {     // (tokens past the chunk repeat the last one's loads and are not finished)
         const float* row = logits + (size_t)min(t + u * step, t_end - 1) * N;
-        key[u] = pick_key(lane < N ? row[lane] : -INFINITY, lane);
+        key[u] = pick_key(row, lane, N);
       }
       if constexpr (PER == 1) {
         sort_keys<64>(key, lane);
@@ -453,7 +456,7 @@ __global__ __launch_bounds__(1024) void topk_gate_kernel(const float* __restrict
 #pragma unroll
         for (int u = 0; u < U; ++u) {
           const float* row = logits + (size_t)min(t + u * step, t_end - 1) * N;
-          upper[u] = pick_key(64 + lane < N ? row[64 + lane] : -INFINITY, 64 + lane);
+          upper[u] = pick_key(row, 64 + lane, N);
         }
         sort_keys<64>(key, lane);
         sort_keys<64>(upper, lane);

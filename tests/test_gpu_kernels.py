@@ -80,3 +80,25 @@ def test_sort_after_topk(oracle, T, k, N, capacity):
         assert (slot.reshape(T, k) == (rank < capacity) * (first[idx] + rank + 1) - 1).all()
     else:
         assert (off == r_off).all() and (slot == r_slot.reshape(-1)).all()
+
+
+# logits of every kind, NaN of either sign and infinities among them: the picks are still k different experts (24 and 72
+# leave lanes past the last expert in the first and in the second half of the network), and finite rows are picked as ever
+@pytest.mark.parametrize("N,k", [(24, 24), (24, 5), (72, 64), (72, 8)])
+def test_picks_of_non_finite_logits(N, k):
+    T, d = 70, 64
+    g = torch.Generator(device=DEV).manual_seed(N + k)
+    x = torch.zeros((T, d), dtype=torch.float32, device=DEV)
+    x[torch.arange(T), torch.arange(T) % d] = 1.0
+    w_gate = torch.randn((d, N), generator=g, device=DEV)
+    odd = torch.tensor([float("nan"), -float("nan"), float("inf"), -float("inf")], device=DEV)
+    bias = torch.randn(N, generator=g, device=DEV)
+    where = torch.randperm(N, generator=g, device=DEV)[:N // 2]
+    dims = B.make_dims(T, d, d, N, k, d, B.F32)
+    idx, w, logits = torch.empty((T, k), dtype=torch.int32, device=DEV), torch.empty((T, k), device=DEV), torch.empty((T, N), device=DEV)
+    B.bigmac_route(dims, x, w_gate, bias, idx, w, logits)
+    assert (idx.long() == torch.sort(logits, dim=1, descending=True, stable=True).indices[:, :k]).all()
+    bias[where] = odd[torch.arange(len(where), device=DEV) % 4]
+    B.bigmac_route(dims, x, w_gate, bias, idx, w, logits)
+    assert logits.isnan().any() and ((idx >= 0) & (idx < N)).all()
+    assert (idx.sort(dim=1).values.diff(dim=1) > 0).all()
