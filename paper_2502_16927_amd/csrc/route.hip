@@ -148,7 +148,7 @@ __device__ __forceinline__ void router_static_for(F&& f) {
 // multiply-adds per lane of the current one run.  Token rows past T and router rows past d lie
 // outside the buffer ranges and arrive as zeros; they are never used anyway.
 #define BIGMAC_ROUTER_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (((n) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
-// TB = tokens per wavefront (8 for large T; 1 or 2 when T is small, so that the few tokens still
+// TB = tokens per wavefront (8 for large T; 1, 2 or 4 when T is small, so that the few tokens still
 // spread over many CUs).  The summation order does not depend on it.
 // SL = 16-expert slices a workgroup computes one after the other on its token tile: the next
 // slice's first tiles are requested before the reduction of the current one, so the fixed cost
@@ -807,10 +807,18 @@ int launch_router_logits(const bigmac_dims& D, const void* x, const float* w_gat
     BIGMAC_CHECK_LAUNCH();
     return BIGMAC_OK;
   }
-  // tokens per wavefront: 8 unless that leaves most CUs without a workgroup; two expert slices per
-  // workgroup while that still gives every CU two workgroups
-  const long groups8 = (long)((D.T + 31) / 32) * gy;
-  const int tb = groups8 >= 1024 ? 8 : (groups8 * 4 >= 512 ? 2 : 1);
+  // Tokens per wavefront: a wavefront's LDS reads of the router columns are spread over them and every workgroup reads its
+  // columns from the L2 once, so more is cheaper until CUs go idle: the fewest that need at most three workgroups per CU.  Eight
+  // where four would need more, except between two and four workgroups of eight per CU, where the last round of them is nearly
+  // empty.  Measured with the top-k at d 4096, N 64 (1 / 2 / 4 / 8 tokens, us): T 500 17.5 / 19.2 / 22.7 / 31.7, T 1024
+  // 26.5 / 19.4 / 22.9 / 31.6, T 2048 44.2 / 32.3 / 25.0 / 32.1, T 3001 62.0 / 41.6 / 33.1 / 35.3, T 4096 81.3 / 54.5 / 41.6 /
+  // 37.5, T 6001 117.5 / 75.9 / 57.6 / 61.4, T 8192 156 / 99.5 / 75.7 / 73.2.  Two expert slices per
+  // workgroup while that still gives every CU two workgroups.
+  auto workgroups = [&](int tokens) { return (long)((D.T + 4 * tokens - 1) / (4 * tokens)) * gy; };
+  const long groups8 = workgroups(8);
+  int tb = 1;
+  while (tb < 8 && workgroups(tb) > 768) tb *= 2;
+  if (tb == 8 && groups8 > 512 && groups8 < 1024) tb = 4;
   const int sl = tb == 8 && gy >= 2 && (long)((D.T + 31) / 32) * ((gy + 1) / 2) >= 512 ? ROUTER_SLICES : 1;
 #define BIGMAC_ROUTER(XT, TBV, SLV)                                                                                  \
   hipLaunchKernelGGL((router_logits_pipelined_kernel<XT, TBV, SLV>),                                                  \
@@ -819,11 +827,13 @@ int launch_router_logits(const bigmac_dims& D, const void* x, const float* w_gat
   if (D.dtype == BIGMAC_BF16) {
     if (tb == 8 && sl == 2) BIGMAC_ROUTER(bf16_t, 8, 2);
     else if (tb == 8) BIGMAC_ROUTER(bf16_t, 8, 1);
+    else if (tb == 4) BIGMAC_ROUTER(bf16_t, 4, 1);
     else if (tb == 2) BIGMAC_ROUTER(bf16_t, 2, 1);
     else BIGMAC_ROUTER(bf16_t, 1, 1);
   } else {
     if (tb == 8 && sl == 2) BIGMAC_ROUTER(float, 8, 2);
     else if (tb == 8) BIGMAC_ROUTER(float, 8, 1);
+    else if (tb == 4) BIGMAC_ROUTER(float, 4, 1);
     else if (tb == 2) BIGMAC_ROUTER(float, 2, 1);
     else BIGMAC_ROUTER(float, 1, 1);
   }

@@ -102,3 +102,19 @@ def test_picks_of_non_finite_logits(N, k):
     B.bigmac_route(dims, x, w_gate, bias, idx, w, logits)
     assert logits.isnan().any() and ((idx >= 0) & (idx < N)).all()
     assert (idx.sort(dim=1).values.diff(dim=1) > 0).all()
+
+
+# router logits, bit for bit: 1, 2, 4 and 8 tokens per wavefront, either side of each line (768 workgroups; 512 and 1024 of eight)
+@pytest.mark.parametrize("dtype", [B.BF16, B.F32])
+@pytest.mark.parametrize("T,N", [(384, 128), (385, 128), (769, 128), (1537, 128), (2049, 128), (4065, 128), (6145, 12), (3073, 40)])
+def test_router_logits_tokens_per_wavefront(oracle, T, N, dtype):
+    d = 192
+    g = torch.Generator(device=DEV).manual_seed(T + N)
+    x = torch.randn((T, d), generator=g, device=DEV).to(torch.bfloat16 if dtype == B.BF16 else torch.float32)
+    w_gate, bias = torch.randn((d, N), generator=g, device=DEV), torch.randn(N, generator=g, device=DEV)
+    dims = B.make_dims(T, d, 64, N, 1, 64, dtype)
+    idx, w, logits = torch.empty((T, 1), dtype=torch.int32, device=DEV), torch.empty((T, 1), device=DEV), torch.empty((T, N), device=DEV)
+    B.bigmac_route(dims, x, w_gate, bias, idx, w, logits)
+    ref = torch.from_numpy(oracle.router_logits(x.float().cpu().numpy(), w_gate.cpu().numpy(), bias.cpu().numpy()))
+    assert torch.equal(logits.cpu().view(torch.int32), ref.view(torch.int32))
+    assert (idx[:, 0].cpu().long() == ref.argmax(dim=1)).all()
