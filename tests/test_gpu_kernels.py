@@ -118,3 +118,18 @@ def test_router_logits_tokens_per_wavefront(oracle, T, N, dtype):
     ref = torch.from_numpy(oracle.router_logits(x.float().cpu().numpy(), w_gate.cpu().numpy(), bias.cpu().numpy()))
     assert torch.equal(logits.cpu().view(torch.int32), ref.view(torch.int32))
     assert (idx[:, 0].cpu().long() == ref.argmax(dim=1)).all()
+
+
+# the summed slices of a dense product, to bf16 as to fp32 (the same sums in the same order): 2, 5 and 10 slices, few elements
+@pytest.mark.parametrize("T,d,r", [(1, 64, 256), (3, 2560, 640), (33, 1280, 1280), (5, 192, 2048)])
+def test_slice_sums_to_bf16(T, d, r):
+    g = torch.Generator(device=DEV).manual_seed(T + r)
+    w = [(torch.randn(s, generator=g, device=DEV) * 0.05).to(torch.bfloat16) for s in ((d, r), (r, d), (8, r, 64), (8, 64, r))]
+    x, w_gate = torch.randn((T, d), generator=g, device=DEV).to(torch.bfloat16), torch.randn((d, 8), generator=g, device=DEV)
+    y = {}
+    for dtype, flags in ((torch.float32, 0), (torch.bfloat16, B.FLAG_OUT_BF16)):
+        dims = B.make_dims(T, d, r, 8, 2, 64, B.BF16, B.ORDER_DCCA, flags)
+        y[dtype] = torch.empty((T, d), dtype=dtype, device=DEV)
+        B.bigmac_layer_forward(dims, B.make_params(w[0], w[1], w_gate, None, w[2], w[3]), x, y[dtype], None,
+                               B.alloc_bytes(B.workspace_bytes(dims, B.WS_LAYER_FORWARD)))
+    assert y[torch.float32].abs().max() > 0 and torch.equal(y[torch.float32].to(torch.bfloat16), y[torch.bfloat16])
