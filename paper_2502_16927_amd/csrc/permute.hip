@@ -19,6 +19,7 @@ namespace bigmac {
 namespace {
 
 constexpr int PP_MAX_EXPERTS = 512;     // experts up to which the one-pass sort runs (32 KB of counters at 16 wavefronts)
+constexpr int PP_SELF_PAIRS = 4096;     // pairs up to which its workgroups count for themselves (see perm_place_kernel)
 
 // The sort of many pairs or experts (see sort_chunks): count, one-workgroup scan, rank.
 // Flat pairs per chunk: small chunks give the count and rank kernels more
@@ -178,6 +179,12 @@ __global__ __launch_bounds__(64) void perm_rank_kernel(const int32_t* __restrict
 // expert, one writer each) and in earlier lanes of its wavefront (ballots): no atomics, flat order.
 // A capacity drops a pair whose slot falls past its expert's range: slot_of = -1, no src_of entry.
 // One workgroup beyond the chunks writes the offsets and the tile maps and clears the tile counters.
+// counts == NULL: up to PP_SELF_PAIRS pairs, nothing is counted in front and no scratch is read or written: every
+// workgroup counts all pairs itself with LDS atomics (order-free).  Bound by latency, so one launch in place of
+// two is the gain: the sort of bigmac_dispatch 5.5 -> 3.5 us at 256 pairs and 64 experts, 6.9 -> 4.5 at 4000, 7.4 -> 5.1 at
+// 4096 and 128 experts (replayed from a graph).  The line: with k = 1 and every pair on one expert the atomics of a wavefront go
+// one after the other; at 4096 pairs that costs as much as the launch saves (6.9 us), at 6144 it is 8.6 against 7.3 us
+// (spread pairs, k 8: 5.1 against 7.4).
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void perm_place_kernel(const int32_t* __restrict__ idx, int Tk, int pairs_per_chunk, int nchunks, int parts, int N, int NP, int nbits,
                                                              int capacity, const int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
@@ -195,31 +202,48 @@ __global__ __launch_bounds__(THREADS) void perm_place_kernel(const int32_t* __re
   const bool live = placing && tid < pairs_per_chunk && f < Tk;
   const int e = live ? idx[f] : 0;
   for (int i = tid; i < WAVES * N; i += THREADS) cnt[i] = 0;
-  // column sums of the counters: THREADS / width groups of chunks x width experts at a time
-  const int width = NP < THREADS ? NP : THREADS, G = THREADS / width, g = tid / width, rows = nchunks * parts;
-  for (int e0 = 0; e0 < N; e0 += width) {
-    const int ee = e0 + tid % width;
-    int total = 0, before = 0;
-    if (ee < N)
-      for (int c0 = g; c0 < rows; c0 += 8 * G) {
-        int v[8];
+  if (counts) {
+    // column sums of the counters: THREADS / width groups of chunks x width experts at a time
+    const int width = NP < THREADS ? NP : THREADS, G = THREADS / width, g = tid / width, rows = nchunks * parts;
+    for (int e0 = 0; e0 < N; e0 += width) {
+      const int ee = e0 + tid % width;
+      int total = 0, before = 0;
+      if (ee < N)
+        for (int c0 = g; c0 < rows; c0 += 8 * G) {
+          int v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = c0 + u * G < rows ? counts[(size_t)(c0 + u * G) * N + ee] : 0;
+          for (int u = 0; u < 8; ++u) v[u] = c0 + u * G < rows ? counts[(size_t)(c0 + u * G) * N + ee] : 0;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          total += v[u];
-          before += c0 + u * G < b * parts ? v[u] : 0;
+          for (int u = 0; u < 8; ++u) {
+            total += v[u];
+            before += c0 + u * G < b * parts ? v[u] : 0;
+          }
         }
+      group_total[tid] = total;
+      group_earlier[tid] = before;
+      __syncthreads();
+      if (tid < width && ee < N) {
+        int t = 0, w = 0;
+        for (int h = 0; h < G; ++h) { t += group_total[h * width + tid]; w += group_earlier[h * width + tid]; }
+        totals[ee] = t;
+        earlier[ee] = w;
       }
-    group_total[tid] = total;
-    group_earlier[tid] = before;
-    __syncthreads();
-    if (tid < width && ee < N) {
-      int t = 0, w = 0;
-      for (int h = 0; h < G; ++h) { t += group_total[h * width + tid]; w += group_earlier[h * width + tid]; }
-      totals[ee] = t;
-      earlier[ee] = w;
+      __syncthreads();
     }
+  } else {
+    for (int i = tid; i < N; i += THREADS) totals[i] = earlier[i] = 0;
+    __syncthreads();
+    const int first = b * pairs_per_chunk;
+    for (int f0 = tid; f0 < Tk; f0 += 8 * THREADS) {
+      int v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = f0 + u * THREADS < Tk ? idx[f0 + u * THREADS] : -1;
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (v[u] >= 0) atomicAdd(f0 + u * THREADS < first ? &earlier[v[u]] : &totals[v[u]], 1);
+    }
+    __syncthreads();
+    for (int i = tid; i < N; i += THREADS) totals[i] += earlier[i];
     __syncthreads();
   }
   // first slots: exclusive scan of the experts' held pairs, THREADS experts at a time
@@ -616,13 +640,14 @@ int launch_build_permutation(int T, int k, int N, int capacity, const int32_t* t
     int nbits = 0, NP = 1;
     while ((1 << nbits) < N) ++nbits;
     while (NP < N) NP <<= 1;
-    if (!counted) {
+    const int32_t* counts = counted || Tk > PP_SELF_PAIRS ? (const int32_t*)ws : nullptr;
+    if (counts && !counted) {
       hipLaunchKernelGGL(perm_count_kernel, dim3(sc.count * sc.parts), dim3(256), N * sizeof(int), s, topk_idx, Tk, N, part, (int32_t*)ws);
       BIGMAC_CHECK_LAUNCH();
     }
 #define BIGMAC_PLACE(THREADS)                                                                                                        \
   hipLaunchKernelGGL(perm_place_kernel<THREADS>, dim3(sc.count + 1), dim3(THREADS), THREADS / 64 * N * sizeof(int), s, topk_idx, Tk, pairs, \
-                     sc.count, sc.parts, N, NP, nbits, capacity, (const int32_t*)ws, expert_offsets, slot_of, src_of, maps)
+                     sc.count, sc.parts, N, NP, nbits, capacity, counts, expert_offsets, slot_of, src_of, maps)
     if (sc.threads == 256) BIGMAC_PLACE(256);
     else if (sc.threads == 512) BIGMAC_PLACE(512);
     else BIGMAC_PLACE(1024);

@@ -82,6 +82,36 @@ def test_sort_after_topk(oracle, T, k, N, capacity):
         assert (off == r_off).all() and (slot == r_slot.reshape(-1)).all()
 
 
+# the sort of up to 4096 pairs (and 512 experts) counts for itself: the workspace keeps its contents.  One pair; chunks of 256 and 1024
+# with a remainder and without; the last pair count on that path and the first past it; all pairs on one expert; dropped pairs
+@pytest.mark.parametrize("T,k,N,capacity,popular", [(1, 1, 8, 0, 0), (32, 8, 64, 0, 0), (4096, 1, 64, 0, 64), (585, 7, 40, 70, 3), (512, 8, 128, 0, 0),
+                                                    (4096, 1, 512, 1000, 512), (1365, 3, 300, 9, 20), (4097, 1, 65, 0, 0), (241, 17, 500, 0, 0)])
+def test_dispatch_sort_of_few_pairs(oracle, T, k, N, capacity, popular):
+    g = torch.Generator(device=DEV).manual_seed(T + N)
+    score = torch.rand((T, N), generator=g, device=DEV)
+    if popular:                                     # this many times likelier to be picked
+        score[:, N // 2] *= popular
+    idx = score.topk(k, dim=1).indices.to(torch.int32)
+    dims = B.make_dims(T, 64, 64, N, k, 64, B.BF16, capacity=capacity)
+    off, (slot, src) = torch.empty(N + 1, dtype=torch.int32, device=DEV), torch.full((2, T * k), -7, dtype=torch.int32, device=DEV)
+    ws = B.alloc_bytes(B.workspace_bytes(dims, B.WS_DISPATCH)).fill_(165)
+    B.bigmac_dispatch(dims, None, idx, None, off, slot, src, ws)
+    if T * k <= 4096:
+        assert bool((ws == 165).all())
+    idx, off, slot, src = idx.cpu().numpy(), off.cpu().numpy(), slot.cpu().numpy(), src.cpu().numpy()
+    r_off, r_slot, r_src = oracle.permutation(idx, N)
+    if capacity:
+        held = (r_off[1:] - r_off[:-1]).clip(max=capacity)
+        first = held.cumsum() - held
+        rank = r_slot.reshape(T, k) - r_off[idx]
+        assert (off[1:] - off[:-1] == held).all()
+        assert (slot.reshape(T, k) == (rank < capacity) * (first[idx] + rank + 1) - 1).all()
+        kept = slot >= 0
+        assert (src[slot[kept]] == kept.nonzero()[0]).all() and (src[off[N]:] == -7).all()
+    else:
+        assert (off == r_off).all() and (slot == r_slot.reshape(-1)).all() and (src == r_src).all()
+
+
 # logits of every kind, NaN of either sign and infinities among them: the picks are still k different experts (24 and 72
 # leave lanes past the last expert in the first and in the second half of the network), and finite rows are picked as ever
 @pytest.mark.parametrize("N,k", [(24, 24), (24, 5), (72, 64), (72, 8)])
