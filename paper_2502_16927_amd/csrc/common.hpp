@@ -206,7 +206,11 @@ int launch_reduce_partials_bf16(const float* part, int nslices, size_t n, void* 
 // ----------------------------------------------------------------------------- route ----
 int launch_router_logits(const bigmac_dims& D, const void* x, const float* w_gate, const float* bias,
                          float* logits, hipStream_t s);
-// counts (optional): the pairs per part of a chunk and expert, for launch_build_permutation (D.T, D.k, D.N must have sort_chunks)
+// counts (optional, where topk_counts holds): the pairs per part of a chunk and expert, for launch_build_permutation
+struct TopkGrid {
+  int workgroups, threads, tokens;   // tokens per workgroup
+};
+TopkGrid topk_grid(int T, int k, int N, bool counting);
 int launch_topk_gate(const bigmac_dims& D, const float* logits, int32_t* topk_idx, float* topk_w, hipStream_t s, int32_t* counts = nullptr);
 // Gate backward (softmax over the k picked logits) and the router's share of dx:
 //   dlogit[t,j] = w[t,j] (dgate[t,j] - sum_m w[t,m] dgate[t,m])
@@ -245,7 +249,8 @@ size_t permutation_ws_bytes(int T, int k, int N);
 struct SortChunks {
   int threads, tokens, parts, count;   // threads per workgroup, tokens per part of a chunk, parts per chunk, chunks; threads == 0: sorted another way
 };
-SortChunks sort_chunks(int T, int k, int N);
+bool topk_counts(int T, int k, int N);                    // whether the top-k kernel counts the chunks' pairs in a layer call
+SortChunks sort_chunks(int T, int k, int N, bool counted);   // counted: by the top-k kernel
 // tile_maps (optional): tile maps of the expert offsets, built by the same launch that finds them
 int launch_build_permutation(int T, int k, int N, int capacity, const int32_t* topk_idx, int32_t* expert_offsets,
                              int32_t* slot_of, int32_t* src_of, void* ws, hipStream_t s, const TileMapJobs* tile_maps = nullptr,

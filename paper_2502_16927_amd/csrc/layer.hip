@@ -641,8 +641,8 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
   const bool aux = D->aux_alpha > 0.0f;                       // the loss lives in the saved block
   float* logits = aux ? (float*)(sv + S.logits) : (float*)(wsb + F.logits);
 
-  // the top-k kernel counts the pairs of the sort's chunks on its way
-  int32_t* chunk_counts = sort_chunks(D->T, D->k, D->N).threads ? (int32_t*)(wsb + F.perm) : nullptr;
+  // the top-k kernel may count the pairs of the sort's chunks on its way
+  int32_t* chunk_counts = topk_counts(D->T, D->k, D->N) ? (int32_t*)(wsb + F.perm) : nullptr;
   const bool low_router = route_low(*D);
   // x' is the workspace's piece, or (router on x': the backward pass reads it again) the saved block's
   void* x_low_buf = (low_router && saved) ? (void*)(sv + S.x_low) : (void*)(wsb + F.x_low);

@@ -7,6 +7,7 @@
 #include "tile_map.hpp"
 #include "wave.hpp"
 
+#include <algorithm>
 #include <atomic>
 
 // Scratch of the allocation-free dispatch (bigmac_dispatch_static): the per-chunk expert counters
@@ -599,12 +600,20 @@ int launch_ragged_colsum(int dtype, const void* src, long ld, int cols, const in
   return BIGMAC_OK;
 }
 
+// In a layer call the top-k kernel counts the pairs of the tokens it picks for, where that is the cheaper way: up to
+// PP_SELF_PAIRS pairs the sort needs no counts, and past 128 experts the top-k ranks by broadcast and wants many small
+// workgroups, for which there would be too many rows of counters to add up (the two kernels, before the ranking lost its
+// branches: 65536 tokens, 256 experts 564 us counting against 459 + 5; 1024 tokens, 512 experts 2273 against 106).
+bool topk_counts(int T, int k, int N) { return N <= 128 && (long)T * k > PP_SELF_PAIRS && sort_chunks(T, k, N, true).threads; }
+
 // Chunks of the one-pass sort: whole tokens, at most `threads` pairs.  Few pairs per chunk
-// give the sort more workgroups, few chunks give each of them less to add up.  A chunk is counted in up to four parts,
-// one row of counters each: the top-k kernel, which counts the tokens it picks for, is bound by its
-// arithmetic and wants every CU busy, so parts are added while there are at most 256 of them.
+// give the sort more workgroups, few chunks give each of them less to add up.  A chunk is counted in parts,
+// one row of counters each: up to four while there are at most 256.  The top-k kernel, whose workgroup takes a part and which is
+// bound by its own chain of exchanges, splits on while a part is more than 16 wavefronts take at once (two tokens each);
+// smaller parts cost the sort more than they give (1025 tokens, k 6: 4.8 + 6.4 us with 10 tokens a part, 4.6 + 8.3 with 5; 4096
+// tokens, k 2, 96 experts: 26.8 + 10.2 us with 128, 9.5 + 11.3 with 32).
 // More than 64 experts: 1024 threads, which is what their tile maps are built by.  threads = 0: the three-kernel sort.
-SortChunks sort_chunks(int T, int k, int N) {
+SortChunks sort_chunks(int T, int k, int N, bool counted) {
   SortChunks c = {0, 0, 0, 0};
   if (N > PP_MAX_EXPERTS) return c;
   for (int threads = N > 64 ? 1024 : 256; threads <= 1024; threads *= 2) {
@@ -612,7 +621,8 @@ SortChunks sort_chunks(int T, int k, int N) {
     const long n = ((long)T + tokens - 1) / tokens;
     if (n <= (threads == 1024 ? 512 : 160)) {
       c.threads = threads;
-      c.parts = n * 4 <= 256 && tokens >= 16 ? 4 : (n * 2 <= 256 && tokens >= 8 ? 2 : 1);
+      c.parts = 1;
+      while (n * c.parts * 2 <= 256 && tokens / (c.parts * 2) >= 4 && (c.parts < 4 || (counted && tokens / c.parts > 32))) c.parts *= 2;
       c.tokens = tokens / c.parts;
       c.count = (int)(((long)T + c.tokens * c.parts - 1) / (c.tokens * c.parts));
       break;
@@ -622,8 +632,8 @@ SortChunks sort_chunks(int T, int k, int N) {
 }
 
 size_t permutation_ws_bytes(int T, int k, int N) {
-  const SortChunks c = sort_chunks(T, k, N);
-  if (c.threads) return align_up((size_t)c.count * c.parts * N * sizeof(int32_t));
+  const SortChunks c = sort_chunks(T, k, N, false), by_topk = sort_chunks(T, k, N, topk_counts(T, k, N));
+  if (c.threads) return align_up((size_t)std::max(c.count * c.parts, by_topk.count * by_topk.parts) * N * sizeof(int32_t));
   const int chunk = perm_chunk(T * k, N);
   const size_t nchunks = ((size_t)T * k + chunk - 1) / chunk;
   return align_up(nchunks * N * sizeof(int32_t));
@@ -634,13 +644,13 @@ int launch_build_permutation(int T, int k, int N, int capacity, const int32_t* t
                              int32_t* slot_of, int32_t* src_of, void* ws, hipStream_t s, const TileMapJobs* tile_maps, bool counted) {
   if (N > 1024) return BIGMAC_ERR_UNSUPPORTED;   // one thread of the scan per expert
   const TileMapJobs maps = tile_maps ? *tile_maps : TileMapJobs{};
-  const SortChunks sc = sort_chunks(T, k, N);
+  const SortChunks sc = sort_chunks(T, k, N, counted);
   if (sc.threads) {
     const int part = sc.tokens * k, pairs = part * sc.parts, Tk = T * k;
     int nbits = 0, NP = 1;
     while ((1 << nbits) < N) ++nbits;
     while (NP < N) NP <<= 1;
-    const int32_t* counts = counted || Tk > PP_SELF_PAIRS ? (const int32_t*)ws : nullptr;
+    const int32_t* counts = Tk > PP_SELF_PAIRS ? (const int32_t*)ws : nullptr;
     if (counts && !counted) {
       hipLaunchKernelGGL(perm_count_kernel, dim3(sc.count * sc.parts), dim3(256), N * sizeof(int), s, topk_idx, Tk, N, part, (int32_t*)ws);
       BIGMAC_CHECK_LAUNCH();

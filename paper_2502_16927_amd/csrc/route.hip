@@ -407,14 +407,14 @@ __device__ __forceinline__ void sort_keys(unsigned long long (&key)[U], int lane
 
 // The k picks of each token in pick order (greater logit first, ties to the lower index) and the softmax over
 // their logits, summed in pick order.  One wavefront per token; a workgroup walks the `tokens` tokens of
-// its chunk and, if counts is given, counts their pairs per expert on the way (the sort's counters,
+// its share and, if counts is given (up to 128 experts), counts their pairs per expert on the way (the sort's counters,
 // see launch_build_permutation).  PER = logits per lane.  Up to 64 experts: one key per lane, sorted across the wavefront by a
 // bitonic network (the order is strict and total, so the result is the unique sorted sequence);
 // lanes 0 .. k-1 then hold the picks.  Up to 128: two keys per lane, both halves sorted the same way;
 // the first 64 of their union are, lane by lane, the first of (half 0 at lane l, half 1 at lane
 // 63 - l), a bitonic sequence that six more steps sort: k <= 64 picks are all there.  More: every lane
 // ranks its logits against all N by broadcast (rank = how many logits come first); ranks below k
-// are the selection.
+// are the selection.  That one is bound by its comparisons, which take no branches (1024 tokens, 512 experts: 106 us with, 52 without).
 // The network is a serial chain of 21 (27) exchanges and bound by its latency: keys of 64 bits cost one
 // comparison, partners are read by DPP moves and row swaps instead of through the LDS, and a
 // wavefront takes two tokens at a time (8192 tokens, 64 experts, counting included: 15.0 us by wavefronts
@@ -422,9 +422,9 @@ __device__ __forceinline__ void sort_keys(unsigned long long (&key)[U], int lane
 template <int PER>
 __global__ __launch_bounds__(1024) void topk_gate_kernel(const float* __restrict__ logits, int T, int N, int k, int tokens,
                                                          int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int32_t* __restrict__ counts) {
-  __shared__ int hist[1024];
+  __shared__ int hist[128];
   const int lane = threadIdx.x & 63;
-  if (counts) {
+  if (PER <= 2 && counts) {
     for (int e = threadIdx.x; e < N; e += blockDim.x) hist[e] = 0;
     __syncthreads();
   }
@@ -436,7 +436,7 @@ __global__ __launch_bounds__(1024) void topk_gate_kernel(const float* __restrict
     if (lane < k) {
       topk_idx[(size_t)t * k + lane] = expert;
       topk_w[(size_t)t * k + lane] = e / s;
-      if (counts) atomicAdd(&hist[expert], 1);
+      if (PER <= 2 && counts) atomicAdd(&hist[expert], 1);
     }
   };
   const int t_end = min(T, (int)(blockIdx.x + 1) * tokens), step = blockDim.x >> 6;
@@ -488,7 +488,7 @@ __global__ __launch_bounds__(1024) void topk_gate_kernel(const float* __restrict
           const float o = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[io]), l));
           const int on = io * 64 + l;
 #pragma unroll
-          for (int i = 0; i < PER; ++i) rank[i] += (o > v[i] || (o == v[i] && on < i * 64 + lane)) ? 1 : 0;
+          for (int i = 0; i < PER; ++i) rank[i] += (int)(o > v[i]) | ((int)(o == v[i]) & (int)(on < i * 64 + lane));   // (no branches)
         }
       }
       // lane j < k collects the j-th pick: its index and logit
@@ -508,7 +508,7 @@ __global__ __launch_bounds__(1024) void topk_gate_kernel(const float* __restrict
       finish(t, selv, seli);
     }
   }
-  if (counts) {
+  if (PER <= 2 && counts) {
     __syncthreads();
     for (int e = threadIdx.x; e < N; e += blockDim.x) counts[(size_t)blockIdx.x * N + e] = hist[e];
   }
@@ -842,14 +842,20 @@ int launch_router_logits(const bigmac_dims& D, const void* x, const float* w_gat
   return BIGMAC_OK;
 }
 
-int launch_topk_gate(const bigmac_dims& D, const float* logits, int32_t* topk_idx, float* topk_w, hipStream_t s, int32_t* counts) {
-  const SortChunks sc = counts ? sort_chunks(D.T, D.k, D.N) : SortChunks{};
-  if (counts && !sc.threads) return BIGMAC_ERR_INVALID_ARG;
+// Counting, a workgroup takes a part of the sort's chunks (a part past the end counts nothing).
+TopkGrid topk_grid(int T, int k, int N, bool counting) {
+  if (!counting) return {(T + 3) / 4, 256, 4};
+  const SortChunks sc = sort_chunks(T, k, N, true);
   // two tokens per wavefront, up to 16 wavefronts: several wavefronts on a SIMD hide each other's latencies
-  const int tokens = counts ? sc.tokens : 4, threads = counts ? std::min(1024, std::max(256, (tokens + 1) / 2 * 64)) : 256;
-  const dim3 g2(counts ? sc.count * sc.parts : (D.T + tokens - 1) / tokens), block(threads);   // (a part past the end counts nothing)
+  return {sc.count * sc.parts, std::min(1024, std::max(256, (sc.tokens + 1) / 2 * 64)), sc.tokens};
+}
+
+int launch_topk_gate(const bigmac_dims& D, const float* logits, int32_t* topk_idx, float* topk_w, hipStream_t s, int32_t* counts) {
+  if (counts && !topk_counts(D.T, D.k, D.N)) return BIGMAC_ERR_INVALID_ARG;
+  const TopkGrid G = topk_grid(D.T, D.k, D.N, counts != nullptr);
+  const dim3 g2(G.workgroups), block(G.threads);
   const int per = (D.N + 63) / 64;
-#define BIGMAC_TOPK(P) hipLaunchKernelGGL(topk_gate_kernel<P>, g2, block, 0, s, logits, D.T, D.N, D.k, tokens, topk_idx, topk_w, counts)
+#define BIGMAC_TOPK(P) hipLaunchKernelGGL(topk_gate_kernel<P>, g2, block, 0, s, logits, D.T, D.N, D.k, G.tokens, topk_idx, topk_w, counts)
   if (per <= 1) BIGMAC_TOPK(1);
   else if (per <= 2) BIGMAC_TOPK(2);
   else if (per <= 4) BIGMAC_TOPK(4);
@@ -978,7 +984,7 @@ int launch_aux_loss(const bigmac_dims& D, const float* logits, const int32_t* to
   BIGMAC_CHECK_LAUNCH();
   int NP = 1;
   while (NP < D.N) NP <<= 1;
-  hipLaunchKernelGGL(aux_finish_kernel, dim3(1), dim3(1024), 0, s, topk_idx, counts, counts ? sort_chunks(D.T, D.k, D.N).count * sort_chunks(D.T, D.k, D.N).parts : 0, partial, parts, D.T, D.N, NP, D.k, D.aux_alpha, share, loss);
+  hipLaunchKernelGGL(aux_finish_kernel, dim3(1), dim3(1024), 0, s, topk_idx, counts, counts ? topk_grid(D.T, D.k, D.N, true).workgroups : 0, partial, parts, D.T, D.N, NP, D.k, D.aux_alpha, share, loss);
   BIGMAC_CHECK_LAUNCH();
   if (dlogits) {
     const float scale = D.aux_alpha * (float)D.N / (float)D.T;
