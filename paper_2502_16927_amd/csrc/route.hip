@@ -417,9 +417,9 @@ __device__ __forceinline__ void sort_keys(unsigned long long (&key)[U], int lane
 // are the selection.  That one is bound by its comparisons, which take no branches (1024 tokens, 512 experts: 106 us with, 52 without).
 // The network is a serial chain of 21 (27) exchanges and bound by its latency: keys of 64 bits cost one
 // comparison, partners are read by DPP moves and row swaps instead of through the LDS, and a
-// wavefront takes two tokens at a time (8192 tokens, 64 experts, counting included: 15.0 us by wavefronts
+// wavefront takes U tokens at a time: two where the grid follows the sort's chunks (8192 tokens, 64 experts, counting included: 15.0 us by wavefronts
 // that take eight one by one, 6.3 us so).
-template <int PER>
+template <int PER, int U>
 __global__ __launch_bounds__(1024) void topk_gate_kernel(const float* __restrict__ logits, int T, int N, int k, int tokens,
                                                          int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int32_t* __restrict__ counts) {
   __shared__ int hist[128];
@@ -440,7 +440,6 @@ __global__ __launch_bounds__(1024) void topk_gate_kernel(const float* __restrict
     }
   };
   const int t_end = min(T, (int)(blockIdx.x + 1) * tokens), step = blockDim.x >> 6;
-  constexpr int U = PER <= 2 ? 2 : 1;
   for (int t = blockIdx.x * tokens + (threadIdx.x >> 6); t < t_end; t += U * step) {
     if constexpr (PER <= 2) {
       unsigned long long key[U];
@@ -842,12 +841,15 @@ int launch_router_logits(const bigmac_dims& D, const void* x, const float* w_gat
   return BIGMAC_OK;
 }
 
-// Counting, a workgroup takes a part of the sort's chunks (a part past the end counts nothing).
+// Counting, a workgroup takes a part of the sort's chunks (a part past the end counts nothing), two tokens per wavefront on up to
+// 16 wavefronts: several on a SIMD hide each other's latencies.  Else four wavefronts of one token each: level with
+// eight tokens in pairs or up to 20 % faster up to 16384 tokens, 1 to 4 % slower from 32768 on.  (Four tokens on wavefronts made for
+// pairs had each of them sort the last token beside its own: bigmac_route at d 64, N 128, T 512 / 4096 / 32768
+// 8.0 / 17.4 / 90.5 us, 7.2 / 14.7 / 75.9 so.)
 TopkGrid topk_grid(int T, int k, int N, bool counting) {
   if (!counting) return {(T + 3) / 4, 256, 4};
   const SortChunks sc = sort_chunks(T, k, N, true);
-  // two tokens per wavefront, up to 16 wavefronts: several wavefronts on a SIMD hide each other's latencies
-  return {sc.count * sc.parts, std::min(1024, std::max(256, (sc.tokens + 1) / 2 * 64)), sc.tokens};
+  return {sc.count * sc.parts, std::min(1024, (sc.tokens + 1) / 2 * 64), sc.tokens};
 }
 
 int launch_topk_gate(const bigmac_dims& D, const float* logits, int32_t* topk_idx, float* topk_w, hipStream_t s, int32_t* counts) {
@@ -855,12 +857,14 @@ int launch_topk_gate(const bigmac_dims& D, const float* logits, int32_t* topk_id
   const TopkGrid G = topk_grid(D.T, D.k, D.N, counts != nullptr);
   const dim3 g2(G.workgroups), block(G.threads);
   const int per = (D.N + 63) / 64;
-#define BIGMAC_TOPK(P) hipLaunchKernelGGL(topk_gate_kernel<P>, g2, block, 0, s, logits, D.T, D.N, D.k, G.tokens, topk_idx, topk_w, counts)
-  if (per <= 1) BIGMAC_TOPK(1);
-  else if (per <= 2) BIGMAC_TOPK(2);
-  else if (per <= 4) BIGMAC_TOPK(4);
-  else if (per <= 8) BIGMAC_TOPK(8);
-  else BIGMAC_TOPK(16);
+#define BIGMAC_TOPK(P, U) hipLaunchKernelGGL((topk_gate_kernel<P, U>), g2, block, 0, s, logits, D.T, D.N, D.k, G.tokens, topk_idx, topk_w, counts)
+  if (per <= 1 && counts) BIGMAC_TOPK(1, 2);
+  else if (per <= 1) BIGMAC_TOPK(1, 1);
+  else if (per <= 2 && counts) BIGMAC_TOPK(2, 2);
+  else if (per <= 2) BIGMAC_TOPK(2, 1);
+  else if (per <= 4) BIGMAC_TOPK(4, 1);
+  else if (per <= 8) BIGMAC_TOPK(8, 1);
+  else BIGMAC_TOPK(16, 1);
 #undef BIGMAC_TOPK
   BIGMAC_CHECK_LAUNCH();
   return BIGMAC_OK;

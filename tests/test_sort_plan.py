@@ -39,6 +39,15 @@ def test_topk_spreads_over_the_chip():
         assert not topk_counts(T, k, N) or (N <= 128 and T * k > 4096)
 
 
+@pytest.mark.parametrize("counting", [False, True])
+def test_no_wavefront_of_the_topk_sorts_for_nothing(counting):
+    """A wavefront takes two tokens at a time where it counts and one elsewhere: as many wavefronts as have tokens to take."""
+    for T, k, N in SIZES:
+        if not counting or topk_counts(T, k, N):
+            g = topk_grid(T, k, N, counting)
+            assert g.threads // 64 == (min(16, -(-g.tokens // 2)) if counting else g.tokens), (T, k, N)
+
+
 @pytest.mark.parametrize("counted", [False, True])
 def test_sort_chunks_hold_whole_tokens_and_every_token(counted):
     for T, k, N in SIZES:
