@@ -19,7 +19,8 @@ namespace bigmac {
 
 namespace {
 
-constexpr int PP_MAX_EXPERTS = 512;     // experts up to which the one-pass sort runs (32 KB of counters at 16 wavefronts)
+constexpr int PP_MAX_EXPERTS = 512;     // experts up to which the one-pass sort runs (32 KB of counters at 16 wavefronts; at the limits of
+                                        // 512 experts and 512 chunks it takes 61 us, the three kernels 80)
 constexpr int PP_SELF_PAIRS = 4096;     // pairs up to which its workgroups count for themselves (see perm_place_kernel)
 
 // The sort of many pairs or experts (see sort_chunks): count, one-workgroup scan, rank.
@@ -179,7 +180,10 @@ __global__ __launch_bounds__(64) void perm_rank_kernel(const int32_t* __restrict
 // expert's pairs in earlier chunks, in earlier wavefronts of its chunk (one counter per wavefront and
 // expert, one writer each) and in earlier lanes of its wavefront (ballots): no atomics, flat order.
 // A capacity drops a pair whose slot falls past its expert's range: slot_of = -1, no src_of entry.
-// One workgroup beyond the chunks writes the offsets and the tile maps and clears the tile counters.
+// The first workgroup writes the offsets; where tile maps are asked for it has no chunk, writes them too and clears the tile
+// counters.  It takes longest then, so it must not come last: 512 workgroups of 1024 threads run at once, and behind 512 chunks it
+// had a round of its own (layer call at 65536 tokens, k 8, 512 experts: this kernel 98 us with it last, 80 so; 32768 and 128: 20.6, 15.5;
+// bigmac_dispatch, which wants no maps, 82 and 61 us, the three kernels 80).
 // counts == NULL: up to PP_SELF_PAIRS pairs, nothing is counted in front and no scratch is read or written: every
 // workgroup counts all pairs itself with LDS atomics (order-free).  Bound by latency, so one launch in place of
 // two is the gain: the sort of bigmac_dispatch 5.5 -> 3.5 us at 256 pairs and 64 experts, 6.9 -> 4.5 at 4000, 7.4 -> 5.1 at
@@ -197,8 +201,8 @@ __global__ __launch_bounds__(THREADS) void perm_place_kernel(const int32_t* __re
   __shared__ int first_slot[PP_MAX_EXPERTS + 1];
   __shared__ int wave_totals[WAVES];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int b = blockIdx.x;
-  const bool placing = b < nchunks;
+  const int b = (int)blockIdx.x - (maps.map[0] ? 1 : 0);
+  const bool placing = b >= 0;
   const int f = b * pairs_per_chunk + tid;
   const bool live = placing && tid < pairs_per_chunk && f < Tk;
   const int e = live ? idx[f] : 0;
@@ -271,10 +275,11 @@ __global__ __launch_bounds__(THREADS) void perm_place_kernel(const int32_t* __re
     }
     __syncthreads();
   }
-  if (!placing) {
+  if (blockIdx.x == 0)
     for (int i = tid; i <= N; i += THREADS) offsets[i] = first_slot[i];
+  if (!placing) {
     for (int i = tid; i < maps.clear_ints; i += THREADS) maps.clear[i] = 0u;
-    if (maps.map[0]) build_tile_map_block(first_slot, N, maps.tile_rows[0], maps.map[0]);
+    build_tile_map_block(first_slot, N, maps.tile_rows[0], maps.map[0]);
     if (maps.map[1]) build_tile_map_block(first_slot, N, maps.tile_rows[1], maps.map[1], maps.map[0]);
     return;
   }
@@ -656,7 +661,7 @@ int launch_build_permutation(int T, int k, int N, int capacity, const int32_t* t
       BIGMAC_CHECK_LAUNCH();
     }
 #define BIGMAC_PLACE(THREADS)                                                                                                        \
-  hipLaunchKernelGGL(perm_place_kernel<THREADS>, dim3(sc.count + 1), dim3(THREADS), THREADS / 64 * N * sizeof(int), s, topk_idx, Tk, pairs, \
+  hipLaunchKernelGGL(perm_place_kernel<THREADS>, dim3(sc.count + (maps.map[0] ? 1 : 0)), dim3(THREADS), THREADS / 64 * N * sizeof(int), s, topk_idx, Tk, pairs, \
                      sc.count, sc.parts, N, NP, nbits, capacity, counts, expert_offsets, slot_of, src_of, maps)
     if (sc.threads == 256) BIGMAC_PLACE(256);
     else if (sc.threads == 512) BIGMAC_PLACE(512);

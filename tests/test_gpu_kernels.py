@@ -112,6 +112,18 @@ def test_dispatch_sort_of_few_pairs(oracle, T, k, N, capacity, popular):
         assert (off == r_off).all() and (slot == r_slot.reshape(-1)).all() and (src == r_src).all()
 
 
+# the one-pass sort at its last chunk (512 of them, counted by a launch of its own) and the three kernels past it
+@pytest.mark.parametrize("T,k,N", [(65536, 8, 72), (65537, 8, 72), (65536, 8, 512), (65500, 8, 512)])
+def test_dispatch_sort_of_many_pairs(oracle, T, k, N):
+    g = torch.Generator(device=DEV).manual_seed(T + N)
+    idx = torch.rand((T, N), generator=g, device=DEV).topk(k, dim=1).indices.to(torch.int32)
+    off, (slot, src) = torch.empty(N + 1, dtype=torch.int32, device=DEV), torch.empty((2, T * k), dtype=torch.int32, device=DEV)
+    dims = B.make_dims(T, 64, 64, N, k, 64, B.BF16)
+    B.bigmac_dispatch(dims, None, idx, None, off, slot, src, B.alloc_bytes(B.workspace_bytes(dims, B.WS_DISPATCH)))
+    r_off, r_slot, r_src = oracle.permutation(idx.cpu().numpy(), N)
+    assert (off.cpu().numpy() == r_off).all() and (slot.cpu().numpy() == r_slot.reshape(-1)).all() and (src.cpu().numpy() == r_src).all()
+
+
 # logits of every kind, NaN of either sign and infinities among them: the picks are still k different experts (24 and 72
 # leave lanes past the last expert in the first and in the second half of the network), and finite rows are picked as ever
 @pytest.mark.parametrize("N,k", [(24, 24), (24, 5), (72, 64), (72, 8)])
