@@ -73,7 +73,7 @@ struct FwdPlan {
   size_t logits, perm, x_low, partials, aux, claims, total;
 };
 struct BwdPlan {
-  size_t dy_low, dgate, do_perm, dx_perm, dact, dx_low, dL, route, dx_f32, part_up, part_gate, part_down, tmp_f32, bias_sums, gate_low, w_up_t, w_down_t, claims, total;
+  size_t dy_low, dgate, do_perm, dx_perm, dact, dx_low, dL, route, dx_f32, part_up, part_gate, part_down, bias_sums, gate_low, w_up_t, w_down_t, claims, total;
 };
 
 inline bool bf(const bigmac_dims& D) { return D.dtype == BIGMAC_BF16; }
@@ -324,7 +324,6 @@ BwdPlan plan_bwd(const bigmac_dims& D) {
   p.part_gate = c.take((size_t)token_wgrad_ksplit(D, dg, D.N) * dg * D.N * 4);
   p.part_up = c.take(dcca ? (size_t)token_wgrad_ksplit(D, D.r, D.d) * D.r * D.d * 4 : 0);
   p.part_down = c.take(dcca ? (size_t)token_wgrad_ksplit(D, D.d, D.r) * D.d * D.r * 4 : 0);
-  p.tmp_f32 = 0;
   // transposed copies of the two shared matrices for the data gradients of the projections (see transposed_projections)
   p.w_up_t = c.take(transposed_projections(D) ? (size_t)D.d * D.r * es : 0);
   p.w_down_t = c.take(transposed_projections(D) ? (size_t)D.d * D.r * es : 0);

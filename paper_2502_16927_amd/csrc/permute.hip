@@ -20,7 +20,7 @@ namespace bigmac {
 namespace {
 
 constexpr int PP_MAX_EXPERTS = 512;     // experts up to which the one-pass sort runs (32 KB of counters at 16 wavefronts; at the limits of
-                                        // 512 experts and 512 chunks it takes 61 us, the three kernels 80)
+                                        // 512 experts and 512 chunks it takes 57 us, the three kernels 80)
 constexpr int PP_SELF_PAIRS = 4096;     // pairs up to which its workgroups count for themselves (see perm_place_kernel)
 
 // The sort of many pairs or experts (see sort_chunks): count, one-workgroup scan, rank.
@@ -175,15 +175,15 @@ __global__ __launch_bounds__(64) void perm_rank_kernel(const int32_t* __restrict
 // perm_count_kernel): a workgroup per chunk of THREADS pairs, one pair per thread.  Every workgroup
 // reads all chunks' counters (at most 512 x N, from the L2) and adds up for itself each expert's total and what
 // lies in front of its own chunk, so no one-workgroup scan sits between the count and the ranks: at 65536
-// pairs and 64 experts count + scan + rank took 5.1 + 10.7 + 5.1 us, this takes 8.0 with the
+// pairs and 64 experts count + scan + rank took 5.1 + 10.7 + 5.1 us, this takes 6.3 with the
 // tile map (the counters come with the top-k kernel).  A pair's slot is its expert's first slot + the
 // expert's pairs in earlier chunks, in earlier wavefronts of its chunk (one counter per wavefront and
 // expert, one writer each) and in earlier lanes of its wavefront (ballots): no atomics, flat order.
 // A capacity drops a pair whose slot falls past its expert's range: slot_of = -1, no src_of entry.
 // The first workgroup writes the offsets; where tile maps are asked for it has no chunk, writes them too and clears the tile
 // counters.  It takes longest then, so it must not come last: 512 workgroups of 1024 threads run at once, and behind 512 chunks it
-// had a round of its own (layer call at 65536 tokens, k 8, 512 experts: this kernel 98 us with it last, 80 so; 32768 and 128: 20.6, 15.5;
-// bigmac_dispatch, which wants no maps, 82 and 61 us, the three kernels 80).
+// had a round of its own (layer call at 65536 tokens, k 8, 512 experts: this kernel 98 us with it last, 74 so; 32768 and 128: 20.7, 15.0;
+// bigmac_dispatch, which wants no maps, 82 and 57 us, the three kernels 80).
 // counts == NULL: up to PP_SELF_PAIRS pairs, nothing is counted in front and no scratch is read or written: every
 // workgroup counts all pairs itself with LDS atomics (order-free).  Bound by latency, so one launch in place of
 // two is the gain: the sort of bigmac_dispatch 5.5 -> 3.5 us at 256 pairs and 64 experts, 6.9 -> 4.5 at 4000, 7.4 -> 5.1 at
@@ -208,33 +208,30 @@ __global__ __launch_bounds__(THREADS) void perm_place_kernel(const int32_t* __re
   const int e = live ? idx[f] : 0;
   for (int i = tid; i < WAVES * N; i += THREADS) cnt[i] = 0;
   if (counts) {
-    // column sums of the counters: THREADS / width groups of chunks x width experts at a time
-    const int width = NP < THREADS ? NP : THREADS, G = THREADS / width, g = tid / width, rows = nchunks * parts;
-    for (int e0 = 0; e0 < N; e0 += width) {
-      const int ee = e0 + tid % width;
-      int total = 0, before = 0;
-      if (ee < N)
-        for (int c0 = g; c0 < rows; c0 += 8 * G) {
-          int v[8];
+    // column sums of the counters: THREADS / NP groups of chunks x NP experts (never more experts than threads: see sort_chunks)
+    const int G = THREADS / NP, ee = tid % NP, rows = nchunks * parts;
+    int total = 0, before = 0;
+    if (ee < N)
+      for (int c0 = tid / NP; c0 < rows; c0 += 8 * G) {
+        int v[8];
 #pragma unroll
-          for (int u = 0; u < 8; ++u) v[u] = c0 + u * G < rows ? counts[(size_t)(c0 + u * G) * N + ee] : 0;
+        for (int u = 0; u < 8; ++u) v[u] = counts[min(c0 + u * G, rows - 1) * N + ee];   // (no branch between the eight loads)
 #pragma unroll
-          for (int u = 0; u < 8; ++u) {
-            total += v[u];
-            before += c0 + u * G < b * parts ? v[u] : 0;
-          }
+        for (int u = 0; u < 8; ++u) {
+          total += c0 + u * G < rows ? v[u] : 0;
+          before += c0 + u * G < b * parts ? v[u] : 0;
         }
-      group_total[tid] = total;
-      group_earlier[tid] = before;
-      __syncthreads();
-      if (tid < width && ee < N) {
-        int t = 0, w = 0;
-        for (int h = 0; h < G; ++h) { t += group_total[h * width + tid]; w += group_earlier[h * width + tid]; }
-        totals[ee] = t;
-        earlier[ee] = w;
       }
-      __syncthreads();
+    group_total[tid] = total;
+    group_earlier[tid] = before;
+    __syncthreads();
+    if (tid < N) {
+      int t = 0, w = 0;
+      for (int h = 0; h < G; ++h) { t += group_total[h * NP + tid]; w += group_earlier[h * NP + tid]; }
+      totals[tid] = t;
+      earlier[tid] = w;
     }
+    __syncthreads();
   } else {
     for (int i = tid; i < N; i += THREADS) totals[i] = earlier[i] = 0;
     __syncthreads();
@@ -251,30 +248,22 @@ __global__ __launch_bounds__(THREADS) void perm_place_kernel(const int32_t* __re
     for (int i = tid; i < N; i += THREADS) totals[i] += earlier[i];
     __syncthreads();
   }
-  // first slots: exclusive scan of the experts' held pairs, THREADS experts at a time
-  int carry = 0;
-  for (int e0 = 0; e0 < N; e0 += THREADS) {
-    const int ee = e0 + tid;
-    const int held = ee < N ? (capacity > 0 ? min(totals[ee], capacity) : totals[ee]) : 0;
-    int v = held;
+  // first slots: exclusive scan of the experts' held pairs, one expert per thread
+  const int held = tid < N ? (capacity > 0 ? min(totals[tid], capacity) : totals[tid]) : 0;
+  int upto = held;
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int o = __shfl_up(v, d, 64);
-      if (lane >= d) v += o;
-    }
-    if (lane == 63) wave_totals[wave] = v;
-    __syncthreads();
-    int before = carry;
-    for (int w = 0; w < WAVES; ++w) {
-      if (w < wave) before += wave_totals[w];
-      carry += wave_totals[w];
-    }
-    if (ee < N) {
-      first_slot[ee] = v - held + before;
-      if (ee == N - 1) first_slot[N] = v + before;
-    }
-    __syncthreads();
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(upto, d, 64);
+    if (lane >= d) upto += o;
   }
+  if (lane == 63) wave_totals[wave] = upto;
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) upto += wave_totals[w];
+  if (tid < N) {
+    first_slot[tid] = upto - held;
+    if (tid == N - 1) first_slot[N] = upto;
+  }
+  __syncthreads();
   if (blockIdx.x == 0)
     for (int i = tid; i <= N; i += THREADS) offsets[i] = first_slot[i];
   if (!placing) {
@@ -294,9 +283,9 @@ __global__ __launch_bounds__(THREADS) void perm_place_kernel(const int32_t* __re
   if (live) {
     int slot = first_slot[e] + earlier[e] + __popcll(same & below);
     for (int w = 0; w < wave; ++w) slot += cnt[w * N + e];
-    const bool held = capacity == 0 || slot < first_slot[e] + capacity;
-    slot_of[f] = held ? slot : -1;
-    if (held) src_of[slot] = f;
+    const bool kept = capacity == 0 || slot < first_slot[e] + capacity;
+    slot_of[f] = kept ? slot : -1;
+    if (kept) src_of[slot] = f;
   }
 }
 
