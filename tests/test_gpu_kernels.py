@@ -31,7 +31,7 @@ def ffn_reference(xp, rows, w1, w2):
 # fp32 products: one wavefront per 32 x 32 tile from 2048 tiles on, four wavefronts on a quarter of K each below
 @pytest.mark.parametrize("rows,r,h", [((1, 0, 31, 32), 64, 64),           # fewer rows than a tile, an empty expert
                                       ((33, 5), 64, 192),                 # a row past a tile
-                                      ((97, 1000, 3), 128, 1984),         # either side of the line: 2170 tiles up, 140 down
+                                      ((97, 1000, 3), 128, 1984),         # either side of the line: 2356 tiles up, 152 down
                                       ((2100, 2100), 64, 1024)])
 def test_f32_expert_products(rows, r, h):
     g = torch.Generator(device=DEV).manual_seed(sum(rows) + r)
@@ -48,10 +48,51 @@ def test_f32_expert_products(rows, r, h):
     assert rel(o, ref_o) < 1e-5
 
 
-# the sort that follows the top-k kernel's counts: chunks of 256, 512 and 1024 pairs in one to four parts, a token past
-# a part or a chunk, picks that do not divide a chunk, dropped pairs, and (600 experts) the three-kernel sort
+# fp32 products from 2048 tiles on in the layouts of the backward pass: both matrices' data gradients (ragged), dx' W_down^T (dense),
+# the experts' weight gradients (ragged K), with an odd token count and an expert without rows
+def test_f32_layer_of_many_tiles():
+    T, d, r, N, k, h = 2001, 1088, 256, 8, 4, 1024
+    g = torch.Generator(device=DEV).manual_seed(5)
+    rand = lambda shape, std: torch.randn(shape, generator=g, device=DEV) * std
+    x, dy = rand((T, d), 1.0), rand((T, d), 1.0)
+    w_down, w_up, w_gate = rand((d, r), d ** -0.5), rand((r, d), r ** -0.5), rand((d, N), d ** -0.5)
+    w1, w2, bias = rand((N, r, h), r ** -0.5), rand((N, h, r), h ** -0.5), torch.zeros(N, device=DEV)
+    bias[3] = -100.0                                # never picked
+    dims = B.make_dims(T, d, r, N, k, h, B.F32)
+    params, saved = B.make_params(w_down, w_up, w_gate, bias, w1, w2), B.alloc_bytes(B.workspace_bytes(dims, B.WS_SAVED))
+    ws = B.alloc_bytes(B.workspace_bytes(dims, B.WS_LAYER_TRAIN))
+    y, dx = torch.empty_like(x), torch.empty_like(x)
+    grads = [torch.empty_like(w) for w in (w_down, w_up, w_gate, w1, w2)]
+    B.bigmac_layer_forward(dims, params, x, y, saved, ws)
+    B.bigmac_layer_backward(dims, params, x, dy, saved, dx, *grads, ws)
+    at = B.saved_layout(dims)["topk_idx"]
+    idx = saved[at:at + 4 * T * k].view(torch.int32).view(T, k).long()
+    assert not bool((idx == 3).any())
+
+    leaves = [t.double().requires_grad_() for t in (x, w_down, w_up, w_gate, w1, w2)]
+    X, Wd, Wu, Wg, W1, W2 = leaves
+    p = (X @ Wg + bias.double()).gather(1, idx).softmax(dim=1)
+    low, mid = X @ Wd, torch.zeros((T, r), dtype=torch.float64, device=DEV)
+    for e in range(N):
+        t, j = (idx == e).nonzero(as_tuple=True)
+        mid = mid.index_add(0, t, p[t, j, None] * (torch.nn.functional.gelu(low[t] @ W1[e]) @ W2[e]))
+    ref = mid @ Wu
+    ref.backward(dy.double())
+    # a sum of K fp32 products is off by about sqrt(K) 2^-24 of its norm (2.7e-6 at K = 2001); at most six follow one another: 6.6e-6.
+    # The gates' gradient w (g - sum w g) loses part of g's norm to the difference: three times that.
+    for name, a, b in zip(("y", "dx", "d_w_down", "d_w_up", "d_w_gate", "d_w1", "d_w2"), [y, dx] + grads,
+                          [ref.detach()] + [t.grad for t in leaves]):
+        assert rel(a, b) < (2e-5 if name == "d_w_gate" else 1e-5), name
+    assert not bool(grads[3][3].any()) and not bool(grads[4][3].any())
+
+
+# the top-k and the sort behind it: up to 4096 pairs and one past them; chunks of 256, 512 and 1024 pairs that the top-k counts in 1, 2, 4, 8,
+# 16 and 32 parts, or that a launch of their own counts (129, 256 and 512 experts); a token past a part or a chunk, picks that do not
+# divide a chunk, dropped pairs, and (600 experts) the three-kernel sort
 @pytest.mark.parametrize("T,k,N,capacity", [(1, 1, 8, 0), (8, 8, 64, 0), (33, 8, 64, 9), (129, 5, 24, 0), (257, 64, 64, 0), (1025, 6, 40, 0),
-                                            (8193, 8, 64, 900), (700, 3, 72, 0), (5000, 8, 128, 0), (90, 2, 600, 0)])
+                                            (8193, 8, 64, 900), (700, 3, 72, 0), (5000, 8, 128, 0), (90, 2, 600, 0),
+                                            (4096, 1, 64, 0), (4097, 1, 64, 0), (8192, 8, 64, 0), (8192, 1, 128, 100), (4097, 2, 96, 0),
+                                            (515, 8, 129, 0), (2051, 3, 256, 40), (33, 8, 512, 0), (1100, 5, 512, 0)])
 def test_sort_after_topk(oracle, T, k, N, capacity):
     g = torch.Generator(device=DEV).manual_seed(T + N)
     d = r = h = 64
@@ -110,6 +151,27 @@ def test_dispatch_sort_of_few_pairs(oracle, T, k, N, capacity, popular):
         assert (src[slot[kept]] == kept.nonzero()[0]).all() and (src[off[N]:] == -7).all()
     else:
         assert (off == r_off).all() and (slot == r_slot.reshape(-1)).all() and (src == r_src).all()
+
+
+# the load-balance loss of a layer call from the top-k's counters (4 and 32 parts per chunk) is the one from the picks, bit for bit
+@pytest.mark.parametrize("T,k,N", [(1025, 6, 40), (8192, 1, 128)])
+def test_loss_from_counters(T, k, N):
+    g = torch.Generator(device=DEV).manual_seed(T)
+    dims = B.make_dims(T, 64, 64, N, k, 64, B.BF16, aux_alpha=0.01)
+    x, w_gate = torch.randn((T, 64), generator=g, device=DEV).to(torch.bfloat16), torch.randn((64, N), generator=g, device=DEV) * 0.1
+    w = [torch.zeros(s, dtype=torch.bfloat16, device=DEV) for s in ((64, 64), (64, 64), (N, 64, 64), (N, 64, 64))]
+    saved = B.alloc_bytes(B.workspace_bytes(dims, B.WS_SAVED))
+    B.bigmac_layer_forward(dims, B.make_params(w[0], w[1], w_gate, None, w[2], w[3]), x, torch.empty((T, 64), device=DEV), saved,
+                           B.alloc_bytes(B.workspace_bytes(dims, B.WS_LAYER_TRAIN)))
+    idx, weights, logits = torch.empty((T, k), dtype=torch.int32, device=DEV), torch.empty((T, k), device=DEV), torch.empty((T, N), device=DEV)
+    B.bigmac_route(dims, x, w_gate, None, idx, weights, logits)
+    loss, share = torch.empty(1, device=DEV), torch.empty(N, device=DEV)
+    B.bigmac_aux_loss(dims, logits, idx, loss, share, None, B.alloc_bytes(B.workspace_bytes(dims, B.WS_AUX_LOSS)))
+    at = B.saved_aux_layout(dims)
+    assert torch.equal(saved[at["aux_share"]:at["aux_share"] + 4 * N].view(torch.float32), share)
+    assert torch.equal(saved[at["aux_loss"]:at["aux_loss"] + 4].view(torch.float32), loss)
+    exact = torch.bincount(idx.view(-1).long(), minlength=N).double() / (T * k)
+    assert bool(((share.double() - exact).abs() <= 2.0 ** -23 * exact).all())     # one rounding of the quotient: 2^-24
 
 
 # the one-pass sort at its last chunk (512 of them, counted by a launch of its own) and the three kernels past it
