@@ -245,7 +245,7 @@ int launch_aux_loss(const bigmac_dims& D, const float* logits, const int32_t* to
                     float* dlogits, void* ws, hipStream_t s, const int32_t* counts = nullptr);   // counts: as above, instead of topk_idx
 
 // ----------------------------------------------------------------------------- permute --
-size_t permutation_ws_bytes(int T, int k, int N);
+size_t permutation_ws_bytes(int T, int k, int N, bool counted);   // counted: by the top-k kernel
 struct SortChunks {
   int threads, tokens, parts, count;   // threads per workgroup, tokens per part of a chunk, parts per chunk, chunks; threads == 0: sorted another way
 };

@@ -236,7 +236,7 @@ FwdPlan plan_fwd(const bigmac_dims& D) {
   Carver c;
   FwdPlan p;
   p.logits = c.take((size_t)D.T * D.N * 4);
-  p.perm = c.take(permutation_ws_bytes(D.T, D.k, D.N));
+  p.perm = c.take(permutation_ws_bytes(D.T, D.k, D.N, topk_counts(D.T, D.k, D.N)));
   p.x_low = c.take(D.order == BIGMAC_ORDER_DCCA ? (size_t)D.T * D.r * esize(D.dtype) : 0);
   p.partials = c.take(forward_partials_bytes(D));
   p.aux = c.take(D.aux_alpha > 0.0f ? aux_loss_ws_bytes(D) : 0);
@@ -434,7 +434,7 @@ size_t bigmac_workspace_bytes(const bigmac_dims* D, int kind) {
   if (check_dims(D) != BIGMAC_OK) return 0;
   switch (kind) {
     case BIGMAC_WS_ROUTE: return align_up((size_t)D->T * D->N * 4);
-    case BIGMAC_WS_DISPATCH: return permutation_ws_bytes(D->T, D->k, D->N);
+    case BIGMAC_WS_DISPATCH: return permutation_ws_bytes(D->T, D->k, D->N, false);
     case BIGMAC_WS_GROUPED_FFN: return ffn_ws_bytes(*D);
     case BIGMAC_WS_LAYER_FORWARD: return plan_fwd(*D).total + plan_saved(*D).total;
     case BIGMAC_WS_LAYER_TRAIN: {

@@ -7,7 +7,6 @@
 #include "tile_map.hpp"
 #include "wave.hpp"
 
-#include <algorithm>
 #include <atomic>
 
 // Scratch of the allocation-free dispatch (bigmac_dispatch_static): the per-chunk expert counters
@@ -625,9 +624,9 @@ SortChunks sort_chunks(int T, int k, int N, bool counted) {
   return c;
 }
 
-size_t permutation_ws_bytes(int T, int k, int N) {
-  const SortChunks c = sort_chunks(T, k, N, false), by_topk = sort_chunks(T, k, N, topk_counts(T, k, N));
-  if (c.threads) return align_up((size_t)std::max(c.count * c.parts, by_topk.count * by_topk.parts) * N * sizeof(int32_t));
+size_t permutation_ws_bytes(int T, int k, int N, bool counted) {
+  const SortChunks c = sort_chunks(T, k, N, counted);
+  if (c.threads) return align_up((size_t)c.count * c.parts * N * sizeof(int32_t));
   const int chunk = perm_chunk(T * k, N);
   const size_t nchunks = ((size_t)T * k + chunk - 1) / chunk;
   return align_up(nchunks * N * sizeof(int32_t));
@@ -853,7 +852,7 @@ extern "C" int bigmac_dispatch_static(const bigmac_dims* D, const void* x_low, c
   if (rc) return rc;
   if (!topk_idx || !expert_offsets || !slot_of || !src_of) return BIGMAC_ERR_INVALID_ARG;
   if ((x_low == nullptr) != (x_perm == nullptr)) return BIGMAC_ERR_INVALID_ARG;
-  if (permutation_ws_bytes(D->T, D->k, D->N) > BIGMAC_STATIC_SCRATCH_BYTES) return BIGMAC_ERR_TOO_LARGE;
+  if (permutation_ws_bytes(D->T, D->k, D->N, false) > BIGMAC_STATIC_SCRATCH_BYTES) return BIGMAC_ERR_TOO_LARGE;
   void* ws = nullptr;
   rc = static_scratch(&ws);
   if (rc) return rc;
