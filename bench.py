@@ -64,18 +64,36 @@ def stage_work(wl, order_cdac: bool, training: bool, wire_bf16: bool = False):
     W["ascend"] = ("mfma", 2.0 * T * r * d, T * low * e + r * d * e + T * d * 4)
     W["bwd_ascend_dgrad"] = ("mfma", 2.0 * T * d * r, T * d * e + r * d * e + T * r * 4)
     W["bwd_ascend_wgrad"] = ("mfma", 2.0 * T * r * d, T * r * e + T * d * e + r * d * 4)
-    W["bwd_combine"] = ("hbm", 4.0 * Tk * win, T * win * 4 + Tk * win * ew + Tk * win * e + 12 * Tk)
+    # up to 128 experts in bf16 the combine's backward also writes the logits' gradient (the gate's backward); the
+    # fine-grained order reads dy itself, and its sum of dx_perm adds to the dx that holds the router's share
+    gate_fused = e == 2 and N <= 128
+    W["bwd_combine"] = ("hbm", 4.0 * Tk * win, T * win * (e if order_cdac else 4) + Tk * win * ew + Tk * win * e + 12 * Tk
+                        + (T * N * e + 4 * Tk if gate_fused else 0))
     W["bwd_down_dgrad"] = ("mfma", 2.0 * Tk * win * hid, Tk * win * e + N * win * hid * e + 2 * Tk * hid * e)
     W["bwd_down_wgrad"] = ("mfma", 2.0 * Tk * win * hid, Tk * hid * e + Tk * win * e + N * win * hid * 4)
     W["bwd_up_wgrad"] = ("mfma", 2.0 * Tk * win * hid, Tk * hid * e + Tk * win * e + N * win * hid * 4)
     W["bwd_up_dgrad"] = ("mfma", 2.0 * Tk * win * hid, Tk * hid * e + N * win * hid * e + Tk * win * ew)
-    W["bwd_dispatch"] = ("hbm", 1.0 * Tk * win, Tk * win * ew + T * (low * e if not order_cdac else d * 4) + 4 * Tk)
-    W["bwd_gate"] = ("hbm", 2.0 * Tk * d, T * d * 4 + T * N * e + 12 * Tk)
+    W["bwd_dispatch"] = ("hbm", 1.0 * Tk * win, Tk * win * ew + T * (low * e if not order_cdac else 2 * d * 4) + 4 * Tk)
+    W["bwd_gate"] = ("hbm", 2.0 * Tk * d, T * d * 4 + (8 * Tk if gate_fused else T * N * e + 12 * Tk))
     W["bwd_router_wgrad"] = ("mfma", 2.0 * T * d * N, T * d * e + T * N * e + d * N * 4)
     W["bwd_descend_wgrad"] = ("mfma", 2.0 * T * d * r, T * d * e + T * r * e + d * r * 4)
     W["bwd_descend_dgrad"] = ("mfma", 2.0 * T * r * d, T * low * e + d * r * e + 2 * T * d * 4)
-    W["bwd_output_cast"] = ("hbm", 0.0, 3 * T * d * 4)
+    W["bwd_output_cast"] = ("hbm", 0.0, 2 * d * N * 4)   # fine-grained order: the sum of the router's weight gradient
     return W
+
+
+def live_stages(order_cdac: bool, training: bool) -> set:
+    """Names of the stages that the layer calls record (a dispatch folded into a product excepted)."""
+    live = {"router_logits", "topk_gate", "permutation", "dispatch", "expert_up", "expert_down", "combine"}
+    if training:
+        live |= {"bwd_combine", "bwd_down_dgrad", "bwd_down_wgrad", "bwd_up_wgrad", "bwd_up_dgrad", "bwd_dispatch", "bwd_gate", "bwd_router_wgrad"}
+    if not order_cdac:
+        live |= {"descend", "ascend"}
+        if training:
+            live |= {"bwd_ascend_dgrad", "bwd_ascend_wgrad", "bwd_descend_wgrad", "bwd_descend_dgrad"}
+    elif training:
+        live.add("bwd_output_cast")
+    return live
 
 
 def roofline_of(name, kind, flops, nbytes, seconds):
@@ -310,7 +328,7 @@ def main():
     B.StageEvents.clear()
     # Pass 2, the timed region: the same step (the library only enqueues kernels, no memsets,
     # no synchronisation) captured once in a HIP graph and replayed K times, which removes the
-    # host's launch gaps between the ~33 kernels of a step.
+    # host's launch gaps between the 15 to 25 kernels of a step.
     elapsed, timed = eager_elapsed, "eager launches"
     if not args.no_graph:
         graph = torch.cuda.CUDAGraph()
@@ -335,13 +353,9 @@ def main():
     stage_ms = {}
     if tables:
         names = [B.stage_name(s) for s in range(B.STAGE_COUNT)]
-        fwd_only = {"router_logits", "topk_gate", "descend", "permutation", "dispatch", "expert_up", "expert_down", "combine", "ascend"}
-        live = [s for s, n in enumerate(names)
-                if (training or n in fwd_only)
-                and not (cdac and n in ("descend", "ascend", "bwd_ascend_wgrad", "bwd_descend_wgrad", "bwd_descend_dgrad"))
-                and not (not cdac and n == "bwd_output_cast")]
+        live = {names.index(n) for n in live_stages(cdac, training)}
         for tb in tables:
-            for s, ms in tb.elapsed_ms(set(live)).items():
+            for s, ms in tb.elapsed_ms(live).items():
                 stage_ms[names[s]] = stage_ms.get(names[s], 0.0) + ms / args.steps
     # a dispatch folded into a product has no stage of its own: its bytes are that product's
     folding = B.dispatch_folding(dims, training)
