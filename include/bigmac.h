@@ -168,10 +168,12 @@ int bigmac_dispatch(const bigmac_dims *dims, const void *x_low, const int32_t *t
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results
  * and kernels as bigmac_dispatch, without `ws`: the counting sort's counters live in a 4 MiB array
  * inside the library's device image (one copy per GPU, held until the process ends).  The call
- * allocates and frees nothing.  It needs ceil(T*k / 1024) * N * 4 bytes of that array (T*k / 256
- * chunks while that many times N stays within 32768) and returns BIGMAC_ERR_TOO_LARGE beyond 4 MiB
- * (e.g. T*k = 2^23 pairs over 128 experts still fit).  All calls on one GPU share the array: calls
- * that overlap in time on one GPU (different streams, or threads) race; calls on one stream do not.
+ * allocates and frees nothing.  Up to 4096 pairs over up to 512 experts it does not touch that
+ * array.  Else it needs BIGMAC_WS_DISPATCH bytes of it: at most 512 * N * 4 up to 512 chunks of
+ * about 1024 pairs over up to 512 experts, ceil(T*k / 1024) * N * 4 past that (T*k / 256 chunks
+ * while that many times N stays within 32768).  Beyond 4 MiB it returns BIGMAC_ERR_TOO_LARGE (e.g.
+ * T*k = 2^23 pairs over 128 experts still fit).  All calls on one GPU that need the array share it: where they
+ * overlap in time on one GPU (different streams, or threads) they race; calls on one stream do not.
  * The first call on a device looks the array's address up (no allocation); make that call outside
  * a graph capture. */
 int bigmac_dispatch_static(const bigmac_dims *dims, const void *x_low, const int32_t *topk_idx,
@@ -230,7 +232,7 @@ typedef enum {
   BIGMAC_STAGE_ROUTER_LOGITS = 0, /* F0  x W_g                                   */
   BIGMAC_STAGE_TOPK_GATE,         /* F1  top-k and gate values                   */
   BIGMAC_STAGE_DESCEND,           /* F2  x' = x W_down                           */
-  BIGMAC_STAGE_PERMUTATION,       /* F3  counting sort (3 small kernels) + tile map */
+  BIGMAC_STAGE_PERMUTATION,       /* F3  counting sort + tile maps               */
   BIGMAC_STAGE_DISPATCH,          /* F4  first All-to-All (row scatter)          */
   BIGMAC_STAGE_EXPERT_UP,         /* F5  act(x_perm W1[e])                       */
   BIGMAC_STAGE_EXPERT_DOWN,       /* F6  . W2[e]                                 */
@@ -238,17 +240,17 @@ typedef enum {
   BIGMAC_STAGE_ASCEND,            /* F8  y = y' W_up                             */
   BIGMAC_STAGE_BWD_ASCEND_DGRAD,  /* B8  dy' = dy W_up^T                         */
   BIGMAC_STAGE_BWD_ASCEND_WGRAD,  /* B8  dW_up (split-K product + reduction)     */
-  BIGMAC_STAGE_BWD_COMBINE,       /* B7  gate gradients, scaled scatter of dy'   */
+  BIGMAC_STAGE_BWD_COMBINE,       /* B7  gate gradients, scaled scatter of dy'; B1 gate backward (bf16, N <= 128) */
   BIGMAC_STAGE_BWD_DOWN_DGRAD,    /* B6  dact = (do W2[e]^T) act'                */
   BIGMAC_STAGE_BWD_DOWN_WGRAD,    /* B6  dW2[e]                                  */
   BIGMAC_STAGE_BWD_UP_WGRAD,      /* B5  dW1[e]                                  */
   BIGMAC_STAGE_BWD_UP_DGRAD,      /* B5  dx_perm = dact W1[e]^T                  */
-  BIGMAC_STAGE_BWD_DISPATCH,      /* B4  dx' = sum_j dx_perm                     */
-  BIGMAC_STAGE_BWD_GATE,          /* B1  gate backward, router share of dx       */
+  BIGMAC_STAGE_BWD_DISPATCH,      /* B4  dx' = sum_j dx_perm (fine-grained: dx += the sum) */
+  BIGMAC_STAGE_BWD_GATE,          /* B1  gate backward (else), router share of dx */
   BIGMAC_STAGE_BWD_ROUTER_WGRAD,  /* B0  dW_g                                    */
   BIGMAC_STAGE_BWD_DESCEND_WGRAD, /* B2  dW_down                                 */
   BIGMAC_STAGE_BWD_DESCEND_DGRAD, /* B2  dx += dx' W_down^T                      */
-  BIGMAC_STAGE_BWD_OUTPUT_CAST,   /* dx to bf16 / fine-grained dx sum            */
+  BIGMAC_STAGE_BWD_OUTPUT_CAST,   /* dx to bf16 / fine-grained: d_w_gate's sum   */
   BIGMAC_STAGE_COUNT
 } bigmac_stage;
 int bigmac_set_stage_events(void *const *events);

@@ -2,7 +2,7 @@
 // a stable counting sort of the (token, choice) pairs by expert, a row scatter (dispatch), a
 // weighted row gather-sum (combine, the middle term of Eq. 2) and their backward forms.
 // Slot assignment uses no atomics whose order could matter: counts are order-free, ranks come
-// from ballots inside one wavefront walking its chunk in order.
+// from ballots inside a wavefront, wavefronts and chunks in order.
 #include "common.hpp"
 #include "tile_map.hpp"
 #include "wave.hpp"

@@ -1,6 +1,6 @@
 // Tile map of a ragged-M problem (rows grouped by expert) and the cost-balanced schedule of the
-// ragged-K one, built by one workgroup of 1024 threads: by the kernel of its own in gemm.hip, or at
-// the end of the counting sort's scan, which has the group offsets at hand.
+// ragged-K one, built by one workgroup: of a kernel of its own in gemm.hip, or of the counting sort,
+// which has the group offsets at hand.
 #pragma once
 #include "wave.hpp"
 
@@ -81,8 +81,8 @@ __device__ __forceinline__ void build_tile_map_wave(const int* offsets, int grou
 
 // tile_map[0] = number of M tiles, [1..9] = the split points of the cost-balanced ragged-K
 // schedule (see balance_ragged_k), then from TILE_MAP_HEADER on (group, first row) per M tile,
-// groups in order.  Called by all 1024 threads of a workgroup, one thread per group; offsets may
-// lie in the LDS.
+// groups in order.  Called by all threads of a workgroup, one thread per group: 1024 of them, or 64 and
+// more for at most 64 groups.  offsets may lie in the LDS.
 // schedule_from: a map built before this one by the same workgroup from the same offsets; its
 // ragged-K schedule (split points and group order do not depend on the tile height) is copied
 // instead of being worked out again.
@@ -170,8 +170,8 @@ __device__ __forceinline__ void build_tile_map_block(const int* offsets, int gro
   // split points are the XCDs' first positions.  Used when the fullest XCD stays within 1.2
   // times the even share (one group that outweighs an eighth of the work does not); else the
   // groups keep their own order and the cut of equal cost.
-  // (16-bit entries: the counting sort's one-workgroup kernels call this with 40 KB of LDS of
-  // their own, and a kernel's static LDS ends at 64 KB)
+  // (16-bit entries: the counting sort's kernels call this with up to 46 KB of LDS of their own, and
+  // a workgroup's LDS ends at 64 KB unless a kernel asks for more)
   __shared__ unsigned short by_cost[1024];      // groups, largest cost first (ties: lower index first)
   __shared__ unsigned short xcd_of[1024], place_in_xcd[1024];
   __shared__ int xcd_first[9];

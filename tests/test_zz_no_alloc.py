@@ -45,12 +45,12 @@ def run_both(T, k, N, width, dtype, seed, capacity=0):
 @pytest.mark.parametrize("dtype", [B.BF16, B.F32])
 def test_static_dispatch_matches_dispatch_twice_in_a_row(oracle, dtype):
     print(f"allocation-free dispatch, dtype {dtype}: 12000 pairs then 6000 pairs", flush=True)
-    # both sizes take the three-kernel counting sort, whose counters live in the scratch
+    # both sizes are counted into the scratch
     off, slot, src, xp = run_both(3000, 4, 16, 192, dtype, seed=1)
     assert int(off[-1]) == 12000
     off, slot, src, xp = run_both(1500, 4, 16, 192, dtype, seed=2)
     assert int(off[-1]) == 6000
-    print("capacity mode, then the one-workgroup sort of a decode batch", flush=True)
+    print("capacity mode, then the sort of a decode batch, which uses no scratch", flush=True)
     off, _, _, _ = run_both(2500, 4, 16, 64, dtype, seed=3, capacity=300)
     assert 0 < int(off[-1]) < 10000
     run_both(100, 4, 16, 64, dtype, seed=4)
