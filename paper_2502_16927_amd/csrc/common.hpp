@@ -150,12 +150,10 @@ struct GemmDesc {
   long gstride_c;            // ragged-K / split-K: elements between consecutive C outputs
   int ksplit;                // dense: number of K slices (each writes C + z*gstride_c); 1 = none
   int kwrap_b;               // B's k index is taken modulo this (0 = off); multiple of 64
-  int tall_tile;             // bf16 only: 256-row workgroup tiles (ragged-M: the tile map must be built for them)
+  int tall_tile;             // bf16 weight gradients: 256 x 128 outputs
   int wide_k;                // bf16, k-contiguous A, K % 64 == 0: the square tile with 64-deep k tiles, two ring stages
   int kloop_priority;        // MFMA kernels: raise the wave priority inside the k loop (see the kernel)
   int deep_tile;             // bf16, dense, store or accumulate (K % 64 == 0 with a k-contiguous operand): 128 x 64 outputs, 64-deep k tiles
-  int long_tile;             // bf16, k-contiguous A only; ragged-M with the GELU epilogue or dense with the plain store: 128 x 256 outputs
-                             //   (four wavefronts side by side, each 128 x 64); ragged-M: tile map of 128-row tiles
   int big_tile;              // bf16: 256 x 256 outputs by eight wavefronts, one workgroup per CU (ragged-M: tile map of 256-row tiles)
   const int* gather;         // ragged-M MFMA kernels with a k-contiguous A, GELU or store epilogue: row m of the product is row gather[m] / gather_div of A (device [max_rows]); NULL: A holds the rows in order
   int gather_rows, gather_div; //   rows of A behind the index; the index is divided by gather_div first (flat (row, pick) pairs)
@@ -182,6 +180,7 @@ int gemm_ragged_tile_rows(int dtype, int tall_tile);
 int launch_gemm(const GemmDesc& g, hipStream_t s);
 int launch_gemm_f32(const GemmDesc& g, hipStream_t s);   // what launch_gemm does with fp32 operands
 int gemm_f32_tile_rows();
+int launch_gemm_phased(const GemmDesc& g, hipStream_t s);   // the 256 x 256 tile of a big_tile product
 // tile_map capacity in int32 for a ragged-M problem: header, the group order of the ragged-K
 // schedule (one int per group), then a (group, first row) pair per M tile
 inline size_t tile_map_ints(int total_rows, int groups, int tile_rows) {

@@ -5,10 +5,8 @@
 // in the same orientation they have in memory (so global reads are row-contiguous for every
 // transposition) with XOR swizzles against bank conflicts; operands whose contraction index is
 // not the fast one in memory are fetched with the gfx950 LDS transpose read (ds_read_b64_tr_b16).
-// Workgroup tiles: 128 x 128; 256 x 128 for products with many tiles and a long K, and the same on
-// its side (128 x 256) where only A is k-contiguous; 256 x 256 (eight wavefronts, one workgroup per
-// CU, 64-deep k tiles) for the per-expert row products with a long K; 128 x 64 and 128 x 128 with
-// 64-deep k tiles for products with few tiles.
+// Workgroup tiles: 128 x 128; 256 x 128 for weight gradients; 128 x 64 and 128 x 128 with 64-deep k tiles for products
+// with few tiles.  The 256 x 256 tile, which most of the larger products run on, is a kernel of its own (gemm_phased.hip).
 // fp32 storage: see gemm_f32.hip.
 #include "gemm_core.hpp"
 
@@ -36,15 +34,12 @@ void mfma_gemm_kernel(GemmDesc p) {
   // bf16 results accumulate the transposed tile (operands swapped in the MFMA): a lane then owns
   // one output row and groups of 4 consecutive columns, which pack into 8-byte pieces
   constexpr bool SWAP = !(EPI == EPI_ACCUM || OUTF32);
-  static_assert(NS >= 2 && NS <= 4, "ring of 2 to 4 stages");
+  static_assert(NS == 2 || NS == 3, "ring of 2 or 3 stages");
   // The ring.  All reads of it are assembly (see lds_read_*), so the only waits on its loads are
   // the counter waits written out below.
   constexpr int STAGE_CHUNKS = A_CHUNKS + B_CHUNKS;
   constexpr int STAGE_BYTES = STAGE_CHUNKS * 16;
-  // Fragment reads address a stage through the 16-bit instruction offset where the whole ring is
-  // within its reach; in a larger ring the stage's start is added to the address register instead.
-  constexpr bool NEAR_RING = (NS - 1) * STAGE_BYTES + 8192 <= 65536;
-  static_assert(NEAR_RING || (TM > TN ? TM : TN) * 32 * (BK / 8) * 16 <= 65536, "a wave tile's sub-tiles must be within reach of the instruction offset");
+  static_assert((NS - 1) * STAGE_BYTES + 8192 <= 65536, "fragment reads address a stage through the 16-bit instruction offset");
   __shared__ uint4 ring[NS * STAGE_CHUNKS];
   const unsigned ring_at = lds_address(ring);
   constexpr unsigned OUT_OF_RANGE = 0x80000000u;
@@ -110,46 +105,7 @@ void mfma_gemm_kernel(GemmDesc p) {
 
   TileSpace ts = tile_space<BM, BN>(p);
   if (p.mode == GEMM_RAGGED_K && p.tile_map) balance_ragged_k(p, ts);
-  // buffers of one tile (id < 0: no tile, empty ranges); ranges end at the last valid row so that
-  // tails read as zeros
-  auto operands = [&](int id) {
-    TileOperands o;
-    o.t = resolve_tile<BM, BN>(p, ts, id, 2);
-    const TileCoord& t = o.t;
-    const int klen = t.kend - t.kbeg;
-    o.nk = (klen + BK - 1) / BK;
-    o.wrap_first = p.kwrap_b ? (t.kbeg / BK) % (p.kwrap_b / BK) : 0;
-    const bf16_t* A = (const bf16_t*)p.A;
-    if (GATHER) {   // all of A: the rows come through the index
-      o.ra = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, t.valid && klen > 0 ? (int)(((size_t)(p.gather_rows - 1) * p.lda + klen) * 2) : 0, 0x00020000);
-      o.step_a = BK * 2u;
-    } else if (AK) {
-      const int rows = min(t.m_end - t.m0, BM);
-      o.ra = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (size_t)t.m0 * p.lda + t.kbeg), 0,
-                                               rows > 0 && klen > 0 ? (int)(((size_t)(rows - 1) * p.lda + klen) * 2) : 0, 0x00020000);
-      o.step_a = BK * 2u;
-    } else {
-      const int cols = t.valid ? min(p.M - t.m0, BM) : 0;
-      o.ra = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (size_t)t.kbeg * p.lda + t.m0), 0,
-                                               klen > 0 && cols > 0 ? (int)(((size_t)(klen - 1) * p.lda + cols) * 2) : 0, 0x00020000);
-      o.step_a = (unsigned)(BK * p.lda * 2);
-    }
-    const bf16_t* B = (const bf16_t*)t.B;
-    const int kb0 = p.kwrap_b ? 0 : t.kbeg;                  // with a wrap the whole B is one k period
-    const int kblen = !t.valid ? 0 : (p.kwrap_b ? p.kwrap_b : klen);
-    if (BKC) {
-      const int rows = min(p.N - t.n0, BN);
-      o.rb = __builtin_amdgcn_make_buffer_rsrc((void*)(B + (size_t)t.n0 * p.ldb + kb0), 0,
-                                               rows > 0 && kblen > 0 ? (int)(((size_t)(rows - 1) * p.ldb + kblen) * 2) : 0, 0x00020000);
-      o.step_b = BK * 2u;
-    } else {
-      const int cols = min(p.N - t.n0, BN);
-      o.rb = __builtin_amdgcn_make_buffer_rsrc((void*)(B + (size_t)kb0 * p.ldb + t.n0), 0,
-                                               kblen > 0 && cols > 0 ? (int)(((size_t)(kblen - 1) * p.ldb + cols) * 2) : 0, 0x00020000);
-      o.step_b = (unsigned)(BK * p.ldb * 2);
-    }
-    return o;
-  };
+  auto operands = [&](int id) { return tile_operands<BM, BN, BK, AK, BKC, GATHER>(p, resolve_tile<BM, BN>(p, ts, id, 2)); };
   // k tile `tile` of tile `o` -> one ring stage.  (The prefetch requests k tiles past the end of a
   // very short K too, out of range: zeros, no memory traffic.)
   auto fetch = [&](const TileOperands& o, int tile, uint4* dst) {
@@ -195,28 +151,11 @@ void mfma_gemm_kernel(GemmDesc p) {
     }
   }
 
-  // Output rows as buffers: the range ends with the last valid row, so rows of the next group
-  // (or past M) fall outside it and their stores are dropped and their loads read as zero
-  // without a branch; columns at or beyond N get an offset that is out of range by itself.
-  // (Tile coordinates are the same in every lane; saying so keeps the descriptor in scalar
-  // registers where the compiler has lost track of it: a descriptor in vector registers costs
-  // a loop over its distinct values around every access.)
-  auto rows_of = [&](const TileCoord& t, const void* base, int esz_out) {
-    const int c_rows = min(t.m_end - t.m0, BM);
-    const size_t first = (size_t)base + (size_t)t.m0 * p.ldc * esz_out;
-    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)first);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(first >> 32));
-    const int bytes = __builtin_amdgcn_readfirstlane(c_rows > 0 ? (int)(((size_t)(c_rows - 1) * p.ldc + p.N) * esz_out) : 0);
-    return __builtin_amdgcn_make_buffer_rsrc((void*)(((size_t)hi << 32) | lo), 0, bytes, 0x00020000);
-  };
+  auto rows_of = [&](const TileCoord& t, const void* base, int esz_out) { return output_rows<BM>(p, t, base, esz_out); };
   // EPI_DGELU multiplies by act'(saved pre-activation): that tile is requested one tile ahead
   // (row layout: 8 lanes per 64-column row, 8 rows per pass) and used in the epilogue
-  // On the tall tile (TM = 4) the saved tile passes through in two halves of TMH sub-tiles: its
-  // registers and those of its quad form would not fit beside 128 accumulators otherwise.
-  constexpr int HALVES = (EPI == EPI_DGELU && TM > 2) ? 2 : 1;
-  constexpr int TMH = TM / HALVES;
-  uint4 aux[EPI == EPI_DGELU ? TMH * 4 : 1];
-  auto request_aux = [&](const TileCoord& t, int half) {
+  uint4 aux[EPI == EPI_DGELU ? TM * 4 : 1];
+  auto request_aux = [&](const TileCoord& t) {
     if (EPI == EPI_DGELU) {
       const __amdgpu_buffer_rsrc_t ra = rows_of(t, p.aux_in, 2);
       const int col = t.n0 + wn + (lane & 7) * 8;
@@ -225,11 +164,11 @@ void mfma_gemm_kernel(GemmDesc p) {
       const unsigned past_n = ((unsigned)(p.N - 1 - col) >> 31) * OUT_OF_RANGE;
       // One offset register, the passes 8 rows apart added per load: the empty statement keeps
       // the compiler from carrying all the per-pass offsets across tiles in registers of their own.
-      unsigned first = (unsigned)(((size_t)(wm + half * TMH * 32 + (lane >> 3)) * p.ldc + col) * 2) | past_n;
+      unsigned first = (unsigned)(((size_t)(wm + (lane >> 3)) * p.ldc + col) * 2) | past_n;
       asm volatile("" : "+v"(first));
       const unsigned pass_step = (unsigned)(8 * p.ldc * 2);
 #pragma unroll
-      for (int c = 0; c < TMH * 4; ++c)
+      for (int c = 0; c < TM * 4; ++c)
         aux[c] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(ra, first + (unsigned)c * pass_step, 0, NON_TEMPORAL));
     }
   };
@@ -265,7 +204,7 @@ void mfma_gemm_kernel(GemmDesc p) {
   gather_request(cur.t);
   gather_apply();
   prefetch(cur);
-  request_aux(cur.t, 0);
+  request_aux(cur.t);
   // Tile order (see TileClaim): the first tile is this workgroup's slot, every later one is claimed.
   __shared__ int claim_box;
   TileClaim claim(p.claim, stride, &claim_box);
@@ -304,7 +243,6 @@ void mfma_gemm_kernel(GemmDesc p) {
         // in flight: NS - 2 of them, fewer over the last steps (nothing is requested past the end).
         const int younger = min(NS - 2, max(nk, NS - 1) - 1 - it);
         if (younger == NS - 2) BIGMAC_WAIT_VMCNT(RING_AHEAD);
-        else if (NS > 3 && younger > 0) BIGMAC_WAIT_VMCNT(LOADS_PER_TILE);
         else BIGMAC_WAIT_VMCNT(0);
         __builtin_amdgcn_s_barrier();                    // ... and so has everyone's; stage (s - 1) is free
         if (it == 0) BIGMAC_TRACE_AT(cur_id, 1);
@@ -313,8 +251,7 @@ void mfma_gemm_kernel(GemmDesc p) {
         // soon as its fragments are there, while those of the second are still arriving.  (A
         // 64-deep k tile takes two such rounds: its fragments would not fit the registers at once.)
         constexpr int KG = KS < 2 ? KS : 2;
-        constexpr int S_IMM = NEAR_RING ? s * STAGE_BYTES : 0;
-        constexpr unsigned S_REG = NEAR_RING ? 0u : (unsigned)(s * STAGE_BYTES);
+        constexpr int S_IMM = s * STAGE_BYTES;
         constexpr int READS_PER_STEP = (AK ? TM : 2 * TM) + (BKC ? TN : 2 * TN);
         static_for<0, KS / KG>([&](auto round) {
           constexpr int k0 = decltype(round)::value * KG;
@@ -324,18 +261,18 @@ void mfma_gemm_kernel(GemmDesc p) {
             constexpr int kk = decltype(kstep)::value, ks = k0 + kk;
             static_for<0, TM>([&](auto sub) {
               constexpr int i = decltype(sub)::value;
-              if constexpr (AK) lds_read_b128<S_IMM + i * 32 * (BK / 8) * 16>(pa[ks][0][0] + S_REG, fa[kk][i].q);
+              if constexpr (AK) lds_read_b128<S_IMM + i * 32 * (BK / 8) * 16>(pa[ks][0][0], fa[kk][i].q);
               else {
-                lds_read_tr_b64<S_IMM>(pa[ks][0][i] + S_REG, fa[kk][i].h[0]);
-                lds_read_tr_b64<S_IMM>(pa[ks][1][i] + S_REG, fa[kk][i].h[1]);
+                lds_read_tr_b64<S_IMM>(pa[ks][0][i], fa[kk][i].h[0]);
+                lds_read_tr_b64<S_IMM>(pa[ks][1][i], fa[kk][i].h[1]);
               }
             });
             static_for<0, TN>([&](auto sub) {
               constexpr int j = decltype(sub)::value;
-              if constexpr (BKC) lds_read_b128<S_IMM + j * 32 * (BK / 8) * 16>(pb[ks][0][0] + S_REG, fb[kk][j].q);
+              if constexpr (BKC) lds_read_b128<S_IMM + j * 32 * (BK / 8) * 16>(pb[ks][0][0], fb[kk][j].q);
               else {
-                lds_read_tr_b64<S_IMM>(pb[ks][0][j] + S_REG, fb[kk][j].h[0]);
-                lds_read_tr_b64<S_IMM>(pb[ks][1][j] + S_REG, fb[kk][j].h[1]);
+                lds_read_tr_b64<S_IMM>(pb[ks][0][j], fb[kk][j].h[0]);
+                lds_read_tr_b64<S_IMM>(pb[ks][1][j], fb[kk][j].h[1]);
               }
             });
           });
@@ -388,12 +325,10 @@ void mfma_gemm_kernel(GemmDesc p) {
     // EPI_DGELU: turn the saved pre-activation from its row layout into the accumulators' quad
     // layout now; its registers are then free for the next tile's request, which goes out ahead
     // of the prefetch and is therefore complete whenever a k tile of that prefetch is.
-    // (Tall tile: the first half now, with the second half requested in its place; the second half
-    // is turned, and the next tile's first half requested, between the two halves of the epilogue.)
-    u32x2_t pre[EPI == EPI_DGELU ? TMH * TN * 4 : 1];
+    u32x2_t pre[EPI == EPI_DGELU ? TM * TN * 4 : 1];
     auto turn_aux = [&]() {
 #pragma unroll
-      for (int i = 0; i < TMH; ++i) {
+      for (int i = 0; i < TM; ++i) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) lds_write_b128(row_at(q), __builtin_bit_cast(u32x4_t, aux[i * 4 + q]));
 #pragma unroll
@@ -405,8 +340,7 @@ void mfma_gemm_kernel(GemmDesc p) {
     };
     if (EPI == EPI_DGELU) {
       turn_aux();
-      if (HALVES == 2) request_aux(t, 1);
-      else request_aux(nxt.t, 0);
+      request_aux(nxt.t);
     }
     prefetch(nxt);
 
@@ -505,10 +439,6 @@ void mfma_gemm_kernel(GemmDesc p) {
       };
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        if (EPI == EPI_DGELU && HALVES == 2 && i == TMH) {
-          turn_aux();
-          request_aux(nxt.t, 0);
-        }
         if (EPI == EPI_GELU && p.aux_out) {   // the pre-activation itself, for the backward pass
 #pragma unroll
           for (int j = 0; j < TN; ++j)
@@ -532,7 +462,7 @@ void mfma_gemm_kernel(GemmDesc p) {
 #pragma unroll
               for (int vr = 0; vr < 4; ++vr) v[vr] = gelu_bf16_f(v[vr]);
             } else if (EPI == EPI_DGELU) {
-              const u32x2_t sv = pre[((i % TMH) * TN + j) * 4 + vq];
+              const u32x2_t sv = pre[(i * TN + j) * 4 + vq];
               v[0] *= gelu_grad_bf16_f(__uint_as_float(sv.x << 16));
               v[1] *= gelu_grad_bf16_f(__uint_as_float(sv.x & 0xFFFF0000u));
               v[2] *= gelu_grad_bf16_f(__uint_as_float(sv.y << 16));
@@ -715,73 +645,10 @@ int launch_mfma(const GemmDesc& g, hipStream_t s) {
   return BIGMAC_OK;
 }
 
-// 256 x 256 outputs by eight wavefronts (each 128 x 64, as in the tall tile), one workgroup per
-// CU, 32-deep k tiles in a ring of four 32 KB stages.  Per flop it asks the L2 for two thirds of
-// the operand bytes the tall tile does (see the comment at launch_gemm).
-template <bool AK, bool BKC>
-int launch_mfma_wide(const GemmDesc& g, hipStream_t s) {
-  constexpr int BM = 256, BN = 256, BK = 32;
-  dim3 grid = grid_for<BM, BN>(g, true, 1), block(512);
-#define BIGMAC_MFMA_WIDE(EPI, OUTF32) \
-  hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 2, 4, AK, BKC, EPI, OUTF32, 4>), grid, block, 0, s, g)
-  if constexpr (AK && !BKC) {
-    if (g.gather) {
-      if (g.epilogue == EPI_GELU) hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 2, 4, AK, BKC, EPI_GELU, false, 4, true>), grid, block, 0, s, g);
-      else if (g.epilogue == EPI_STORE && !g.out_f32)
-        hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 2, 4, AK, BKC, EPI_STORE, false, 4, true>), grid, block, 0, s, g);
-      else return BIGMAC_ERR_UNSUPPORTED;
-      BIGMAC_CHECK_LAUNCH();
-      return BIGMAC_OK;
-    }
-  }
-  switch (g.epilogue) {
-    case EPI_STORE:
-      if (g.out_f32) BIGMAC_MFMA_WIDE(EPI_STORE, true);
-      else BIGMAC_MFMA_WIDE(EPI_STORE, false);
-      break;
-    case EPI_GELU: BIGMAC_MFMA_WIDE(EPI_GELU, false); break;
-    case EPI_DGELU: BIGMAC_MFMA_WIDE(EPI_DGELU, false); break;
-    case EPI_ACCUM: BIGMAC_MFMA_WIDE(EPI_ACCUM, true); break;
-    default: return BIGMAC_ERR_INVALID_ARG;
-  }
-#undef BIGMAC_MFMA_WIDE
-  BIGMAC_CHECK_LAUNCH();
-  return BIGMAC_OK;
-}
-
-// 128 x 256 outputs: the tall tile turned on its side (four wavefronts side by side, each 128 x 64;
-// the same ring and registers).  For the expert-up product, whose A rows are k-contiguous (64
-// bytes of a row per k tile, half a cache line) while its B rows are whole lines: half the A rows
-// and twice the B columns per tile mean fewer of the half-line requests per flop, and an expert's
-// last tile pads half as many rows.  Measured against the tall tile: expert-up -5.5 % at
-// zipf_stress, -7 % at gpt_xl and gpt_6p7b; the two shared projections of the forward pass, which
-// have the same operand layouts, -6 % and -9 % at zipf_stress.  (Products whose B is k-contiguous
-// too gain nothing.)
-int launch_mfma_long(const GemmDesc& g, hipStream_t s) {
-  constexpr int BM = 128, BN = 256, BK = BIGMAC_TILE_BK;
-  dim3 grid = grid_for<BM, BN>(g, true, BIGMAC_TALL_BLOCKS_PER_CU), block(256);
-  if (g.epilogue == EPI_ACCUM) hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 1, 4, true, false, EPI_ACCUM, true>), grid, block, 0, s, g);
-  else if (g.epilogue == EPI_STORE) {   // the dense projections
-    if (g.scatter) hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 1, 4, true, false, EPI_STORE, false, BIGMAC_TILE_STAGES, false, true>), grid, block, 0, s, g);
-    else if (g.out_f32) hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 1, 4, true, false, EPI_STORE, true>), grid, block, 0, s, g);
-    else hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 1, 4, true, false, EPI_STORE, false>), grid, block, 0, s, g);
-  } else if (g.gather) hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 1, 4, true, false, EPI_GELU, false, BIGMAC_TILE_STAGES, true>), grid, block, 0, s, g);
-  else hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 1, 4, true, false, EPI_GELU, false>), grid, block, 0, s, g);
-  BIGMAC_CHECK_LAUNCH();
-  return BIGMAC_OK;
-}
-
-// The 256 x 256 tile with 64-deep k tiles in a ring of two 64 KB stages: k-contiguous operands
-// arrive as whole 128-byte lines, half the requests to the L2.  Plain stores and the GELU' epilogue.
-template <bool AK, bool BKC>
-int launch_mfma_wide64(const GemmDesc& g, hipStream_t s) {
-  constexpr int BM = 256, BN = 256, BK = 64;
-  dim3 grid = grid_for<BM, BN>(g, true, 1), block(512);
-  if (g.gather || g.scatter) return BIGMAC_ERR_UNSUPPORTED;
-  if (g.epilogue == EPI_DGELU) hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 2, 4, AK, BKC, EPI_DGELU, false, 2>), grid, block, 0, s, g);
-  else if (g.epilogue != EPI_STORE) return BIGMAC_ERR_UNSUPPORTED;
-  else if (g.out_f32) hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 2, 4, AK, BKC, EPI_STORE, true, 2>), grid, block, 0, s, g);
-  else hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 2, 4, AK, BKC, EPI_STORE, false, 2>), grid, block, 0, s, g);
+// The tall tile: 256 x 128 outputs (each wavefront 128 x 64), for the weight gradients.
+int launch_mfma_tall(const GemmDesc& g, hipStream_t s) {
+  hipLaunchKernelGGL((mfma_gemm_kernel<BIGMAC_TALL_BM, BIGMAC_TILE_BN, BIGMAC_TILE_BK, 2, 2, false, false, EPI_ACCUM, true>),
+                     (grid_for<BIGMAC_TALL_BM, BIGMAC_TILE_BN>(g, true)), dim3(256), 0, s, g);
   BIGMAC_CHECK_LAUNCH();
   return BIGMAC_OK;
 }
@@ -879,11 +746,16 @@ ClaimScope::~ClaimScope() { claim_pool = {nullptr, 0}; }
 
 int launch_gemm(const GemmDesc& desc, hipStream_t s) {
   GemmDesc g = desc;
-  // The claimed order for the ragged-M products only.  Measured on zipf_stress: the four per-expert
-  // row products 13-19 % faster with it; the ragged-K weight gradients 40 % slower (the tiles of a
-  // group all cost the same, and with the fixed stride every workgroup of an XCD is on the same
-  // group and k range at once, which the claimed order breaks up); dense products level or 1-3 % slower.
-  if (!g.claim && g.dtype == BIGMAC_BF16 && g.mode == GEMM_RAGGED_M && claim_pool.base && claim_pool.next < CLAIM_SLOTS)
+  // The claimed order for the ragged-M products.  Measured on zipf_stress: the four per-expert row products 13-19 %
+  // faster with it; the ragged-K weight gradients 40 % slower on the 256 x 128 tile (the tiles of a group all cost the
+  // same, and with the fixed stride every workgroup of an XCD is on the same group and k range at once, which the
+  // claimed order breaks up); dense products level or 1-3 % slower.  On the 256 x 256 tile a group of at most 8 tiles
+  // does not occupy an XCD's 32 workgroups by itself, and under skewed routing the claimed order is what keeps the
+  // others busy (1024 x 256 outputs of 64 experts, 65536 rows, Zipf 1.2: 220 -> 146 us; level where routing is even;
+  // 16 tiles per group 274 -> 319 us).
+  const long group_tiles = (long)((g.M + 255) / 256) * ((g.N + 255) / 256);
+  if (!g.claim && g.dtype == BIGMAC_BF16 && (g.mode == GEMM_RAGGED_M || (g.mode == GEMM_RAGGED_K && g.big_tile && group_tiles <= 8)) && claim_pool.base &&
+      claim_pool.next < CLAIM_SLOTS)
     g.claim = claim_pool.base + (size_t)CLAIM_SLOT_INTS * claim_pool.next++;
   // host-side shape checks: the kernels move 16-byte chunks and 64-wide k tiles
   if (g.N <= 0 || (g.mode != GEMM_RAGGED_M && g.M <= 0) || (g.mode != GEMM_RAGGED_K && g.K <= 0)) return BIGMAC_ERR_INVALID_ARG;
@@ -916,31 +788,13 @@ int launch_gemm(const GemmDesc& desc, hipStream_t s) {
   }
   if (g.scatter) {  // see the kernel: a dense bf16 product's rows written through an index, the same operand layout as above
     if (g.dtype != BIGMAC_BF16 || g.mode != GEMM_DENSE || combo != 2 || g.epilogue != EPI_STORE || g.out_f32 || g.ksplit != 1 || g.wide_k ||
-        g.big_tile || g.gather || g.bias || g.scatter_k <= 0 || g.scatter_rows <= 0 ||
+        g.gather || g.bias || g.scatter_k <= 0 || g.scatter_rows <= 0 ||
         (size_t)g.M * (size_t)g.scatter_k * 4 >= (1ull << 31) || (size_t)g.scatter_rows * (size_t)g.ldc * 2 >= (1ull << 31))
       return BIGMAC_ERR_UNSUPPORTED;
   }
-  if (g.long_tile) {   // the expert-up product and the forward pass's shared projections
-    const bool expert_up = g.mode == GEMM_RAGGED_M && g.epilogue == EPI_GELU && !g.scatter;
-    const bool projection = g.mode == GEMM_DENSE && (g.epilogue == EPI_STORE || g.epilogue == EPI_ACCUM) && g.ksplit == 1 && !g.gather &&
-                            (!g.scatter || g.epilogue == EPI_STORE);
-    if (g.dtype != BIGMAC_BF16 || combo != 2 || !(expert_up || projection) || g.tall_tile || g.big_tile || g.wide_k || g.deep_tile)
-      return BIGMAC_ERR_INVALID_ARG;
-    return launch_mfma_long(g, s);
-  }
   if (g.big_tile) {
     if (g.dtype != BIGMAC_BF16 || g.tall_tile || g.wide_k || g.deep_tile || g.touch_bytes) return BIGMAC_ERR_INVALID_ARG;
-    // k-contiguous A and a K of whole 64-deep k tiles: the 64-deep form (whole-line requests).  Measured at
-    // zipf_stress against the 32-deep ring of four: expert-down -3.5 %, the first matrix's data gradient
-    // (both operands k-contiguous) -8.3 %, the GELU' product -1.3 %; expert-up +6 %, which keeps its own tile.
-    if (g.a_kcontig && g.K % 64 == 0 && !g.gather && (g.epilogue == EPI_STORE || g.epilogue == EPI_DGELU))
-      return g.b_kcontig ? launch_mfma_wide64<true, true>(g, s) : launch_mfma_wide64<true, false>(g, s);
-    switch (combo) {
-      case 2: return launch_mfma_wide<true, false>(g, s);
-      case 3: return launch_mfma_wide<true, true>(g, s);
-      case 0: return launch_mfma_wide<false, false>(g, s);
-      default: return BIGMAC_ERR_UNSUPPORTED;
-    }
+    return launch_gemm_phased(g, s);
   }
   if (g.dtype == BIGMAC_BF16) {
     if (g.wide_k) {
@@ -959,12 +813,8 @@ int launch_gemm(const GemmDesc& desc, hipStream_t s) {
       }
     }
     if (g.tall_tile) {
-      switch (combo) {
-        case 2: return launch_mfma<BIGMAC_TALL_BM, true, false>(g, s);
-        case 3: return launch_mfma<BIGMAC_TALL_BM, true, true>(g, s);
-        case 0: return launch_mfma<BIGMAC_TALL_BM, false, false>(g, s);
-        default: return BIGMAC_ERR_UNSUPPORTED;
-      }
+      if (combo != 0 || g.epilogue != EPI_ACCUM) return BIGMAC_ERR_UNSUPPORTED;   // the weight gradients
+      return launch_mfma_tall(g, s);
     }
     switch (combo) {
       case 2: return launch_mfma<BIGMAC_TILE_BM, true, false>(g, s);

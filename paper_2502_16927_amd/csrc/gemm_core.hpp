@@ -368,4 +368,60 @@ struct TileOperands {
   int wrap_first;            // with a wrapped B: k tile index (within the wrap period) of this tile's first k tile
 };
 
+// Buffers of one tile (no tile: empty ranges); ranges end at the last valid row, so that tails read as zeros.
+template <int BM, int BN, int BK, bool AK, bool BKC, bool GATHER = false>
+__device__ __forceinline__ TileOperands tile_operands(const GemmDesc& p, const TileCoord& t) {
+  TileOperands o;
+  o.t = t;
+  const int klen = t.kend - t.kbeg;
+  o.nk = (klen + BK - 1) / BK;
+  o.wrap_first = p.kwrap_b ? (t.kbeg / BK) % (p.kwrap_b / BK) : 0;
+  const bf16_t* A = (const bf16_t*)p.A;
+  if (GATHER) {   // all of A: the rows come through the index
+    o.ra = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, t.valid && klen > 0 ? (int)(((size_t)(p.gather_rows - 1) * p.lda + klen) * 2) : 0, 0x00020000);
+    o.step_a = BK * 2u;
+  } else if (AK) {
+    const int rows = min(t.m_end - t.m0, BM);
+    o.ra = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (size_t)t.m0 * p.lda + t.kbeg), 0,
+                                             rows > 0 && klen > 0 ? (int)(((size_t)(rows - 1) * p.lda + klen) * 2) : 0, 0x00020000);
+    o.step_a = BK * 2u;
+  } else {
+    const int cols = t.valid ? min(p.M - t.m0, BM) : 0;
+    o.ra = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (size_t)t.kbeg * p.lda + t.m0), 0,
+                                             klen > 0 && cols > 0 ? (int)(((size_t)(klen - 1) * p.lda + cols) * 2) : 0, 0x00020000);
+    o.step_a = (unsigned)(BK * p.lda * 2);
+  }
+  const bf16_t* B = (const bf16_t*)t.B;
+  const int kb0 = p.kwrap_b ? 0 : t.kbeg;                  // with a wrap the whole B is one k period
+  const int kblen = !t.valid ? 0 : (p.kwrap_b ? p.kwrap_b : klen);
+  if (BKC) {
+    const int rows = min(p.N - t.n0, BN);
+    o.rb = __builtin_amdgcn_make_buffer_rsrc((void*)(B + (size_t)t.n0 * p.ldb + kb0), 0,
+                                             rows > 0 && kblen > 0 ? (int)(((size_t)(rows - 1) * p.ldb + kblen) * 2) : 0, 0x00020000);
+    o.step_b = BK * 2u;
+  } else {
+    const int cols = min(p.N - t.n0, BN);
+    o.rb = __builtin_amdgcn_make_buffer_rsrc((void*)(B + (size_t)kb0 * p.ldb + t.n0), 0,
+                                             kblen > 0 && cols > 0 ? (int)(((size_t)(kblen - 1) * p.ldb + cols) * 2) : 0, 0x00020000);
+    o.step_b = (unsigned)(BK * p.ldb * 2);
+  }
+  return o;
+}
+
+// Output rows as buffers: the range ends with the last valid row, so rows of the next group
+// (or past M) fall outside it and their stores are dropped and their loads read as zero
+// without a branch; columns at or beyond N get an offset that is out of range by itself.
+// (Tile coordinates are the same in every lane; saying so keeps the descriptor in scalar
+// registers where the compiler has lost track of it: a descriptor in vector registers costs
+// a loop over its distinct values around every access.)
+template <int BM>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t output_rows(const GemmDesc& p, const TileCoord& t, const void* base, int esz_out) {
+  const int c_rows = min(t.m_end - t.m0, BM);
+  const size_t first = (size_t)base + (size_t)t.m0 * p.ldc * esz_out;
+  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)first);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(first >> 32));
+  const int bytes = __builtin_amdgcn_readfirstlane(c_rows > 0 ? (int)(((size_t)(c_rows - 1) * p.ldc + p.N) * esz_out) : 0);
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(((size_t)hi << 32) | lo), 0, bytes, 0x00020000);
+}
+
 }  // namespace bigmac

@@ -73,7 +73,7 @@ struct FwdPlan {
   size_t logits, perm, x_low, partials, aux, claims, total;
 };
 struct BwdPlan {
-  size_t dy_low, dgate, do_perm, dx_perm, dact, dx_low, dL, route, dx_f32, part_up, part_gate, part_down, bias_sums, gate_low, w_up_t, w_down_t, claims, total;
+  size_t dy_low, dgate, do_perm, dx_perm, dact, dx_low, dL, route, dx_f32, part_up, part_gate, part_down, bias_sums, gate_low, claims, total;
 };
 
 inline bool bf(const bigmac_dims& D) { return D.dtype == BIGMAC_BF16; }
@@ -102,25 +102,10 @@ inline bool wire_f32(const bigmac_dims& D) { return bf(D) && !(D.flags & BIGMAC_
 inline int wire_dtype(const bigmac_dims& D) { return wire_f32(D) ? BIGMAC_F32 : D.dtype; }
 inline size_t low_bytes(const bigmac_dims& D) { return (size_t)D.T * (bf(D) ? 2 * D.r * 2 : D.r * 4); }
 
-// Which products run on the GEMM's tall (256-row) workgroup tiles.  The per-expert products on
-// permuted rows (expert up/down, the data gradient of the first matrix): when there are enough
-// tall tiles to fill the chip a few times over, K is at least 512 and the experts hold 512 rows
-// on average (measured: 4-18 % faster at the gpt_xl to zipf_stress shapes; level or slower at
-// the gpt_medium shapes, where K = r = 256 or the tile count is low).  The per-expert weight
-// gradients: whenever their M divides into tall tiles (22-30 % faster at the large shapes, level
-// at gpt_medium).  The products over the token index have few tiles and stay on the square tile.
-inline bool tall_rows(const bigmac_dims& D, int cols, int K) {
-  if (!bf(D)) return false;
-  const long Tk = (long)D.T * D.k;
-  const long tiles = (Tk / 256 + D.N) * ((cols + 127) / 128);
-  return tiles >= 1536 && K >= 512 && Tk / D.N >= 512;
-}
-inline bool tall_wgrad(const bigmac_dims& D, int M) {   // up to a fifth of padding in M still pays
+// Per-expert weight gradients on the 256 x 128 tile: up to a fifth of padding in M still pays (measured against the
+// square tile: 22-30 % faster at the large shapes, level at gpt_medium).
+inline bool tall_wgrad(const bigmac_dims& D, int M) {
   return bf(D) && (long)((M + 255) / 256) * 256 * 5 <= (long)M * 6;
-}
-// The shared projections and their data gradients: the same rule as for the per-expert products.
-inline bool tall_dense(const bigmac_dims& D, int M, int N, int K) {
-  return bf(D) && (long)(M / 256) * ((N + 127) / 128) >= 1024 && K >= 512;
 }
 // Few 128 x 128 tiles under a long K: the narrower tile with deeper k tiles (see launch_gemm).
 inline bool deep_dense(const bigmac_dims& D, int M, int N, int K) {
@@ -159,29 +144,61 @@ inline void touch_weights(const bigmac_dims& D, GemmDesc& g, const void* w, int 
 inline bool wide_k_ok(const bigmac_dims& D, int K, int bit) {
   return bf(D) && (BIGMAC_WIDEK_MASK & bit) && K % 64 == 0;
 }
-// Which products run on 256 x 256 tiles (eight wavefronts, one workgroup per CU): the per-expert
-// row products that qualify for the tall tile and have K >= 2048.  Per flop that tile asks the L2
-// for two thirds of the operand bytes of the tall one, and these products run at the rate their
-// operands arrive at; its epilogue is not overlapped by another workgroup's k loop, which is what
-// a shorter K does not pay for.  Measured (tall -> 256 x 256): zipf_stress expert-down and the
-// first matrix's data gradient (K = 2048) 1.27 -> 1.19 ms and 1.36 -> 1.27 ms, gpt_xl 0.287 ->
-// 0.275 ms and level; expert-up at K = 512 / 1024 3-6 % slower; the ragged-K weight gradients
-// 5-7 % slower, so they take it only under BIGMAC_FLAG_TILES_LARGE.
-inline bool big_rows(const bigmac_dims& D, int cols, int K) {
-  if (!bf(D) || (D.flags & BIGMAC_FLAG_TILES_SMALL)) return false;
-  if (D.flags & BIGMAC_FLAG_TILES_LARGE) return true;
-  return K >= 2048 && cols % 256 == 0 && tall_rows(D, cols, K);
+// Which products run on 256 x 256 tiles (gemm_phased.hip).  Times are those of one product, the tiles of gemm.hip -> 256 x 256.
+inline bool tiles_forced(const bigmac_dims& D, bool* large) {
+  *large = (D.flags & BIGMAC_FLAG_TILES_LARGE) != 0;
+  return !bf(D) || (D.flags & (BIGMAC_FLAG_TILES_LARGE | BIGMAC_FLAG_TILES_SMALL));
 }
-inline bool big_wgrad(const bigmac_dims& D) { return bf(D) && (D.flags & BIGMAC_FLAG_TILES_LARGE) && !(D.flags & BIGMAC_FLAG_TILES_SMALL); }
-inline bool any_tall_rows(const bigmac_dims& D) {   // a tile map of 256-row tiles is needed
+// Per-expert row products: estimated tiles (half of an expert's last row tile) against the 256 CUs.  With a plain
+// store the tile pays from about a third of a round (94 tiles: 33 -> 27 us and 50 -> 45 us; 41 and 46 tiles: 19 -> 22.5,
+// 33 -> 42 us) if its columns are not mostly padding (width 128: 51 -> 59 us).  The activation epilogues are not
+// overlapped by another workgroup's k loop, so they want a longer K and more tiles: K 512, 376 tiles 38 -> 40 us, 792
+// tiles 64 -> 56 us; K 1024, 288 tiles 67 -> 62 us; K 256, 1152 tiles 79 -> 89 us with GELU and its two results, 98 -> 93 us
+// with GELU'; and few rows per expert, whose products stream the weights, keep more of the smaller workgroups in flight
+// (4 rows 102 -> 112 us, 16 rows 111 -> 115 us, 62 rows 127 -> 118 us).
+inline bool big_rows(const bigmac_dims& D, int cols, int K, GemmEpilogue epilogue) {
+  bool large;
+  if (tiles_forced(D, &large)) return bf(D) && large;
+  const long rows = (long)D.T * D.k, tiles = (rows / 256 + D.N / 2) * ((cols + 255) / 256);
+  if (epilogue == EPI_STORE) return K >= 256 && cols >= 192 && tiles >= 90;
+  if (rows / D.N < 48 || K < (epilogue == EPI_GELU ? 384 : 256)) return false;
+  return tiles >= (K >= 1024 ? 256 : K >= 384 ? 512 : 1024);
+}
+// Per-expert weight gradients: enough tiles, and no more padded columns than on 128-wide tiles (2560 x 640 outputs: 149 -> 158 us,
+// 640 x 2560: 164 -> 140 us; 1024 x 256 of 64 experts: 52 -> 47 us; of 16 experts, 64 tiles: 78 -> 80 us).
+// A tile is one chain over its expert's rows, up to T of them under skewed routing, against T k per_group / 256 rows that
+// a workgroup walks on average.  With up to 8 tiles per expert the workgroups claim their tiles (see launch_gemm), which
+// levels the rest; with more a factor of three is where the longer chain of the larger tile shows (12 tiles, k 4, Zipf
+// 1.2: 111 -> 148 us; 16 tiles, k 8: 251 -> 268 us, even routing 232 -> 213 us).
+inline bool big_wgrad(const bigmac_dims& D, int M, int N) {
+  bool large;
+  if (tiles_forced(D, &large)) return bf(D) && large;
+  const long per_group = (long)((M + 255) / 256) * ((N + 255) / 256);
+  if (per_group > 8 && per_group * D.k < 90) return false;
+  return D.N * per_group >= 256 && (long)((N + 255) / 256) * 256 * 10 <= (long)((N + 127) / 128) * 128 * 11;
+}
+// The shared projections and their data gradients: by how full the rounds of 256 tiles are (a last round of at most
+// 128 tiles runs as row halves, three quarters of a round).  Ascending and its counterpart at 512, 472 and 252 tiles: 78 -> 77 us
+// and 112 -> 103, 53 -> 51 and 73 -> 70, 32 -> 30 and 43 -> 42; at 320 and 128 tiles: 53 -> 59 and 70 -> 74, 20 -> 22 and 26 -> 30.
+// The product dy W_up^T, whose operands are both k-contiguous, gains from 80 tiles on where it does not run on the
+// 128 x 64 tile (53 -> 44 us; 128 tiles: 62 -> 49 us).
+inline bool big_dense(const bigmac_dims& D, int M, int N, int K) {
+  bool large;
+  if (K % 64) return false;
+  if (tiles_forced(D, &large)) return bf(D) && large;
+  const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256), last = tiles % 256;
+  const double rounds = (double)(tiles / 256) + (last == 0 ? 0.0 : last <= 128 ? 0.75 : 1.0);
+  return tiles >= 512 || (double)tiles >= 0.8 * 256.0 * rounds;
+}
+inline bool any_big_rows(const bigmac_dims& D) {   // a tile map of 256-row tiles is needed
   const Widths W = widths(D);
-  return tall_rows(D, W.hid, W.win) || tall_rows(D, W.win, W.hid) || big_rows(D, W.hid, W.win) || big_rows(D, W.win, W.hid);
+  return big_rows(D, W.hid, W.win, EPI_GELU) || big_rows(D, W.hid, W.win, EPI_DGELU) || big_rows(D, W.win, W.hid, EPI_STORE);
 }
 
 TileMapJobs tile_map_jobs(const bigmac_dims& D, int* tile_map, int* tile_map_tall, unsigned* claims) {
   TileMapJobs maps = {};
   maps.tile_rows[0] = gemm_ragged_tile_rows(D.dtype, 0); maps.map[0] = tile_map;
-  if (any_tall_rows(D)) { maps.tile_rows[1] = gemm_ragged_tile_rows(D.dtype, 1); maps.map[1] = tile_map_tall; }
+  if (any_big_rows(D)) { maps.tile_rows[1] = gemm_ragged_tile_rows(D.dtype, 1); maps.map[1] = tile_map_tall; }
   maps.clear = claims; maps.clear_ints = CLAIM_INTS;
   return maps;
 }
@@ -197,7 +214,7 @@ SavedPlan plan_saved(const bigmac_dims& D) {
   p.slot_of = c.take(Tk * 4);
   p.src_of = c.take(Tk * 4);
   p.tile_map = c.take(tile_map_ints((int)Tk, D.N, gemm_ragged_tile_rows(D.dtype, 0)) * 4);
-  p.tile_map_tall = c.take(any_tall_rows(D) ? tile_map_ints((int)Tk, D.N, gemm_ragged_tile_rows(D.dtype, 1)) * 4 : 0);
+  p.tile_map_tall = c.take(any_big_rows(D) ? tile_map_ints((int)Tk, D.N, gemm_ragged_tile_rows(D.dtype, 1)) * 4 : 0);
   p.x_perm = c.take(Tk * W.win * es);
   p.act = c.take(Tk * wide_ld(D) * es);
   p.hact = c.take(Tk * wide_ld(D) * es);
@@ -283,26 +300,6 @@ inline TileShape token_wgrad_shape(const bigmac_dims& D, int M, int N) {
 }
 inline int token_wgrad_ksplit(const bigmac_dims& D, int M, int N) { return choose_ksplit(M, N, D.T, token_wgrad_shape(D, M, N)); }
 
-// The data gradients of the two shared projections (dy W_up^T, dx' W_down^T) contract over the
-// fast index of the weight as it is stored: both operands k-contiguous, half a cache line per
-// row and k tile.  Where those products are large enough for the 256-row tile, a transposed copy
-// of the weight (8 MB at d = 4096, r = 1024: two launches of a few microseconds) gives them the
-// operand layouts of the forward projections and with them the 128 x 256 tile.
-inline bool transposed_projections(const bigmac_dims& D) {
-  return D.order == BIGMAC_ORDER_DCCA && bf(D) && tall_dense(D, D.T, D.r, D.d) && tall_dense(D, D.T, D.d, low_ld(D)) &&
-         D.r % 8 == 0 && D.d % 8 == 0;
-}
-// out[c][r] = in[r][c] for 16-bit elements, 64 x 64 tiles through the LDS
-__global__ __launch_bounds__(256) void transpose_b16_kernel(const uint16_t* __restrict__ in, uint16_t* __restrict__ out, int rows, int cols) {
-  __shared__ uint16_t tile[64][66];
-  const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64, tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int i = ty; i < 64; i += 4)
-    if (r0 + i < rows && c0 + tx < cols) tile[i][tx] = in[(size_t)(r0 + i) * cols + c0 + tx];
-  __syncthreads();
-  for (int i = ty; i < 64; i += 4)
-    if (c0 + i < cols && r0 + tx < rows) out[(size_t)(c0 + i) * rows + r0 + tx] = tile[tx][i];
-}
-
 BwdPlan plan_bwd(const bigmac_dims& D) {
   const Widths W = widths(D);
   const size_t Tk = (size_t)D.T * D.k, es = esize(D.dtype);
@@ -324,9 +321,6 @@ BwdPlan plan_bwd(const bigmac_dims& D) {
   p.part_gate = c.take((size_t)token_wgrad_ksplit(D, dg, D.N) * dg * D.N * 4);
   p.part_up = c.take(dcca ? (size_t)token_wgrad_ksplit(D, D.r, D.d) * D.r * D.d * 4 : 0);
   p.part_down = c.take(dcca ? (size_t)token_wgrad_ksplit(D, D.d, D.r) * D.d * D.r * 4 : 0);
-  // transposed copies of the two shared matrices for the data gradients of the projections (see transposed_projections)
-  p.w_up_t = c.take(transposed_projections(D) ? (size_t)D.d * D.r * es : 0);
-  p.w_down_t = c.take(transposed_projections(D) ? (size_t)D.d * D.r * es : 0);
   // expert biases: partial column sums (sized for the wider of the two bias vectors; taken always,
   // the plan does not see the parameters); router on x': its share of dx' in fp32
   p.bias_sums = c.take(ragged_colsum_ws_bytes(D.N, W.hid > W.win ? W.hid : W.win));
@@ -369,10 +363,9 @@ int run_experts_forward(const bigmac_dims& D, const void* x_perm, const int* off
   g.groups = D.N; g.max_rows = Tk; g.offsets = offsets;
   // hact = gelu(x_perm W1[e])
   g.epilogue = EPI_GELU;
-  g.big_tile = big_rows(D, W.hid, W.win);
-  g.tall_tile = !g.big_tile && tall_rows(D, W.hid, W.win); g.tile_map = (g.tall_tile || g.big_tile) ? tile_map_tall : tile_map;
-  if (g.tall_tile) { g.tall_tile = 0; g.long_tile = 1; g.tile_map = tile_map; }   // this product: the tall tile on its side (see launch_mfma_long)
-  g.wide_k = !g.tall_tile && !g.big_tile && !g.long_tile && !gather && wide_k_ok(D, W.win, 1);
+  g.big_tile = big_rows(D, W.hid, W.win, EPI_GELU);
+  g.tile_map = g.big_tile ? tile_map_tall : tile_map;
+  g.wide_k = !g.big_tile && !gather && wide_k_ok(D, W.win, 1);
   g.A = x_perm; g.lda = W.win; g.K = W.win;
   g.gather = gather; g.gather_rows = D.T; g.gather_div = D.k;   // with an index, x_perm is the [T, win] rows before the dispatch
   g.B = w1; g.ldb = W.hid; g.gstride_b = (long)W.win * W.hid; g.N = W.hid;
@@ -395,10 +388,9 @@ int run_experts_forward(const bigmac_dims& D, const void* x_perm, const int* off
   g.B = w2; g.ldb = W.win; g.gstride_b = (long)W.hid * W.win; g.N = W.win;
   g.C = o_perm; g.ldc = W.win;
   g.bias = b2; g.gstride_bias = W.win;
-  g.big_tile = big_rows(D, W.win, W.hid);
-  g.long_tile = 0;
-  g.tall_tile = !g.big_tile && tall_rows(D, W.win, W.hid); g.tile_map = (g.tall_tile || g.big_tile) ? tile_map_tall : tile_map;
-  g.wide_k = !g.tall_tile && !g.big_tile && wide_k_ok(D, W.hid, 2);
+  g.big_tile = big_rows(D, W.win, W.hid, EPI_STORE);
+  g.tile_map = g.big_tile ? tile_map_tall : tile_map;
+  g.wide_k = !g.big_tile && wide_k_ok(D, W.hid, 2);
   g.kloop_priority = 1;
   g.touch = nullptr; g.touch_bytes = 0;
   if (!g.big_tile) touch_weights(D, g, w2, 2);
@@ -674,8 +666,8 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
   // stored: nothing else reads it).  Not where the product is summed from K slices, nor where the
   // copy is too large for one 32-bit byte offset.
   const int descend_ksplit = dcca ? forward_ksplit(*D, D->T, D->r, D->d) : 1;
-  const bool descend_tall = dcca && descend_ksplit == 1 && tall_dense(*D, D->T, D->r, D->d);
-  const bool descend_deep = dcca && descend_ksplit == 1 && !descend_tall && deep_dense(*D, D->T, D->r, D->d);
+  const bool descend_big = dcca && descend_ksplit == 1 && big_dense(*D, D->T, D->r, D->d);
+  const bool descend_deep = dcca && descend_ksplit == 1 && !descend_big && deep_dense(*D, D->T, D->r, D->d);
   const bool scatter_descend = saved && descend_scatters(*D);
   if (scatter_descend) {
     rc = permute();
@@ -691,13 +683,12 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
     {
       BIGMAC_STAGE(BIGMAC_STAGE_DESCEND);
       g.ksplit = descend_ksplit;
-      g.tall_tile = descend_tall;
+      g.big_tile = descend_big;
       g.deep_tile = descend_deep;
       if (scatter_descend) {
         g.scatter = slot_of; g.scatter_k = D->k; g.scatter_rows = D->T * D->k;
         g.C = x_perm;
       }
-      if (g.tall_tile) { g.tall_tile = 0; g.long_tile = 1; }   // k-contiguous A, whole-line B: the tall tile on its side (see launch_mfma_long)
       if (g.ksplit > 1) {   // fp32 partials, then one rounding to bf16
         g.out_f32 = 1; g.C = wsb + F.partials; g.gstride_c = (long)D->T * D->r;
         rc = launch_gemm(g, s);
@@ -747,9 +738,8 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
     g.C = y; g.ldc = D->d;
     BIGMAC_STAGE(BIGMAC_STAGE_ASCEND);
     g.ksplit = forward_ksplit(*D, D->T, D->d, low_ld(*D));
-    g.tall_tile = g.ksplit == 1 && tall_dense(*D, D->T, D->d, low_ld(*D));
-    g.wide_k = g.ksplit == 1 && !g.tall_tile && wide_k_ok(*D, low_ld(*D), 32);
-    if (g.tall_tile) { g.tall_tile = 0; g.long_tile = 1; }     // as for the descending projection
+    g.big_tile = g.ksplit == 1 && big_dense(*D, D->T, D->d, low_ld(*D));
+    g.wide_k = g.ksplit == 1 && !g.big_tile && wide_k_ok(*D, low_ld(*D), 32);
     if (g.ksplit > 1) {
       g.out_f32 = 1; g.C = wsb + F.partials; g.gstride_c = (long)D->T * D->d;
       rc = launch_gemm(g, s);
@@ -776,6 +766,7 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
   if (bf(*D) && D->N % 8) return BIGMAC_ERR_UNSUPPORTED;  // the dense logit gradient has 16-byte rows
   if (ws_bytes < bigmac_workspace_bytes(D, BIGMAC_WS_LAYER_TRAIN)) return BIGMAC_ERR_WORKSPACE;
   hipStream_t s = (hipStream_t)stream;
+  bool large;
   const Widths W = widths(*D);
   const SavedPlan S = plan_saved(*D);
   const BwdPlan B = plan_bwd(*D);
@@ -815,17 +806,11 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
     g.A = dy; g.lda = D->d; g.M = D->T; g.K = D->d;
     g.B = P->w_up; g.ldb = D->d; g.N = D->r;
     g.C = dy_low; g.ldc = D->r;
-    g.tall_tile = tall_dense(*D, D->T, D->r, D->d);
-    g.deep_tile = !g.tall_tile && deep_dense(*D, D->T, D->r, D->d);
+    g.deep_tile = deep_dense(*D, D->T, D->r, D->d);
+    g.big_tile = big_dense(*D, D->T, D->r, D->d) || (!g.deep_tile && !tiles_forced(*D, &large) && D->d >= 1024);
+    g.deep_tile = g.deep_tile && !g.big_tile;
     {
       BIGMAC_STAGE(BIGMAC_STAGE_BWD_ASCEND_DGRAD);
-      if (transposed_projections(*D)) {   // W_up^T [d, r]: B with the output index fast
-        hipLaunchKernelGGL(transpose_b16_kernel, dim3((D->d + 63) / 64, (D->r + 63) / 64), dim3(256), 0, s, (const uint16_t*)P->w_up,
-                           (uint16_t*)(wsb + B.w_up_t), D->r, D->d);
-        BIGMAC_CHECK_LAUNCH();
-        g.B = wsb + B.w_up_t; g.ldb = D->r; g.b_kcontig = 0;
-        g.tall_tile = 0; g.long_tile = 1;
-      }
       rc = launch_gemm(g, s);
     }
     if (rc) return rc;
@@ -859,11 +844,9 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
     g.A = do_perm; g.lda = W.win; g.K = W.win;
     g.B = P->w2; g.ldb = W.win; g.gstride_b = (long)W.hid * W.win; g.N = W.hid;
     g.C = dact; g.ldc = wide_ld(*D); g.aux_in = act;
-    g.big_tile = big_rows(*D, W.hid, W.win);
-    g.tall_tile = !g.big_tile && tall_rows(*D, W.hid, W.win); g.tile_map = (g.tall_tile || g.big_tile) ? tile_map_tall : tile_map;
-    g.wide_k = !g.tall_tile && !g.big_tile && wide_k_ok(*D, W.win, 4);
-    // with 64-deep k tiles the 256 x 256 tile pays for this product from K = 1024 on (zipf_stress: 1.423 -> 1.404 ms)
-    if (g.tall_tile && W.win >= 1024 && W.win % 64 == 0 && W.hid % 256 == 0 && !(D->flags & BIGMAC_FLAG_TILES_SMALL)) { g.tall_tile = 0; g.big_tile = 1; }
+    g.big_tile = big_rows(*D, W.hid, W.win, EPI_DGELU);
+    if (g.big_tile) g.tile_map = tile_map_tall;
+    g.wide_k = !g.big_tile && wide_k_ok(*D, W.win, 4);
     g.kloop_priority = 1;              // measured: -3.5 % (gpt_medium), -1.7 % (gpt_xl)
     if (!g.big_tile) touch_weights(*D, g, P->w2, 4);
     {
@@ -883,7 +866,7 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
     g.A = hact; g.lda = wide_ld(*D); g.M = W.hid;
     g.B = do_perm; g.ldb = W.win; g.N = W.win;
     g.C = d_w2; g.ldc = W.win; g.gstride_c = (long)W.hid * W.win;
-    g.big_tile = big_wgrad(*D);
+    g.big_tile = big_wgrad(*D, W.hid, W.win);
     g.tall_tile = !g.big_tile && tall_wgrad(*D, W.hid);
     {
       BIGMAC_STAGE(BIGMAC_STAGE_BWD_DOWN_WGRAD);
@@ -894,7 +877,7 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
     g.A = x_perm; g.lda = W.win; g.M = W.win;
     g.B = dact; g.ldb = wide_ld(*D); g.N = W.hid;
     g.C = d_w1; g.ldc = W.hid; g.gstride_c = (long)W.win * W.hid;
-    g.big_tile = big_wgrad(*D);
+    g.big_tile = big_wgrad(*D, W.win, W.hid);
     g.tall_tile = !g.big_tile && tall_wgrad(*D, W.win);
     BIGMAC_STAGE(BIGMAC_STAGE_BWD_UP_WGRAD);
     rc = launch_gemm(g, s);
@@ -907,9 +890,9 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
     g.A = dact; g.lda = wide_ld(*D); g.K = W.hid;
     g.B = P->w1; g.ldb = W.hid; g.gstride_b = (long)W.win * W.hid; g.N = W.win;
     g.C = dx_perm; g.ldc = W.win;
-    g.big_tile = big_rows(*D, W.win, W.hid);
-    g.tall_tile = !g.big_tile && tall_rows(*D, W.win, W.hid); g.tile_map = (g.tall_tile || g.big_tile) ? tile_map_tall : tile_map;
-      g.wide_k = !g.tall_tile && !g.big_tile && wide_k_ok(*D, W.hid, 8);
+    g.big_tile = big_rows(*D, W.win, W.hid, EPI_STORE);
+    if (g.big_tile) g.tile_map = tile_map_tall;
+    g.wide_k = !g.big_tile && wide_k_ok(*D, W.hid, 8);
     g.kloop_priority = 1;
     if (!g.big_tile) touch_weights(*D, g, P->w1, 8);
     BIGMAC_STAGE(BIGMAC_STAGE_BWD_UP_DGRAD);
@@ -946,16 +929,9 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
       g.A = dx_low; g.lda = low_ld(*D); g.M = D->T; g.K = low_ld(*D);
       g.B = P->w_down; g.ldb = D->r; g.N = D->d; g.kwrap_b = bf(*D) ? D->r : 0;
       g.C = dx_f32; g.ldc = D->d;
-      g.tall_tile = tall_dense(*D, D->T, D->d, low_ld(*D));
-      g.wide_k = !g.tall_tile && wide_k_ok(*D, low_ld(*D), 16);
+      g.big_tile = big_dense(*D, D->T, D->d, low_ld(*D));
+      g.wide_k = !g.big_tile && wide_k_ok(*D, low_ld(*D), 16);
       BIGMAC_STAGE(BIGMAC_STAGE_BWD_DESCEND_DGRAD);
-      if (transposed_projections(*D)) {   // W_down^T [r, d]
-        hipLaunchKernelGGL(transpose_b16_kernel, dim3((D->r + 63) / 64, (D->d + 63) / 64), dim3(256), 0, s, (const uint16_t*)P->w_down,
-                           (uint16_t*)(wsb + B.w_down_t), D->d, D->r);
-        BIGMAC_CHECK_LAUNCH();
-        g.B = wsb + B.w_down_t; g.ldb = D->d; g.b_kcontig = 0;
-        g.tall_tile = 0; g.long_tile = 1;
-      }
       rc = launch_gemm(g, s);
       if (rc) return rc;
     }

@@ -6,7 +6,7 @@
 
 namespace bigmac {
 
-constexpr int TILE_MAP_HEADER = 16;   // ints in front of the group order: [0] tile count, [1..9] split points of the ragged-K schedule;
+constexpr int TILE_MAP_HEADER = 16;   // ints in front of the group order: [0] tile count, [1..9] split points of the ragged-K schedule, [10] cost of its heaviest group;
                                       // then `groups` ints of group order (positions -> groups), then the (group, first row) pairs
 constexpr int TILE_MAP_K_ROWS = 32;   // rows per k tile in the cost of a group (the square tile's depth)
 
@@ -46,6 +46,10 @@ __device__ __forceinline__ void build_tile_map_wave(const int* offsets, int grou
   const int cost = g < groups ? (rows + TILE_MAP_K_ROWS - 1) / TILE_MAP_K_ROWS + 8 : 0;
   const int upto = inclusive_scan(cost);
   const long long total = __shfl(upto, 63, 64);
+  int heaviest = cost;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) heaviest = max(heaviest, __shfl_xor(heaviest, off, 64));
+  if (g == 0) tile_map[10] = heaviest;
   // cost in front of position q = group * 65536 + fraction (every lane takes part in the shuffles)
   auto cost_before = [&](long long q) {
     const int gi = (int)(q >> 16);
@@ -129,7 +133,7 @@ __device__ __forceinline__ void build_tile_map_block(const int* offsets, int gro
   if (g == 1023) tile_map[0] = last_tile;
   if (schedule_from) {
     __syncthreads();                 // the other map's entries were written by this workgroup
-    if (g < 9) tile_map[1 + g] = schedule_from[1 + g];
+    if (g < 10) tile_map[1 + g] = schedule_from[1 + g];
     if (g < groups) tile_map[TILE_MAP_HEADER + g] = schedule_from[TILE_MAP_HEADER + g];
     return;
   }
@@ -183,6 +187,7 @@ __device__ __forceinline__ void build_tile_map_block(const int* offsets, int gro
       rank += (co > cost || (co == cost && o < g)) ? 1 : 0;
     }
     by_cost[rank] = (unsigned short)g;
+    if (rank == 0) tile_map[10] = cost;
   }
   if (g == 0) whole_ok = 0;
   __syncthreads();

@@ -115,6 +115,31 @@ def test_large_tiles_give_the_same_bits(case):
         assert torch.equal(u, v)
 
 
+@pytest.mark.parametrize("T", [127, 128, 129, 256, 257, 385])
+@pytest.mark.parametrize("width", [(64, 64), (128, 192), (192, 320)], ids=lambda w: "r%d_h%d" % w)
+def test_large_tile_edges(T, width):
+    """The 256 x 256 tile at its edges: one, two, three and five k tiles of 64; rows that fill half of a
+    tile, one more, all of it, one more (every expert gets all T tokens, k = N, so the last round of tiles is
+    cut into row halves, one of them empty); rows through the index (inference) and by copy."""
+    r, h = width
+    wl = synth.small(T=T, d=128, r=r, N=8, k=8, h=h)
+    data = synth.generate(wl)
+    outs = []
+    for flags, training in ((B.FLAG_TILES_SMALL, True), (B.FLAG_TILES_LARGE, True), (B.FLAG_TILES_LARGE, False)):
+        layer = DeviceLayer(wl, data, flags=flags)
+        out = {"y": host(layer.forward(training=training)).copy()}
+        if training:
+            layer.alloc_grads()
+            layer.backward()
+            torch.cuda.synchronize()
+            out.update({n: host(g).copy() for n, g in layer.grads.items()}, dx=host(layer.dx).copy())
+        outs.append(out)
+    assert np.isfinite(outs[0]["y"]).all() and np.abs(outs[0]["y"]).max() > 0
+    for out in outs[1:]:
+        for n in out:
+            assert np.array_equal(outs[0][n], out[n]), n
+
+
 @pytest.mark.parametrize("order", [B.ORDER_DCCA, B.ORDER_CDAC])
 @pytest.mark.parametrize("tiles", [0, B.FLAG_TILES_LARGE])
 def test_dispatch_folded_into_the_expert_product(order, tiles):
