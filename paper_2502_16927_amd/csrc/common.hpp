@@ -181,6 +181,19 @@ int launch_gemm(const GemmDesc& g, hipStream_t s);
 int launch_gemm_f32(const GemmDesc& g, hipStream_t s);   // what launch_gemm does with fp32 operands
 int gemm_f32_tile_rows();
 int launch_gemm_phased(const GemmDesc& g, hipStream_t s);   // the 256 x 256 tile of a big_tile product
+// out = gelu(x W1[e]) W2[e] over ragged per-expert rows, bf16 operands, width 128, 192 or 256 (expert_pair.hip)
+struct ExpertPairDesc {
+  const void* x;             // [x_rows, width]; with gather, row m of the problem is row gather[m] / gather_div of it
+  const int* gather;
+  int x_rows, gather_div;
+  const void* w1;            // [groups, width, hid]
+  const void* w2;            // [groups, hid, width]
+  void* out;                 // [max_rows, width], bf16 or (out_f32) fp32
+  const int* offsets;        // device [groups + 1]
+  const int* tile_map;       // of 128-row tiles
+  int groups, max_rows, width, hid, out_f32;
+};
+int launch_expert_pair(const ExpertPairDesc& p, hipStream_t s);
 // tile_map capacity in int32 for a ragged-M problem: header, the group order of the ragged-K
 // schedule (one int per group), then a (group, first row) pair per M tile
 inline size_t tile_map_ints(int total_rows, int groups, int tile_rows) {

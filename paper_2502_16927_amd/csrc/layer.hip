@@ -195,6 +195,22 @@ inline bool any_big_rows(const bigmac_dims& D) {   // a tile map of 256-row tile
   return big_rows(D, W.hid, W.win, EPI_GELU) || big_rows(D, W.hid, W.win, EPI_DGELU) || big_rows(D, W.win, W.hid, EPI_STORE);
 }
 
+// Both expert products in one kernel (expert_pair.hip): calls that keep no activations, without biases, where no tile
+// size is asked for.  A tile walks all hidden columns by itself, where the separate products spread them over the chip,
+// so at widths 192 and 256 it wants a tile for every second or third CU (estimated tiles, whole layer in us, separate
+// products -> here; width 256: 94 tiles 68 -> 69, 97: 106 -> 114, 101: 95 -> 99, 128: 91 -> 91, 141: 105 -> 94, 160: 101
+// -> 94, 544: 224 -> 193; width 192: 70 tiles 66 -> 68, 94: 69 -> 67, 101: 78 -> 76, 544: 172 -> 137).  At width 128 and up
+// to 512 columns the launch saved outweighs it at any size (6 tiles 48 -> 44, 36 tiles 50 -> 45, 544 tiles 119 -> 95).
+// Training calls stay with the separate products: stored from this kernel's registers, in pieces of 32 bytes per row, the
+// two [rows, hidden] tensors took more than the products saved (width 256, 65536 rows: the step 634 -> 685 us).
+inline bool pair_experts(const bigmac_dims& D, const void* b1, const void* b2, const void* act) {
+  bool large;
+  const Widths W = widths(D);
+  if (act || b1 || b2 || tiles_forced(D, &large) || (W.win != 128 && W.win != 192 && W.win != 256) || (size_t)W.win * W.hid * 2 >= (1ull << 31)) return false;
+  const long tiles = (long)D.T * D.k / 128 + D.N / 2;
+  return tiles >= (W.win == 256 ? 128 : 96) || (W.win == 128 && W.hid <= 512);
+}
+
 TileMapJobs tile_map_jobs(const bigmac_dims& D, int* tile_map, int* tile_map_tall, unsigned* claims) {
   TileMapJobs maps = {};
   maps.tile_rows[0] = gemm_ragged_tile_rows(D.dtype, 0); maps.map[0] = tile_map;
@@ -357,6 +373,19 @@ int run_experts_forward(const bigmac_dims& D, const void* x_perm, const int* off
                         hipStream_t s, const int* gather = nullptr) {
   const Widths W = widths(D);
   const int Tk = D.T * D.k;
+  if (pair_experts(D, b1, b2, act)) {
+    ExpertPairDesc e = {};
+    e.x = x_perm; e.gather = gather; e.x_rows = D.T; e.gather_div = D.k;
+    e.w1 = w1; e.w2 = w2; e.out = o_perm; e.out_f32 = o_f32;
+    e.offsets = offsets; e.tile_map = tile_map; e.groups = D.N; e.max_rows = Tk; e.width = W.win; e.hid = W.hid;
+    int rc;
+    {
+      BIGMAC_STAGE(BIGMAC_STAGE_EXPERT_UP);       // both products
+      rc = launch_expert_pair(e, s);
+    }
+    BIGMAC_STAGE(BIGMAC_STAGE_EXPERT_DOWN);
+    return rc;
+  }
   GemmDesc g = base_desc(D);
   g.mode = GEMM_RAGGED_M;
   g.a_kcontig = 1; g.b_kcontig = 0;

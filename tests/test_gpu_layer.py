@@ -140,6 +140,27 @@ def test_large_tile_edges(T, width):
             assert np.array_equal(outs[0][n], out[n]), n
 
 
+@pytest.mark.parametrize("flags", [0, B.FLAG_WIRE_BF16, B.FLAG_NO_FUSED_DISPATCH])
+@pytest.mark.parametrize("case", [dict(T=1, d=128, r=128, N=8, k=1, h=64), dict(T=127, d=128, r=128, N=8, k=8, h=448), dict(T=129, d=128, r=128, N=8, k=8, h=512, capacity=100),
+                                  dict(T=1537, d=128, r=192, N=8, k=8, h=320), dict(T=300, d=128, r=192, N=192, k=3, h=64, zipf_s=1.2),
+                                  dict(T=160, d=256, r=256, N=256, k=4, h=64), dict(T=2049, d=128, r=256, N=8, k=8, h=192), dict(T=9000, d=128, r=256, N=16, k=8, h=128, zipf_s=1.2)],
+                         ids=lambda c: "T%d_r%d_N%d_h%d" % (c["T"], c["r"], c["N"], c["h"]))
+def test_expert_products_in_one_kernel(case, flags):
+    """The one-kernel expert products of a forward-only call against the separate ones (tile size forced): the same sums in the
+    same order, so the same bits.  Rows that fill a wavefront's 32, a tile's 128, one more, none at all; one chunk pair and
+    more of the hidden columns; more tiles than workgroups; rows through the index and by copy; both kinds of result."""
+    case = dict(case)
+    capacity = case.pop("capacity", 0)
+    wl = synth.small(**case)
+    data = synth.generate(wl)
+    ys = []
+    for f in (flags, flags | B.FLAG_TILES_SMALL):
+        layer = DeviceLayer(wl, data, flags=f, capacity=capacity)
+        ys.append(host(layer.forward(training=False)).copy())
+    assert np.isfinite(ys[0]).all() and np.abs(ys[0]).max() > 0
+    assert np.array_equal(ys[0], ys[1])
+
+
 @pytest.mark.parametrize("order", [B.ORDER_DCCA, B.ORDER_CDAC])
 @pytest.mark.parametrize("tiles", [0, B.FLAG_TILES_LARGE])
 def test_dispatch_folded_into_the_expert_product(order, tiles):
