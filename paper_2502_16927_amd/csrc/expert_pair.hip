@@ -9,11 +9,12 @@
 // lane holds four consecutive hidden columns of its row; exchanging halves between lanes l and l + 32 makes the
 // eight consecutive ones that the second product wants, in the order of the separate products: bits unchanged.
 // Four wavefronts per workgroup, two workgroups per CU (three at width 128) out of step with each other: one's GELU runs
-// beside the other's matrix instructions, which are half of a wavefront's time.  Measured (65536 rows of 64 experts, width
-// 256, 1024 hidden columns): 113 us where the two products take 68 + 63 and the passes over the hidden rows alone
-// 50; 262144 rows: 355 us, 0.77 PFLOP/s.  A full round of 512 tiles is 85 us, a tile that has its CU to itself 49;
-// without the GELU the kernel is a fifth faster, without the requests or with half of the LDS reads 5 to 10 percent: none
-// of them is what it waits for alone.
+// beside the other's matrix instructions, which are half of a wavefront's time.  Results leave as whole 128-byte lines through
+// the LDS (stored from the registers, 32 bytes of a row at a time, the layer took 188 instead of 177 us).  Measured
+// (65536 rows of 64 experts, width 256, 1024 hidden columns): about 100 us where the two products take 68 + 63 and
+// the passes over the hidden rows alone 50.  A full round of 512 tiles is some 80 us, a tile that has its CU to itself
+// 45; without the GELU the kernel is a fifth faster, without the requests or with half of the LDS reads 5 to
+// 10 percent: none of them is what it waits for alone.
 #include "gemm_core.hpp"
 
 namespace bigmac {
@@ -31,7 +32,7 @@ void expert_pair_kernel(ExpertPairDesc p) {
   constexpr unsigned OUT_OF_RANGE = 0x80000000u;
   constexpr int FRAGS = KS + 2 * NJ;              // matrix fragments, and instructions, of a chunk
   constexpr int AHEAD = 3;                        // fragments read ahead of their instruction (six: no faster at width 128, spills at 256)
-  __shared__ uint4 ring[2 * STAGE / 16];
+  __shared__ __attribute__((aligned(128))) uint4 ring[2 * STAGE / 16];
   const unsigned ring_at = lds_address(ring);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int half = lane >> 5;
@@ -227,27 +228,46 @@ void expert_pair_kernel(ExpertPairDesc p) {
     }
     load_rows(nxt, index);
 
-    // results: lane l holds columns 32 j + 8 q + 4 (l / 32) .. + 3 of row l % 32
-    const int esz = OUTF32 ? 4 : 2;
-    const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc((char*)p.out + (size_t)cur.m0 * R * esz, 0, (cur.m_end - cur.m0) * R * esz, 0x00020000);
-    const unsigned at = (unsigned)((wave * 32 + (lane & 31)) * R + half * 4) * esz;
+    // Results: lane l holds columns 32 j + 8 q + 4 (l / 32) .. + 3 of row l % 32.  They leave as whole 128-byte lines (32 columns
+    // in fp32, 64 in bf16) through a strip per wavefront in the stage that everyone has read.
+    __builtin_amdgcn_s_barrier();
     if (live) {
+      constexpr int ESZ = OUTF32 ? 4 : 2, PER_LINE = OUTF32 ? 1 : 2;   // sub-tiles per line
+      const __amdgpu_buffer_rsrc_t rc =
+          __builtin_amdgcn_make_buffer_rsrc((char*)p.out + (size_t)cur.m0 * R * ESZ, 0, (cur.m_end - cur.m0) * R * ESZ, 0x00020000);
+      int l = lane;
+      asm volatile("" : "+v"(l));                 // (or the addresses below would have registers of their own throughout)
+      // (16-byte chunk c of row r sits at c ^ (r / 2) % 8, see mfma_gemm_kernel)
+      const unsigned strip = ring_at + (stage ^ STAGE) + wave * 4096, put = strip + (l & 31) * 128, swz = (l >> 1) & 7;
+      const unsigned get = strip + (l >> 3) * 128 + (((l & 7) ^ (l >> 4)) << 4);
+      unsigned at = (unsigned)((wave * 32 + (l >> 3)) * R * ESZ + (l & 7) * 16);
 #pragma unroll
-      for (int j = 0; j < NJ; ++j)
+      for (int j = 0; j < NJ; j += PER_LINE) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (OUTF32) {
-            u32x4_t v;
-            v.x = __float_as_uint(acc[j][q * 4 + 0]); v.y = __float_as_uint(acc[j][q * 4 + 1]);
-            v.z = __float_as_uint(acc[j][q * 4 + 2]); v.w = __float_as_uint(acc[j][q * 4 + 3]);
-            __builtin_amdgcn_raw_buffer_store_b128(v, rc, at + (unsigned)(j * 32 + q * 8) * 4u, 0, 0);
-          } else {
-            u32x2_t v;
-            v.x = f2bf_pair(acc[j][q * 4 + 0], acc[j][q * 4 + 1]);
-            v.y = f2bf_pair(acc[j][q * 4 + 2], acc[j][q * 4 + 3]);
-            __builtin_amdgcn_raw_buffer_store_b64(v, rc, at + (unsigned)(j * 32 + q * 8) * 2u, 0, 0);
+        for (int jj = 0; jj < PER_LINE; ++jj)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x16_t& v = acc[j + jj];
+            if (OUTF32) {
+              u32x4_t w;
+#pragma unroll
+              for (int i = 0; i < 4; ++i) w[i] = __float_as_uint(v[q * 4 + i]);
+              lds_write_b128(put + (((unsigned)(q * 2 + (l >> 5)) ^ swz) << 4), w);
+            } else {
+              u32x2_t w;
+              w.x = f2bf_pair(v[q * 4 + 0], v[q * 4 + 1]);
+              w.y = f2bf_pair(v[q * 4 + 2], v[q * 4 + 3]);
+              lds_write_b64(put + (l >> 5) * 8 + (((unsigned)(jj * 4 + q) ^ swz) << 4), w);
+            }
           }
-        }
+        u32x4_t line[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) lds_read_b128((q & 1 ? get ^ 64u : get) + q * 1024, line[q]);
+        lds_wait(line);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) __builtin_amdgcn_raw_buffer_store_b128(line[q], rc, at + (unsigned)(q * 8 * R * ESZ), 0, 0);
+        at += 128;
+      }
     }
     if (!more) break;
     cur = nxt;
