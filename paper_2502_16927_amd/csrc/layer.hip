@@ -768,7 +768,10 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
     BIGMAC_STAGE(BIGMAC_STAGE_ASCEND);
     g.ksplit = forward_ksplit(*D, D->T, D->d, low_ld(*D));
     g.big_tile = g.ksplit == 1 && big_dense(*D, D->T, D->d, low_ld(*D));
-    g.wide_k = g.ksplit == 1 && !g.big_tile && wide_k_ok(*D, low_ld(*D), 32);
+    // up to one square tile per CU the 128 x 64 tile, twice as many of half the size (whole layer of 8 experts at d 4096, T 500
+    // / 700 / 1000: 113 -> 105, 117 -> 115, 130 -> 131 us; d 2048, T 1000 / 2000: 75 -> 72, 83 -> 81; d 1024, T 2000: 59 -> 57)
+    g.deep_tile = g.ksplit == 1 && !g.big_tile && deep_dense(*D, D->T, D->d, low_ld(*D));
+    g.wide_k = g.ksplit == 1 && !g.big_tile && !g.deep_tile && wide_k_ok(*D, low_ld(*D), 32);
     if (g.ksplit > 1) {
       g.out_f32 = 1; g.C = wsb + F.partials; g.gstride_c = (long)D->T * D->d;
       rc = launch_gemm(g, s);
