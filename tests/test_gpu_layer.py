@@ -161,6 +161,20 @@ def test_expert_products_in_one_kernel(case, flags):
     assert np.array_equal(ys[0], ys[1])
 
 
+@pytest.mark.parametrize("flags", [0, B.FLAG_OUT_BF16])
+@pytest.mark.parametrize("T", [1025, 1100, 1151])
+def test_ascending_product_on_narrow_tiles(T, flags):
+    """144 square tiles of the ascending product (K = 512, twice through the 256 rows of W_up) run as 128 x 64 tiles; in a batch
+    of 2300 tokens they are 288 square ones.  Same sums in the same order: the shared tokens' results have the same bits."""
+    case = dict(d=2048, r=256, N=8, k=2, h=64)
+    data = synth.generate(synth.small(T=2300, **case))
+    part = dict(data, x=data["x"][:T], dy=data["dy"][:T])
+    whole = host(DeviceLayer(synth.small(T=2300, **case), data, flags=flags).forward(training=False))[:T]
+    few = host(DeviceLayer(synth.small(T=T, **case), part, flags=flags).forward(training=False))
+    assert np.isfinite(few).all() and np.abs(few).max() > 0
+    assert np.array_equal(few, whole)
+
+
 @pytest.mark.parametrize("order", [B.ORDER_DCCA, B.ORDER_CDAC])
 @pytest.mark.parametrize("tiles", [0, B.FLAG_TILES_LARGE])
 def test_dispatch_folded_into_the_expert_product(order, tiles):
