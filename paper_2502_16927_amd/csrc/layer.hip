@@ -43,7 +43,7 @@ struct StageTimer {  // records the caller's events around the launches of one s
 #define BIGMAC_DEEP_MAX_TILES 256   // 128 x 128 tiles (one per CU) up to which a dense product takes the 128 x 64 x 64 tile
 #endif
 // Which products take the square tile with 64-deep k tiles (two ring stages) when they do not
-// take the tall one: 1 expert-up, 2 expert-down, 4 the GELU' product, 8 the data gradient of the
+// take the 256 x 256 one: 1 expert-up, 2 expert-down, 4 the GELU' product, 8 the data gradient of the
 // first matrix, 16 the data gradient of the descending projection, 32 the ascending projection.
 // Measured at gpt_medium: -1 %, +2.5 %, +3 %, -6 %, -11 %, -8 %.
 #ifndef BIGMAC_WIDEK_MASK
@@ -151,30 +151,42 @@ inline bool tiles_forced(const bigmac_dims& D, bool* large) {
 }
 // Per-expert row products: estimated tiles (half of an expert's last row tile) against the 256 CUs.  With a plain
 // store the tile pays from about a third of a round (94 tiles: 33 -> 27 us and 50 -> 45 us; 41 and 46 tiles: 19 -> 22.5,
-// 33 -> 42 us) if its columns are not mostly padding (width 128: 51 -> 59 us).  The activation epilogues are not
-// overlapped by another workgroup's k loop, so they want a longer K and more tiles: K 512, 376 tiles 38 -> 40 us, 792
-// tiles 64 -> 56 us; K 1024, 288 tiles 67 -> 62 us; K 256, 1152 tiles 79 -> 89 us with GELU and its two results, 98 -> 93 us
-// with GELU'; and few rows per expert, whose products stream the weights, keep more of the smaller workgroups in flight
-// (4 rows 102 -> 112 us, 16 rows 111 -> 115 us, 62 rows 127 -> 118 us).
+// 33 -> 42 us) if three quarters of its columns are no padding (width 128: 51 -> 59 us; width 320, whole layer: 83 -> 91 us).
+// The activation epilogues are not overlapped by another workgroup's k loop, so they want a longer K and more tiles: K 384,
+// 804 tiles 77 -> 75 us, K 448, 536 tiles, whole call 132 -> 142 us; K 512, 376 tiles 38 -> 40 us, 792 tiles 64 -> 56 us; K 1024,
+// 288 tiles 67 -> 62 us; K 256, 1152 tiles 79 -> 89 us with GELU and its two results, 98 -> 93 us with GELU'.
+// Few rows per expert, whose products stream the weights, keep more of the smaller workgroups in flight (GELU, 4 rows 102 ->
+// 112 us, 16 rows 111 -> 115 us, 62 rows 127 -> 118 us; plain stores of 10 rows, whole layer 195 -> 204 us).
+// Experts that a 128-row tile holds whole leave half of a 256-row one idle, which only a long K and, for plain stores, a
+// round that is nearly full make up for: with GELU and GELU' at K 384 72 rows 47 -> 54 and 44 -> 57 us, at K 512 100 rows
+// 48 -> 49 and 42 -> 47, 140 rows 63 -> 58 and 57 -> 53 us, at K 1024 72 rows 84 -> 83 and 73 -> 70 us; plain stores of 72 rows,
+// 128 tiles 43 -> 48 and 20 -> 25 us, 256 tiles 53 -> 48 and 69 -> 62 us (at K 256 14 -> 15), 288 tiles, step 1132 -> 1188 us.
 inline bool big_rows(const bigmac_dims& D, int cols, int K, GemmEpilogue epilogue) {
   bool large;
   if (tiles_forced(D, &large)) return bf(D) && large;
-  const long rows = (long)D.T * D.k, tiles = (rows / 256 + D.N / 2) * ((cols + 255) / 256);
-  if (epilogue == EPI_STORE) return K >= 256 && cols >= 192 && tiles >= 90;
-  if (rows / D.N < 48 || K < (epilogue == EPI_GELU ? 384 : 256)) return false;
-  return tiles >= (K >= 1024 ? 256 : K >= 384 ? 512 : 1024);
+  const long rows = (long)D.T * D.k, gx = (cols + 255) / 256, tiles = (rows / 256 + D.N / 2) * gx;
+  const bool one_tile = rows / D.N < 128;
+  if (rows / D.N < 48 || cols * 4 < gx * 256 * 3) return false;
+  if (epilogue == EPI_STORE) {
+    if (one_tile) return K >= 512 && D.N * gx * 5 >= (D.N * gx + 255) / 256 * 256 * 4;
+    return K >= 256 && tiles >= 90;
+  }
+  if ((one_tile && K < 1024) || K < (epilogue == EPI_GELU ? 384 : 256)) return false;
+  return tiles >= (K >= 1024 ? 256 : K >= 512 ? 512 : K >= 384 ? 768 : 1024);
 }
 // Per-expert weight gradients: enough tiles, and no more padded columns than on 128-wide tiles (2560 x 640 outputs: 149 -> 158 us,
 // 640 x 2560: 164 -> 140 us; 1024 x 256 of 64 experts: 52 -> 47 us; of 16 experts, 64 tiles: 78 -> 80 us).
 // A tile is one chain over its expert's rows, up to T of them under skewed routing, against T k per_group / 256 rows that
 // a workgroup walks on average.  With up to 8 tiles per expert the workgroups claim their tiles (see launch_gemm), which
-// levels the rest; with more a factor of three is where the longer chain of the larger tile shows (12 tiles, k 4, Zipf
-// 1.2: 111 -> 148 us; 16 tiles, k 8: 251 -> 268 us, even routing 232 -> 213 us).
+// levels a factor of sixteen (128 x 512 outputs, half of each tile padding, k 6, Zipf 1.2: the step 1365 -> 1471 us); with
+// more a factor of three is where the longer chain of the larger tile shows (12 tiles, k 4, Zipf 1.2: 111 -> 148 us; 16 tiles,
+// k 8: 251 -> 268 us, even routing 232 -> 213 us).
+// Under 128 rows per expert the store is most of it (1024 x 256 of 64 experts, 72 rows: 20 -> 22 us; 4096 x 1024: 112 -> 117).
 inline bool big_wgrad(const bigmac_dims& D, int M, int N) {
   bool large;
   if (tiles_forced(D, &large)) return bf(D) && large;
   const long per_group = (long)((M + 255) / 256) * ((N + 255) / 256);
-  if (per_group > 8 && per_group * D.k < 90) return false;
+  if (per_group * D.k < (per_group > 8 ? 90 : 16) || (long)D.T * D.k / D.N < 128 || M * 4 < (M + 255) / 256 * 256 * 3) return false;
   return D.N * per_group >= 256 && (long)((N + 255) / 256) * 256 * 10 <= (long)((N + 127) / 128) * 128 * 11;
 }
 // The shared projections and their data gradients: by how full the rounds of 256 tiles are (a last round of at most
