@@ -27,7 +27,7 @@ SMALL = [
     # enough rows, tiles and K for the 256-row workgroup tiles in expert-up and the GELU' product
     # (not in expert-down and its counterpart, which have 4 column tiles): both tile maps in one step
     dict(T=2560, d=512, r=512, N=16, k=8, h=2048, dtype=B.BF16),
-    # the same with a hidden width that ends inside a 256-column tile (expert-up's 128 x 256 tiles)
+    # the same with a hidden width that ends inside a 256-column tile (of expert-up)
     dict(T=2560, d=512, r=512, N=16, k=8, h=1984, dtype=B.BF16, zipf_s=0.8),
     # the router's share of dx: 65..128 experts (narrower LDS tile), N % 4 != 0 (scalar tile fill),
     # k = 8 + 4 + 1 picks, k = 64 (staging limit), d not a multiple of the tile width, and more than
@@ -259,7 +259,7 @@ def test_variants_agree_bit_for_bit_on_random_shapes():
 
 
 def test_variants_agree_bit_for_bit_on_mid_size_shapes():
-    """The same at sizes where the tile policy leaves the square tile (128 x 256 and 256 x 256 tiles,
+    """The same at sizes where the tile policy leaves the square tile (256 x 256 tiles,
     64-deep k tiles, 128 experts with whole-group weight-gradient schedules, hidden widths that end
     inside a column tile): every variant gives the bits of the step that forbids the large tiles
     and dispatches with the copy kernel, gradients included."""
