@@ -41,11 +41,12 @@ MEASURED_TRAFFIC = {   # stage -> (MiB read, MiB written) per launch
 }
 
 
-def stage_work(wl, order_cdac: bool, training: bool, wire_bf16: bool = False):
+def stage_work(wl, order_cdac: bool, training: bool, wire_bf16: bool = False, paired: bool = False):
     """Algorithmic work per stage: (kind, flops, bytes).  Bytes are compulsory traffic: every
     input read once, every output written once, real rows only.  e = bytes per stored element,
     ew = bytes per element of the rows that return through the second All-to-All (expert outputs)
-    and of their backward counterpart (fp32 unless the all-bf16 wire format is asked for)."""
+    and of their backward counterpart (fp32 unless the all-bf16 wire format is asked for).  paired: one
+    kernel does both expert products, as the stage of the first; the hidden rows never reach memory."""
     T, d, r, N, k, h = wl.T, wl.d, wl.r, wl.N, wl.k, wl.h
     e = 2 if wl.dtype == 1 else 4
     ew = 2 if (e == 2 and wire_bf16) else 4
@@ -60,6 +61,9 @@ def stage_work(wl, order_cdac: bool, training: bool, wire_bf16: bool = False):
     W["dispatch"] = ("hbm", 0.0, (T + Tk) * win * e + 4 * Tk)
     W["expert_up"] = ("mfma", 2.0 * Tk * win * hid, Tk * win * e + N * win * hid * e + Tk * hid * e * (2 if training else 1))
     W["expert_down"] = ("mfma", 2.0 * Tk * hid * win, Tk * hid * e + N * win * hid * e + Tk * win * ew)
+    if paired:
+        W["expert_up"] = ("mfma", 4.0 * Tk * win * hid, Tk * win * e + 2 * N * win * hid * e + Tk * win * ew)
+        del W["expert_down"]
     W["combine"] = ("hbm", 2.0 * Tk * win, Tk * win * ew + T * (low * e if not order_cdac else d * 4) + 8 * Tk)
     W["ascend"] = ("mfma", 2.0 * T * r * d, T * low * e + r * d * e + T * d * 4)
     W["bwd_ascend_dgrad"] = ("mfma", 2.0 * T * d * r, T * d * e + r * d * e + T * r * 4)
@@ -82,9 +86,11 @@ def stage_work(wl, order_cdac: bool, training: bool, wire_bf16: bool = False):
     return W
 
 
-def live_stages(order_cdac: bool, training: bool) -> set:
-    """Names of the stages that the layer calls record (a dispatch folded into a product excepted)."""
-    live = {"router_logits", "topk_gate", "permutation", "dispatch", "expert_up", "expert_down", "combine"}
+def live_stages(order_cdac: bool, training: bool, paired: bool = False) -> set:
+    """Names of the stages that the layer calls record (a dispatch folded into a product excepted).  paired: see stage_work."""
+    live = {"router_logits", "topk_gate", "permutation", "dispatch", "expert_up", "combine"}
+    if not paired:
+        live.add("expert_down")
     if training:
         live |= {"bwd_combine", "bwd_down_dgrad", "bwd_down_wgrad", "bwd_up_wgrad", "bwd_up_dgrad", "bwd_dispatch", "bwd_gate", "bwd_router_wgrad"}
     if not order_cdac:
@@ -349,11 +355,12 @@ def main():
                 elapsed, timed = dt, "replays of the step captured in a HIP graph"
 
     ms_per_step = elapsed / args.steps * 1e3
-    work = stage_work(wl, cdac, training, args.wire_bf16)
+    paired = B.expert_pairing(dims, training)
+    work = stage_work(wl, cdac, training, args.wire_bf16, paired)
     stage_ms = {}
     if tables:
         names = [B.stage_name(s) for s in range(B.STAGE_COUNT)]
-        live = {names.index(n) for n in live_stages(cdac, training)}
+        live = {names.index(n) for n in live_stages(cdac, training, paired)}
         for tb in tables:
             for s, ms in tb.elapsed_ms(live).items():
                 stage_ms[names[s]] = stage_ms.get(names[s], 0.0) + ms / args.steps
@@ -410,6 +417,7 @@ def main():
         "permute_bytes_per_step": B.permute_bytes(dims) * (1.0 if training else 0.5),
         "dispatch": {0: "copy kernel", 1: "folded into the expert-up product (rows read through src_of)",
                      2: "folded into the descending projection (rows written through slot_of)"}[folding],
+        **({"experts": "one kernel for both products (expert_up)"} if paired else {}),
         "stage_ms": {n: round(v, 4) for n, v in stage_ms.items()},
         "stage_roofline": stage_roofline,
         "stage_sum_ms": round(sum(stage_ms.values()), 4),

@@ -234,8 +234,8 @@ typedef enum {
   BIGMAC_STAGE_DESCEND,           /* F2  x' = x W_down                           */
   BIGMAC_STAGE_PERMUTATION,       /* F3  counting sort + tile maps               */
   BIGMAC_STAGE_DISPATCH,          /* F4  first All-to-All (row scatter)          */
-  BIGMAC_STAGE_EXPERT_UP,         /* F5  act(x_perm W1[e])                       */
-  BIGMAC_STAGE_EXPERT_DOWN,       /* F6  . W2[e]                                 */
+  BIGMAC_STAGE_EXPERT_UP,         /* F5  act(x_perm W1[e]); with . W2[e] where one kernel does both (bigmac_expert_pairing) */
+  BIGMAC_STAGE_EXPERT_DOWN,       /* F6  . W2[e], unless F5's kernel has done it */
   BIGMAC_STAGE_COMBINE,           /* F7  second All-to-All + weighted sum        */
   BIGMAC_STAGE_ASCEND,            /* F8  y = y' W_up                             */
   BIGMAC_STAGE_BWD_ASCEND_DGRAD,  /* B8  dy' = dy W_up^T                         */
@@ -282,6 +282,12 @@ const char *bigmac_stage_name(int stage);
  * calls).  See BIGMAC_FLAG_NO_FUSED_DISPATCH.  Measurement code uses it to price the stages.
  * training: 0 = a call with saved == NULL.  Negative: an error code for bad dims. */
 int bigmac_dispatch_folding(const bigmac_dims *dims, int training);
+/* Whether a layer forward with these dims and no expert biases runs both expert products in one
+ * kernel (some forward-only calls of narrow bf16 layers): 1 = one kernel, timed as
+ * BIGMAC_STAGE_EXPERT_UP while BIGMAC_STAGE_EXPERT_DOWN records nothing; 0 = one kernel each.  For
+ * measurement code, like the call above.  training: 0 = a call with saved == NULL.  Negative: an
+ * error code for bad dims. */
+int bigmac_expert_pairing(const bigmac_dims *dims, int training);
 
 #ifdef __cplusplus
 }

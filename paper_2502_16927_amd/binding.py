@@ -74,6 +74,8 @@ def lib() -> ctypes.CDLL:
         L.bigmac_set_stage_events.argtypes = [ctypes.POINTER(vp)]
         L.bigmac_dispatch_folding.restype = ci
         L.bigmac_dispatch_folding.argtypes = [dp, ci]
+        L.bigmac_expert_pairing.restype = ci
+        L.bigmac_expert_pairing.argtypes = [dp, ci]
         L.bigmac_stage_name.restype = ctypes.c_char_p
         L.bigmac_stage_name.argtypes = [ci]
         L.bigmac_gather_probe.restype = ci
@@ -86,7 +88,7 @@ def lib() -> ctypes.CDLL:
 
 EXPORTS = ("bigmac_workspace_bytes", "bigmac_status_string", "bigmac_forward_matrix_flops", "bigmac_permute_bytes",
            "bigmac_saved_layout", "bigmac_saved_aux_layout", "bigmac_aux_loss", "bigmac_route", "bigmac_dispatch", "bigmac_dispatch_static", "bigmac_grouped_ffn", "bigmac_combine",
-           "bigmac_layer_forward", "bigmac_layer_backward", "bigmac_set_stage_events", "bigmac_stage_name", "bigmac_dispatch_folding",
+           "bigmac_layer_forward", "bigmac_layer_backward", "bigmac_set_stage_events", "bigmac_stage_name", "bigmac_dispatch_folding", "bigmac_expert_pairing",
            "bigmac_mfma_probe", "bigmac_gather_probe")
 STAGE_COUNT = 22
 
@@ -220,6 +222,14 @@ def dispatch_folding(dims, training: bool) -> int:
     if rc < 0:
         _check(rc, "bigmac_dispatch_folding")
     return rc
+
+
+def expert_pairing(dims, training: bool) -> bool:
+    """Whether one kernel does both expert products of a forward call without biases."""
+    rc = lib().bigmac_expert_pairing(ctypes.byref(dims), int(bool(training)))
+    if rc < 0:
+        _check(rc, "bigmac_expert_pairing")
+    return rc == 1
 
 
 def stage_name(stage: int) -> str:

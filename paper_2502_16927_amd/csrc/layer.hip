@@ -390,13 +390,8 @@ int run_experts_forward(const bigmac_dims& D, const void* x_perm, const int* off
     e.x = x_perm; e.gather = gather; e.x_rows = D.T; e.gather_div = D.k;
     e.w1 = w1; e.w2 = w2; e.out = o_perm; e.out_f32 = o_f32;
     e.offsets = offsets; e.tile_map = tile_map; e.groups = D.N; e.max_rows = Tk; e.width = W.win; e.hid = W.hid;
-    int rc;
-    {
-      BIGMAC_STAGE(BIGMAC_STAGE_EXPERT_UP);       // both products
-      rc = launch_expert_pair(e, s);
-    }
-    BIGMAC_STAGE(BIGMAC_STAGE_EXPERT_DOWN);
-    return rc;
+    BIGMAC_STAGE(BIGMAC_STAGE_EXPERT_UP);         // both products; the stage of the second records nothing
+    return launch_expert_pair(e, s);
   }
   GemmDesc g = base_desc(D);
   g.mode = GEMM_RAGGED_M;
@@ -545,6 +540,12 @@ int bigmac_dispatch_folding(const bigmac_dims* D, int training) {
   if (rc) return rc;
   if (training) return descend_scatters(*D) ? 2 : 0;
   return expert_up_gathers(*D) ? 1 : 0;
+}
+
+int bigmac_expert_pairing(const bigmac_dims* D, int training) {
+  const int rc = check_dims(D);
+  if (rc) return rc;
+  return !training && pair_experts(*D, nullptr, nullptr, nullptr) ? 1 : 0;
 }
 
 const char* bigmac_stage_name(int stage) {

@@ -100,6 +100,30 @@ def test_null_pointers_and_small_workspaces_are_rejected():
     assert B.workspace_bytes(fg, B.WS_LAYER_FORWARD) == 0
 
 
+def test_expert_pairing_and_its_price():
+    """bigmac_expert_pairing: host logic only.  Forward-only bf16 calls of widths 128, 192 and 256 with enough rows, no tile size
+    asked for.  The benchmark prices the one kernel with both products' flops and without the hidden rows' bytes."""
+    import bench
+    from paper_2502_16927_amd import synth
+    medium = dict(T=8192, d=1024, r=256, N=64, k=8, h=1024)
+    assert B.expert_pairing(B.make_dims(**medium), training=False)
+    assert not B.expert_pairing(B.make_dims(**medium), training=True)
+    for flag in (B.FLAG_TILES_LARGE, B.FLAG_TILES_SMALL):
+        assert not B.expert_pairing(B.make_dims(**medium, flags=flag), training=False)
+    assert not B.expert_pairing(B.make_dims(**dict(medium, r=320)), training=False)
+    assert not B.expert_pairing(B.make_dims(**dict(medium, T=500)), training=False)
+    assert not B.expert_pairing(B.make_dims(**medium, dtype=B.F32), training=False)
+    assert B.expert_pairing(B.make_dims(200, 128, 128, 8, 2, 128), training=False)
+    with pytest.raises(B.BigmacError):
+        B.expert_pairing(B.make_dims(0, 128, 128, 8, 2, 128), training=False)
+    wl = synth.small(**medium)
+    apart, one = bench.stage_work(wl, False, False), bench.stage_work(wl, False, False, paired=True)
+    hidden = 8192 * 8 * 1024 * 2                                   # bytes: written by the one, read by the other
+    assert one["expert_up"][1] == apart["expert_up"][1] + apart["expert_down"][1]
+    assert one["expert_up"][2] == apart["expert_up"][2] + apart["expert_down"][2] - 2 * hidden
+    assert set(apart) - set(one) == {"expert_down"} == bench.live_stages(False, False) - bench.live_stages(False, False, paired=True)
+
+
 def test_where_the_dispatch_step_runs():
     """bigmac_dispatch_folding: host logic only.  Forward-only bf16 calls fold the dispatch into the
     expert-up product; DCCA training calls into the descending projection unless the router reads

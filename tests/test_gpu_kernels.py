@@ -4,6 +4,7 @@ import pytest
 import torch
 
 from paper_2502_16927_amd import binding as B
+from paper_2502_16927_amd import synth
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -153,11 +154,12 @@ def test_dispatch_sort_of_few_pairs(oracle, T, k, N, capacity, popular):
         assert (off == r_off).all() and (slot == r_slot.reshape(-1)).all() and (src == r_src).all()
 
 
-# bench.py times exactly the stages that the layer calls record, in both orders
-@pytest.mark.parametrize("order", [B.ORDER_DCCA, B.ORDER_CDAC])
-def test_stages_that_the_benchmark_times(order):
+# bench.py times exactly the stages that the layer calls record: training in both orders, forward-only calls with the
+# expert products apart (width 64) and in one kernel (width 128), and prices exactly those
+@pytest.mark.parametrize("order,training,r", [(B.ORDER_DCCA, True, 64), (B.ORDER_CDAC, True, 64), (B.ORDER_DCCA, False, 64), (B.ORDER_DCCA, False, 128)])
+def test_stages_that_the_benchmark_times(order, training, r):
     import bench
-    T, d, r, N, k, h = 200, 128, 64, 8, 2, 128
+    T, d, N, k, h = 200, 128, 8, 2, 128
     cdac = order == B.ORDER_CDAC
     win, hid = (d, r) if cdac else (r, h)
     bf = lambda *s: torch.randn(s, device=DEV).to(torch.bfloat16)
@@ -165,8 +167,8 @@ def test_stages_that_the_benchmark_times(order):
     dims = B.make_dims(T, d, r, N, k, h, B.BF16, order)
     w = [None if cdac else bf(d, r), None if cdac else bf(r, d), torch.randn((d, N), device=DEV), bf(N, win, hid), bf(N, hid, win)]
     params = B.make_params(w[0], w[1], w[2], None, w[3], w[4])
-    x, dy, saved = bf(T, d), bf(T, d), B.alloc_bytes(B.workspace_bytes(dims, B.WS_SAVED))
-    ws = B.alloc_bytes(B.workspace_bytes(dims, B.WS_LAYER_TRAIN))
+    x, dy, saved = bf(T, d), bf(T, d), B.alloc_bytes(B.workspace_bytes(dims, B.WS_SAVED)) if training else None
+    ws = B.alloc_bytes(B.workspace_bytes(dims, B.WS_LAYER_TRAIN if training else B.WS_LAYER_FORWARD))
     events = B.StageEvents()
     torch.cuda.synchronize()
     before = torch.cuda.Event(enable_timing=True)
@@ -174,13 +176,17 @@ def test_stages_that_the_benchmark_times(order):
     torch.cuda.synchronize()
     events.install()
     B.bigmac_layer_forward(dims, params, x, f32(T, d), saved, ws)
-    B.bigmac_layer_backward(dims, params, x, dy, saved, f32(T, d), None if cdac else f32(d, r), None if cdac else f32(r, d), f32(d, N),
-                            f32(N, win, hid), f32(N, hid, win), ws)
+    if training:
+        B.bigmac_layer_backward(dims, params, x, dy, saved, f32(T, d), None if cdac else f32(d, r), None if cdac else f32(r, d), f32(d, N),
+                                f32(N, win, hid), f32(N, hid, win), ws)
     events.clear()
     torch.cuda.synchronize()
     recorded = {B.stage_name(s) for s in range(B.STAGE_COUNT) if before.elapsed_time(events.events[2 * s]) > 0}
-    folded = {"dispatch"} if B.dispatch_folding(dims, training=True) else set()
-    assert recorded == bench.live_stages(cdac, True) - folded
+    folded = {"dispatch"} if B.dispatch_folding(dims, training) else set()
+    paired = B.expert_pairing(dims, training)
+    assert paired == (not training and r == 128)
+    assert recorded == bench.live_stages(cdac, training, paired) - folded
+    assert recorded <= set(bench.stage_work(synth.small(T=T, d=d, r=r, N=N, k=k, h=h), cdac, training, False, paired))
 
 
 # the load-balance loss of a layer call from the top-k's counters (4 and 32 parts per chunk) is the one from the picks, bit for bit
