@@ -174,20 +174,23 @@ inline bool big_rows(const bigmac_dims& D, int cols, int K, GemmEpilogue epilogu
   if ((one_tile && K < 1024) || K < (epilogue == EPI_GELU ? 384 : 256)) return false;
   return tiles >= (K >= 1024 ? 256 : K >= 512 ? 512 : K >= 384 ? 768 : 1024);
 }
-// Per-expert weight gradients: enough tiles, and no more padded columns than on 128-wide tiles (2560 x 640 outputs: 149 -> 158 us,
-// 640 x 2560: 164 -> 140 us; 1024 x 256 of 64 experts: 52 -> 47 us; of 16 experts, 64 tiles: 78 -> 80 us).
-// A tile is one chain over its expert's rows, up to T of them under skewed routing, against T k per_group / 256 rows that
-// a workgroup walks on average.  With up to 8 tiles per expert the workgroups claim their tiles (see launch_gemm), which
-// levels a factor of sixteen (128 x 512 outputs, half of each tile padding, k 6, Zipf 1.2: the step 1365 -> 1471 us); with
-// more a factor of three is where the longer chain of the larger tile shows (12 tiles, k 4, Zipf 1.2: 111 -> 148 us; 16 tiles,
-// k 8: 251 -> 268 us, even routing 232 -> 213 us).
-// Under 128 rows per expert the store is most of it (1024 x 256 of 64 experts, 72 rows: 20 -> 22 us; 4096 x 1024: 112 -> 117).
-inline bool big_wgrad(const bigmac_dims& D, int M, int N) {
+// Per-expert weight gradients [M, rows] x [rows, N]: enough tiles and rows (under 128 per expert the store is most of it: 1024 x 256
+// of 64 experts, 72 rows 20 -> 22 us), at least one tile high, and not much more padding than on 128-wide tiles: a tenth in the
+// columns (2560 x 640: 149 -> 158 us), a fifth in the rows (576 x 2304: 0.81 to 0.89 of the time; 384 x 1536: 0.9, under
+// skewed routing 1.2 to 1.5).
+// Where one expert can hold one and a half times the rows that a CU walks on average (it holds at most T; see ragged_k_uneven), the routing
+// decides, on the device: both tiles are launched and one returns at once, which costs 2 to 3 us and pays from a product
+// of some 50 us (1024 x 256 of 64 experts, 65536 rows, even routing 52 -> 47 us).
+enum ExpertWgradTile { WGRAD_SMALL, WGRAD_BIG, WGRAD_BY_ROUTING };
+inline ExpertWgradTile expert_wgrad_tile(const bigmac_dims& D, int M, int N) {
   bool large;
-  if (tiles_forced(D, &large)) return bf(D) && large;
-  const long per_group = (long)((M + 255) / 256) * ((N + 255) / 256);
-  if (per_group * D.k < (per_group > 8 ? 90 : 16) || (long)D.T * D.k / D.N < 128 || M * 4 < (M + 255) / 256 * 256 * 3) return false;
-  return D.N * per_group >= 256 && (long)((N + 255) / 256) * 256 * 10 <= (long)((N + 127) / 128) * 128 * 11;
+  if (tiles_forced(D, &large)) return bf(D) && large ? WGRAD_BIG : WGRAD_SMALL;
+  const long gy = (M + 255) / 256, gx = (N + 255) / 256, rows = (long)D.T * D.k;
+  if (M < 256 || rows / D.N < 128 || D.N * gx * gy < 256 || gx * 256 * 10 > (long)((N + 127) / 128) * 128 * 11 ||
+      gy * 256 * 5 > (long)((M + 127) / 128) * 128 * 6)
+    return WGRAD_SMALL;
+  if ((double)M * N * D.k * 3 >= 65536.0 * 256 * 2) return WGRAD_BIG;
+  return 2.0 * rows * M * N >= 3e10 ? WGRAD_BY_ROUTING : WGRAD_SMALL;
 }
 // The shared projections and their data gradients: by how full the rounds of 256 tiles are (a last round of at most
 // 128 tiles runs as row halves, three quarters of a round).  Ascending and its counterpart at 512, 472 and 252 tiles: 78 -> 77 us
@@ -431,6 +434,21 @@ int run_experts_forward(const bigmac_dims& D, const void* x_perm, const int* off
   g.touch = nullptr; g.touch_bytes = 0;
   if (!g.big_tile) touch_weights(D, g, w2, 2);
   BIGMAC_STAGE(BIGMAC_STAGE_EXPERT_DOWN);
+  return launch_gemm(g, s);
+}
+
+// One expert matrix's gradients (ragged-K, see expert_wgrad_tile).
+int run_expert_wgrad(const bigmac_dims& D, GemmDesc g, hipStream_t s) {
+  const ExpertWgradTile tile = expert_wgrad_tile(D, g.M, g.N);
+  if (tile != WGRAD_SMALL) {
+    g.big_tile = 1;
+    g.when = tile == WGRAD_BY_ROUTING ? WHEN_EVEN : WHEN_ALWAYS;
+    const int rc = launch_gemm(g, s);
+    if (rc || tile == WGRAD_BIG) return rc;
+    g.big_tile = 0;
+    g.when = WHEN_UNEVEN;
+  }
+  g.tall_tile = tall_wgrad(D, g.M);
   return launch_gemm(g, s);
 }
 
@@ -911,21 +929,17 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
     g.A = hact; g.lda = wide_ld(*D); g.M = W.hid;
     g.B = do_perm; g.ldb = W.win; g.N = W.win;
     g.C = d_w2; g.ldc = W.win; g.gstride_c = (long)W.hid * W.win;
-    g.big_tile = big_wgrad(*D, W.hid, W.win);
-    g.tall_tile = !g.big_tile && tall_wgrad(*D, W.hid);
     {
       BIGMAC_STAGE(BIGMAC_STAGE_BWD_DOWN_WGRAD);
-      rc = launch_gemm(g, s);
+      rc = run_expert_wgrad(*D, g, s);
     }
     if (rc) return rc;
     // dW1[e] (+)= x_perm_e^T dact_e
     g.A = x_perm; g.lda = W.win; g.M = W.win;
     g.B = dact; g.ldb = wide_ld(*D); g.N = W.hid;
     g.C = d_w1; g.ldc = W.hid; g.gstride_c = (long)W.win * W.hid;
-    g.big_tile = big_wgrad(*D, W.win, W.hid);
-    g.tall_tile = !g.big_tile && tall_wgrad(*D, W.win);
     BIGMAC_STAGE(BIGMAC_STAGE_BWD_UP_WGRAD);
-    rc = launch_gemm(g, s);
+    rc = run_expert_wgrad(*D, g, s);
     if (rc) return rc;
   }
   {  // dx_perm = dact W1[e]^T

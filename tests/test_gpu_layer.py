@@ -161,6 +161,29 @@ def test_expert_products_in_one_kernel(case, flags):
     assert np.array_equal(ys[0], ys[1])
 
 
+@pytest.mark.parametrize("accumulate", [0, B.FLAG_ACCUMULATE])
+@pytest.mark.parametrize("case", [dict(d=256, r=256, N=64, k=8, h=1024), dict(d=256, r=448, N=128, k=6, h=896)], ids=lambda c: "r%d_N%d" % (c["r"], c["N"]))
+@pytest.mark.parametrize("zipf_s", [0.0, 0.35, 1.2])
+def test_weight_gradients_chosen_by_the_routing(case, zipf_s, accumulate):
+    """Expert weight gradients that are launched on both tiles, of which the heaviest expert's rows let one run: even routing,
+    mildly and strongly skewed.  Exactly one of the two works, also where the
+    results are added to the buffers: the bits of the step that forbids the large tiles."""
+    wl = synth.small(T=8192, zipf_s=zipf_s, **case)
+    data = synth.generate(wl)
+    held = {"d_w1": np.full((wl.N, wl.r, wl.h), 0.5, np.float32), "d_w2": np.full((wl.N, wl.h, wl.r), 0.5, np.float32)} if accumulate else None
+    outs = []
+    for flags in (0, B.FLAG_TILES_SMALL):
+        layer = DeviceLayer(wl, data, flags=flags | accumulate)
+        layer.forward(training=True)
+        layer.alloc_grads(held)
+        layer.backward()
+        torch.cuda.synchronize()
+        outs.append({n: layer.grads[n].clone() for n in ("d_w1", "d_w2")})
+    for n in outs[0]:
+        assert torch.isfinite(outs[0][n]).all() and outs[0][n].abs().max() > 0
+        assert torch.equal(outs[0][n], outs[1][n]), n
+
+
 @pytest.mark.parametrize("flags", [0, B.FLAG_OUT_BF16])
 @pytest.mark.parametrize("T", [1025, 1100, 1151])
 def test_ascending_product_on_narrow_tiles(T, flags):
