@@ -435,3 +435,35 @@ def test_tiny_fp32_workload_full(oracle):
     torch.cuda.synchronize()
     assert rel_err(y, oracle_forward(oracle, data, wl.k)) < 1e-4
     check_routing(oracle, layer, data)
+
+
+SLOW_ON_LARGE_TILES = [
+    # weight gradients of narrow experts under skewed routing: one expert's rows are a serial chain (192 -> 348 us)
+    (dict(T=15026, d=1536, r=384, N=64, k=8, h=768, zipf_s=1.2), "bwd_up_wgrad"),
+]
+
+
+@pytest.mark.parametrize("case,stage", SLOW_ON_LARGE_TILES, ids=lambda v: v if isinstance(v, str) else "T{T}_r{r}_N{N}_h{h}".format(**v))
+def test_tiles_chosen_by_default_are_not_the_slower_ones(case, stage):
+    """Products that were 1.3 to 1.8 times slower on 256 x 256 tiles than on the smaller ones: the default stays within 1.2
+    times of the step that forbids the large ones (two equal runs differ by 1 to 3 percent)."""
+    wl = synth.small(**case)
+    data = synth.generate(wl)
+    layers = [DeviceLayer(wl, data), DeviceLayer(wl, data, flags=B.FLAG_TILES_SMALL)]
+    for layer in layers:
+        layer.alloc_grads()
+    at = 2 * next(s for s in range(B.STAGE_COUNT) if B.stage_name(s) == stage)
+    times = ([], [])
+    for turn in range(12):
+        for layer, t in zip(layers, times):
+            events = B.StageEvents()
+            events.install()
+            layer.forward(training=True)
+            layer.backward()
+            events.clear()
+            torch.cuda.synchronize()
+            if turn >= 3:
+                t.append(events.events[at].elapsed_time(events.events[at + 1]) * 1e3)
+    default, small = (float(np.median(t)) for t in times)
+    print(f"{stage}: default {default:.1f} us, small tiles {small:.1f} us", flush=True)
+    assert default < 1.2 * small
