@@ -149,30 +149,45 @@ inline bool tiles_forced(const bigmac_dims& D, bool* large) {
   *large = (D.flags & BIGMAC_FLAG_TILES_LARGE) != 0;
   return !bf(D) || (D.flags & (BIGMAC_FLAG_TILES_LARGE | BIGMAC_FLAG_TILES_SMALL));
 }
-// Per-expert row products: estimated tiles (half of an expert's last row tile) against the 256 CUs.  With a plain
-// store the tile pays from about a third of a round (94 tiles: 33 -> 27 us and 50 -> 45 us; 41 and 46 tiles: 19 -> 22.5,
-// 33 -> 42 us) if three quarters of its columns are no padding (width 128: 51 -> 59 us; width 320, whole layer: 83 -> 91 us).
-// The activation epilogues are not overlapped by another workgroup's k loop, so they want a longer K and more tiles: K 384,
-// 804 tiles 77 -> 75 us, K 448, 536 tiles, whole call 132 -> 142 us; K 512, 376 tiles 38 -> 40 us, 792 tiles 64 -> 56 us; K 1024,
-// 288 tiles 67 -> 62 us; K 256, 1152 tiles 79 -> 89 us with GELU and its two results, 98 -> 93 us with GELU'.
+// How full the rounds of 256 tiles are; a last round of at most 128 tiles runs as row halves, three quarters of a round.
+inline double round_fill(long tiles) {
+  const long last = tiles % 256;
+  return (double)tiles / 256.0 / ((double)(tiles / 256) + (last == 0 ? 0.0 : last <= 128 ? 0.75 : 1.0));
+}
+// Per-expert row products: the tiles that the results would fill (full), and the estimated tiles with each expert's last one
+// half empty, against the 256 CUs.  Figures are one product's (or the whole layer's, where said) under even or skewed routing.
+// Plain stores pay from a quarter of the CUs on: K 512 to 2048, 49 to 62 full 22 -> 26, 15 -> 18, 27 -> 27 us, 72 to 99 full 51 -> 43,
+// 24 -> 20, 34 -> 29 us.  Results that leave an eighth or more of their column tiles empty (widths 192, 320, 384, 576, ...)
+// also want well filled rounds: K 768 to 2304, 147 tiles 37 -> 27 us, 236 to 248 tiles 30 -> 28, 46 -> 40, 64 -> 50 us, 270 to 304 tiles
+// 58 -> 66, 63 -> 63, 80 -> 78 us; whole forward call, 270 tiles 182 -> 200 us; width 128 51 -> 59 us.
+// The activation epilogues are not overlapped by another workgroup's k loop, so they want a longer K and more tiles (GELU and
+// GELU', even routing unless said): K 384, 621 full 67 -> 70, 705 full 102 -> 79, 1037 full 140 -> 111 and 121 -> 107 us; K 512 to 768,
+// 203 full 36 -> 42, 260 full under skew 71 -> 70 and 60 -> 71, 323 full of 129 rows per expert under skew 78 -> 87, 424 full 81 -> 62 and
+// 67 -> 57 us; K 960, 267 full 109 -> 79 and 94 -> 73 us; K 1024, 140 full 60 -> 39 us and under skew 51 -> 58 (GELU'), 200 full 66 -> 45
+// and 59 -> 43 us.  (The routing moves these lines: both expert products, K 576, 479 full of 213 rows per expert 163 -> 140 us with
+// even, 167 -> 190 us with strongly skewed routing.)
 // Few rows per expert, whose products stream the weights, keep more of the smaller workgroups in flight (GELU, 4 rows 102 ->
-// 112 us, 16 rows 111 -> 115 us, 62 rows 127 -> 118 us; plain stores of 10 rows, whole layer 195 -> 204 us).
-// Experts that a 128-row tile holds whole leave half of a 256-row one idle, which only a long K and, for plain stores, a
-// round that is nearly full make up for: with GELU and GELU' at K 384 72 rows 47 -> 54 and 44 -> 57 us, at K 512 100 rows
-// 48 -> 49 and 42 -> 47, 140 rows 63 -> 58 and 57 -> 53 us, at K 1024 72 rows 84 -> 83 and 73 -> 70 us; plain stores of 72 rows,
-// 128 tiles 43 -> 48 and 20 -> 25 us, 256 tiles 53 -> 48 and 69 -> 62 us (at K 256 14 -> 15), 288 tiles, step 1132 -> 1188 us.
+// 112 us, 16 rows 111 -> 115 us; plain stores of 10 rows, whole layer 195 -> 204 us).  Experts that a 128-row tile holds whole
+// leave half of a 256-row one idle, which only a long K makes up for (K 384, 72 rows 47 -> 54 and 44 -> 57 us; K 1024, 75 full 50 ->
+// 61, 112 full 44 -> 57 (GELU'), 180 full 82 -> 76, 186 full 94 -> 89, 248 full 136 -> 124 and 135 -> 130 us) and, for plain stores, a
+// round that is nearly full (72 rows, 128 tiles 43 -> 48 and 20 -> 25 us, 256 tiles 53 -> 48 and 69 -> 62 us, at K 256 14 -> 15).
 inline bool big_rows(const bigmac_dims& D, int cols, int K, GemmEpilogue epilogue) {
   bool large;
   if (tiles_forced(D, &large)) return bf(D) && large;
-  const long rows = (long)D.T * D.k, gx = (cols + 255) / 256, tiles = (rows / 256 + D.N / 2) * gx;
-  const bool one_tile = rows / D.N < 128;
-  if (rows / D.N < 48 || cols * 4 < gx * 256 * 3) return false;
+  const long rows = (long)D.T * D.k, gx = (cols + 255) / 256, tiles = (rows / 256 + D.N / 2) * gx, full = rows * cols / 65536, each = rows / D.N;
+  const bool gelu = epilogue == EPI_GELU;
+  if (each < 48 || cols * 4 < gx * 256 * 3) return false;
   if (epilogue == EPI_STORE) {
-    if (one_tile) return K >= 512 && D.N * gx * 5 >= (D.N * gx + 255) / 256 * 256 * 4;
-    return K >= 256 && tiles >= 90;
+    if (full < 64) return false;
+    if (each < 128) return K >= 512 && D.N * gx * 5 >= (D.N * gx + 255) / 256 * 256 * 4;
+    if (K < 256 || tiles < 90) return false;
+    if (cols * 8 >= gx * 256 * 7) return true;
+    const long likely = each <= 224 ? D.N * gx : tiles;   // (up to 224 rows per expert nearly every one has a single tile)
+    return likely <= 256 ? likely >= 150 : round_fill(likely) >= 0.7;
   }
-  if ((one_tile && K < 1024) || K < (epilogue == EPI_GELU ? 384 : 256)) return false;
-  return tiles >= (K >= 1024 ? 256 : K >= 512 ? 512 : K >= 384 ? 768 : 1024);
+  if (each < 128) return K >= 1024 && full >= (gelu ? 176 : 240);
+  if (K >= 512) return tiles >= (K >= 1024 ? 256 : 512) && (full >= 400 || (K >= 896 ? gelu || full >= 192 : gelu && each >= 224));
+  return K >= (gelu ? 384 : 256) && full >= 640 && tiles >= (K >= 384 ? 768 : 1024);
 }
 // Per-expert weight gradients [M, rows] x [rows, N]: enough tiles and rows (under 128 per expert the store is most of it: 1024 x 256
 // of 64 experts, 72 rows 20 -> 22 us), at least one tile high, and not much more padding than on 128-wide tiles: a tenth in the
@@ -192,8 +207,7 @@ inline ExpertWgradTile expert_wgrad_tile(const bigmac_dims& D, int M, int N) {
   if ((double)M * N * D.k * 3 >= 65536.0 * 256 * 2) return WGRAD_BIG;
   return 2.0 * rows * M * N >= 3e10 ? WGRAD_BY_ROUTING : WGRAD_SMALL;
 }
-// The shared projections and their data gradients: by how full the rounds of 256 tiles are (a last round of at most
-// 128 tiles runs as row halves, three quarters of a round).  Ascending and its counterpart at 512, 472 and 252 tiles: 78 -> 77 us
+// The shared projections and their data gradients: by how full the rounds of 256 tiles are.  Ascending and its counterpart at 512, 472 and 252 tiles: 78 -> 77 us
 // and 112 -> 103, 53 -> 51 and 73 -> 70, 32 -> 30 and 43 -> 42; at 320 and 128 tiles: 53 -> 59 and 70 -> 74, 20 -> 22 and 26 -> 30.
 // The product dy W_up^T, whose operands are both k-contiguous, gains from 80 tiles on where it does not run on the
 // 128 x 64 tile (53 -> 44 us; 128 tiles: 62 -> 49 us).
@@ -201,9 +215,8 @@ inline bool big_dense(const bigmac_dims& D, int M, int N, int K) {
   bool large;
   if (K % 64) return false;
   if (tiles_forced(D, &large)) return bf(D) && large;
-  const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256), last = tiles % 256;
-  const double rounds = (double)(tiles / 256) + (last == 0 ? 0.0 : last <= 128 ? 0.75 : 1.0);
-  return tiles >= 512 || (double)tiles >= 0.8 * 256.0 * rounds;
+  const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
+  return tiles >= 512 || round_fill(tiles) >= 0.8;
 }
 inline bool any_big_rows(const bigmac_dims& D) {   // a tile map of 256-row tiles is needed
   const Widths W = widths(D);

@@ -124,6 +124,19 @@ def test_expert_pairing_and_its_price():
     assert set(apart) - set(one) == {"expert_down"} == bench.live_stages(False, False) - bench.live_stages(False, False, paired=True)
 
 
+def test_which_shapes_have_a_map_of_256_row_tiles():
+    """Host logic only: the saved block holds a second tile map exactly where some row product of the step runs on 256 x 256 tiles.
+    Shapes whose products had become slower there (padded columns or experts counted as tiles) are back on the smaller
+    ones; large products are not."""
+    def has_map(**dims):
+        return B.workspace_bytes(B.make_dims(**dims), B.WS_SAVED) != B.workspace_bytes(B.make_dims(**dims, flags=B.FLAG_TILES_SMALL), B.WS_SAVED)
+
+    for T, r, h, N, k in ((2892, 576, 2304, 16, 2), (4421, 384, 1536, 64, 6), (7594, 384, 1536, 32, 1), (493, 896, 1792, 16, 8), (1796, 640, 1280, 48, 4)):
+        assert not has_map(T=T, d=4 * r, r=r, N=N, k=k, h=h), (T, r, h, N, k)
+    for T, r, h, N, k in ((8192, 256, 1024, 64, 8), (16384, 512, 2048, 64, 6), (500, 1024, 4096, 64, 8), (2048, 1024, 4096, 64, 8), (3001, 640, 2560, 64, 8)):
+        assert has_map(T=T, d=4 * r, r=r, N=N, k=k, h=h), (T, r, h, N, k)
+
+
 def test_where_the_dispatch_step_runs():
     """bigmac_dispatch_folding: host logic only.  Forward-only bf16 calls fold the dispatch into the
     expert-up product; DCCA training calls into the descending projection unless the router reads
