@@ -207,16 +207,24 @@ inline ExpertWgradTile expert_wgrad_tile(const bigmac_dims& D, int M, int N) {
   if ((double)M * N * D.k * 3 >= 65536.0 * 256 * 2) return WGRAD_BIG;
   return 2.0 * rows * M * N >= 3e10 ? WGRAD_BY_ROUTING : WGRAD_SMALL;
 }
-// The shared projections and their data gradients: by how full the rounds of 256 tiles are.  Ascending and its counterpart at 512, 472 and 252 tiles: 78 -> 77 us
-// and 112 -> 103, 53 -> 51 and 73 -> 70, 32 -> 30 and 43 -> 42; at 320 and 128 tiles: 53 -> 59 and 70 -> 74, 20 -> 22 and 26 -> 30.
-// The product dy W_up^T, whose operands are both k-contiguous, gains from 80 tiles on where it does not run on the
-// 128 x 64 tile (53 -> 44 us; 128 tiles: 62 -> 49 us).
-inline bool big_dense(const bigmac_dims& D, int M, int N, int K) {
+// The shared projections and their data gradients: by how full the rounds of 256 tiles are.  Ascending and its counterpart at 472 and
+// 252 tiles: 53 -> 51 us and 73 -> 70, 32 -> 30 and 43 -> 42; at 320 and 128 tiles: 53 -> 59 and 70 -> 74, 20 -> 22 and 26 -> 30.  The one that
+// adds to dx (accumulate) keeps it from two rounds on (0.80 to 0.88 of the time); plain stores of a K under 896 are left to the
+// smaller tiles (ascending, K 640, 560 tiles 60 -> 70 us, 432 tiles 52 -> 56 us; K 768, 528 tiles 71 -> 78 us).
+inline bool big_dense(const bigmac_dims& D, int M, int N, int K, bool accumulate = false) {
   bool large;
   if (K % 64) return false;
   if (tiles_forced(D, &large)) return bf(D) && large;
   const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
-  return tiles >= 512 || round_fill(tiles) >= 0.8;
+  if (accumulate) return tiles >= 512 || round_fill(tiles) >= 0.8;
+  return K >= 896 && round_fill(tiles) >= 0.8;
+}
+// dy W_up^T, whose operands are both k-contiguous, gains from 90 tiles on where it does not run on the 128 x 64 tile (53 -> 44 us;
+// 128 tiles 62 -> 49 us; 81 tiles 47 -> 59 us, 84 tiles 40 -> 51 us).
+inline bool big_ascend_dgrad(const bigmac_dims& D) {
+  bool large;
+  if (tiles_forced(D, &large) || big_dense(D, D.T, D.r, D.d)) return big_dense(D, D.T, D.r, D.d);
+  return !deep_dense(D, D.T, D.r, D.d) && D.d >= 1024 && (long)((D.T + 255) / 256) * ((D.r + 255) / 256) >= 90;
 }
 inline bool any_big_rows(const bigmac_dims& D) {   // a tile map of 256-row tiles is needed
   const Widths W = widths(D);
@@ -842,7 +850,6 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
   if (bf(*D) && D->N % 8) return BIGMAC_ERR_UNSUPPORTED;  // the dense logit gradient has 16-byte rows
   if (ws_bytes < bigmac_workspace_bytes(D, BIGMAC_WS_LAYER_TRAIN)) return BIGMAC_ERR_WORKSPACE;
   hipStream_t s = (hipStream_t)stream;
-  bool large;
   const Widths W = widths(*D);
   const SavedPlan S = plan_saved(*D);
   const BwdPlan B = plan_bwd(*D);
@@ -882,9 +889,8 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
     g.A = dy; g.lda = D->d; g.M = D->T; g.K = D->d;
     g.B = P->w_up; g.ldb = D->d; g.N = D->r;
     g.C = dy_low; g.ldc = D->r;
-    g.deep_tile = deep_dense(*D, D->T, D->r, D->d);
-    g.big_tile = big_dense(*D, D->T, D->r, D->d) || (!g.deep_tile && !tiles_forced(*D, &large) && D->d >= 1024);
-    g.deep_tile = g.deep_tile && !g.big_tile;
+    g.big_tile = big_ascend_dgrad(*D);
+    g.deep_tile = !g.big_tile && deep_dense(*D, D->T, D->r, D->d);
     {
       BIGMAC_STAGE(BIGMAC_STAGE_BWD_ASCEND_DGRAD);
       rc = launch_gemm(g, s);
@@ -1001,7 +1007,7 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
       g.A = dx_low; g.lda = low_ld(*D); g.M = D->T; g.K = low_ld(*D);
       g.B = P->w_down; g.ldb = D->r; g.N = D->d; g.kwrap_b = bf(*D) ? D->r : 0;
       g.C = dx_f32; g.ldc = D->d;
-      g.big_tile = big_dense(*D, D->T, D->d, low_ld(*D));
+      g.big_tile = big_dense(*D, D->T, D->d, low_ld(*D), true);
       g.wide_k = !g.big_tile && wide_k_ok(*D, low_ld(*D), 16);
       BIGMAC_STAGE(BIGMAC_STAGE_BWD_DESCEND_DGRAD);
       rc = launch_gemm(g, s);
