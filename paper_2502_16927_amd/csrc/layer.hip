@@ -247,10 +247,16 @@ inline bool pair_experts(const bigmac_dims& D, const void* b1, const void* b2, c
   return tiles >= (W.win == 256 ? 128 : 96) || (W.win == 128 && W.hid <= 512);
 }
 
-TileMapJobs tile_map_jobs(const bigmac_dims& D, int* tile_map, int* tile_map_tall, unsigned* claims) {
+// ... by the expert products of a forward pass (the backward pass has one more with an activation)
+inline bool big_forward_rows(const bigmac_dims& D, const void* b1, const void* b2, const void* act) {
+  const Widths W = widths(D);
+  return !pair_experts(D, b1, b2, act) && (big_rows(D, W.hid, W.win, EPI_GELU) || big_rows(D, W.win, W.hid, EPI_STORE));
+}
+// big: whether a row product of this call runs on 256 x 256 tiles
+TileMapJobs tile_map_jobs(const bigmac_dims& D, bool big, int* tile_map, int* tile_map_tall, unsigned* claims) {
   TileMapJobs maps = {};
   maps.tile_rows[0] = gemm_ragged_tile_rows(D.dtype, 0); maps.map[0] = tile_map;
-  if (any_big_rows(D)) { maps.tile_rows[1] = gemm_ragged_tile_rows(D.dtype, 1); maps.map[1] = tile_map_tall; }
+  if (big) { maps.tile_rows[1] = gemm_ragged_tile_rows(D.dtype, 1); maps.map[1] = tile_map_tall; }
   maps.clear = claims; maps.clear_ints = CLAIM_INTS;
   return maps;
 }
@@ -670,7 +676,7 @@ int bigmac_grouped_ffn(const bigmac_dims* D, const void* x_perm, const int32_t* 
   int* tile_map_tall = (int*)((char*)tile_map + align_up(tile_map_ints((int)Tk, D->N, gemm_ragged_tile_rows(D->dtype, 0)) * 4));
   unsigned* claim_counters = (unsigned*)((char*)tile_map_tall + align_up(tile_map_ints((int)Tk, D->N, gemm_ragged_tile_rows(D->dtype, 0)) * 4));
   ClaimScope claims(claim_counters);
-  rc = launch_build_tile_map(expert_offsets, D->N, tile_map_jobs(*D, tile_map, tile_map_tall, claim_counters), s);
+  rc = launch_build_tile_map(expert_offsets, D->N, tile_map_jobs(*D, big_forward_rows(*D, b1, b2, act_saved), tile_map, tile_map_tall, claim_counters), s);
   if (rc) return rc;
   return run_experts_forward(*D, x_perm, expert_offsets, tile_map, tile_map_tall, w1, w2, b1, b2, act_saved, hact, W.hid, o_perm, 0, s);
 }
@@ -738,7 +744,8 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
   }
   auto permute = [&]() -> int {
     BIGMAC_STAGE(BIGMAC_STAGE_PERMUTATION);
-    const TileMapJobs maps = tile_map_jobs(*D, tile_map, tile_map_tall, (unsigned*)(wsb + F.claims));
+    const bool big = saved ? any_big_rows(*D) : big_forward_rows(*D, P->b1, P->b2, nullptr);
+    const TileMapJobs maps = tile_map_jobs(*D, big, tile_map, tile_map_tall, (unsigned*)(wsb + F.claims));
     return launch_build_permutation(D->T, D->k, D->N, D->capacity, topk_idx, offsets, slot_of, src_of, wsb + F.perm, s, &maps, chunk_counts != nullptr);
   };
   // A training forward on bf16 storage whose router reads x folds the dispatch into the descending

@@ -87,9 +87,9 @@ __device__ __forceinline__ void build_tile_map_wave(const int* offsets, int grou
 // schedule (see balance_ragged_k), then from TILE_MAP_HEADER on (group, first row) per M tile,
 // groups in order.  Called by all threads of a workgroup, one thread per group: 1024 of them, or 64 and
 // more for at most 64 groups.  offsets may lie in the LDS.
-// schedule_from: a map built before this one by the same workgroup from the same offsets; its
-// ragged-K schedule (split points and group order do not depend on the tile height) is copied
-// instead of being worked out again.
+// schedule_from: a map built before this one by the same workgroup from the same offsets; past 64
+// groups its ragged-K schedule (split points and group order do not depend on the tile height) is
+// copied instead of being worked out again.
 // Forced inline, like every device function of this library: left to the compiler, the second
 // call site turned this into a real call (stack pointer, scratch, LDS of the callee in a
 // module-wide block), and the one-workgroup counting sort that calls it then lost the counters
@@ -97,7 +97,8 @@ __device__ __forceinline__ void build_tile_map_wave(const int* offsets, int grou
 __device__ __forceinline__ void build_tile_map_block(const int* offsets, int groups, int tile_rows, int* __restrict__ tile_map,
                                             const int* schedule_from = nullptr) {
   if (groups <= 64) {                // one wavefront holds every group: the same steps without LDS or barriers
-    if (threadIdx.x < 64) build_tile_map_wave(offsets, groups, tile_rows, tile_map);
+    const int builder = schedule_from && blockDim.x > 64 ? 1 : 0;   // (a second map beside the first: behind it 12 -> 15, 16 -> 23 us in all)
+    if ((int)(threadIdx.x >> 6) == builder) build_tile_map_wave(offsets, groups, tile_rows, tile_map);
     return;
   }
   __shared__ int scan[16];

@@ -189,6 +189,29 @@ def test_stages_that_the_benchmark_times(order, training, r):
     assert recorded <= set(bench.stage_work(synth.small(T=T, d=d, r=r, N=N, k=k, h=h), cdac, training, False, paired))
 
 
+# the map of 256-row tiles: written (its tile count, behind the 128-row one in the plan) where a product of the call runs on such
+# tiles, beside the 128-row map (up to 64 experts) or behind it, and left alone where none does (the one-kernel expert products)
+@pytest.mark.parametrize("N,flags,written", [(64, 0, False), (64, B.FLAG_TILES_LARGE, True), (96, 0, False), (96, B.FLAG_TILES_LARGE, True)])
+def test_second_tile_map_of_a_forward_only_call(N, flags, written):
+    T, d, r, k, h = 4096, 256, 256, 8, 512
+    g = torch.Generator(device=DEV).manual_seed(N)
+    bf = lambda *s: torch.randn(s, generator=g, device=DEV).to(torch.bfloat16)
+    dims = B.make_dims(T, d, r, N, k, h, B.BF16, flags=flags)
+    x, w_gate = bf(T, d), torch.randn((d, N), generator=g, device=DEV)
+    params = B.make_params(bf(d, r), bf(r, d), w_gate, None, bf(N, r, h), bf(N, h, r))
+    assert B.expert_pairing(dims, training=False) == (not written)
+    up = lambda n: (n + 255) // 256 * 256
+    size = B.workspace_bytes(dims, B.WS_LAYER_FORWARD)
+    at = size - B.workspace_bytes(dims, B.WS_SAVED) + B.saved_layout(dims)["slot_of"] + 2 * up(4 * T * k) + up(4 * (16 + N + 2 * (T * k // 128 + N + 1)))
+    ws = B.alloc_bytes(size)
+    ws[at:at + 4].view(torch.int32).fill_(-7)
+    B.bigmac_layer_forward(dims, params, x, torch.empty((T, d), device=DEV), None, ws)
+    idx, weights = torch.empty((T, k), dtype=torch.int32, device=DEV), torch.empty((T, k), device=DEV)
+    B.bigmac_route(dims, x, w_gate, None, idx, weights, None, B.alloc_bytes(B.workspace_bytes(dims, B.WS_ROUTE)))
+    rows = torch.bincount(idx.flatten().long(), minlength=N)
+    assert int(ws[at:at + 4].view(torch.int32)) == (int(((rows + 255) // 256).sum()) if written else -7)
+
+
 # the load-balance loss of a layer call from the top-k's counters (4 and 32 parts per chunk) is the one from the picks, bit for bit
 @pytest.mark.parametrize("T,k,N", [(1025, 6, 40), (8192, 1, 128)])
 def test_loss_from_counters(T, k, N):
