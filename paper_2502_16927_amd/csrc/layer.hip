@@ -232,19 +232,22 @@ inline bool any_big_rows(const bigmac_dims& D) {   // a tile map of 256-row tile
 }
 
 // Both expert products in one kernel (expert_pair.hip): calls that keep no activations, without biases, where no tile
-// size is asked for.  A tile walks all hidden columns by itself, where the separate products spread them over the chip,
-// so at widths 192 and 256 it wants a tile for every second or third CU (estimated tiles, whole layer in us, separate
-// products -> here; width 256: 94 tiles 68 -> 69, 97: 106 -> 114, 101: 95 -> 99, 128: 91 -> 91, 141: 105 -> 94, 160: 101
-// -> 94, 544: 224 -> 193; width 192: 70 tiles 66 -> 68, 94: 69 -> 67, 101: 78 -> 76, 544: 172 -> 137).  At width 128 and up
-// to 512 columns the launch saved outweighs it at any size (6 tiles 48 -> 44, 36 tiles 50 -> 45, 544 tiles 119 -> 95).
+// size is asked for.  A tile walks all hidden columns by itself, where the separate products spread them over the chip.  For
+// expert matrices of at most 72 K elements the launch saved outweighs that at any size (whole layer in us, separate products ->
+// here, by tiles of 128 rows that the batch fills and experts: width 128, 512 columns: 22 of 16 48 -> 42, 46 of 64 60 -> 56, 12 of 256 86 -> 83;
+// width 192, 384 columns: 29 of 48 60 -> 57; width 256, 256 columns: 2 of 128 62 -> 56, 80 of 32 64 -> 60).  Larger ones want tiles
+// for a good part of the CUs, counted from the batch: experts with few rows each add nearly empty ones, which cost a whole walk
+// under even routing and are not there under skewed routing (width 256: 2 of 256, 2048 columns 135 -> 150, 2 of 256 with Zipf 0.6, 4096
+// columns 136 -> 205, 45 of 128 with Zipf 0.6, 4096 columns 215 -> 262, 80 of 8, 1024 columns 87 -> 95, 106 of 16, 4096 columns 161 -> 192, 110 of
+// 48 with Zipf 1.2 142 -> 144, 144 of 96, 2048 columns 169 -> 137, 177 of 64 124 -> 110, 512 of 64 224 -> 193; width 192: 31 of 32, 768 columns
+// 60 -> 63, 71 of 48 77 -> 73, 86 of 64 79 -> 70, 71 of 48 with Zipf 1.2, 3072 columns 113 -> 134; width 128, 1024 columns: 22 of 8 55 -> 59, 56 of 48 67 -> 64, 84 of 96 94 -> 91).
 // Training calls stay with the separate products: stored from this kernel's registers, in pieces of 32 bytes per row, the
 // two [rows, hidden] tensors took more than the products saved (width 256, 65536 rows: the step 634 -> 685 us).
 inline bool pair_experts(const bigmac_dims& D, const void* b1, const void* b2, const void* act) {
   bool large;
   const Widths W = widths(D);
   if (act || b1 || b2 || tiles_forced(D, &large) || (W.win != 128 && W.win != 192 && W.win != 256) || (size_t)W.win * W.hid * 2 >= (1ull << 31)) return false;
-  const long tiles = (long)D.T * D.k / 128 + D.N / 2;
-  return tiles >= (W.win == 256 ? 128 : 96) || (W.win == 128 && W.hid <= 512);
+  return (size_t)W.win * W.hid <= 72 * 1024 || (long)D.T * D.k / 128 >= (W.win == 256 || W.hid > 1024 ? 120 : 64);
 }
 
 // ... by the expert products of a forward pass (the backward pass has one more with an activation)

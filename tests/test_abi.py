@@ -114,6 +114,11 @@ def test_expert_pairing_and_its_price():
     assert not B.expert_pairing(B.make_dims(**dict(medium, T=500)), training=False)
     assert not B.expert_pairing(B.make_dims(**medium, dtype=B.F32), training=False)
     assert B.expert_pairing(B.make_dims(200, 128, 128, 8, 2, 128), training=False)
+    # many experts with few rows each do not count as tiles: the one kernel was up to 1.5 times slower there; small matrices take it at any size
+    assert not B.expert_pairing(B.make_dims(32, 1024, 256, 256, 8, 4096), training=False)
+    assert not B.expert_pairing(B.make_dims(1400, 1024, 256, 96, 8, 1024), training=False)
+    assert B.expert_pairing(B.make_dims(1600, 768, 192, 64, 6, 768), training=False)
+    assert B.expert_pairing(B.make_dims(32, 1024, 256, 256, 8, 256), training=False)
     with pytest.raises(B.BigmacError):
         B.expert_pairing(B.make_dims(0, 128, 128, 8, 2, 128), training=False)
     wl = synth.small(**medium)
