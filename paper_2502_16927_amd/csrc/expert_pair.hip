@@ -22,6 +22,7 @@ namespace bigmac {
 namespace {
 
 constexpr int EP_ROWS = 128, EP_THREADS = 256, EP_CHUNK = 32;   // rows per workgroup, hidden columns per chunk
+static_assert(EP_ROWS == BIGMAC_TILE_BM, "the kernel walks the square tile's map");
 
 template <int R, bool GATHER, bool OUTF32>
 __global__ __launch_bounds__(EP_THREADS) __attribute__((amdgpu_waves_per_eu(R <= 128 ? 3 : 2, R <= 128 ? 3 : 2)))

@@ -15,6 +15,7 @@ namespace bigmac {
 namespace {
 
 constexpr int PH_BM = 256, PH_BN = 256, PH_BK = 64, PH_THREADS = 512;
+static_assert(PH_BM == BIGMAC_TALL_BM, "its ragged-M products walk the second tile map");
 constexpr unsigned PH_STAGE = 65536, PH_B_AT = 32768, PH_HALF = 16384;   // bytes: a ring stage, B's place in it, half of A's
 constexpr int PH_STRIP = 4096;                                          // epilogue staging: 32 rows x 128 bytes per wavefront
 
