@@ -154,13 +154,13 @@ struct GemmDesc {
   long gstride_c;            // ragged-K / split-K: elements between consecutive C outputs
   int ksplit;                // dense: number of K slices (each writes C + z*gstride_c); 1 = none
   int kwrap_b;               // B's k index is taken modulo this (0 = off); multiple of 64
-  int tall_tile;             // bf16 weight gradients: 256 x 128 outputs
+  int tall_tile;             // bf16 weight gradients: 256 x 128 outputs (gemm_core.hpp)
   int wide_k;                // bf16, k-contiguous A, K % 64 == 0: the square tile with 64-deep k tiles, two ring stages
   int kloop_priority;        // MFMA kernels: raise the wave priority inside the k loop (see the kernel)
   int deep_tile;             // bf16, dense, store or accumulate (K % 64 == 0 with a k-contiguous operand): 128 x 64 outputs, 64-deep k tiles
   int big_tile;              // bf16: 256 x 256 outputs by eight wavefronts, one workgroup per CU (ragged-M: tile map of 256-row tiles)
   int when;                  // WHEN_*: MFMA kernels, ragged-K with a tile map: the launch does nothing unless the groups' rows are spread like that
-  const int* gather;         // ragged-M MFMA kernels with a k-contiguous A, GELU or store epilogue: row m of the product is row gather[m] / gather_div of A (device [max_rows]); NULL: A holds the rows in order
+  const int* gather;         // ragged-M MFMA kernels with a k-contiguous A, GELU epilogue: row m of the product is row gather[m] / gather_div of A (device [max_rows]); NULL: A holds the rows in order
   int gather_rows, gather_div; //   rows of A behind the index; the index is divided by gather_div first (flat (row, pick) pairs)
   const int* scatter;        // dense bf16 products with a k-contiguous A, B not k-contiguous, plain bf16 store: row m of the product is
                              //   written to the rows scatter[m * scatter_k + j], j < scatter_k, of C (negative: no row); NULL: row m of C

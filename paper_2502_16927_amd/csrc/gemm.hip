@@ -23,7 +23,7 @@ namespace bigmac {
 template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, bool AK, bool BKC, int EPI, bool OUTF32, int NS = BIGMAC_TILE_STAGES, bool GATHER = false,
           bool SCATTER = false>
 __global__ __launch_bounds__(64 * WAVES_M* WAVES_N)
-    __attribute__((amdgpu_waves_per_eu(BM * BN > BIGMAC_TILE_BM * BIGMAC_TILE_BN || BK > BIGMAC_TILE_BK ? BIGMAC_TALL_BLOCKS_PER_CU : BIGMAC_BLOCKS_PER_CU)))   // (eight wavefronts, one block per CU: also 2)
+    __attribute__((amdgpu_waves_per_eu(BM * BN > BIGMAC_TILE_BM * BIGMAC_TILE_BN || BK > BIGMAC_TILE_BK ? BIGMAC_TALL_BLOCKS_PER_CU : BIGMAC_BLOCKS_PER_CU)))
 void mfma_gemm_kernel(GemmDesc p) {
   constexpr int THREADS = 64 * WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
@@ -593,53 +593,46 @@ int launch_reduce_partials_multi(const ReduceJob* jobs, int count, int beta, hip
 
 namespace {
 
-// One-dimensional launch, a multiple of the 8 XCDs.  `persistent`: at most two workgroups per CU
-// (256 CUs), each walking several tiles; otherwise one workgroup per tile (surplus ones exit).
+// One-dimensional launch, a multiple of the 8 XCDs.  `persistent`: at most as many workgroups as
+// the 256 CUs hold, each walking several tiles; otherwise one workgroup per tile (surplus ones exit).
 template <int BM, int BN>
-dim3 grid_for(const GemmDesc& g, bool persistent, int blocks_per_cu = 0) {
+dim3 grid_for(const GemmDesc& g, bool persistent) {
   long gx = (g.N + BN - 1) / BN, gy, gz = 1;
   if (g.mode == GEMM_RAGGED_M) gy = g.max_rows / BM + g.groups + 1;
   else gy = (g.M + BM - 1) / BM;
   if (g.mode == GEMM_RAGGED_K) gz = g.groups;
   if (g.mode == GEMM_DENSE) gz = g.ksplit;
   long blocks = (gx * gy * gz + 7) / 8 * 8;
-  const long resident = 256 * (blocks_per_cu ? blocks_per_cu : BM > BIGMAC_TILE_BM ? BIGMAC_TALL_BLOCKS_PER_CU : BIGMAC_BLOCKS_PER_CU);
+  const long resident = 256 * (BM > BIGMAC_TILE_BM ? BIGMAC_TALL_BLOCKS_PER_CU : BIGMAC_BLOCKS_PER_CU);
   if (persistent && blocks > resident) blocks = resident;
   return dim3((unsigned)blocks, 1, 1);
 }
 
-template <int BM, bool AK, bool BKC>
+// The square tile, with the epilogues that the layer's products have in each operand layout.
+template <bool AK, bool BKC>
 int launch_mfma(const GemmDesc& g, hipStream_t s) {
-  constexpr int BN = BIGMAC_TILE_BN, BK = BIGMAC_TILE_BK, WMs = BIGMAC_TILE_WM, WNs = BIGMAC_TILE_WN;
+  constexpr int BM = BIGMAC_TILE_BM, BN = BIGMAC_TILE_BN, BK = BIGMAC_TILE_BK, WMs = BIGMAC_TILE_WM, WNs = BIGMAC_TILE_WN;
   dim3 grid = grid_for<BM, BN>(g, true), block(64 * WMs * WNs);
-#define BIGMAC_MFMA(EPI, OUTF32) \
-  hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, WMs, WNs, AK, BKC, EPI, OUTF32>), grid, block, 0, s, g)
-  if constexpr (AK && !BKC) {
-    if (g.scatter) {  // scattered rows: the descending projection's plain bf16 store
-      hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, WMs, WNs, AK, BKC, EPI_STORE, false, BIGMAC_TILE_STAGES, false, true>), grid, block, 0, s, g);
-      BIGMAC_CHECK_LAUNCH();
-      return BIGMAC_OK;
-    }
-    if (g.gather) {   // gathered rows: the two epilogues of the expert-up product
-      if (g.epilogue == EPI_GELU)
-        hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, WMs, WNs, AK, BKC, EPI_GELU, false, BIGMAC_TILE_STAGES, true>), grid, block, 0, s, g);
-      else if (g.epilogue == EPI_STORE && !g.out_f32)
-        hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, WMs, WNs, AK, BKC, EPI_STORE, false, BIGMAC_TILE_STAGES, true>), grid, block, 0, s, g);
-      else
-        return BIGMAC_ERR_UNSUPPORTED;
-      BIGMAC_CHECK_LAUNCH();
-      return BIGMAC_OK;
-    }
-  }
-  switch (g.epilogue) {
-    case EPI_STORE:
-      if (g.out_f32) BIGMAC_MFMA(EPI_STORE, true);
-      else BIGMAC_MFMA(EPI_STORE, false);
-      break;
-    case EPI_GELU: BIGMAC_MFMA(EPI_GELU, false); break;
-    case EPI_DGELU: BIGMAC_MFMA(EPI_DGELU, false); break;
-    case EPI_ACCUM: BIGMAC_MFMA(EPI_ACCUM, true); break;
-    default: return BIGMAC_ERR_INVALID_ARG;
+#define BIGMAC_MFMA(EPI, OUTF32, ...) \
+  hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, WMs, WNs, AK, BKC, EPI, OUTF32, BIGMAC_TILE_STAGES, __VA_ARGS__>), grid, block, 0, s, g)
+  if constexpr (!AK && !BKC) {   // weight gradients
+    if (g.epilogue != EPI_ACCUM) return BIGMAC_ERR_UNSUPPORTED;
+    BIGMAC_MFMA(EPI_ACCUM, true, false);
+  } else if constexpr (AK && !BKC) {
+    if (g.scatter) BIGMAC_MFMA(EPI_STORE, false, false, true);   // the descending projection's plain bf16 store, rows scattered
+    else if (g.gather) {                                         // expert-up, rows gathered
+      if (g.epilogue != EPI_GELU) return BIGMAC_ERR_UNSUPPORTED;
+      BIGMAC_MFMA(EPI_GELU, false, true);
+    } else if (g.epilogue == EPI_GELU) BIGMAC_MFMA(EPI_GELU, false, false);
+    else if (g.epilogue != EPI_STORE) return BIGMAC_ERR_UNSUPPORTED;
+    else if (g.out_f32) BIGMAC_MFMA(EPI_STORE, true, false);
+    else BIGMAC_MFMA(EPI_STORE, false, false);
+  } else {
+    if (g.epilogue == EPI_DGELU) BIGMAC_MFMA(EPI_DGELU, false, false);
+    else if (g.epilogue == EPI_ACCUM) BIGMAC_MFMA(EPI_ACCUM, true, false);
+    else if (g.epilogue != EPI_STORE) return BIGMAC_ERR_UNSUPPORTED;
+    else if (g.out_f32) BIGMAC_MFMA(EPI_STORE, true, false);
+    else BIGMAC_MFMA(EPI_STORE, false, false);
   }
 #undef BIGMAC_MFMA
   BIGMAC_CHECK_LAUNCH();
@@ -790,7 +783,7 @@ int launch_gemm(const GemmDesc& desc, hipStream_t s) {
       return BIGMAC_ERR_UNSUPPORTED;
   }
   if (g.big_tile) {
-    if (g.dtype != BIGMAC_BF16 || g.tall_tile || g.wide_k || g.deep_tile || g.touch_bytes) return BIGMAC_ERR_INVALID_ARG;
+    if (g.dtype != BIGMAC_BF16 || g.tall_tile || g.wide_k || g.deep_tile || g.touch_bytes || g.ksplit != 1) return BIGMAC_ERR_INVALID_ARG;
     return launch_gemm_phased(g, s);
   }
   if (g.dtype == BIGMAC_BF16) {
@@ -814,9 +807,9 @@ int launch_gemm(const GemmDesc& desc, hipStream_t s) {
       return launch_mfma_tall(g, s);
     }
     switch (combo) {
-      case 2: return launch_mfma<BIGMAC_TILE_BM, true, false>(g, s);
-      case 3: return launch_mfma<BIGMAC_TILE_BM, true, true>(g, s);
-      case 0: return launch_mfma<BIGMAC_TILE_BM, false, false>(g, s);
+      case 2: return launch_mfma<true, false>(g, s);
+      case 3: return launch_mfma<true, true>(g, s);
+      case 0: return launch_mfma<false, false>(g, s);
       default: return BIGMAC_ERR_UNSUPPORTED;
     }
   }

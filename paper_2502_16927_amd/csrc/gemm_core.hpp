@@ -25,9 +25,9 @@
 #ifndef BIGMAC_BLOCKS_PER_CU
 #define BIGMAC_BLOCKS_PER_CU (BIGMAC_TILE_STAGES <= 3 ? 3 : 2)
 #endif
-// The tall tile (GemmDesc::tall_tile): twice the rows per workgroup, each wavefront a 128 x 64
-// sub-tile (128 accumulator registers), two workgroups per CU.  A third fewer operand bytes per
-// flop: what products with many tiles and a long K are short of.
+// The tall tile (GemmDesc::tall_tile) of the weight gradients: twice the rows per workgroup, each
+// wavefront a 128 x 64 sub-tile (128 accumulator registers), two workgroups per CU.  A third fewer
+// operand bytes per flop than the square tile.
 #define BIGMAC_TALL_BM (2 * BIGMAC_TILE_BM)
 #define BIGMAC_TALL_BLOCKS_PER_CU 2
 

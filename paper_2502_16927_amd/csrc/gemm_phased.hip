@@ -46,7 +46,8 @@ __global__ __launch_bounds__(PH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
 void phased_gemm_kernel(GemmDesc desc) {
   GemmDesc p = desc;
   p.mode = MODE;                            // a constant from here on, as is what only one mode has
-  if (MODE != GEMM_DENSE) { p.ksplit = 1; p.kwrap_b = 0; }
+  p.ksplit = 1;
+  if (MODE != GEMM_DENSE) p.kwrap_b = 0;
   if (MODE == GEMM_RAGGED_K) p.bias = nullptr;
   constexpr bool SWAP = !(EPI == EPI_ACCUM || OUTF32);   // bf16 results accumulate the transposed tile (see mfma_gemm_kernel)
   constexpr unsigned OUT_OF_RANGE = 0x80000000u;
@@ -526,7 +527,6 @@ int launch_gemm_phased(const GemmDesc& g, hipStream_t s) {
   if (g.mode == GEMM_RAGGED_M) gy = g.max_rows / PH_BM + g.groups + 1;
   else gy = (g.M + PH_BM - 1) / PH_BM;
   if (g.mode == GEMM_RAGGED_K) gz = g.groups;
-  if (g.mode == GEMM_DENSE) gz = g.ksplit;
   long blocks = (2 * gx * gy * gz + 7) / 8 * 8;   // (few tiles are cut into row halves)
   if (blocks > 256) blocks = 256;
   if ((g.a_kcontig || g.b_kcontig) && g.K % PH_BK) return BIGMAC_ERR_INVALID_ARG;
@@ -553,7 +553,6 @@ int launch_gemm_phased(const GemmDesc& g, hipStream_t s) {
     else if (combo == 2 && g.epilogue == EPI_STORE) BIGMAC_PHASED(GEMM_DENSE, true, false, EPI_STORE, false);
     else if (combo == 3 && g.epilogue == EPI_STORE && g.out_f32) BIGMAC_PHASED(GEMM_DENSE, true, true, EPI_STORE, true);
     else if (combo == 3 && g.epilogue == EPI_ACCUM) BIGMAC_PHASED(GEMM_DENSE, true, true, EPI_ACCUM, true);
-    else if (combo == 2 && g.epilogue == EPI_ACCUM) BIGMAC_PHASED(GEMM_DENSE, true, false, EPI_ACCUM, true);
     else return BIGMAC_ERR_UNSUPPORTED;
   }
 #undef BIGMAC_PHASED

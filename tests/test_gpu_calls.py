@@ -166,6 +166,9 @@ FFN_CASES = [
     (500, 256, 192, 24, 8, B.BF16, B.ORDER_DCCA),
     (200, 64, 128, 8, 2, B.F32, B.ORDER_DCCA),
     (260, 64, 64, 8, 4, B.BF16, B.ORDER_CDAC),      # expert d=256 -> r=64 -> d
+    # rows in order through the one-kernel expert products (the call that keeps no pre-activation) at their other widths
+    (1500, 192, 448, 24, 8, B.BF16, B.ORDER_DCCA),
+    (3000, 256, 640, 24, 8, B.BF16, B.ORDER_DCCA),
     # many rows: narrow results with a long K for the second product ...
     (2560, 512, 2048, 16, 8, B.BF16, B.ORDER_DCCA),
     # ... and the other way round

@@ -118,9 +118,9 @@ def test_large_tiles_give_the_same_bits(case):
 @pytest.mark.parametrize("T", [127, 128, 129, 256, 257, 385])
 @pytest.mark.parametrize("width", [(64, 64), (128, 192), (192, 320)], ids=lambda w: "r%d_h%d" % w)
 def test_large_tile_edges(T, width):
-    """The 256 x 256 tile at its edges: one, two, three and five k tiles of 64; rows that fill half of a
-    tile, one more, all of it, one more (every expert gets all T tokens, k = N, so the last round of tiles is
-    cut into row halves, one of them empty); rows through the index (inference) and by copy."""
+    """The 256 x 256 tile at its edges, one tile or half of one per workgroup: one, two, three and five k tiles of 64;
+    rows that fill half of a tile, one more, all of it, one more (every expert gets all T tokens, k = N; the tiles
+    are cut into row halves, one of them empty); rows through the index (inference) and by copy."""
     r, h = width
     wl = synth.small(T=T, d=128, r=r, N=8, k=8, h=h)
     data = synth.generate(wl)
@@ -140,15 +140,44 @@ def test_large_tile_edges(T, width):
             assert np.array_equal(outs[0][n], out[n]), n
 
 
+@pytest.mark.parametrize("case", [dict(T=4097, r=64, k=8, h=1024), dict(T=4097, r=128, k=8, h=1024), dict(T=4097, r=192, k=8, h=1024),
+                                  dict(T=8000, r=64, k=4, h=1024, zipf_s=1.2), dict(T=8000, r=192, k=4, h=1024, zipf_s=1.2),
+                                  dict(T=4097, r=1024, k=8, h=64), dict(T=4097, r=1024, k=8, h=128), dict(T=8000, r=1024, k=4, h=192, zipf_s=1.2)],
+                         ids=lambda c: "T%d_r%d_k%d_h%d" % (c["T"], c["r"], c["k"], c["h"]))
+def test_large_tiles_in_a_row(case):
+    """More 256 x 256 tiles than workgroups (500 to 560 of the activation products or, with few hidden columns, of the plain stores)
+    over one, two and three k tiles: the requests move on to the workgroup's next tile, and its row index is read, while the
+    last k tiles of the one before are worked on.  Experts of 4097 rows (16 tiles and one row) and of skewed numbers; rows
+    through the index, by copy, and of the training step."""
+    wl = synth.small(d=128, N=8, **case)
+    data = synth.generate(wl)
+    outs = []
+    for flags, training in ((B.FLAG_TILES_SMALL, True), (B.FLAG_TILES_LARGE, True), (B.FLAG_TILES_LARGE, False), (B.FLAG_TILES_LARGE | B.FLAG_NO_FUSED_DISPATCH, False)):
+        layer = DeviceLayer(wl, data, flags=flags)
+        out = {"y": host(layer.forward(training=training)).copy()}
+        if training:
+            layer.alloc_grads()
+            layer.backward()
+            torch.cuda.synchronize()
+            out.update({n: host(g).copy() for n, g in layer.grads.items()}, dx=host(layer.dx).copy())
+        outs.append(out)
+    assert np.isfinite(outs[0]["y"]).all() and np.abs(outs[0]["y"]).max() > 0
+    for out in outs[1:]:
+        for n in out:
+            assert np.array_equal(outs[0][n], out[n]), n
+
+
 @pytest.mark.parametrize("flags", [0, B.FLAG_WIRE_BF16, B.FLAG_NO_FUSED_DISPATCH])
 @pytest.mark.parametrize("case", [dict(T=1, d=128, r=128, N=8, k=1, h=64), dict(T=127, d=128, r=128, N=8, k=8, h=448), dict(T=129, d=128, r=128, N=8, k=8, h=512, capacity=100),
                                   dict(T=1537, d=128, r=192, N=8, k=8, h=320), dict(T=300, d=128, r=192, N=192, k=3, h=64, zipf_s=1.2),
-                                  dict(T=160, d=256, r=256, N=256, k=4, h=64), dict(T=2049, d=128, r=256, N=8, k=8, h=192), dict(T=9000, d=128, r=256, N=16, k=8, h=128, zipf_s=1.2)],
+                                  dict(T=160, d=256, r=256, N=256, k=4, h=64), dict(T=2049, d=128, r=256, N=8, k=8, h=192), dict(T=9000, d=128, r=256, N=16, k=8, h=128, zipf_s=1.2),
+                                  dict(T=13000, d=128, r=128, N=16, k=8, h=64, zipf_s=1.2), dict(T=9000, d=128, r=192, N=16, k=8, h=64, zipf_s=1.2),
+                                  dict(T=1000, d=128, r=192, N=24, k=12, h=768), dict(T=2049, d=128, r=256, N=8, k=8, h=1088)],
                          ids=lambda c: "T%d_r%d_N%d_h%d" % (c["T"], c["r"], c["N"], c["h"]))
 def test_expert_products_in_one_kernel(case, flags):
     """The one-kernel expert products of a forward-only call against the separate ones (tile size forced): the same sums in the
     same order, so the same bits.  Rows that fill a wavefront's 32, a tile's 128, one more, none at all; one chunk pair and
-    more of the hidden columns; more tiles than workgroups; rows through the index and by copy; both kinds of result."""
+    more of the hidden columns; more tiles than workgroups at each width; rows through the index and by copy; both kinds of result."""
     case = dict(case)
     capacity = case.pop("capacity", 0)
     wl = synth.small(**case)
@@ -156,6 +185,7 @@ def test_expert_products_in_one_kernel(case, flags):
     ys = []
     for f in (flags, flags | B.FLAG_TILES_SMALL):
         layer = DeviceLayer(wl, data, flags=f, capacity=capacity)
+        assert B.expert_pairing(layer.dims, training=False) == (f == flags)
         ys.append(host(layer.forward(training=False)).copy())
     assert np.isfinite(ys[0]).all() and np.abs(ys[0]).max() > 0
     assert np.array_equal(ys[0], ys[1])
