@@ -127,10 +127,6 @@ enum GemmEpilogue {
   EPI_ACCUM = 3    // fp32 C = (beta ? C : 0) + acc
 };
 
-// A ragged-K product that may run on either of two tiles is launched on both, each under a condition that the kernel looks
-// up in the tile map (the host does not know the groups' rows): see ragged_k_uneven in gemm_core.hpp.
-enum GemmWhen { WHEN_ALWAYS = 0, WHEN_EVEN = 1, WHEN_UNEVEN = 2 };
-
 struct GemmDesc {
   int dtype;                 // BIGMAC_F32 or BIGMAC_BF16: element type of A, B, aux
   int a_kcontig, b_kcontig;
@@ -159,7 +155,6 @@ struct GemmDesc {
   int kloop_priority;        // MFMA kernels: raise the wave priority inside the k loop (see the kernel)
   int deep_tile;             // bf16, dense, store or accumulate (K % 64 == 0 with a k-contiguous operand): 128 x 64 outputs, 64-deep k tiles
   int big_tile;              // bf16: 256 x 256 outputs by eight wavefronts, one workgroup per CU (ragged-M: tile map of 256-row tiles)
-  int when;                  // WHEN_*: MFMA kernels, ragged-K with a tile map: the launch does nothing unless the groups' rows are spread like that
   const int* gather;         // ragged-M MFMA kernels with a k-contiguous A, GELU epilogue: row m of the product is row gather[m] / gather_div of A (device [max_rows]); NULL: A holds the rows in order
   int gather_rows, gather_div; //   rows of A behind the index; the index is divided by gather_div first (flat (row, pick) pairs)
   const int* scatter;        // dense bf16 products with a k-contiguous A, B not k-contiguous, plain bf16 store: row m of the product is

@@ -103,7 +103,6 @@ void mfma_gemm_kernel(GemmDesc p) {
   };
   const int wrap_tiles = p.kwrap_b ? p.kwrap_b / BK : 0x7FFFFFFF;
 
-  if (p.when && ragged_k_uneven(p) != (p.when == WHEN_UNEVEN)) return;
   TileSpace ts = tile_space<BM, BN>(p);
   if (p.mode == GEMM_RAGGED_K && p.tile_map) balance_ragged_k(p, ts);
   auto operands = [&](int id) { return tile_operands<BM, BN, BK, AK, BKC, GATHER>(p, resolve_tile<BM, BN>(p, ts, id, 2)); };
@@ -740,17 +739,21 @@ ClaimScope::~ClaimScope() { claim_pool = {nullptr, 0}; }
 
 int launch_gemm(const GemmDesc& desc, hipStream_t s) {
   GemmDesc g = desc;
-  // The claimed order for the ragged-M products only.  Measured on zipf_stress: the four per-expert row products 13-19 %
+  // The claimed order for the ragged-M products.  Measured on zipf_stress: the four per-expert row products 13-19 %
   // faster with it; the ragged-K weight gradients 40 % slower on the 256 x 128 tile (the tiles of a group all cost the
   // same, and with the fixed stride every workgroup of an XCD is on the same group and k range at once, which the
-  // claimed order breaks up); dense products level or 1-3 % slower.
-  if (!g.claim && g.dtype == BIGMAC_BF16 && g.mode == GEMM_RAGGED_M && claim_pool.base && claim_pool.next < CLAIM_SLOTS)
+  // claimed order breaks up); dense products level or 1-3 % slower.  On the 256 x 256 tile a group of at most 8 tiles
+  // does not occupy an XCD's 32 workgroups by itself, and under skewed routing the claimed order is what keeps the
+  // others busy (1024 x 256 outputs of 64 experts, 65536 rows, Zipf 1.2: 220 -> 146 us; level where routing is even;
+  // 16 tiles per group 274 -> 319 us).
+  const long group_tiles = (long)((g.M + 255) / 256) * ((g.N + 255) / 256);
+  if (!g.claim && g.dtype == BIGMAC_BF16 && (g.mode == GEMM_RAGGED_M || (g.mode == GEMM_RAGGED_K && g.big_tile && group_tiles <= 8)) && claim_pool.base &&
+      claim_pool.next < CLAIM_SLOTS)
     g.claim = claim_pool.base + (size_t)CLAIM_SLOT_INTS * claim_pool.next++;
   // host-side shape checks: the kernels move 16-byte chunks and 64-wide k tiles
   if (g.N <= 0 || (g.mode != GEMM_RAGGED_M && g.M <= 0) || (g.mode != GEMM_RAGGED_K && g.K <= 0)) return BIGMAC_ERR_INVALID_ARG;
   if (g.mode != GEMM_DENSE && (!g.offsets || g.groups <= 0)) return BIGMAC_ERR_INVALID_ARG;
   if (g.mode == GEMM_RAGGED_M && !g.tile_map) return BIGMAC_ERR_INVALID_ARG;
-  if (g.when && (g.dtype != BIGMAC_BF16 || g.mode != GEMM_RAGGED_K || !g.tile_map)) return BIGMAC_ERR_INVALID_ARG;
   if (g.dtype == BIGMAC_BF16) {
     // (a k-contiguous operand is moved in whole k tiles: past a K that is no multiple of the
     // tile the next row's elements would follow, not zeros)

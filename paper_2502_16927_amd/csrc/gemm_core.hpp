@@ -134,16 +134,6 @@ __device__ __forceinline__ void balance_ragged_k(const GemmDesc& p, TileSpace& t
   ts.last = (b >> 16) * tiles_per_group + (((b & 0xFFFF) * tiles_per_group) >> 16);
 }
 
-// Whether the heaviest group of a ragged-K product has more than one and a half times the rows that each of 256 CUs walks on
-// average (all rows x outputs / 65536 / 256).  A tile is one serial chain over its group's rows, and the chain of a large
-// tile is the longer one.  Weight gradients on 256 x 256 tiles against the smaller ones, by this ratio (1300 products,
-// even and skewed routing): below 1 0.95 of the time, 1 to 1.5 0.98, 1.5 to 2 1.0, 2 to 3 1.07 to 1.14, above 1.11 (384 x 768
-// outputs, Zipf 1.2: 192 -> 348 us).
-__device__ __forceinline__ bool ragged_k_uneven(const GemmDesc& p) {
-  const long long heaviest = (long long)(table_at(p.tile_map, 10) - 8) * TILE_MAP_K_ROWS, all = table_at(p.offsets, p.groups);
-  return heaviest * (2 * 256ll * 65536) > 3 * all * p.M * p.N;
-}
-
 template <int BM, int BN>
 __device__ __forceinline__ TileCoord resolve_tile(const GemmDesc& p, const TileSpace& ts, int id, int esz) {
   TileCoord t;

@@ -69,14 +69,19 @@ void phased_gemm_kernel(GemmDesc desc) {
   const int wave_chunk = wave * 64;
   const int wrap_tiles = p.kwrap_b ? p.kwrap_b / PH_BK : 0x7FFFFFFF;
 
-  if (MODE == GEMM_RAGGED_K && p.when && ragged_k_uneven(p) != (p.when == WHEN_UNEVEN)) return;
   TileSpace ts = tile_space<PH_BM, PH_BN>(p);
   if (p.mode == GEMM_RAGGED_K && p.tile_map) balance_ragged_k(p, ts);
   // Positions of the XCD's run: its tiles in order; where the last round would keep at most half of the XCD's
   // workgroups, that round's tiles are cut into row halves, one workgroup each.
   const int stride = (int)(gridDim.x >> 3), tiles = ts.last - ts.first;
   const int last_round = tiles > 0 ? tiles % stride : 0;
-  const int whole = 2 * last_round <= stride ? tiles - last_round : tiles;
+  int whole = 2 * last_round <= stride ? tiles - last_round : tiles;
+  if (MODE == GEMM_RAGGED_K && p.tile_map) {
+    // skewed routing: a tile of the heaviest group is one serial chain over all of its rows; where that is more than
+    // twice the rows that a workgroup walks on average, every tile is cut
+    const long long heaviest = (long long)(table_at(p.tile_map, 10) - 8) * TILE_MAP_K_ROWS, all = table_at(p.offsets, p.groups);
+    if (heaviest * (long long)gridDim.x > 2 * all * ts.gx * ts.gy) whole = 0;
+  }
   auto operands = [&](int at) {   // of a position; none: empty ranges
     const int half = at - whole, i = half < 0 ? at : whole + (half >> 1);
     TileCoord t = resolve_tile<PH_BM, PH_BN>(p, ts, i < tiles ? ts.first + i : -1, 2);

@@ -1,5 +1,7 @@
 // C ABI of libbigmac: argument checks, workspace planning and the launch sequences of the
 // layer (Eq. 2 with the expert of Eq. 4; CDAC order with the expert of Eq. 3) and its backward.
+#include <cmath>
+
 #include "common.hpp"
 #include "tile_map.hpp"
 
@@ -159,7 +161,7 @@ inline double round_fill(long tiles) {
 // Plain stores pay from a quarter of the CUs on: K 512 to 2048, 49 to 62 full 22 -> 26, 15 -> 18, 27 -> 27 us, 72 to 99 full 51 -> 43,
 // 24 -> 20, 34 -> 29 us.  Results that leave an eighth or more of their column tiles empty (widths 192, 320, 384, 576, ...)
 // also want well filled rounds: K 768 to 2304, 147 tiles 37 -> 27 us, 236 to 248 tiles 30 -> 28, 46 -> 40, 64 -> 50 us, 270 to 304 tiles
-// 58 -> 66, 63 -> 63, 80 -> 78 us; whole forward call, 270 tiles 182 -> 200 us; width 128 51 -> 59 us.
+// 58 -> 66, 63 -> 63, 80 -> 78 us; width 128 51 -> 59 us.
 // The activation epilogues are not overlapped by another workgroup's k loop, so they want a longer K and more tiles (GELU and
 // GELU', even routing unless said): K 384, 621 full 67 -> 70, 705 full 102 -> 79, 1037 full 140 -> 111 and 121 -> 107 us; K 512 to 768,
 // 203 full 36 -> 42, 260 full under skew 71 -> 70 and 60 -> 71, 323 full of 129 rows per expert under skew 78 -> 87, 424 full 81 -> 62 and
@@ -178,11 +180,11 @@ inline bool big_rows(const bigmac_dims& D, int cols, int K, GemmEpilogue epilogu
   const bool gelu = epilogue == EPI_GELU;
   if (each < 48 || cols * 4 < gx * 256 * 3) return false;
   if (epilogue == EPI_STORE) {
-    if (full < 64) return false;
     if (each < 128) return K >= 512 && D.N * gx * 5 >= (D.N * gx + 255) / 256 * 256 * 4;
-    if (K < 256 || tiles < 90) return false;
+    if (K < 256 || tiles < 90 || full < 64) return false;
     if (cols * 8 >= gx * 256 * 7) return true;
-    const long likely = each <= 224 ? D.N * gx : tiles;   // (up to 224 rows per expert nearly every one has a single tile)
+    // (rows per expert under even routing stay within two standard deviations)
+    const long even = ((long)((double)each + 2.0 * std::sqrt((double)each)) + 255) / 256 * D.N * gx, likely = even < tiles ? even : tiles;
     return likely <= 256 ? likely >= 150 : round_fill(likely) >= 0.7;
   }
   if (each < 128) return K >= 1024 && full >= (gelu ? 176 : 240);
@@ -190,22 +192,24 @@ inline bool big_rows(const bigmac_dims& D, int cols, int K, GemmEpilogue epilogu
   return K >= (gelu ? 384 : 256) && full >= 640 && tiles >= (K >= 384 ? 768 : 1024);
 }
 // Per-expert weight gradients [M, rows] x [rows, N]: enough tiles and rows (under 128 per expert the store is most of it: 1024 x 256
-// of 64 experts, 72 rows 20 -> 22 us), at least one tile high, and not much more padding than on 128-wide tiles: a tenth in the
-// columns (2560 x 640: 149 -> 158 us), a fifth in the rows (576 x 2304: 0.81 to 0.89 of the time; 384 x 1536: 0.9, under
-// skewed routing 1.2 to 1.5).
-// Where one expert can hold one and a half times the rows that a CU walks on average (it holds at most T; see ragged_k_uneven), the routing
-// decides, on the device: both tiles are launched and one returns at once, which costs 2 to 3 us and pays from a product
-// of some 50 us (1024 x 256 of 64 experts, 65536 rows, even routing 52 -> 47 us).
-enum ExpertWgradTile { WGRAD_SMALL, WGRAD_BIG, WGRAD_BY_ROUTING };
-inline ExpertWgradTile expert_wgrad_tile(const bigmac_dims& D, int M, int N) {
+// of 64 experts, 72 rows 20 -> 22 us; 4096 x 1024 112 -> 117), at least one tile high, and not much more padding than on 128-wide tiles:
+// a tenth in the columns (2560 x 640: 149 -> 158 us, 640 x 2560: 164 -> 140), a fifth in the rows (576 x 2304: 440 -> 343 us with Zipf
+// 1.2; 384 x 1536: 94 -> 84 us under even, 86 -> 127 under skewed routing).
+// A tile is one chain over its expert's rows, at most T of them, and the chain of the larger tile is the longer one.  Against the
+// rows that a CU walks on average, T k M N / 65536 / 256, by this ratio and for whole tiles: below 1 0.95 of the time, 1 to 2 0.98
+// to 1.0, above 2 1.07 to 1.1, with padded rows up to 1.8 (384 x 768, k 8, Zipf 1.2: 192 -> 348 us).  With at least 90 tiles'
+// worth of work per token (k M N / 65536) the ratio hardly passes 2 (512 x 2048, k 6, even routing 384 -> 349 us, Zipf 1.2 368 -> 390;
+// 448 x 1792, k 8: 132 -> 125, Zipf 0.6 181 -> 201; under it 512 x 1024, k 8: 91 -> 83, Zipf 0.6 135 -> 215).
+// Up to four whole tiles per expert are claimed (see launch_gemm) and cut, which levels more (1024 x 256 of 64 experts, k 8, 1024 rows
+// each: 52 -> 47 us, Zipf 0.6 161 -> 138, Zipf 1.2 203 -> 172; with 400 rows 33 -> 33, Zipf 1.2 67 -> 88).
+inline bool big_wgrad(const bigmac_dims& D, int M, int N) {
   bool large;
-  if (tiles_forced(D, &large)) return bf(D) && large ? WGRAD_BIG : WGRAD_SMALL;
-  const long gy = (M + 255) / 256, gx = (N + 255) / 256, rows = (long)D.T * D.k;
-  if (M < 256 || rows / D.N < 128 || D.N * gx * gy < 256 || gx * 256 * 10 > (long)((N + 127) / 128) * 128 * 11 ||
-      gy * 256 * 5 > (long)((M + 127) / 128) * 128 * 6)
-    return WGRAD_SMALL;
-  if ((double)M * N * D.k * 3 >= 65536.0 * 256 * 2) return WGRAD_BIG;
-  return 2.0 * rows * M * N >= 3e10 ? WGRAD_BY_ROUTING : WGRAD_SMALL;
+  if (tiles_forced(D, &large)) return bf(D) && large;
+  const long gy = (M + 255) / 256, gx = (N + 255) / 256, each = (long)D.T * D.k / D.N;
+  if (M < 256 || each < 128 || D.N * gx * gy < 256 || gx * 256 * 10 > (long)((N + 127) / 128) * 128 * 11 || gy * 256 * 5 > (long)((M + 127) / 128) * 128 * 6)
+    return false;
+  const double per_token = (double)M * N * D.k / 65536.0;
+  return per_token >= 90 || (gx * gy <= 4 && M % 256 == 0 && N % 256 == 0 && per_token >= 32 && each >= 512);
 }
 // The shared projections and their data gradients: by how full the rounds of 256 tiles are.  Ascending and its counterpart at 472 and
 // 252 tiles: 53 -> 51 us and 73 -> 70, 32 -> 30 and 43 -> 42; at 320 and 128 tiles: 53 -> 59 and 70 -> 74, 20 -> 22 and 26 -> 30.  The one that
@@ -238,7 +242,7 @@ inline bool any_big_rows(const bigmac_dims& D) {   // a tile map of 256-row tile
 // width 192, 384 columns: 29 of 48 60 -> 57; width 256, 256 columns: 2 of 128 62 -> 56, 80 of 32 64 -> 60).  Larger ones want tiles
 // for a good part of the CUs, counted from the batch: experts with few rows each add nearly empty ones, which cost a whole walk
 // under even routing and are not there under skewed routing (width 256: 2 of 256, 2048 columns 135 -> 150, 2 of 256 with Zipf 0.6, 4096
-// columns 136 -> 205, 45 of 128 with Zipf 0.6, 4096 columns 215 -> 262, 80 of 8, 1024 columns 87 -> 95, 106 of 16, 4096 columns 161 -> 192, 110 of
+// columns 136 -> 205, 45 of 128 with Zipf 0.6, 4096 columns 215 -> 262, 80 of 8, 1024 columns 87 -> 95 (512 columns: 47 of 4 67 -> 71, 68 of 8 68 -> 69, 112 of 48 69 -> 60), 106 of 16, 4096 columns 161 -> 192, 110 of
 // 48 with Zipf 1.2 142 -> 144, 144 of 96, 2048 columns 169 -> 137, 177 of 64 124 -> 110, 512 of 64 224 -> 193; width 192: 31 of 32, 768 columns
 // 60 -> 63, 71 of 48 77 -> 73, 86 of 64 79 -> 70, 71 of 48 with Zipf 1.2, 3072 columns 113 -> 134; width 128, 1024 columns: 22 of 8 55 -> 59, 56 of 48 67 -> 64, 84 of 96 94 -> 91).
 // Training calls stay with the separate products: stored from this kernel's registers, in pieces of 32 bytes per row, the
@@ -247,7 +251,7 @@ inline bool pair_experts(const bigmac_dims& D, const void* b1, const void* b2, c
   bool large;
   const Widths W = widths(D);
   if (act || b1 || b2 || tiles_forced(D, &large) || (W.win != 128 && W.win != 192 && W.win != 256) || (size_t)W.win * W.hid * 2 >= (1ull << 31)) return false;
-  return (size_t)W.win * W.hid <= 72 * 1024 || (long)D.T * D.k / 128 >= (W.win == 256 || W.hid > 1024 ? 120 : 64);
+  return (size_t)W.win * W.hid <= 72 * 1024 || (long)D.T * D.k / 128 >= (W.hid > (W.win == 256 ? 512 : 1024) ? 120 : 64);
 }
 
 // ... by the expert products of a forward pass (the backward pass has one more with an activation)
@@ -464,21 +468,6 @@ int run_experts_forward(const bigmac_dims& D, const void* x_perm, const int* off
   g.touch = nullptr; g.touch_bytes = 0;
   if (!g.big_tile) touch_weights(D, g, w2, 2);
   BIGMAC_STAGE(BIGMAC_STAGE_EXPERT_DOWN);
-  return launch_gemm(g, s);
-}
-
-// One expert matrix's gradients (ragged-K, see expert_wgrad_tile).
-int run_expert_wgrad(const bigmac_dims& D, GemmDesc g, hipStream_t s) {
-  const ExpertWgradTile tile = expert_wgrad_tile(D, g.M, g.N);
-  if (tile != WGRAD_SMALL) {
-    g.big_tile = 1;
-    g.when = tile == WGRAD_BY_ROUTING ? WHEN_EVEN : WHEN_ALWAYS;
-    const int rc = launch_gemm(g, s);
-    if (rc || tile == WGRAD_BIG) return rc;
-    g.big_tile = 0;
-    g.when = WHEN_UNEVEN;
-  }
-  g.tall_tile = tall_wgrad(D, g.M);
   return launch_gemm(g, s);
 }
 
@@ -958,17 +947,21 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
     g.A = hact; g.lda = wide_ld(*D); g.M = W.hid;
     g.B = do_perm; g.ldb = W.win; g.N = W.win;
     g.C = d_w2; g.ldc = W.win; g.gstride_c = (long)W.hid * W.win;
+    g.big_tile = big_wgrad(*D, W.hid, W.win);
+    g.tall_tile = !g.big_tile && tall_wgrad(*D, W.hid);
     {
       BIGMAC_STAGE(BIGMAC_STAGE_BWD_DOWN_WGRAD);
-      rc = run_expert_wgrad(*D, g, s);
+      rc = launch_gemm(g, s);
     }
     if (rc) return rc;
     // dW1[e] (+)= x_perm_e^T dact_e
     g.A = x_perm; g.lda = W.win; g.M = W.win;
     g.B = dact; g.ldb = wide_ld(*D); g.N = W.hid;
     g.C = d_w1; g.ldc = W.hid; g.gstride_c = (long)W.win * W.hid;
+    g.big_tile = big_wgrad(*D, W.win, W.hid);
+    g.tall_tile = !g.big_tile && tall_wgrad(*D, W.win);
     BIGMAC_STAGE(BIGMAC_STAGE_BWD_UP_WGRAD);
-    rc = run_expert_wgrad(*D, g, s);
+    rc = launch_gemm(g, s);
     if (rc) return rc;
   }
   {  // dx_perm = dact W1[e]^T
