@@ -85,7 +85,7 @@ __device__ __forceinline__ void build_tile_map_wave(const int* offsets, int grou
 
 // tile_map[0] = number of M tiles, [1..9] = the split points of the cost-balanced ragged-K
 // schedule (see balance_ragged_k), then from TILE_MAP_HEADER on (group, first row) per M tile,
-// groups in order.  Called by all threads of a workgroup, one thread per group: 1024 of them, or 64 and
+// groups in order.  Called by all threads of a workgroup, one thread per group: 1024 of them, or 128 and
 // more for at most 64 groups.  offsets may lie in the LDS.
 // schedule_from: a map built before this one by the same workgroup from the same offsets; past 64
 // groups its ragged-K schedule (split points and group order do not depend on the tile height) is
@@ -97,8 +97,8 @@ __device__ __forceinline__ void build_tile_map_wave(const int* offsets, int grou
 __device__ __forceinline__ void build_tile_map_block(const int* offsets, int groups, int tile_rows, int* __restrict__ tile_map,
                                             const int* schedule_from = nullptr) {
   if (groups <= 64) {                // one wavefront holds every group: the same steps without LDS or barriers
-    const int builder = schedule_from && blockDim.x > 64 ? 1 : 0;   // (a second map beside the first: behind it 12 -> 15, 16 -> 23 us in all)
-    if ((int)(threadIdx.x >> 6) == builder) build_tile_map_wave(offsets, groups, tile_rows, tile_map);
+    // (a second map by the second wavefront, beside the first: behind it 12 -> 15, 16 -> 23 us in all)
+    if (threadIdx.x >> 6 == (schedule_from ? 1u : 0u)) build_tile_map_wave(offsets, groups, tile_rows, tile_map);
     return;
   }
   __shared__ int scan[16];
