@@ -63,9 +63,12 @@ enum {
                                  gradient of the dispatched rows) travel in bf16, the format of the
                                  paper's Table 4; default: those win-wide rows stay fp32, which is
                                  what keeps y and dx within 2e-2 of their RMS at the widest shapes,*/
-  BIGMAC_FLAG_TILES_LARGE = 8, /* tuning: run every expert product that can on 256 x 256 workgroup tiles,  */
-  BIGMAC_FLAG_TILES_SMALL = 16,/* or none of them (default: chosen from the shape).  Results do not depend
-                                  on the tile: the same products are added in the same order.            */
+  BIGMAC_FLAG_TILES_LARGE = 8, /* tuning: run every product that can (expert products, shared projections and
+                                  their data gradients) on 256 x 256 workgroup tiles,                    */
+  BIGMAC_FLAG_TILES_SMALL = 16,/* or none of them (default: chosen from the shape).  Either flag also keeps the
+                                  two expert products of a forward-only call apart (bigmac_expert_pairing);
+                                  both together are refused.  Results do not depend on the tile: the
+                                  same products are added in the same order.                             */
   BIGMAC_FLAG_ROUTE_LOW = 32,  /* layer calls, DCCA order: the router reads x' instead of x (Section 3.1
                                   names both inputs): w_gate and d_w_gate are [r, N], the logits are those of
                                   bigmac_route on the stored x' (dtype) with d = r, and the gate's gradient
