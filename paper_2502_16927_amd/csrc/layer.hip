@@ -158,10 +158,13 @@ inline double round_fill(long tiles) {
 }
 // Per-expert row products: the tiles that the results would fill (full), and the estimated tiles with each expert's last one
 // half empty, against the 256 CUs.  Figures are one product's (or the whole layer's, where said) under even or skewed routing.
-// Plain stores pay from a quarter of the CUs on: K 512 to 2048, 49 to 62 full 22 -> 26, 15 -> 18, 27 -> 27 us, 72 to 99 full 51 -> 43,
-// 24 -> 20, 34 -> 29 us.  Results that leave an eighth or more of their column tiles empty (widths 192, 320, 384, 576, ...)
-// also want well filled rounds: K 768 to 2304, 147 tiles 37 -> 27 us, 236 to 248 tiles 30 -> 28, 46 -> 40, 64 -> 50 us, 270 to 304 tiles
-// 58 -> 66, 63 -> 63, 80 -> 78 us; width 128 51 -> 59 us.
+// Plain stores pay from about a quarter of the CUs on (K 512 to 2048, 49 to 56 full 1.15 of the time, 56 to 64 0.91, 72 to 99 51 -> 43,
+// 24 -> 20, 34 -> 29 us; with a K of 2048 and experts that a single 256-row tile holds, which is two of the smaller ones, from 40: 44
+// to 54 full 70 -> 56, 72 -> 58, 87 -> 68 us), the data gradient of the first matrix, whose both operands are k-contiguous and which the smaller tile also
+// reads in whole lines, from a third on (56 to 80 full 1.04, 80 to 100 0.99, 100 to 128 0.94).  Results that leave an eighth or
+// more of their column tiles empty (widths 192, 320, 384, 576, ...) also want the rounds past the first well filled: K 768 to 2304, 147
+// tiles 37 -> 27 us, 236 to 248 tiles 30 -> 28, 46 -> 40, 64 -> 50 us, 270 to 320 tiles 58 -> 66, 63 -> 63, 80 -> 78 us, one call of the
+// steps 134 -> 139 us; width 128 51 -> 59 us.
 // The activation epilogues are not overlapped by another workgroup's k loop, so they want a longer K and more tiles (GELU and
 // GELU', even routing unless said): K 384, 621 full 67 -> 70, 705 full 102 -> 79, 1037 full 140 -> 111 and 121 -> 107 us; K 512 to 768,
 // 203 full 36 -> 42, 260 full under skew 71 -> 70 and 60 -> 71, 323 full of 129 rows per expert under skew 78 -> 87, 424 full 81 -> 62 and
@@ -173,7 +176,7 @@ inline double round_fill(long tiles) {
 // leave half of a 256-row one idle, which only a long K makes up for (K 384, 72 rows 47 -> 54 and 44 -> 57 us; K 1024, 75 full 50 ->
 // 61, 112 full 44 -> 57 (GELU'), 180 full 82 -> 76, 186 full 94 -> 89, 248 full 136 -> 124 and 135 -> 130 us) and, for plain stores, a
 // round that is nearly full (72 rows, 128 tiles 43 -> 48 and 20 -> 25 us, 256 tiles 53 -> 48 and 69 -> 62 us, at K 256 14 -> 15).
-inline bool big_rows(const bigmac_dims& D, int cols, int K, GemmEpilogue epilogue) {
+inline bool big_rows(const bigmac_dims& D, int cols, int K, GemmEpilogue epilogue, bool data_gradient = false) {
   bool large;
   if (tiles_forced(D, &large)) return bf(D) && large;
   const long rows = (long)D.T * D.k, gx = (cols + 255) / 256, tiles = (rows / 256 + D.N / 2) * gx, full = rows * cols / 65536, each = rows / D.N;
@@ -181,11 +184,11 @@ inline bool big_rows(const bigmac_dims& D, int cols, int K, GemmEpilogue epilogu
   if (each < 48 || cols * 4 < gx * 256 * 3) return false;
   if (epilogue == EPI_STORE) {
     if (each < 128) return K >= 512 && D.N * gx * 5 >= (D.N * gx + 255) / 256 * 256 * 4;
-    if (K < 256 || tiles < 90 || full < 64) return false;
-    if (cols * 8 >= gx * 256 * 7) return true;
+    const bool padded = cols * 8 < gx * 256 * 7;
+    if (K < 256 || full < (data_gradient ? 96 : K >= 2048 && each <= 256 ? 40 : padded ? 64 : 56)) return false;
     // (rows per expert under even routing stay within two standard deviations)
     const long even = ((long)((double)each + 2.0 * std::sqrt((double)each)) + 255) / 256 * D.N * gx, likely = even < tiles ? even : tiles;
-    return likely <= 256 ? likely >= 150 : round_fill(likely) >= 0.7;
+    return !padded || likely <= 256 || round_fill(likely) >= 0.75;
   }
   if (each < 128) return K >= 1024 && full >= (gelu ? 176 : 240);
   if (K >= 512) return tiles >= (K >= 1024 ? 256 : 512) && (full >= 400 || (K >= 896 ? gelu || full >= 192 : gelu && each >= 224));
@@ -232,7 +235,8 @@ inline bool big_ascend_dgrad(const bigmac_dims& D) {
 }
 inline bool any_big_rows(const bigmac_dims& D) {   // a tile map of 256-row tiles is needed
   const Widths W = widths(D);
-  return big_rows(D, W.hid, W.win, EPI_GELU) || big_rows(D, W.hid, W.win, EPI_DGELU) || big_rows(D, W.win, W.hid, EPI_STORE);
+  return big_rows(D, W.hid, W.win, EPI_GELU) || big_rows(D, W.hid, W.win, EPI_DGELU) || big_rows(D, W.win, W.hid, EPI_STORE) ||
+         big_rows(D, W.win, W.hid, EPI_STORE, true);
 }
 
 // Both expert products in one kernel (expert_pair.hip): calls that keep no activations, without biases, where no tile
@@ -971,7 +975,7 @@ int bigmac_layer_backward(const bigmac_dims* D, const bigmac_params* P, const vo
     g.A = dact; g.lda = wide_ld(*D); g.K = W.hid;
     g.B = P->w1; g.ldb = W.hid; g.gstride_b = (long)W.win * W.hid; g.N = W.win;
     g.C = dx_perm; g.ldc = W.win;
-    g.big_tile = big_rows(*D, W.win, W.hid, EPI_STORE);
+    g.big_tile = big_rows(*D, W.win, W.hid, EPI_STORE, true);
     if (g.big_tile) g.tile_map = tile_map_tall;
     g.wide_k = !g.big_tile && wide_k_ok(*D, W.hid, 8);
     g.kloop_priority = 1;

@@ -136,7 +136,7 @@ def test_which_shapes_have_a_map_of_256_row_tiles():
     def has_map(**dims):
         return B.workspace_bytes(B.make_dims(**dims), B.WS_SAVED) != B.workspace_bytes(B.make_dims(**dims, flags=B.FLAG_TILES_SMALL), B.WS_SAVED)
 
-    for T, r, h, N, k in ((2892, 576, 2304, 16, 2), (4800, 384, 768, 48, 6), (7594, 384, 1536, 32, 1), (493, 896, 1792, 16, 8), (1796, 640, 1280, 48, 4)):
+    for T, r, h, N, k in ((2892, 576, 2304, 16, 2), (4800, 384, 768, 48, 6), (7594, 384, 1536, 32, 1), (493, 896, 1792, 16, 8), (1500, 640, 1280, 48, 4)):
         assert not has_map(T=T, d=4 * r, r=r, N=N, k=k, h=h), (T, r, h, N, k)
     for T, r, h, N, k in ((8192, 256, 1024, 64, 8), (16384, 512, 2048, 64, 6), (500, 1024, 4096, 64, 8), (2048, 1024, 4096, 64, 8), (3001, 640, 2560, 64, 8)):
         assert has_map(T=T, d=4 * r, r=r, N=N, k=k, h=h), (T, r, h, N, k)
