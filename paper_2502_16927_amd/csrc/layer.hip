@@ -160,8 +160,8 @@ inline double round_fill(long tiles) {
 // half empty, against the 256 CUs.  Figures are one product's (or the whole layer's, where said) under even or skewed routing.
 // Plain stores pay from about a quarter of the CUs on (K 512 to 2048, 49 to 56 full 1.15 of the time, 56 to 64 0.91, 72 to 99 51 -> 43,
 // 24 -> 20, 34 -> 29 us; with a K of 2048 and experts that a single 256-row tile holds, which is two of the smaller ones, from 40: 44
-// to 54 full 70 -> 56, 72 -> 58, 87 -> 68 us), the data gradient of the first matrix, whose both operands are k-contiguous and which the smaller tile also
-// reads in whole lines, from a third on (56 to 80 full 1.04, 80 to 100 0.99, 100 to 128 0.94).  Results that leave an eighth or
+// to 54 full 70 -> 56, 72 -> 58, 87 -> 68 us), the data gradient of the first matrix, whose both operands are k-contiguous and which the
+// smaller tile also reads in whole lines, from a third on (56 to 80 full 1.04, 80 to 100 0.99, 100 to 128 0.94).  Results that leave an eighth or
 // more of their column tiles empty (widths 192, 320, 384, 576, ...) also want the rounds past the first well filled: K 768 to 2304, 147
 // tiles 37 -> 27 us, 236 to 248 tiles 30 -> 28, 46 -> 40, 64 -> 50 us, 270 to 320 tiles 58 -> 66, 63 -> 63, 80 -> 78 us, one call of the
 // steps 134 -> 139 us; width 128 51 -> 59 us.
@@ -169,7 +169,8 @@ inline double round_fill(long tiles) {
 // GELU', even routing unless said): K 384, 621 full 67 -> 70, 705 full 102 -> 79, 1037 full 140 -> 111 and 121 -> 107 us; K 512 to 768,
 // 203 full 36 -> 42, 260 full under skew 71 -> 70 and 60 -> 71, 323 full of 129 rows per expert under skew 78 -> 87, 424 full 81 -> 62 and
 // 67 -> 57 us; K 960, 267 full 109 -> 79 and 94 -> 73 us; K 1024, 140 full 60 -> 39 us and under skew 51 -> 58 (GELU'), 200 full 66 -> 45
-// and 59 -> 43 us.  (The routing moves these lines: both expert products, K 576, 479 full of 213 rows per expert 163 -> 140 us with
+// and 59 -> 43 us.  K 256 to 320: GELU' 0.85 to 0.98 of the time from 1024 tiles on under every routing (94 -> 88 us, 131 -> 117, 245 ->
+// 220; 400 to 500 full 0.86 to 1.13), GELU 1.1 to 1.2 (77 -> 88 us, 100 -> 113) up to 1700 tiles.  (The routing moves these lines: both expert products, K 576, 479 full of 213 rows per expert 163 -> 140 us with
 // even, 167 -> 190 us with strongly skewed routing.)
 // Few rows per expert, whose products stream the weights, keep more of the smaller workgroups in flight (GELU, 4 rows 102 ->
 // 112 us, 16 rows 111 -> 115 us; plain stores of 10 rows, whole layer 195 -> 204 us).  Experts that a 128-row tile holds whole
