@@ -4,24 +4,13 @@
 //   p_l  = fma(x[t, 64q + l], W_g[64q + l, n], p_l),  q ascending, l = 0..63   (one lane each)
 //   tree = p_l + p_{l+off} for off = 32, 16, 8, 4, 2, 1;  logit = tree (+ bias[n], added last)
 // The tree is evaluated as a reduce-scatter over the wavefront: same pairs, 1/6 of the adds.
+#include "gemm_core.hpp"
 #include "wave.hpp"
 
 namespace bigmac {
 
 namespace {
 
-#ifndef ROUTER_TB_LARGE
-#define ROUTER_TB_LARGE 8   // tokens per wavefront of the pipelined router kernel when there are plenty of tokens
-#endif
-#ifndef ROUTER_TILE_BLOCKS
-#define ROUTER_TILE_BLOCKS 2      // 64-row blocks of d per LDS tile of the pipelined router kernel
-#endif
-#ifndef ROUTER_TILE_STAGES
-#define ROUTER_TILE_STAGES 3      // tiles in its ring (at most 4: the waits count up to two younger tiles); 2 to 4 measured alike
-#endif
-#ifndef ROUTER_SLICES
-#define ROUTER_SLICES 2     // 16-expert slices per workgroup of the pipelined router kernel when there are plenty of workgroups
-#endif
 constexpr int R_TB = 8;     // tokens per wave
 constexpr int R_NB = 16;    // experts per pass
 constexpr int R_QT = 4;     // 64-row blocks of W_g staged per LDS tile
@@ -119,257 +108,410 @@ __global__ __launch_bounds__(256) void router_logits_kernel(const XT* __restrict
   }
 }
 
-// LDS reads with a compile-time instruction offset, as assembly (see the kernel below for why).
+// The same sums on the matrix cores, for N % 4 == 0.  v_mfma_f32_16x16x1_4b_f32 has a contraction of one: every output
+// element takes part in exactly one fused multiply-add per instruction (bit for bit that of fmaf, subnormals, infinities
+// and NaN included), so 64 accumulators per logit, each fed in ascending q, are the partial sums p_l in their order.
+// The four blocks of an instruction hold residues l of the four runs 16 b .. 16 b + 15.  With c = l % 16 = 8 h + 2 q + p, a
+// wavefront holds RR of the c's for a tile of 16 tokens x 16 ET experts: one (h, p) with all four q, or one (h, p, q % 2).  Block b of an
+// instruction takes another q, that is another word of a 16-byte chunk, in each block: with the rows' chunks swizzled by the token
+// the 64 lanes of an operand read fall on the 64 banks.  The tree's distances 32 and 16 stay inside a lane's registers; the rest goes
+// through the LDS, with (h, p) wavefronts as two exchanges (8; 4 and 2 in registers; 1).
+// What bounds it: the matrix rate of fp32, 157 TFLOP/s by the clock and 140 in a register-only loop on all CUs.  These instructions
+// run on the vector ALU's multipliers: a vector instruction among them costs some 9 cycles of theirs, and a stretch of other
+// instructions that both wavefronts of a SIMD run at once leaves the multipliers idle.  So the loop has no vector instruction but the
+// ring's address steps, and everything else stands between the matrix instructions, one or two at a time.  Operands travel
+// global -> LDS directly (16 bytes per lane) through a ring of S stages of QQT 64-row blocks, the next tile's behind this one's
+// reduction.  Token rows past T and columns past N arrive as zeros and are never used.
+template <typename XT, int TT, int ET, int QQT>
+struct RouterTile {
+  static constexpr int THREADS = 512;
+  static constexpr int WPT = 8 / TT, RR = 16 / WPT, M = RR * ET;          // wavefronts per token tile, c's of each, instructions per block
+  static constexpr int TOKENS = 16 * TT, EXPERTS = 16 * ET;
+  static constexpr int XROW = 64 * (int)sizeof(XT) / 16;                  // 16-byte chunks of a token's 64-element block: 8, 16
+  static constexpr int XCH = TOKENS * XROW * QQT, WCH = 64 * QQT * 4 * ET;  // chunks of a stage: tokens, router rows
+  static constexpr int XL = XCH / THREADS, WL = WCH / THREADS, LPT = XL + WL;
+  static_assert((TT == 1 || (TT == 2 && ET == 2)) && XCH % THREADS == 0 && WCH % THREADS == 0, "whole passes");
+  static_assert(QQT % 2 == 0, "a stage starts with the first register set");
+  static constexpr int STAGE = (XCH + WCH) * 16;
+  static constexpr int S = 5 * 24576 / STAGE > 6 ? 6 : 5 * 24576 / STAGE; // ring stages
+  static constexpr int SUMS_AT = S * STAGE, BIAS_AT = SUMS_AT + (TT == 2 ? 36864 : ET * 16384), LDS = BIAS_AT + 4096;
+  static_assert(S >= 3 && LDS <= 160 * 1024, "LDS of a CU");
+};
 template <int OFFSET>
-__device__ __forceinline__ void router_lds_read_u16(unsigned addr, unsigned& v) {
-  asm volatile("ds_read_u16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFFSET) : "memory");
-}
-template <int OFFSET>
-__device__ __forceinline__ void router_lds_read_b32(unsigned addr, unsigned& v) {
+__device__ __forceinline__ void lds_read_b32(unsigned addr, unsigned& v) {
   asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFFSET) : "memory");
 }
-typedef unsigned int router_u32x4 __attribute__((ext_vector_type(4)));
 template <int OFFSET>
-__device__ __forceinline__ void router_lds_read_b128(unsigned addr, router_u32x4& v) {
-  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFFSET) : "memory");
+__device__ __forceinline__ void lds_read_high_u16(unsigned addr, unsigned& v) {   // to the upper half; the lower one stays as it is
+  asm volatile("ds_read_u16_d16_hi %0, %1 offset:%2" : "+v"(v) : "v"(addr), "n"(OFFSET) : "memory");
 }
-template <int I> struct RouterIndex { static constexpr int value = I; };
-template <int BEGIN, int END, typename F>
-__device__ __forceinline__ void router_static_for(F&& f) {
-  if constexpr (BEGIN < END) {
-    f(RouterIndex<BEGIN>{});
-    router_static_for<BEGIN + 1, END>(f);
+template <int OFFSET>
+__device__ __forceinline__ void lds_read_b64(unsigned addr, u32x2_t& v) {
+  asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(OFFSET) : "memory");
+}
+template <int FIRST, int SECOND>   // bytes
+__device__ __forceinline__ void lds_read_two_b32(unsigned addr, u32x2_t& v) {
+  static_assert(FIRST % 256 == 0 && SECOND % 256 == 0 && SECOND < 65536, "instruction offsets");
+  asm volatile("ds_read2st64_b32 %0, %1 offset0:%2 offset1:%3" : "=v"(v) : "v"(addr), "n"(FIRST / 256), "n"(SECOND / 256) : "memory");
+}
+template <int OFFSET>
+__device__ __forceinline__ void lds_write_b64(unsigned addr, u32x2_t v) {
+  asm volatile("ds_write_b64 %0, %1 offset:%2" ::"v"(addr), "v"(v), "n"(OFFSET) : "memory");
+}
+struct RouterJob {
+  const void* x;
+  const float *wg, *bias;
+  float* logits;
+  int T, d, N, slices, blocks, stages;   // expert slices, token blocks; ring stages of a tile
+  int stride, block_step, slice_step;    // tiles of an XCD from one of a workgroup to its next, in blocks and slices
+  unsigned slices_inverse;               // ceil(65536 / slices): i / slices of the first tiles (i < 32) by multiplication
+  int warm_lines;                        // 128-byte lines of w_gate that workgroups without a tile read (0: none)
+};
+template <typename XT, int TT, int ET, int QQT>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void router_logits_matrix_kernel(RouterJob job) {
+  const XT* const x = (const XT*)job.x;
+  const float *const wg = job.wg, *const bias = job.bias;
+  float* const logits = job.logits;
+  const int T = job.T, d = job.d, N = job.N;
+  typedef RouterTile<XT, TT, ET, QQT> C;
+  constexpr int S = C::S, ES = (int)sizeof(XT), RR = C::RR, M = C::M;
+  __shared__ __attribute__((aligned(128))) uint4 lds[C::LDS / 16];
+  const unsigned lds_at = lds_address(lds);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  // Workgroup -> tiles.  Token blocks are dealt to the XCDs in turn and an XCD walks the expert slices of a block one after the
+  // other: the block's token rows come from memory once, then from that XCD's L2, and every XCD keeps all of w_gate.
+  const int slices = job.slices, blocks = job.blocks, stride = job.stride, block_step = job.block_step, slice_step = job.slice_step;
+  const int xcd = (int)(blockIdx.x & 7), tiles = xcd < blocks ? ((blocks - 1 - xcd) / 8 + 1) * slices : 0;
+  int tile = (int)(blockIdx.x >> 3);
+  const int nq = d / 64, stages = job.stages;             // of a tile
+  if (tile >= tiles) {
+    // Few tiles: each is one CU's stream of w_gate from memory, at what a CU has in flight.  The XCD's workgroups without a tile
+    // read a word of every line, all at once, and the streams find it in the L2.
+    if (tiles > 0)
+      for (int i = (tile - tiles) * C::THREADS + (int)threadIdx.x; i < job.warm_lines; i += (stride - tiles) * C::THREADS) {
+        const float word = wg[(size_t)i * 32];
+        asm volatile("" ::"v"(word));
+      }
+    return;
   }
-}
-
-// Same computation for N % 4 == 0, software-pipelined: token tiles (32 tokens x 64 QQT elements)
-// and router tiles (64 QQT rows x 16 columns) travel global -> LDS directly (16 bytes per lane, no
-// registers) through a ring of S stages, S - 1 tiles in flight while the 128 QQT fused
-// multiply-adds per lane of the current one run.  Token rows past T and router rows past d lie
-// outside the buffer ranges and arrive as zeros; they are never used anyway.
-#define BIGMAC_ROUTER_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (((n) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
-// TB = tokens per wavefront (8 for large T; 1, 2 or 4 when T is small, so that the few tokens still
-// spread over many CUs).  The summation order does not depend on it.
-// SL = 16-expert slices a workgroup computes one after the other on its token tile: the next
-// slice's first tiles are requested before the reduction of the current one, so the fixed cost
-// of a workgroup (set-up, first-tile latency) is paid once per SL slices.
-template <typename XT, int TB, int SL>
-__global__ __launch_bounds__(256) void router_logits_pipelined_kernel(const XT* __restrict__ x, const float* __restrict__ wg,
-                                                                      const float* __restrict__ bias, float* __restrict__ logits,
-                                                                      int T, int d, int N) {
-  constexpr int QQT = ROUTER_TILE_BLOCKS;           // 64-row blocks of d per tile
-  constexpr int S = sizeof(XT) == 2 ? ROUTER_TILE_STAGES : 3;   // ring of S tiles, S - 1 in flight while one is consumed
-  static_assert(S >= 2 && S <= 4 && QQT >= 1 && QQT <= 4, "the counter waits below cover up to two younger tiles");
-  constexpr int TROWS = 64 * QQT;                   // rows of d per tile
-  constexpr int XROW = TROWS * sizeof(XT) / 16;     // 16-byte chunks per token row of a tile
-  constexpr int TOKENS = 4 * TB;                    // tokens per workgroup
-  constexpr int XCH = TOKENS * XROW;                // chunks of a token tile
-  constexpr int WCH = TROWS * 4;                    // chunks of a router tile (TROWS rows x 16 floats)
-  constexpr int XL = (XCH + 255) / 256, WL = (WCH + 255) / 256;   // loads per thread
-  constexpr int LPT = XL + WL;
-  __shared__ uint4 xring[S * XL * 256];             // (a tile of fewer than 256 chunks is padded: the surplus lanes load out of range)
-  __shared__ uint4 wring[S * WL * 256];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  // Workgroup -> (token block, expert slices).  The workgroups that share a token block (one per
-  // group of SL slices) get linear indices 8 apart: consecutive indices go round the 8 XCDs, so
-  // these land on one XCD at about the same time and the block's token rows come from memory
-  // once, then from that XCD's L2; every XCD keeps all of w_gate.  (With the slice index as the
-  // slow grid dimension the token rows were fetched once per slice group and the router columns
-  // did not stay in the L2 behind them: 8 times the algorithmic bytes at d = 4096, N = 128.)
-  const int slice_groups = (N + SL * R_NB - 1) / (SL * R_NB);
-  const int lin = (int)(blockIdx.x >> 3);
-  const int token_block = (lin / slice_groups) * 8 + (int)(blockIdx.x & 7);
-  const int tb = token_block * TOKENS, t0 = tb + wave * TB;
-  if (tb >= T) return;
-  int n0 = (lin % slice_groups) * (SL * R_NB);
-  const int nq = d / 64, ntiles = (nq + QQT - 1) / QQT;
-  const int rows = min(TOKENS, T - tb);
-  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)(x + (size_t)tb * d), 0, (int)((size_t)rows * d * sizeof(XT)), 0x00020000);
-  auto router_columns = [&](int first) {   // the slice's 16 columns of w_gate as a buffer
-    const int cols = min(R_NB, N - first);
-    return __builtin_amdgcn_make_buffer_rsrc((void*)(wg + first), 0, (int)(((size_t)(d - 1) * N + cols) * 4), 0x00020000);
+  int block = (int)((unsigned)tile * job.slices_inverse >> 16), slice = tile - block * slices;
+  auto advance = [&](int& bl, int& sl) {
+    bl += block_step;
+    sl += slice_step;
+    if (sl >= slices) { sl -= slices; ++bl; }
   };
-  __amdgpu_buffer_rsrc_t rw = router_columns(n0);
-  const int wave_chunk = __builtin_amdgcn_readfirstlane((int)(threadIdx.x & ~63u));
-  unsigned xoff[XL], woff[WL];
-#pragma unroll
-  for (int i = 0; i < XL; ++i) {
-    const int q = i * 256 + threadIdx.x;
-    xoff[i] = q < XCH ? (unsigned)((q / XROW) * d * sizeof(XT) + (q % XROW) * 16) : 0x80000000u;
+  if (bias) {
+    float* sb = (float*)(lds + C::BIAS_AT / 16);
+    for (int n = threadIdx.x; n < N; n += C::THREADS) sb[n] = bias[n];
+    __syncthreads();
   }
-  // LDS position q holds column chunk (q & 3) ^ ((row >> 2) & 3) of row q >> 2: the 16 rows that one
-  // pass of a 16-byte read touches (64 bytes apart, 4 to every 256 bytes the banks span) then fall
-  // on 16 different bank groups
+
+  // the wavefront's token tile and c's: (h, p) and instruction row r has q = (r + b) % 4, or (h, p, q % 2) and q / 2 = (r + b) % 2
+  const int part = wave % C::WPT, tt = wave / C::WPT;
+  const int h = C::WPT == 4 ? part >> 1 : part >> 2, p = C::WPT == 4 ? part & 1 : (part >> 1) & 1;
+  auto q_of = [&](int r, int b) { return C::WPT == 4 ? (r + b) & 3 : (part & 1) + 2 * ((r + b) & 1); };
+
+  // requests: lane q of a pass fills chunk q of the stage
+  unsigned xoff[C::XL], woff[C::WL], wcol[C::WL];
 #pragma unroll
-  for (int i = 0; i < WL; ++i) {
-    const int q = i * 256 + threadIdx.x, row = q >> 2;
-    woff[i] = q < WCH ? (unsigned)((row * N + (((q & 3) ^ ((row >> 2) & 3)) << 2)) * 4) : 0x80000000u;
+  for (int i = 0; i < C::XL; ++i) {                       // block by block, token rows of 8 (16) chunks, swizzled by the 256-byte window
+    const int q = i * C::THREADS + (int)threadIdx.x, row = q / C::XROW, t = row % C::TOKENS, c = (q % C::XROW) ^ (C::XROW == 8 ? (t >> 1) & 7 : t & 15);
+    xoff[i] = (unsigned)((t * d + row / C::TOKENS * 64) * ES + c * 16);
   }
-  auto issue = [&](int tile) {
-    uint4* xs = xring + (tile % S) * (XL * 256);
-    uint4* ws = wring + (tile % S) * (WL * 256);
+#pragma unroll
+  for (int i = 0; i < C::WL; ++i) {                       // the four rows of an instruction lie side by side, in the order of their use
+    const int q = i * C::THREADS + (int)threadIdx.x, at = q / (4 * ET), b = at & 3, n = (at >> 2) & 15;
+    int c;
+    if (C::WPT == 4) c = 8 * (n >> 3) + 2 * (((n & 3) + b) & 3) + ((n >> 2) & 1);
+    else c = 8 * (n >> 3) + 2 * (((n >> 1) & 1) + 2 * (((n & 1) + b) & 1)) + ((n >> 2) & 1);
+    wcol[i] = (unsigned)(q % (4 * ET)) * 4;
+    woff[i] = (unsigned)((((at & ~63) + 16 * b + c) * N + (int)wcol[i]) * 4);
+  }
+  const int wave_chunk = wave * 64;
+  int ask_tile = tile, ask_block = block, ask_slice = slice, ask_stage = 0, ask_slot = 0;   // the next stage to request, and its place in the ring
+  // (the vector ALU and these matrix instructions do not run side by side, so what changes from stage to stage is kept in scalars)
+  // (A tile's stages are filled up in front: `pad` blocks of zeros, which leave the zeros that the sums start from.)
+  const int pad = stages * QQT - nq;
+  const XT* from_x = x;
+  const float* from_w = wg;
+  __amdgpu_buffer_rsrc_t rx, rw;
+  uint4* to = lds;
+  unsigned vx[C::XL], vw[C::WL];
+  constexpr unsigned DEAD = 0x80000000u;                  // an offset past the buffers' ends: arrives as zeros
+  auto aim = [&]() {                                      // at the next stage to request; past the workgroup's last one: at nothing
+    to = lds + ask_slot * (C::STAGE / 16) + wave_chunk;
+    if (++ask_slot == S) ask_slot = 0;
+    const int bytes = ask_tile < tiles ? (int)DEAD : 0;
+    if (ask_stage <= 1 && bytes) {
+      const int tb = (ask_block * 8 + xcd) * C::TOKENS, n0 = ask_slice * C::EXPERTS, skip = ask_stage == 0 ? pad : 0;
+      if (ask_stage == 0) {
+        from_x = x + (long)tb * d - 64 * pad;
+        from_w = wg + n0 - (long)64 * pad * N;
+      }
+#pragma unroll
+      for (int i = 0; i < C::XL; ++i) {
+        const int row = (i * C::THREADS + (int)threadIdx.x) / C::XROW;
+        vx[i] = tb + row % C::TOKENS < T && row / C::TOKENS >= skip ? xoff[i] : DEAD;
+      }
+#pragma unroll
+      for (int i = 0; i < C::WL; ++i)
+        vw[i] = n0 + (int)wcol[i] < N && (i * C::THREADS + (int)threadIdx.x) / (256 * ET) >= skip ? woff[i] : DEAD;
+    }
+    rx = __builtin_amdgcn_make_buffer_rsrc((void*)from_x, 0, bytes, 0x00020000);
+    rw = __builtin_amdgcn_make_buffer_rsrc((void*)from_w, 0, bytes, 0x00020000);
+    from_x += 64 * QQT;
+    from_w += (size_t)64 * QQT * N;
+    if (++ask_stage == stages) {
+      ask_stage = 0;
+      ask_tile += stride;
+      advance(ask_block, ask_slice);
+    }
+  };
+  auto request = [&](auto n) {                            // number n of a stage's LPT
 #if defined(__HIP_DEVICE_COMPILE__)
-#pragma unroll
-    for (int i = 0; i < XL; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(xs + i * 256 + wave_chunk), 16,
-                                               xoff[i] + (unsigned)(tile * TROWS * sizeof(XT)), 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < WL; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(ws + i * 256 + wave_chunk), 16,
-                                               woff[i] + (unsigned)(tile * TROWS * N * 4), 0, 0, 0);
+    constexpr int I = decltype(n)::value;
+    if constexpr (I < C::XL)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(to + I * C::THREADS), 16, vx[I], 0, 0, 0);
+    else
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(to + C::XCH + (I - C::XL) * C::THREADS), 16, vw[I - C::XL], 0, 0, 0);
 #else
-    (void)xs; (void)ws;
+    (void)n;
 #endif
   };
-  constexpr int ACCS = TB * R_NB;
-  float acc[ACCS];
-  // The tile reads are assembly: for LDS accesses it can see, the compiler waits for every
-  // direct-to-LDS load in flight, the next tiles' included, which would put the loads and the
-  // arithmetic one after the other instead of side by side.  The only waits on the loads are the
-  // counter waits of the loop below.
-  const unsigned xring_at = (unsigned)(size_t)(__attribute__((address_space(3))) const void*)xring + (unsigned)(((wave * TB) * TROWS + lane) * sizeof(XT));
-  const unsigned wring_at = (unsigned)(size_t)(__attribute__((address_space(3))) const void*)wring;
-  unsigned wlane[4];   // the swizzle term (row >> 2) & 3 is the same in every 64-row block
+
+  // Operands of a 64-row block: lane l holds token or router column l % 16 of residue run b = l / 16.  A bf16 element arrives in the
+  // upper half of a register whose lower half is zero for good: no conversion.
+  const int tok = lane & 15, b = lane >> 4;
+  unsigned xat[RR];
 #pragma unroll
-  for (int c4 = 0; c4 < 4; ++c4) wlane[c4] = wring_at + (unsigned)((lane * 4 + (c4 ^ ((lane >> 2) & 3))) * 16);
-  auto compute = [&](int tile) {
-    // one address register for the token rows, four for the router columns; everything else is
-    // instruction offsets
-    const unsigned stage = (unsigned)(tile % S);
-    const unsigned xat = xring_at + stage * (XL * 256 * 16);
-    unsigned wat[4];
+  for (int i = 0; i < RR; ++i) {
+    const int t = tt * 16 + tok;
+    const unsigned e = (unsigned)((16 * b + 8 * h + 2 * q_of(i, b) + p) * ES);   // byte within the block's 64 elements
+    xat[i] = lds_at + (unsigned)(t * C::XROW * 16) + (((e >> 4) ^ (unsigned)(C::XROW == 8 ? (t >> 1) & 7 : t & 15)) << 4) + (e & 15);
+  }
+  unsigned wat = lds_at + (unsigned)(C::XCH * 16 + part * RR * (256 * ET) + lane * 4 * ET);
+  // [register set].  Two values of w in one read: neighbouring columns 2 n, 2 n + 1 (ET = 2: column tile j holds the columns
+  // 2 n + j), or the two instruction rows
+  constexpr int WR = M / 2, READS = RR + WR;
+  unsigned xv[2][RR];
+  u32x2_t wv[2][WR];
 #pragma unroll
-    for (int c4 = 0; c4 < 4; ++c4) wat[c4] = wlane[c4] + stage * (WL * 256 * 16);
-    unsigned xraw[2][TB];
-    router_u32x4 wraw[2][4];
-    // the reads of 64-row block QQ of the tile, into register set QQ % 2
-    auto request = [&](auto block) {
-      constexpr int QQ = decltype(block)::value;
-      router_static_for<0, TB>([&](auto token) {
-        constexpr int I = decltype(token)::value;
-        if constexpr (sizeof(XT) == 2) router_lds_read_u16<(I * TROWS + QQ * 64) * 2>(xat, xraw[QQ & 1][I]);
-        else router_lds_read_b32<(I * TROWS + QQ * 64) * 4>(xat, xraw[QQ & 1][I]);
-      });
-      router_static_for<0, 4>([&](auto chunk) {
-        constexpr int C4 = decltype(chunk)::value;
-        router_lds_read_b128<QQ * 64 * 4 * 16>(wat[C4], wraw[QQ & 1][C4]);
-      });
-    };
-    request(RouterIndex<0>{});
-    router_static_for<0, QQT>([&](auto block) {
-      constexpr int QQ = decltype(block)::value;
-      if (tile * QQT + QQ >= nq) return;
-      // block QQ has arrived (it was requested before the previous block's arithmetic); the next
-      // block is requested now and arrives while this one's 128 multiply-adds run
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  for (int i = 0; i < 2 * RR; ++i) xv[i & 1][i >> 1] = 0u;
+  auto read = [&](auto block, auto set, auto n) {         // number n of a block's READS
+    constexpr int QQ = decltype(block)::value, R = decltype(set)::value, I = decltype(n)::value;
+    auto& xs = xv[R];
+    auto& ws = wv[R];
+    if constexpr (I < RR) {
+      constexpr int OFFSET = QQ * C::TOKENS * C::XROW * 16;
+      const unsigned a = xat[I];
+      if constexpr (ES == 4) lds_read_b32<OFFSET>(a, xs[I]);
+      else lds_read_high_u16<OFFSET>(a, xs[I]);
+    } else {
+      constexpr int J = I - RR;
+      if constexpr (ET == 2) lds_read_b64<QQ * 8192 + J * 512>(wat, ws[J]);
+      else lds_read_two_b32<QQ * 4096, QQ * 4096 + 256>(wat, ws[J]);
+    }
+  };
+  auto turn = [&](unsigned step) {                        // to the next stage of the ring
 #pragma unroll
-      for (int i = 0; i < TB; ++i) asm volatile("" : "+v"(xraw[QQ & 1][i]));
+    for (int i = 0; i < RR; ++i) xat[i] += step;
+    wat += step;
+  };
+  auto settle = [&](auto set) {
+    constexpr int R = decltype(set)::value;
+    auto& xs = xv[R];
+    auto& ws = wv[R];
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-      for (int c4 = 0; c4 < 4; ++c4) asm volatile("" : "+v"(wraw[QQ & 1][c4]));
-      if constexpr (QQ + 1 < QQT) request(RouterIndex<QQ + 1>{});   // (a block past d holds zeros or stale rows: never used)
-      float xv[TB], wv[R_NB];
+    for (int i = 0; i < RR; ++i) asm volatile("" : "+v"(xs[i]));
 #pragma unroll
-      for (int i = 0; i < TB; ++i) xv[i] = __uint_as_float(sizeof(XT) == 2 ? xraw[QQ & 1][i] << 16 : xraw[QQ & 1][i]);
+    for (int i = 0; i < WR; ++i) asm volatile("" : "+v"(ws[i]));
+  };
+  f32x16_t acc[C::M];                                     // [instruction row r, column tile j: r ET + j]
+  auto clear = [&]() {
 #pragma unroll
-      for (int c4 = 0; c4 < 4; ++c4) {
-        const router_u32x4 w = wraw[QQ & 1][c4];
-        wv[c4 * 4 + 0] = __uint_as_float(w.x); wv[c4 * 4 + 1] = __uint_as_float(w.y);
-        wv[c4 * 4 + 2] = __uint_as_float(w.z); wv[c4 * 4 + 3] = __uint_as_float(w.w);
-      }
+    for (int m = 0; m < C::M; ++m)
 #pragma unroll
-      for (int i = 0; i < TB; ++i)
-#pragma unroll
-        for (int c = 0; c < R_NB; ++c) acc[i * R_NB + c] = fmaf(xv[i], wv[c], acc[i * R_NB + c]);
+      for (int v = 0; v < 16; ++v) acc[m][v] = 0.0f;
+  };
+  // instructions FIRST .. LAST - 1 of the block in register set SET, each followed by some of the reads of the next block
+  auto multiply = [&](auto set, auto first, auto last, auto&& reads) {
+    constexpr int R = decltype(set)::value;
+    static_for<decltype(first)::value, decltype(last)::value>([&](auto n) {
+      constexpr int m = decltype(n)::value;
+      auto& xs = xv[R];
+      auto& ws = wv[R];
+      acc[m] = __builtin_amdgcn_mfma_f32_16x16x1f32(__uint_as_float(ws[m >> 1][m & 1]), __uint_as_float(xs[m / ET]), acc[m], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      reads(n);
+      __builtin_amdgcn_sched_barrier(0);
     });
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // a request past the last block used: done before the stage is refilled
   };
-  // The ring: tiles 0 .. S-2 are requested up front; at tile t a wavefront waits until only the
-  // tiles requested after t are in flight, the barrier makes that true for everyone's part of t
-  // and says that everyone has left tile t - 1, whose stage then takes tile t + S - 1.
-  auto start_ring = [&]() {
+  // the sums of a tile: lane l holds router columns 4 (l / 16) + v, v = 0 .. 3, of token l % 16
+  auto finish = [&]() {
+    const int t0 = (block * 8 + xcd) * C::TOKENS, n0 = slice * C::EXPERTS;
+    if constexpr (C::WPT == 4) {
+      float sum[4][2][4];                                 // [q][column tile][v]: distances 32 and 16
 #pragma unroll
-    for (int a = 0; a < S - 1; ++a)
-      if (a < ntiles) issue(a);
-  };
-  start_ring();
-#pragma unroll 1
-  for (int sl = 0; sl < SL; ++sl) {
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
-  for (int v = 0; v < ACCS; ++v) acc[v] = 0.0f;
-  for (int tile = 0; tile < ntiles; ++tile) {
-    const int younger = min(S - 2, ntiles - 1 - tile);
-    if (younger >= 2) BIGMAC_ROUTER_WAIT_VMCNT(2 * LPT);
-    else if (younger == 1) BIGMAC_ROUTER_WAIT_VMCNT(LPT);
-    else BIGMAC_ROUTER_WAIT_VMCNT(0);
-    __builtin_amdgcn_s_barrier();
-    if (tile + S - 1 < ntiles) issue(tile + S - 1);
-    compute(tile);
-  }
-  // once every wavefront has left the last tile, the next slice's first tiles can be on their way
-  // while this slice is reduced and stored
-  const int n_cur = n0;
-  const bool more = sl + 1 < SL && n0 + R_NB < N;
-  if (more) {
-    __builtin_amdgcn_s_barrier();
-    n0 += R_NB;
-    rw = router_columns(n0);
-    start_ring();
-  }
-  // Halving tree (lane l with lane l ^ off, off = 32 .. 1).  While a lane still holds two or more
-  // sums the step is a reduce-scatter: each half of the pair keeps one half of the sums (see
-  // router_logits_kernel); once a lane is down to one sum, both lanes of a pair add the other's
-  // (the same addition, a + b, in both).  The sum of accumulator v ends on the lanes whose top
-  // bits spell v.
-  constexpr int SCATTER_STEPS = ACCS >= 64 ? 6 : (ACCS == 32 ? 5 : 4);
-  static_assert(ACCS == 128 || ACCS == 64 || ACCS == 32 || ACCS == 16, "1, 2, 4 or 8 tokens per wavefront");
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-  for (int step = 0; step < 6; ++step) {
-    const int off = 32 >> step;
-    if (step < SCATTER_STEPS && off >= 16) {
-      // distances 32 and 16: one swap instruction exchanges the upper half (odd 16-lane rows) of
-      // acc[v] with the lower half (even rows) of acc[v + half]; afterwards every lane holds what
-      // it keeps in one register and what its partner sent in the other, and a + b = b + a
-      const int half = ACCS >> (step + 1);
+          for (int v = 0; v < 4; ++v) {
+            auto of = [&](int bb) { return acc[((q - bb) & 3) * 2 + j][4 * bb + v]; };
+            sum[q][j][v] = (of(0) + of(2)) + (of(1) + of(3));
+          }
+      // distance 8: the two wavefronts of a p keep two of the four v each
+      const unsigned to8 = lds_at + (unsigned)(C::SUMS_AT + wave * 4096 + lane * 8), from8 = lds_at + (unsigned)(C::SUMS_AT + (wave ^ 2) * 4096 + lane * 8);
+      static_for<0, 8>([&](auto i) {
+        constexpr int q = decltype(i)::value >> 1, j = decltype(i)::value & 1;
+        u32x2_t v;
+        v.x = __float_as_uint(h ? sum[q][j][0] : sum[q][j][2]);
+        v.y = __float_as_uint(h ? sum[q][j][1] : sum[q][j][3]);
+        lds_write_b64<decltype(i)::value * 512>(to8, v);
+      });
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      u32x2_t theirs[8];
+      static_for<0, 8>([&](auto i) {
+        auto& v = theirs[decltype(i)::value];
+        lds_read_b64<decltype(i)::value * 512>(from8, v);
+      });
+      lds_wait(theirs);
+      float even[2][2];                                   // [column tile][v]: distances 4 and 2
 #pragma unroll
-      for (int v = 0; v < half; ++v) {
-        const unsigned a = __float_as_uint(acc[v]), b = __float_as_uint(acc[v + half]);
-        if (off == 32) {
-          const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-          acc[v] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-        } else {
-          const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-          acc[v] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+          float c[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) c[q] = (h ? sum[q][j][2 + v] : sum[q][j][v]) + __uint_as_float(theirs[q * 2 + j][v]);
+          even[j][v] = (c[0] + c[2]) + (c[1] + c[3]);
         }
-      }
-    } else if (step < SCATTER_STEPS) {
-      const int half = ACCS >> (step + 1);
-      const bool hi = (lane & off) != 0;
-#pragma unroll
-      for (int v = 0; v < half; ++v) {
-        const float send = hi ? acc[v] : acc[v + half];
-        const float keep = hi ? acc[v + half] : acc[v];
-        acc[v] = keep + __shfl_xor(send, off, 64);
+      // distance 1: the two wavefronts of an h keep one v each
+      const unsigned to1 = lds_at + (unsigned)(C::SUMS_AT + 32768 + wave * 512 + lane * 8), from1 = lds_at + (unsigned)(C::SUMS_AT + 32768 + (wave ^ 1) * 512 + lane * 8);
+      u32x2_t send, got[1];
+      send.x = __float_as_uint(p ? even[0][0] : even[0][1]);
+      send.y = __float_as_uint(p ? even[1][0] : even[1][1]);
+      lds_write_b64<0>(to1, send);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      lds_read_b64<0>(from1, got[0]);
+      lds_wait(got);
+      const int t = t0 + tt * 16 + tok, n = n0 + (b * 4 + h * 2 + p) * 2;
+      float out[2] = {(p ? even[0][1] : even[0][0]) + __uint_as_float(got[0].x), (p ? even[1][1] : even[1][0]) + __uint_as_float(got[0].y)};
+      if (t < T && n < N) {
+        if (bias) {
+          u32x2_t add[1];
+          lds_read_b64<0>(lds_at + (unsigned)(C::BIAS_AT + n * 4), add[0]);
+          lds_wait(add);
+          out[0] = out[0] + __uint_as_float(add[0].x);
+          out[1] = out[1] + __uint_as_float(add[0].y);
+        }
+        *(float2*)(logits + (size_t)t * N + n) = make_float2(out[0], out[1]);
       }
     } else {
-      acc[0] = acc[0] + __shfl_xor(acc[0], off, 64);
-    }
-  }
-  constexpr int LEFT = ACCS >> SCATTER_STEPS;          // sums per lane at the end: 2 (ACCS = 128) or 1
-  constexpr int SHARE = 6 - SCATTER_STEPS;             // low lane bits that hold copies of the same sum
-  if ((lane & ((1 << SHARE) - 1)) == 0) {
+      // residue by residue through the LDS, 16 bytes per lane; lanes of column group g at token ^ 4 g, which spreads the reads below over the banks
+      const unsigned to = lds_at + (unsigned)C::SUMS_AT + (unsigned)((lane ^ (b << 2)) << 4);
 #pragma unroll
-    for (int u = 0; u < LEFT; ++u) {
-      const int v = LEFT * (lane >> SHARE) + u;
-      const int t = t0 + v / R_NB, n = n_cur + v % R_NB;
-      if (t < T && n < N) {
-        float val = acc[u];
-        if (bias) val = val + bias[n];
-        logits[(size_t)t * N + n] = val;
+      for (int i = 0; i < 2; ++i)                         // the wavefront's two q
+#pragma unroll
+        for (int j = 0; j < ET; ++j) {
+          u32x4_t sum;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            auto of = [&](int bb) { return acc[((i + bb) & 1) * ET + j][4 * bb + v]; };
+            sum[v] = __float_as_uint((of(0) + of(2)) + (of(1) + of(3)));
+          }
+          lds_write_b128(to + (unsigned)(((8 * h + 2 * ((part & 1) + 2 * i) + p) * ET + j) * 1024), sum);
+        }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      if ((int)threadIdx.x < 256 * ET) {
+        const int j = (int)threadIdx.x % ET, row = ((int)threadIdx.x / ET) & 15, token = (int)threadIdx.x / (16 * ET);
+        const unsigned from = lds_at + (unsigned)(C::SUMS_AT + j * 1024 + ((((row >> 2) << 4) + (token ^ (row & 12))) << 4) + (row & 3) * 4);
+        const int t = t0 + token, n = n0 + row * ET + j;
+        unsigned bits[16];
+        static_for<0, 16>([&](auto c) {
+          auto& v = bits[decltype(c)::value];
+          lds_read_b32<decltype(c)::value * ET * 1024>(from, v);
+        });
+        lds_wait(bits);
+        float sum[16];
+#pragma unroll
+        for (int c = 0; c < 16; ++c) sum[c] = __uint_as_float(bits[c]);
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1)
+#pragma unroll
+          for (int c = 0; c < off; ++c) sum[c] = sum[c] + sum[c + off];
+        if (t < T && n < N) {
+          if (bias) {
+            unsigned add[1];
+            lds_read_b32<0>(lds_at + (unsigned)(C::BIAS_AT + n * 4), add[0]);
+            lds_wait(add);
+            sum[0] = sum[0] + __uint_as_float(add[0]);
+          }
+          logits[(size_t)t * N + n] = sum[0];
+        }
       }
     }
+  };
+
+  int todo = stages;                                      // of the tile at hand
+  int asked = 0;
+#pragma clang loop unroll(disable)
+  for (; asked < S && ask_tile < tiles; ++asked) {
+    aim();
+    static_for<0, C::LPT>([&](auto n) { request(n); });
   }
-  if (!more) break;
+  if (asked == S) BIGMAC_WAIT_VMCNT((S - 1) * C::LPT);     // the first stage
+  else BIGMAC_WAIT_VMCNT(0);                               // all of the workgroup's; the waits of the loop then wait for nothing
+  __builtin_amdgcn_s_barrier();
+  int slot = 0;                                           // the stage at hand
+  static_for<0, READS>([&](auto n) { read(StaticIndex<0>{}, StaticIndex<0>{}, n); });
+  settle(StaticIndex<0>{});
+  clear();
+  constexpr StaticIndex<0> I0{};
+  constexpr StaticIndex<1> I1{};
+  constexpr int EARLY = M / 4, SPREAD = M > 2 ? M - 1 : M;   // instructions of the last block before the barrier; of a block, with reads behind them
+  constexpr StaticIndex<EARLY> IE{};
+  constexpr StaticIndex<M> END{};
+  while (true) {
+    // A stage, block by block, each block's operands read between the instructions of the one before it.  Between those of the last
+    // block the next stage is awaited, and this one, which everyone has read by then, requested anew.  No branch lies between a read
+    // and the wait for it: the compiler may copy a register at a branch, and would copy what is still on its way.
+    static_for<0, QQT - 1>([&](auto block) {
+      constexpr int QQ = decltype(block)::value, R = QQ & 1;
+      multiply(StaticIndex<R>{}, I0, END, [&](auto n) {
+        constexpr int K = decltype(n)::value, N0 = K < SPREAD ? K * READS / SPREAD : READS, N1 = K < SPREAD ? (K + 1) * READS / SPREAD : READS;
+        static_for<N0, N1>([&](auto i) { read(StaticIndex<QQ + 1>{}, StaticIndex<R ^ 1>{}, i); });
+      });
+      settle(StaticIndex<R ^ 1>{});
+    });
+    if constexpr (EARLY == 0) aim();
+    multiply(I1, I0, IE, [&](auto n) { if constexpr (decltype(n)::value == 0) aim(); });
+    BIGMAC_WAIT_VMCNT((S - 2) * C::LPT);                   // (logits on their way out count too: a longer wait, once a tile)
+    __builtin_amdgcn_s_barrier();
+    if (++slot == S) slot = 0;
+    turn(slot ? (unsigned)C::STAGE : (unsigned)-(S - 1) * C::STAGE);
+    multiply(I1, IE, END, [&](auto n) {                    // (past the workgroup's last stage the reads are stale, and never used)
+      constexpr int K = decltype(n)::value - EARLY, G = SPREAD - EARLY, N0 = K < G ? K * READS / G : READS, N1 = K < G ? (K + 1) * READS / G : READS;
+      static_for<N0, N1>([&](auto i) { read(I0, I0, i); });
+      constexpr int ALL = M - EARLY, L0 = K * C::LPT / ALL, L1 = (K + 1) * C::LPT / ALL;
+      static_for<L0, L1>([&](auto i) { request(i); });
+    });
+    settle(I0);
+    if (--todo == 0) {
+      finish();
+      tile += stride;
+      if (tile >= tiles) break;
+      advance(block, slice);
+      todo = stages;
+      clear();
+    }
   }
+  BIGMAC_WAIT_VMCNT(0);                                    // the requests of nothing write the LDS too
 }
 
 // (logit, expert) as one number: the greater key comes first, equal logits (-0 counts as 0) by lower index.  NaN logits
@@ -796,46 +938,56 @@ __global__ __launch_bounds__(ROUTER_DX_THREADS) void router_dx_kernel(const int3
 }  // namespace
 
 int launch_router_logits(const bigmac_dims& D, const void* x, const float* w_gate, const float* bias, float* logits, hipStream_t s) {
-  const bool pipelined = D.N % 4 == 0 && (size_t)D.d * D.N * 4 < (1ull << 31);   // 16-byte router rows, 32-bit buffer range
-  const dim3 block(256);
-  const unsigned gy = (unsigned)((D.N + R_NB - 1) / R_NB);
-  if (!pipelined) {
+  const bool whole_chunks = D.N % 4 == 0 && (size_t)D.d * D.N * 4 < (1ull << 30);   // 16-byte pieces of a router row; 32-bit offsets within a stage
+  if (!whole_chunks) {
+    const dim3 block(256);
+    const unsigned gy = (unsigned)((D.N + R_NB - 1) / R_NB);
     const dim3 grid((D.T + 31) / 32, gy);
     if (D.dtype == BIGMAC_BF16) hipLaunchKernelGGL(router_logits_kernel<bf16_t>, grid, block, 0, s, (const bf16_t*)x, w_gate, bias, logits, D.T, D.d, D.N);
     else hipLaunchKernelGGL(router_logits_kernel<float>, grid, block, 0, s, (const float*)x, w_gate, bias, logits, D.T, D.d, D.N);
     BIGMAC_CHECK_LAUNCH();
     return BIGMAC_OK;
   }
-  // Tokens per wavefront: a wavefront's LDS reads of the router columns are spread over them and every workgroup reads its
-  // columns from the L2 once, so more is cheaper until CUs go idle: the fewest that need at most three workgroups per CU.  Eight
-  // where four would need more, except between two and four workgroups of eight per CU, where the last round of them is nearly
-  // empty.  Measured with the top-k at d 4096, N 64 (1 / 2 / 4 / 8 tokens, us): T 500 17.5 / 19.2 / 22.7 / 31.7, T 1024
-  // 26.5 / 19.4 / 22.9 / 31.6, T 2048 44.2 / 32.3 / 25.0 / 32.1, T 3001 62.0 / 41.6 / 33.1 / 35.3, T 4096 81.3 / 54.5 / 41.6 /
-  // 37.5, T 6001 117.5 / 75.9 / 57.6 / 61.4, T 8192 156 / 99.5 / 75.7 / 73.2.  Two expert slices per
-  // workgroup while that still gives every CU two workgroups.
-  auto workgroups = [&](int tokens) { return (long)((D.T + 4 * tokens - 1) / (4 * tokens)) * gy; };
-  const long groups8 = workgroups(8);
-  int tb = 1;
-  while (tb < 8 && workgroups(tb) > 768) tb *= 2;
-  if (tb == 8 && groups8 > 512 && groups8 < 1024) tb = 4;
-  const int sl = tb == 8 && gy >= 2 && (long)((D.T + 31) / 32) * ((gy + 1) / 2) >= 512 ? ROUTER_SLICES : 1;
-#define BIGMAC_ROUTER(XT, TBV, SLV)                                                                                  \
-  hipLaunchKernelGGL((router_logits_pipelined_kernel<XT, TBV, SLV>),                                                  \
-                     dim3((((D.T + 4 * TBV - 1) / (4 * TBV) + 7) / 8) * 8 * ((gy + SLV - 1) / SLV)), block, 0, s,     \
-                     (const XT*)x, w_gate, bias, logits, D.T, D.d, D.N)
-  if (D.dtype == BIGMAC_BF16) {
-    if (tb == 8 && sl == 2) BIGMAC_ROUTER(bf16_t, 8, 2);
-    else if (tb == 8) BIGMAC_ROUTER(bf16_t, 8, 1);
-    else if (tb == 4) BIGMAC_ROUTER(bf16_t, 4, 1);
-    else if (tb == 2) BIGMAC_ROUTER(bf16_t, 2, 1);
-    else BIGMAC_ROUTER(bf16_t, 1, 1);
-  } else {
-    if (tb == 8 && sl == 2) BIGMAC_ROUTER(float, 8, 2);
-    else if (tb == 8) BIGMAC_ROUTER(float, 8, 1);
-    else if (tb == 4) BIGMAC_ROUTER(float, 4, 1);
-    else if (tb == 2) BIGMAC_ROUTER(float, 2, 1);
-    else BIGMAC_ROUTER(float, 1, 1);
+  // Tile of a workgroup: 32 x 32 logits keep the multipliers busiest, smaller ones give more workgroups.  A tile takes a time per 64 rows
+  // of d and one of its own (start, reduction), and a CU, which holds one workgroup, its share of the tiles one after the other.
+  // Measured, us with the top-k, 32 x 32 / 16 x 32 / 16 x 16: d 4096, N 64: T 32 25.2 / 17.8 / 12.9, T 2048 25.5 / 19.5 / 21.8,
+  // T 8192 48.3 / 56.9 / 65.0; d 1024, N 64: T 3001 12.7 / 14.9 / 14.3, T 8192 20.7 / 24.8 / 27.7; T 32768, d 4096, N 128 355 / 415 / 542;
+  // T 30000, d 1280, N 8 45.1 / 52.9 / 36.6.  The kernel of fused multiply-adds on the vector ALU that this one took the place of: 16.1,
+  // 25.5, 67.0; 13.5, 26.3; 504; 37.3 (and 3.4 us where this one takes 4.2 at the smallest fp32 sizes: T 256, d 256, N 8).
+  auto tile_rounds = [&](int tokens, int experts) {   // tiles of an XCD over its 32 CUs
+    const long groups = (((long)D.T + tokens - 1) / tokens + 7) / 8 * ((D.N + experts - 1) / experts);
+    return (double)((groups + 31) / 32);
+  };
+  const double nq = D.d / 64;
+  const double us22 = tile_rounds(32, 32) * (0.27 * nq + 2.0), us12 = tile_rounds(16, 32) * (0.155 * nq + 1.7), us11 = tile_rounds(16, 16) * (0.077 * nq + 1.2);
+  auto job_of = [&](int tokens, int experts, int blocks_per_stage) {
+    RouterJob j = {};
+    j.x = x; j.wg = w_gate; j.bias = bias; j.logits = logits;
+    j.T = D.T; j.d = D.d; j.N = D.N;
+    j.slices = (D.N + experts - 1) / experts;
+    j.blocks = (int)(((long)D.T + tokens - 1) / tokens);
+    j.stages = (D.d / 64 + blocks_per_stage - 1) / blocks_per_stage;
+    const long groups = ((long)j.blocks + 7) / 8 * j.slices, bytes = (long)D.d * D.N * 4;
+    // (from 128 KB, a third of a microsecond of a CU's stream, up to half an XCD's L2)
+    if (groups <= 24 && bytes >= 131072 && bytes <= 2097152) j.warm_lines = (int)(bytes / 128);
+    j.stride = (int)(j.warm_lines ? 32 : std::min(groups, 32l));
+    j.block_step = j.stride / j.slices;
+    j.slice_step = j.stride % j.slices;
+    j.slices_inverse = (65536u + j.slices - 1) / j.slices;
+    return j;
+  };
+#define BIGMAC_ROUTER(XT, TT, ET, QQT)                                                                                                  \
+  {                                                                                                                                   \
+    const RouterJob job = job_of(16 * TT, 16 * ET, QQT);                                                                              \
+    hipLaunchKernelGGL((router_logits_matrix_kernel<XT, TT, ET, QQT>), dim3((unsigned)(8 * job.stride)), dim3(512), 0, s, job);       \
   }
+#define BIGMAC_ROUTER_TILES(XT, MIDDLE)                               \
+  if (us22 <= us12 && us22 <= us11) BIGMAC_ROUTER(XT, 2, 2, 2)        \
+  else if (us12 <= us11) BIGMAC_ROUTER(XT, 1, 2, MIDDLE)              \
+  else BIGMAC_ROUTER(XT, 1, 1, 4)
+  if (D.dtype == BIGMAC_BF16) { BIGMAC_ROUTER_TILES(bf16_t, 4) }
+  else { BIGMAC_ROUTER_TILES(float, 2) }
+#undef BIGMAC_ROUTER_TILES
 #undef BIGMAC_ROUTER
   BIGMAC_CHECK_LAUNCH();
   return BIGMAC_OK;

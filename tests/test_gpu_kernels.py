@@ -283,6 +283,32 @@ def test_router_logits_tokens_per_wavefront(oracle, T, N, dtype):
     assert (idx[:, 0].cpu().long() == ref.argmax(dim=1)).all()
 
 
+# router logits on the matrix cores, bit for bit: each tile (32 x 32: many tokens; 16 x 32; 16 x 16: few), ragged tokens and columns, one
+# to five 64-row blocks of d (stages filled up with none to three of zeros), several tiles per workgroup; subnormal products (of
+# either sign, alone in some rows) and a row of infinities and NaN, which leaves its neighbours alone
+@pytest.mark.parametrize("dtype", [B.BF16, B.F32])
+@pytest.mark.parametrize("T,d,N", [(1, 64, 4), (17, 128, 20), (33, 192, 36), (47, 256, 64), (2040, 320, 64), (5001, 64, 60), (9000, 64, 64), (9001, 192, 68),
+                                   (20011, 128, 16), (70, 576, 1024)])
+def test_router_logits_on_the_matrix_cores(oracle, T, d, N, dtype):
+    g = torch.Generator(device=DEV).manual_seed(T + N)
+    x = torch.randn((T, d), generator=g, device=DEV)
+    x[T // 2] *= 1e-30
+    x = x.to(torch.bfloat16 if dtype == B.BF16 else torch.float32)
+    w_gate = torch.randn((d, N), generator=g, device=DEV)
+    w_gate[:, N // 2] *= 1e-12
+    dims = B.make_dims(T, d, 64, N, 1, 64, dtype)
+    idx, w, logits = torch.empty((T, 1), dtype=torch.int32, device=DEV), torch.empty((T, 1), device=DEV), torch.empty((T, N), device=DEV)
+    for bias in (None, torch.randn(N, generator=g, device=DEV)):
+        B.bigmac_route(dims, x, w_gate, bias, idx, w, logits)
+        ref = torch.from_numpy(oracle.router_logits(x.float().cpu().numpy(), w_gate.cpu().numpy(), None if bias is None else bias.cpu().numpy()))
+        assert torch.equal(logits.cpu().view(torch.int32), ref.view(torch.int32))
+    odd = T // 3
+    x[odd, 0::2], x[odd, 1::4] = float("inf"), float("nan")
+    B.bigmac_route(dims, x, w_gate, bias, idx, w, logits)
+    rest = torch.arange(T) != odd
+    assert torch.equal(logits.cpu()[rest].view(torch.int32), ref[rest].view(torch.int32)) and logits[odd].isnan().all()
+
+
 # the summed slices of a dense product, to bf16 as to fp32 (the same sums in the same order): 2, 5 and 10 slices, few elements
 @pytest.mark.parametrize("T,d,r", [(1, 64, 256), (3, 2560, 640), (33, 1280, 1280), (5, 192, 2048)])
 def test_slice_sums_to_bf16(T, d, r):
