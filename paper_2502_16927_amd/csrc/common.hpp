@@ -216,8 +216,10 @@ int launch_reduce_partials_multi(const ReduceJob* jobs, int count, int beta, hip
 int launch_reduce_partials_bf16(const float* part, int nslices, size_t n, void* out, hipStream_t s);
 
 // ----------------------------------------------------------------------------- route ----
+// topk_idx, topk_w (optional, where router_picks holds): the top-k and gate in the same launch
+bool router_picks(const bigmac_dims& D);
 int launch_router_logits(const bigmac_dims& D, const void* x, const float* w_gate, const float* bias,
-                         float* logits, hipStream_t s);
+                         float* logits, hipStream_t s, int32_t* topk_idx = nullptr, float* topk_w = nullptr);
 // counts (optional, where topk_counts holds): the pairs per part of a chunk and expert, for launch_build_permutation
 struct TopkGrid {
   int workgroups, threads, tokens;   // tokens per workgroup

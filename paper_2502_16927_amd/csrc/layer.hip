@@ -641,8 +641,9 @@ int bigmac_route(const bigmac_dims* D, const void* x, const float* w_gate, const
     if (ws_bytes < bigmac_workspace_bytes(D, BIGMAC_WS_ROUTE)) return BIGMAC_ERR_WORKSPACE;
     logits = (float*)ws;
   }
-  rc = launch_router_logits(*D, x, w_gate, gate_bias, logits, (hipStream_t)stream);
-  if (rc) return rc;
+  const bool picks = router_picks(*D);
+  rc = launch_router_logits(*D, x, w_gate, gate_bias, logits, (hipStream_t)stream, picks ? topk_idx : nullptr, picks ? topk_w : nullptr);
+  if (rc || picks) return rc;
   return launch_topk_gate(*D, logits, topk_idx, topk_w, (hipStream_t)stream);
 }
 
@@ -723,14 +724,15 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
   void* x_low_buf = (low_router && saved) ? (void*)(sv + S.x_low) : (void*)(wsb + F.x_low);
   auto route = [&](const void* router_in) -> int {
     const bigmac_dims R = router_dims(*D);
+    const bool picks = !chunk_counts && router_picks(R);   // all experts in one tile of the logits, and no pairs to count
     int rr;
     {
       BIGMAC_STAGE(BIGMAC_STAGE_ROUTER_LOGITS);
-      rr = launch_router_logits(R, router_in, P->w_gate, P->gate_bias, logits, s);
+      rr = launch_router_logits(R, router_in, P->w_gate, P->gate_bias, logits, s, picks ? topk_idx : nullptr, picks ? topk_w : nullptr);
     }
     if (rr) return rr;
     BIGMAC_STAGE(BIGMAC_STAGE_TOPK_GATE);
-    rr = launch_topk_gate(*D, logits, topk_idx, topk_w, s, chunk_counts);
+    if (!picks) rr = launch_topk_gate(*D, logits, topk_idx, topk_w, s, chunk_counts);
     if (!rr && aux)
       rr = launch_aux_loss(*D, logits, topk_idx, (float*)(sv + S.aux + 256), (float*)(sv + S.aux), nullptr, wsb + F.aux, s, chunk_counts);
     return rr;

@@ -108,6 +108,41 @@ __global__ __launch_bounds__(256) void router_logits_kernel(const XT* __restrict
   }
 }
 
+// (logit, expert) as one number: the greater key comes first, equal logits (-0 counts as 0) by lower index.  NaN logits
+// have a place in that order too (by their sign, past the infinities), and a lane past the N experts comes after every
+// expert, so that whatever the logits are the k <= N picks are k different experts: the sort writes to slots counted by them.
+__device__ __forceinline__ unsigned long long logit_key(float logit, int expert) {
+  const unsigned u = __float_as_uint(logit + 0.0f);
+  return ((unsigned long long)((u & 0x80000000u) ? ~u : u | 0x80000000u) << 32) | (unsigned)~expert;
+}
+__device__ __forceinline__ unsigned long long pick_key(const float* row, int expert, int N) {
+  return expert >= N ? (unsigned)~expert : logit_key(row[expert], expert);
+}
+__device__ __forceinline__ float key_logit(unsigned long long key) {
+  const unsigned u = (unsigned)(key >> 32);
+  return __uint_as_float((u & 0x80000000u) ? u & 0x7FFFFFFFu : ~u);
+}
+// One compare-exchange step of a bitonic network over the wavefront, for U independent networks: partner lane
+// ^ J, the greater key of the pair goes to the lane for which greater_here holds.
+template <int J, int U>
+__device__ __forceinline__ void exchange_keys(unsigned long long (&key)[U], int lane, bool greater_here) {
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const unsigned long long other = ((unsigned long long)from_lane_xor<J>((unsigned)(key[u] >> 32), lane) << 32) | from_lane_xor<J>((unsigned)key[u], lane);
+    if ((key[u] > other) != greater_here) key[u] = other;
+  }
+}
+template <int SIZE, int J, int U>
+__device__ __forceinline__ void merge_keys(unsigned long long (&key)[U], int lane) {
+  exchange_keys<J>(key, lane, ((lane & J) == 0) == ((lane & SIZE) == 0));   // lower lane of a descending block
+  if constexpr (J > 1) merge_keys<SIZE, J / 2>(key, lane);
+}
+template <int SIZE, int U>
+__device__ __forceinline__ void sort_keys(unsigned long long (&key)[U], int lane) {   // lane 0 ends with the greatest
+  if constexpr (SIZE > 2) sort_keys<SIZE / 2>(key, lane);
+  merge_keys<SIZE, SIZE / 2>(key, lane);
+}
+
 // The same sums on the matrix cores, for N % 4 == 0.  v_mfma_f32_16x16x1_4b_f32 has a contraction of one: every output
 // element takes part in exactly one fused multiply-add per instruction (bit for bit that of fmaf, subnormals, infinities
 // and NaN included), so 64 accumulators per logit, each fed in ascending q, are the partial sums p_l in their order.
@@ -166,8 +201,13 @@ struct RouterJob {
   int stride, block_step, slice_step;    // tiles of an XCD from one of a workgroup to its next, in blocks and slices
   unsigned slices_inverse;               // ceil(65536 / slices): i / slices of the first tiles (i < 32) by multiplication
   int warm_lines;                        // 128-byte lines of w_gate that workgroups without a tile read (0: none)
+  int32_t* topk_idx;                     // PICK: the picks and their weights
+  float* topk_w;
+  int k;
 };
-template <typename XT, int TT, int ET, int QQT>
+// PICK (one 16-wide tile holds all experts): the tile's top-k and gate behind its logits, as topk_gate_kernel works them out, in 16 lanes
+// per token.
+template <typename XT, int TT, int ET, int QQT, bool PICK = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void router_logits_matrix_kernel(RouterJob job) {
   const XT* const x = (const XT*)job.x;
@@ -176,6 +216,7 @@ void router_logits_matrix_kernel(RouterJob job) {
   const int T = job.T, d = job.d, N = job.N;
   typedef RouterTile<XT, TT, ET, QQT> C;
   constexpr int S = C::S, ES = (int)sizeof(XT), RR = C::RR, M = C::M;
+  static_assert(!PICK || (TT == 1 && ET == 1), "all experts of a token in one tile");
   __shared__ __attribute__((aligned(128))) uint4 lds[C::LDS / 16];
   const unsigned lds_at = lds_address(lds);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -454,6 +495,26 @@ void router_logits_matrix_kernel(RouterJob job) {
           }
           logits[(size_t)t * N + n] = sum[0];
         }
+        if constexpr (PICK) asm volatile("ds_write_b32 %0, %1" ::"v"(lds_at + (unsigned)(C::BIAS_AT + 1024 + threadIdx.x * 4)), "v"(sum[0]) : "memory");
+      }
+      if constexpr (PICK) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        if (wave < 4) {                                   // lane l: expert l % 16 of token 4 wave + l / 16
+          const int expert = lane & 15, t = t0 + wave * 4 + (lane >> 4), first = lane & 48;
+          unsigned own[1];
+          lds_read_b32<0>(lds_at + (unsigned)(C::BIAS_AT + 1024 + wave * 256 + lane * 4), own[0]);
+          lds_wait(own);
+          unsigned long long key[1] = {expert < N ? logit_key(__uint_as_float(own[0]), expert) : (unsigned)~expert};
+          sort_keys<16>(key, expert);
+          const float logit = key_logit(key[0]), m = __shfl(logit, first, 64), e = expert < job.k ? expf(logit - m) : 0.0f;
+          float all = 0.0f;
+          for (int j = 0; j < job.k; ++j) all += __shfl(e, first + j, 64);
+          if (expert < job.k && t < T) {
+            job.topk_idx[(size_t)t * job.k + expert] = (int)~(unsigned)key[0];
+            job.topk_w[(size_t)t * job.k + expert] = e / all;
+          }
+        }
       }
     }
   };
@@ -512,39 +573,6 @@ void router_logits_matrix_kernel(RouterJob job) {
     }
   }
   BIGMAC_WAIT_VMCNT(0);                                    // the requests of nothing write the LDS too
-}
-
-// (logit, expert) as one number: the greater key comes first, equal logits (-0 counts as 0) by lower index.  NaN logits
-// have a place in that order too (by their sign, past the infinities), and a lane past the N experts comes after every
-// expert, so that whatever the logits are the k <= N picks are k different experts: the sort writes to slots counted by them.
-__device__ __forceinline__ unsigned long long pick_key(const float* row, int expert, int N) {
-  if (expert >= N) return (unsigned)~expert;
-  const unsigned u = __float_as_uint(row[expert] + 0.0f);
-  return ((unsigned long long)((u & 0x80000000u) ? ~u : u | 0x80000000u) << 32) | (unsigned)~expert;
-}
-__device__ __forceinline__ float key_logit(unsigned long long key) {
-  const unsigned u = (unsigned)(key >> 32);
-  return __uint_as_float((u & 0x80000000u) ? u & 0x7FFFFFFFu : ~u);
-}
-// One compare-exchange step of a bitonic network over the wavefront, for U independent networks: partner lane
-// ^ J, the greater key of the pair goes to the lane for which greater_here holds.
-template <int J, int U>
-__device__ __forceinline__ void exchange_keys(unsigned long long (&key)[U], int lane, bool greater_here) {
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const unsigned long long other = ((unsigned long long)from_lane_xor<J>((unsigned)(key[u] >> 32), lane) << 32) | from_lane_xor<J>((unsigned)key[u], lane);
-    if ((key[u] > other) != greater_here) key[u] = other;
-  }
-}
-template <int SIZE, int J, int U>
-__device__ __forceinline__ void merge_keys(unsigned long long (&key)[U], int lane) {
-  exchange_keys<J>(key, lane, ((lane & J) == 0) == ((lane & SIZE) == 0));   // lower lane of a descending block
-  if constexpr (J > 1) merge_keys<SIZE, J / 2>(key, lane);
-}
-template <int SIZE, int U>
-__device__ __forceinline__ void sort_keys(unsigned long long (&key)[U], int lane) {   // lane 0 ends with the greatest
-  if constexpr (SIZE > 2) sort_keys<SIZE / 2>(key, lane);
-  merge_keys<SIZE, SIZE / 2>(key, lane);
 }
 
 // The k picks of each token in pick order (greater logit first, ties to the lower index) and the softmax over
@@ -937,9 +965,13 @@ __global__ __launch_bounds__(ROUTER_DX_THREADS) void router_dx_kernel(const int3
 
 }  // namespace
 
-int launch_router_logits(const bigmac_dims& D, const void* x, const float* w_gate, const float* bias, float* logits, hipStream_t s) {
-  const bool whole_chunks = D.N % 4 == 0 && (size_t)D.d * D.N * 4 < (1ull << 30);   // 16-byte pieces of a router row; 32-bit offsets within a stage
-  if (!whole_chunks) {
+static bool router_whole_chunks(const bigmac_dims& D) { return D.N % 4 == 0 && (size_t)D.d * D.N * 4 < (1ull << 30); }   // 16-byte pieces of a router row; 32-bit offsets within a stage
+
+bool router_picks(const bigmac_dims& D) { return D.N <= 16 && router_whole_chunks(D); }
+
+int launch_router_logits(const bigmac_dims& D, const void* x, const float* w_gate, const float* bias, float* logits, hipStream_t s, int32_t* topk_idx, float* topk_w) {
+  if (topk_idx && !router_picks(D)) return BIGMAC_ERR_INVALID_ARG;
+  if (!router_whole_chunks(D)) {
     const dim3 block(256);
     const unsigned gy = (unsigned)((D.N + R_NB - 1) / R_NB);
     const dim3 grid((D.T + 31) / 32, gy);
@@ -976,18 +1008,27 @@ int launch_router_logits(const bigmac_dims& D, const void* x, const float* w_gat
     j.slices_inverse = (65536u + j.slices - 1) / j.slices;
     return j;
   };
-#define BIGMAC_ROUTER(XT, TT, ET, QQT)                                                                                                  \
-  {                                                                                                                                   \
-    const RouterJob job = job_of(16 * TT, 16 * ET, QQT);                                                                              \
-    hipLaunchKernelGGL((router_logits_matrix_kernel<XT, TT, ET, QQT>), dim3((unsigned)(8 * job.stride)), dim3(512), 0, s, job);       \
+#define BIGMAC_ROUTER(XT, TT, ET, ...)                                                                                                       \
+  hipLaunchKernelGGL((router_logits_matrix_kernel<XT, TT, ET, __VA_ARGS__>), dim3((unsigned)(8 * job.stride)), dim3(512), 0, s, job)
+  RouterJob job;
+  if (topk_idx) {
+    job = job_of(16, 16, 4);
+    job.topk_idx = topk_idx; job.topk_w = topk_w; job.k = D.k;
+    if (D.dtype == BIGMAC_BF16) BIGMAC_ROUTER(bf16_t, 1, 1, 4, true);
+    else BIGMAC_ROUTER(float, 1, 1, 4, true);
+  } else if (us22 <= us12 && us22 <= us11) {
+    job = job_of(32, 32, 2);
+    if (D.dtype == BIGMAC_BF16) BIGMAC_ROUTER(bf16_t, 2, 2, 2);
+    else BIGMAC_ROUTER(float, 2, 2, 2);
+  } else if (us12 <= us11) {
+    job = job_of(16, 32, D.dtype == BIGMAC_BF16 ? 4 : 2);
+    if (D.dtype == BIGMAC_BF16) BIGMAC_ROUTER(bf16_t, 1, 2, 4);
+    else BIGMAC_ROUTER(float, 1, 2, 2);
+  } else {
+    job = job_of(16, 16, 4);
+    if (D.dtype == BIGMAC_BF16) BIGMAC_ROUTER(bf16_t, 1, 1, 4);
+    else BIGMAC_ROUTER(float, 1, 1, 4);
   }
-#define BIGMAC_ROUTER_TILES(XT, MIDDLE)                               \
-  if (us22 <= us12 && us22 <= us11) BIGMAC_ROUTER(XT, 2, 2, 2)        \
-  else if (us12 <= us11) BIGMAC_ROUTER(XT, 1, 2, MIDDLE)              \
-  else BIGMAC_ROUTER(XT, 1, 1, 4)
-  if (D.dtype == BIGMAC_BF16) { BIGMAC_ROUTER_TILES(bf16_t, 4) }
-  else { BIGMAC_ROUTER_TILES(float, 2) }
-#undef BIGMAC_ROUTER_TILES
 #undef BIGMAC_ROUTER
   BIGMAC_CHECK_LAUNCH();
   return BIGMAC_OK;

@@ -309,6 +309,26 @@ def test_router_logits_on_the_matrix_cores(oracle, T, d, N, dtype):
     assert torch.equal(logits.cpu()[rest].view(torch.int32), ref[rest].view(torch.int32)) and logits[odd].isnan().all()
 
 
+# up to 16 experts the picks and gates come from the launch that works out the logits: the oracle's, ties to the lower index (columns repeat),
+# and k different experts whatever the logits are; a layer of more than 4096 pairs, which counts them, picks the same
+@pytest.mark.parametrize("dtype", [B.BF16, B.F32])
+@pytest.mark.parametrize("T,d,N,k", [(1, 64, 4, 4), (17, 320, 12, 1), (300, 128, 16, 16), (4100, 64, 8, 2), (777, 192, 16, 3)])
+def test_picks_beside_the_logits(oracle, T, d, N, k, dtype):
+    g = torch.Generator(device=DEV).manual_seed(T + N)
+    x = torch.randn((T, d), generator=g, device=DEV).to(torch.bfloat16 if dtype == B.BF16 else torch.float32)
+    w_gate = torch.randn((d, N), generator=g, device=DEV)
+    w_gate[:, N // 2:] = w_gate[:, :N - N // 2].flip(1)
+    dims = B.make_dims(T, d, 64, N, k, 64, dtype)
+    idx, w, logits = torch.empty((T, k), dtype=torch.int32, device=DEV), torch.empty((T, k), device=DEV), torch.empty((T, N), device=DEV)
+    B.bigmac_route(dims, x, w_gate, None, idx, w, logits)
+    r_idx, r_gate, r_logits = oracle.route(x.float().cpu().numpy(), w_gate.cpu().numpy(), None, k)
+    assert (logits.cpu().numpy().view("uint32") == r_logits.view("uint32")).all() and (idx.cpu().numpy() == r_idx).all()
+    assert abs(w.cpu().numpy() - r_gate).max() < 1e-6
+    x[::3, 0], x[1::3, 1], w_gate[0, ::2] = float("inf"), float("nan"), -1.0
+    B.bigmac_route(dims, x, w_gate, None, idx, w, logits)
+    assert ((idx >= 0) & (idx < N)).all() and (idx.sort(dim=1).values.diff(dim=1) > 0).all()
+
+
 # the summed slices of a dense product, to bf16 as to fp32 (the same sums in the same order): 2, 5 and 10 slices, few elements
 @pytest.mark.parametrize("T,d,r", [(1, 64, 256), (3, 2560, 640), (33, 1280, 1280), (5, 192, 2048)])
 def test_slice_sums_to_bf16(T, d, r):
