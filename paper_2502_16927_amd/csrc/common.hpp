@@ -127,6 +127,15 @@ enum GemmEpilogue {
   EPI_ACCUM = 3    // fp32 C = (beta ? C : 0) + acc
 };
 
+// Top-k and gate over logits [T, N] (route.hip): the workgroup's tokens, and how many workgroups
+struct TopkJob {
+  const float* logits;
+  int32_t* topk_idx;
+  float* topk_w;
+  int32_t* counts;           // optional: pairs per workgroup and expert
+  int T, N, k, tokens, workgroups;
+};
+
 struct GemmDesc {
   int dtype;                 // BIGMAC_F32 or BIGMAC_BF16: element type of A, B, aux
   int a_kcontig, b_kcontig;
@@ -163,6 +172,8 @@ struct GemmDesc {
   unsigned* claim;           // MFMA kernels, optional: zeroed tile counters of this launch (ClaimScope hands them out; see tile order in gemm_core.hpp)
   const void* touch;         // MFMA kernels, optional: a region (device) every line of which is read once as the kernel starts,
   size_t touch_bytes;        //   so that its first use in a k loop meets the caches and not the memory (0 = off)
+  TopkJob topk;              // where gemm_takes_topk holds, optional (logits != NULL): workgroups behind the product's own that pick the experts
+  int product_blocks;        //   (set by launch_gemm: the product's workgroups)
 };
 // Tile counters for the MFMA kernels' dynamic tile order: one slot per launch, one counter per XCD
 // (64 bytes apart).  An entry point opens a scope over a piece of its workspace, and every launch_gemm of
@@ -178,6 +189,7 @@ struct ClaimScope {
 // Rows per M tile of the ragged-M schedule for this dtype (the tile map must be built with it).
 int gemm_ragged_tile_rows(int dtype, int tall_tile);
 int launch_gemm(const GemmDesc& g, hipStream_t s);
+bool gemm_takes_topk(const GemmDesc& g, int N);
 int launch_gemm_f32(const GemmDesc& g, hipStream_t s);   // what launch_gemm does with fp32 operands
 int gemm_f32_tile_rows();
 int launch_gemm_phased(const GemmDesc& g, hipStream_t s);   // the 256 x 256 tile of a big_tile product
@@ -212,8 +224,16 @@ struct ReduceJob {
   int nslices;
 };
 int launch_reduce_partials_multi(const ReduceJob* jobs, int count, int beta, hipStream_t s);
-// out[i] = bf16(sum_z part[z*n + i]); n a multiple of 8
-int launch_reduce_partials_bf16(const float* part, int nslices, size_t n, void* out, hipStream_t s);
+// out[i] = bf16(sum_z part[z*n + i]), n a multiple of 8: a launch of its own, or workgroups beside the sort (see launch_build_permutation)
+struct SliceSum {
+  const float* part;
+  void* out;
+  size_t n;
+  int nslices;
+};
+constexpr int SLICE_SUM_LANES = 64;
+inline unsigned slice_sum_blocks(const SliceSum& j) { return (unsigned)((j.n / 4 + SLICE_SUM_LANES - 1) / SLICE_SUM_LANES); }
+int launch_reduce_partials_bf16(const SliceSum& job, hipStream_t s);
 
 // ----------------------------------------------------------------------------- route ----
 // topk_idx, topk_w (optional, where router_picks holds): the top-k and gate in the same launch
@@ -225,6 +245,7 @@ struct TopkGrid {
   int workgroups, threads, tokens;   // tokens per workgroup
 };
 TopkGrid topk_grid(int T, int k, int N, bool counting);
+TopkJob topk_job(const bigmac_dims& D, const float* logits, int32_t* topk_idx, float* topk_w, int32_t* counts);
 int launch_topk_gate(const bigmac_dims& D, const float* logits, int32_t* topk_idx, float* topk_w, hipStream_t s, int32_t* counts = nullptr);
 // Gate backward (softmax over the k picked logits) and the router's share of dx:
 //   dlogit[t,j] = w[t,j] (dgate[t,j] - sum_m w[t,m] dgate[t,m])
@@ -268,7 +289,7 @@ SortChunks sort_chunks(int T, int k, int N, bool counted);   // counted: by the 
 // tile_maps (optional): tile maps of the expert offsets, built by the same launch that finds them
 int launch_build_permutation(int T, int k, int N, int capacity, const int32_t* topk_idx, int32_t* expert_offsets,
                              int32_t* slot_of, int32_t* src_of, void* ws, hipStream_t s, const TileMapJobs* tile_maps = nullptr,
-                             bool counted = false);
+                             bool counted = false, const SliceSum* beside = nullptr);
 int launch_gather_probe(const void* table, const int32_t* order, long rows, long row_bytes, int streaming, unsigned* sink, hipStream_t s);
 int launch_dispatch_rows(int dtype, int T, int k, int width, const void* x_low, const int32_t* slot_of,
                          void* x_perm, hipStream_t s);

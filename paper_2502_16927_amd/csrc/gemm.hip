@@ -9,6 +9,7 @@
 // with few tiles.  The 256 x 256 tile, which most of the larger products run on, is a kernel of its own (gemm_phased.hip).
 // fp32 storage: see gemm_f32.hip.
 #include "gemm_core.hpp"
+#include "topk.hpp"
 
 namespace bigmac {
 
@@ -20,8 +21,9 @@ namespace bigmac {
 // happen are pushed out of their buffer's range instead of being branched around): the number of
 // instructions in flight behind any load is then a compile-time constant, which is what the
 // counter waits below and the compiler's own ones are derived from.
+// SIDE: the workgroups past the product's own take the top-k and gate of some tokens (see gemm_takes_topk).
 template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, bool AK, bool BKC, int EPI, bool OUTF32, int NS = BIGMAC_TILE_STAGES, bool GATHER = false,
-          bool SCATTER = false>
+          bool SCATTER = false, bool SIDE = false>
 __global__ __launch_bounds__(64 * WAVES_M* WAVES_N)
     __attribute__((amdgpu_waves_per_eu(BM * BN > BIGMAC_TILE_BM * BIGMAC_TILE_BN || BK > BIGMAC_TILE_BK ? BIGMAC_TALL_BLOCKS_PER_CU : BIGMAC_BLOCKS_PER_CU)))
 void mfma_gemm_kernel(GemmDesc p) {
@@ -41,6 +43,15 @@ void mfma_gemm_kernel(GemmDesc p) {
   constexpr int STAGE_BYTES = STAGE_CHUNKS * 16;
   static_assert((NS - 1) * STAGE_BYTES + 8192 <= 65536, "fragment reads address a stage through the 16-bit instruction offset");
   __shared__ uint4 ring[NS * STAGE_CHUNKS];
+  if constexpr (SIDE) {
+    const TopkJob& j = p.topk;
+    if ((int)blockIdx.x >= p.product_blocks) {
+      const int block = (int)blockIdx.x - p.product_blocks;
+      if (j.N <= 64) topk_gate_block<1, 2>(j.logits, j.T, j.N, j.k, j.tokens, block, j.topk_idx, j.topk_w, j.counts, (int*)ring);
+      else topk_gate_block<2, 2>(j.logits, j.T, j.N, j.k, j.tokens, block, j.topk_idx, j.topk_w, j.counts, (int*)ring);
+      return;
+    }
+  }
   const unsigned ring_at = lds_address(ring);
   constexpr unsigned OUT_OF_RANGE = 0x80000000u;
   // Cache policy of the layer's big one-pass streams: non-temporal.  These are the results of
@@ -196,7 +207,7 @@ void mfma_gemm_kernel(GemmDesc p) {
     asm volatile("" ::"v"(seen));   // the reads have to happen; their values are of no interest
   }
 
-  const int stride = (int)(gridDim.x >> 3);
+  const int stride = (SIDE ? p.product_blocks : (int)gridDim.x) >> 3;
   int pos = (int)(blockIdx.x >> 3);
   int id = tile_at(ts, pos);
   if (id < 0) return;
@@ -549,24 +560,11 @@ int launch_build_tile_map(const int* offsets, int groups, const TileMapJobs& map
 // slice, so it is bound by latency: eight loads in flight per thread, four columns per thread and one wavefront per
 // workgroup to reach more CUs (16 slices of 32 x 1024 took 10.1 us with
 // eight columns and one slice at a time; the forward-only call around it, 32 tokens at d 4096, went 248.9 -> 242.9 us).
-__global__ __launch_bounds__(64) void reduce_partials_bf16_kernel(const float* __restrict__ part, int nslices, size_t n, bf16_t* __restrict__ out) {
-  const size_t i = ((size_t)blockIdx.x * 64 + threadIdx.x) * 4;
-  if (i >= n) return;
-  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int z = 0; z < nslices; z += 8) {
-    float4 v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = *(const float4*)(part + (size_t)min(z + u, nslices - 1) * n + i);
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (z + u < nslices) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
-  }
-  *(uint2*)(out + i) = make_uint2(f2bf_pair(s.x, s.y), f2bf_pair(s.z, s.w));
-}
+__global__ __launch_bounds__(SLICE_SUM_LANES) void reduce_partials_bf16_kernel(SliceSum job) { slice_sum_block(job, (int)blockIdx.x); }
 
-int launch_reduce_partials_bf16(const float* part, int nslices, size_t n, void* out, hipStream_t s) {
-  if (n % 8) return BIGMAC_ERR_INVALID_ARG;
-  hipLaunchKernelGGL(reduce_partials_bf16_kernel, dim3((unsigned)((n / 4 + 63) / 64)), dim3(64), 0, s, part, nslices, n, (bf16_t*)out);
+int launch_reduce_partials_bf16(const SliceSum& job, hipStream_t s) {
+  if (job.n % 8) return BIGMAC_ERR_INVALID_ARG;
+  hipLaunchKernelGGL(reduce_partials_bf16_kernel, dim3(slice_sum_blocks(job)), dim3(SLICE_SUM_LANES), 0, s, job);
   BIGMAC_CHECK_LAUNCH();
   return BIGMAC_OK;
 }
@@ -612,8 +610,11 @@ template <bool AK, bool BKC>
 int launch_mfma(const GemmDesc& g, hipStream_t s) {
   constexpr int BM = BIGMAC_TILE_BM, BN = BIGMAC_TILE_BN, BK = BIGMAC_TILE_BK, WMs = BIGMAC_TILE_WM, WNs = BIGMAC_TILE_WN;
   dim3 grid = grid_for<BM, BN>(g, true), block(64 * WMs * WNs);
+  GemmDesc d = g;
+  d.product_blocks = (int)grid.x;
+  if (g.topk.logits) grid.x += g.topk.workgroups;
 #define BIGMAC_MFMA(EPI, OUTF32, ...) \
-  hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, WMs, WNs, AK, BKC, EPI, OUTF32, BIGMAC_TILE_STAGES, __VA_ARGS__>), grid, block, 0, s, g)
+  hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, WMs, WNs, AK, BKC, EPI, OUTF32, BIGMAC_TILE_STAGES, __VA_ARGS__>), grid, block, 0, s, d)
   if constexpr (!AK && !BKC) {   // weight gradients
     if (g.epilogue != EPI_ACCUM) return BIGMAC_ERR_UNSUPPORTED;
     BIGMAC_MFMA(EPI_ACCUM, true, false);
@@ -624,6 +625,8 @@ int launch_mfma(const GemmDesc& g, hipStream_t s) {
       BIGMAC_MFMA(EPI_GELU, false, true);
     } else if (g.epilogue == EPI_GELU) BIGMAC_MFMA(EPI_GELU, false, false);
     else if (g.epilogue != EPI_STORE) return BIGMAC_ERR_UNSUPPORTED;
+    else if (g.topk.logits && g.out_f32) BIGMAC_MFMA(EPI_STORE, true, false, false, true);
+    else if (g.topk.logits) BIGMAC_MFMA(EPI_STORE, false, false, false, true);
     else if (g.out_f32) BIGMAC_MFMA(EPI_STORE, true, false);
     else BIGMAC_MFMA(EPI_STORE, false, false);
   } else {
@@ -679,10 +682,16 @@ int launch_mfma_deep(const GemmDesc& g, hipStream_t s) {
   constexpr int BM = 128, BN = 64, BK = 64;
   dim3 grid = grid_for<BM, BN>(g, false), block(256);
   if (grid.x > 512) grid.x = 512;
+  GemmDesc d = g;
+  d.product_blocks = (int)grid.x;
+  if (g.topk.logits) grid.x += g.topk.workgroups;
 #define BIGMAC_MFMA_DEEP(EPI, OUTF32) \
-  hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 4, 1, AK, BKC, EPI, OUTF32>), grid, block, 0, s, g)
+  hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 4, 1, AK, BKC, EPI, OUTF32>), grid, block, 0, s, d)
   if (g.scatter) {   // the descending projection writing the dispatched rows (k-contiguous A, whole-line B only)
-    if constexpr (AK && !BKC) hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 4, 1, AK, BKC, EPI_STORE, false, BIGMAC_TILE_STAGES, false, true>), grid, block, 0, s, g);
+    if constexpr (AK && !BKC) hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 4, 1, AK, BKC, EPI_STORE, false, BIGMAC_TILE_STAGES, false, true>), grid, block, 0, s, d);
+    else return BIGMAC_ERR_UNSUPPORTED;
+  } else if (g.topk.logits) {
+    if constexpr (AK && !BKC) hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 4, 1, AK, BKC, EPI_STORE, false, BIGMAC_TILE_STAGES, false, false, true>), grid, block, 0, s, d);
     else return BIGMAC_ERR_UNSUPPORTED;
   } else if (g.epilogue == EPI_ACCUM) BIGMAC_MFMA_DEEP(EPI_ACCUM, true);
   else if (g.out_f32) BIGMAC_MFMA_DEEP(EPI_STORE, true);
@@ -737,6 +746,14 @@ thread_local ClaimPool claim_pool = {nullptr, 0};
 ClaimScope::ClaimScope(void* region) { claim_pool = {(unsigned*)region, 0}; }
 ClaimScope::~ClaimScope() { claim_pool = {nullptr, 0}; }
 
+// Which products have workgroups for the top-k beside their own: the descending projection on the tiles of this file (x W_down), of which
+// neither needs the other.  A launch of its own costs the top-k 5 to 6 us; beside the product, whose few tiles leave CUs
+// idle or wait for memory, 1 to 3 (T 32, d 4096: product 8.8 -> 9.8 us; T 500 14.5 -> 15.6; T 8192, d 1024 11.5 -> 14.3).  Up to 128 experts (two keys per lane); not on the 256 x 256 tile, which fills every CU's LDS.
+bool gemm_takes_topk(const GemmDesc& g, int N) {
+  return g.dtype == BIGMAC_BF16 && N <= 128 && g.mode == GEMM_DENSE && g.a_kcontig && !g.b_kcontig && g.epilogue == EPI_STORE && !g.big_tile && !g.tall_tile &&
+         !g.wide_k && !g.gather && !g.scatter && (!g.deep_tile || !g.out_f32);
+}
+
 int launch_gemm(const GemmDesc& desc, hipStream_t s) {
   GemmDesc g = desc;
   // The claimed order for the ragged-M products.  Measured on zipf_stress: the four per-expert row products 13-19 %
@@ -785,6 +802,7 @@ int launch_gemm(const GemmDesc& desc, hipStream_t s) {
         (size_t)g.M * (size_t)g.scatter_k * 4 >= (1ull << 31) || (size_t)g.scatter_rows * (size_t)g.ldc * 2 >= (1ull << 31))
       return BIGMAC_ERR_UNSUPPORTED;
   }
+  if (g.topk.logits && !gemm_takes_topk(g, g.topk.N)) return BIGMAC_ERR_UNSUPPORTED;
   if (g.big_tile) {
     if (g.dtype != BIGMAC_BF16 || g.tall_tile || g.wide_k || g.deep_tile || g.touch_bytes || g.ksplit != 1) return BIGMAC_ERR_INVALID_ARG;
     return launch_gemm_phased(g, s);

@@ -722,7 +722,8 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
   const bool low_router = route_low(*D);
   // x' is the workspace's piece, or (router on x': the backward pass reads it again) the saved block's
   void* x_low_buf = (low_router && saved) ? (void*)(sv + S.x_low) : (void*)(wsb + F.x_low);
-  auto route = [&](const void* router_in) -> int {
+  // The top-k stands in a launch of its own unless the router's tiles hold all experts or (beside) the descending projection takes it along.
+  auto route = [&](const void* router_in, bool beside) -> int {
     const bigmac_dims R = router_dims(*D);
     const bool picks = !chunk_counts && router_picks(R);   // all experts in one tile of the logits, and no pairs to count
     int rr;
@@ -732,20 +733,16 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
     }
     if (rr) return rr;
     BIGMAC_STAGE(BIGMAC_STAGE_TOPK_GATE);
-    if (!picks) rr = launch_topk_gate(*D, logits, topk_idx, topk_w, s, chunk_counts);
+    if (!picks && !beside) rr = launch_topk_gate(*D, logits, topk_idx, topk_w, s, chunk_counts);
     if (!rr && aux)
       rr = launch_aux_loss(*D, logits, topk_idx, (float*)(sv + S.aux + 256), (float*)(sv + S.aux), nullptr, wsb + F.aux, s, chunk_counts);
     return rr;
   };
-  if (!low_router) {   // Section 3.1's default: the router reads the full-width token
-    rc = route(x);
-    if (rc) return rc;
-  }
-  auto permute = [&]() -> int {
+  auto permute = [&](const SliceSum* beside = nullptr) -> int {
     BIGMAC_STAGE(BIGMAC_STAGE_PERMUTATION);
     const bool big = saved ? any_big_rows(*D) : big_forward_rows(*D, P->b1, P->b2, nullptr);
     const TileMapJobs maps = tile_map_jobs(*D, big, tile_map, tile_map_tall, (unsigned*)(wsb + F.claims));
-    return launch_build_permutation(D->T, D->k, D->N, D->capacity, topk_idx, offsets, slot_of, src_of, wsb + F.perm, s, &maps, chunk_counts != nullptr);
+    return launch_build_permutation(D->T, D->k, D->N, D->capacity, topk_idx, offsets, slot_of, src_of, wsb + F.perm, s, &maps, chunk_counts != nullptr, beside);
   };
   // A training forward on bf16 storage whose router reads x folds the dispatch into the descending
   // projection: the permutation is built first, and the product's epilogue writes every token's
@@ -756,44 +753,58 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
   const bool descend_big = dcca && descend_ksplit == 1 && big_dense(*D, D->T, D->r, D->d);
   const bool descend_deep = dcca && descend_ksplit == 1 && !descend_big && deep_dense(*D, D->T, D->r, D->d);
   const bool scatter_descend = saved && descend_scatters(*D);
+  GemmDesc down = base_desc(*D);   // x' = x W_down
+  if (dcca) {
+    down.a_kcontig = 1; down.b_kcontig = 0; down.epilogue = EPI_STORE; down.out_f32 = bf(*D) && descend_ksplit == 1 ? 0 : 1;
+    down.A = x; down.lda = D->d; down.M = D->T; down.K = D->d;
+    down.B = P->w_down; down.ldb = D->r; down.N = D->r;
+    down.C = x_low_buf; down.ldc = D->r;
+    down.ksplit = descend_ksplit;
+    down.big_tile = descend_big;
+    down.deep_tile = descend_deep;
+    if (scatter_descend) {
+      down.scatter = slot_of; down.scatter_k = D->k; down.scatter_rows = D->T * D->k;
+      down.C = x_perm;
+    }
+    // (the loss reads the picks, and 16 experts' are there already)
+    if (!low_router && !scatter_descend && !aux && (chunk_counts || !router_picks(*D)) && gemm_takes_topk(down, D->N))
+      down.topk = topk_job(*D, logits, topk_idx, topk_w, chunk_counts);
+  }
+  if (!low_router) {   // Section 3.1's default: the router reads the full-width token
+    rc = route(x, down.topk.logits != nullptr);
+    if (rc) return rc;
+  }
   if (scatter_descend) {
     rc = permute();
     if (rc) return rc;
   }
+  // The sum of the projection's slices and the sort do not need each other either: in one launch (decode shape, 32 tokens 5.0 + 5.0 ->
+  // 5.1 us, 500 8.5 + 7.0 -> 10.9, 2048 8.4 + 9.7 -> 14.7), unless the router reads the sum.
+  const bool sum_beside_sort = !low_router;
+  SliceSum descend_sum = {};
   const void* x_low = x;
-  if (dcca) {  // x' = x W_down
-    GemmDesc g = base_desc(*D);
-    g.a_kcontig = 1; g.b_kcontig = 0; g.epilogue = EPI_STORE; g.out_f32 = bf(*D) ? 0 : 1;
-    g.A = x; g.lda = D->d; g.M = D->T; g.K = D->d;
-    g.B = P->w_down; g.ldb = D->r; g.N = D->r;
-    g.C = x_low_buf; g.ldc = D->r;
+  if (dcca) {
     {
       BIGMAC_STAGE(BIGMAC_STAGE_DESCEND);
-      g.ksplit = descend_ksplit;
-      g.big_tile = descend_big;
-      g.deep_tile = descend_deep;
-      if (scatter_descend) {
-        g.scatter = slot_of; g.scatter_k = D->k; g.scatter_rows = D->T * D->k;
-        g.C = x_perm;
-      }
-      if (g.ksplit > 1) {   // fp32 partials, then one rounding to bf16
-        g.out_f32 = 1; g.C = wsb + F.partials; g.gstride_c = (long)D->T * D->r;
-        rc = launch_gemm(g, s);
+      if (down.ksplit > 1) {   // fp32 partials, then one rounding to bf16
+        down.C = wsb + F.partials; down.gstride_c = (long)D->T * D->r;
+        rc = launch_gemm(down, s);
         if (rc) return rc;
-        rc = launch_reduce_partials_bf16((const float*)(wsb + F.partials), g.ksplit, (size_t)D->T * D->r, x_low_buf, s);
+        if (sum_beside_sort) descend_sum = {(const float*)(wsb + F.partials), x_low_buf, (size_t)D->T * D->r, down.ksplit};
+        else rc = launch_reduce_partials_bf16({(const float*)(wsb + F.partials), x_low_buf, (size_t)D->T * D->r, down.ksplit}, s);
       } else {
-        rc = launch_gemm(g, s);
+        rc = launch_gemm(down, s);
       }
     }
     if (rc) return rc;
     x_low = x_low_buf;
   }
   if (low_router) {    // the alternative Section 3.1 names: the router reads x' (as stored)
-    rc = route(x_low);
+    rc = route(x_low, false);
     if (rc) return rc;
   }
   if (!scatter_descend) {
-    rc = permute();
+    rc = permute(descend_sum.part ? &descend_sum : nullptr);
     if (rc) return rc;
   }
   // Forward-only calls on bf16 storage fold the dispatch into the expert-up product: its A rows are
@@ -834,7 +845,7 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
       g.out_f32 = 1; g.C = wsb + F.partials; g.gstride_c = (long)D->T * D->d;
       rc = launch_gemm(g, s);
       if (rc) return rc;
-      if (out_bf16) rc = launch_reduce_partials_bf16((const float*)(wsb + F.partials), g.ksplit, (size_t)D->T * D->d, y, s);
+      if (out_bf16) rc = launch_reduce_partials_bf16({(const float*)(wsb + F.partials), y, (size_t)D->T * D->d, g.ksplit}, s);
       else rc = launch_reduce_partials((const float*)(wsb + F.partials), g.ksplit, (size_t)D->T * D->d, (float*)y, 0, s);
     } else {
       rc = launch_gemm(g, s);

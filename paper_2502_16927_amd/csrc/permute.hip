@@ -192,7 +192,11 @@ __global__ __launch_bounds__(64) void perm_rank_kernel(const int32_t* __restrict
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void perm_place_kernel(const int32_t* __restrict__ idx, int Tk, int pairs_per_chunk, int nchunks, int parts, int N, int NP, int nbits,
                                                              int capacity, const int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
-                                                             int32_t* __restrict__ slot_of, int32_t* __restrict__ src_of, TileMapJobs maps) {
+                                                             int32_t* __restrict__ slot_of, int32_t* __restrict__ src_of, TileMapJobs maps, SliceSum beside, int sorting) {
+  if ((int)blockIdx.x >= sorting) {      // the first wavefront of a workgroup past the sort's own
+    slice_sum_block(beside, (int)blockIdx.x - sorting);
+    return;
+  }
   constexpr int WAVES = THREADS / 64;
   extern __shared__ int cnt[];           // [wavefront][expert]
   __shared__ int totals[PP_MAX_EXPERTS], earlier[PP_MAX_EXPERTS];
@@ -634,7 +638,7 @@ size_t permutation_ws_bytes(int T, int k, int N, bool counted) {
 
 // counted: ws holds the chunks' counters (see sort_chunks) already
 int launch_build_permutation(int T, int k, int N, int capacity, const int32_t* topk_idx, int32_t* expert_offsets,
-                             int32_t* slot_of, int32_t* src_of, void* ws, hipStream_t s, const TileMapJobs* tile_maps, bool counted) {
+                             int32_t* slot_of, int32_t* src_of, void* ws, hipStream_t s, const TileMapJobs* tile_maps, bool counted, const SliceSum* beside) {
   if (N > 1024) return BIGMAC_ERR_UNSUPPORTED;   // one thread of the scan per expert
   const TileMapJobs maps = tile_maps ? *tile_maps : TileMapJobs{};
   const SortChunks sc = sort_chunks(T, k, N, counted);
@@ -648,15 +652,22 @@ int launch_build_permutation(int T, int k, int N, int capacity, const int32_t* t
       hipLaunchKernelGGL(perm_count_kernel, dim3(sc.count * sc.parts), dim3(256), N * sizeof(int), s, topk_idx, Tk, N, part, (int32_t*)ws);
       BIGMAC_CHECK_LAUNCH();
     }
+    const int sorting = sc.count + (maps.map[0] ? 1 : 0);
+    const dim3 grid(sorting + (beside ? slice_sum_blocks(*beside) : 0));
+    const SliceSum sum = beside ? *beside : SliceSum{};
 #define BIGMAC_PLACE(THREADS)                                                                                                        \
-  hipLaunchKernelGGL(perm_place_kernel<THREADS>, dim3(sc.count + (maps.map[0] ? 1 : 0)), dim3(THREADS), THREADS / 64 * N * sizeof(int), s, topk_idx, Tk, pairs, \
-                     sc.count, sc.parts, N, NP, nbits, capacity, counts, expert_offsets, slot_of, src_of, maps)
+  hipLaunchKernelGGL(perm_place_kernel<THREADS>, grid, dim3(THREADS), THREADS / 64 * N * sizeof(int), s, topk_idx, Tk, pairs, \
+                     sc.count, sc.parts, N, NP, nbits, capacity, counts, expert_offsets, slot_of, src_of, maps, sum, sorting)
     if (sc.threads == 256) BIGMAC_PLACE(256);
     else if (sc.threads == 512) BIGMAC_PLACE(512);
     else BIGMAC_PLACE(1024);
 #undef BIGMAC_PLACE
     BIGMAC_CHECK_LAUNCH();
     return BIGMAC_OK;
+  }
+  if (beside) {                                   // (the three kernels have no place for it)
+    const int rc = launch_reduce_partials_bf16(*beside, s);
+    if (rc) return rc;
   }
   const int Tk = T * k;
   const int chunk = perm_chunk(Tk, N);

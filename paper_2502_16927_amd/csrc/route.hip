@@ -5,7 +5,7 @@
 //   tree = p_l + p_{l+off} for off = 32, 16, 8, 4, 2, 1;  logit = tree (+ bias[n], added last)
 // The tree is evaluated as a reduce-scatter over the wavefront: same pairs, 1/6 of the adds.
 #include "gemm_core.hpp"
-#include "wave.hpp"
+#include "topk.hpp"
 
 namespace bigmac {
 
@@ -106,41 +106,6 @@ __global__ __launch_bounds__(256) void router_logits_kernel(const XT* __restrict
       logits[(size_t)t * N + n] = val;
     }
   }
-}
-
-// (logit, expert) as one number: the greater key comes first, equal logits (-0 counts as 0) by lower index.  NaN logits
-// have a place in that order too (by their sign, past the infinities), and a lane past the N experts comes after every
-// expert, so that whatever the logits are the k <= N picks are k different experts: the sort writes to slots counted by them.
-__device__ __forceinline__ unsigned long long logit_key(float logit, int expert) {
-  const unsigned u = __float_as_uint(logit + 0.0f);
-  return ((unsigned long long)((u & 0x80000000u) ? ~u : u | 0x80000000u) << 32) | (unsigned)~expert;
-}
-__device__ __forceinline__ unsigned long long pick_key(const float* row, int expert, int N) {
-  return expert >= N ? (unsigned)~expert : logit_key(row[expert], expert);
-}
-__device__ __forceinline__ float key_logit(unsigned long long key) {
-  const unsigned u = (unsigned)(key >> 32);
-  return __uint_as_float((u & 0x80000000u) ? u & 0x7FFFFFFFu : ~u);
-}
-// One compare-exchange step of a bitonic network over the wavefront, for U independent networks: partner lane
-// ^ J, the greater key of the pair goes to the lane for which greater_here holds.
-template <int J, int U>
-__device__ __forceinline__ void exchange_keys(unsigned long long (&key)[U], int lane, bool greater_here) {
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const unsigned long long other = ((unsigned long long)from_lane_xor<J>((unsigned)(key[u] >> 32), lane) << 32) | from_lane_xor<J>((unsigned)key[u], lane);
-    if ((key[u] > other) != greater_here) key[u] = other;
-  }
-}
-template <int SIZE, int J, int U>
-__device__ __forceinline__ void merge_keys(unsigned long long (&key)[U], int lane) {
-  exchange_keys<J>(key, lane, ((lane & J) == 0) == ((lane & SIZE) == 0));   // lower lane of a descending block
-  if constexpr (J > 1) merge_keys<SIZE, J / 2>(key, lane);
-}
-template <int SIZE, int U>
-__device__ __forceinline__ void sort_keys(unsigned long long (&key)[U], int lane) {   // lane 0 ends with the greatest
-  if constexpr (SIZE > 2) sort_keys<SIZE / 2>(key, lane);
-  merge_keys<SIZE, SIZE / 2>(key, lane);
 }
 
 // The same sums on the matrix cores, for N % 4 == 0.  v_mfma_f32_16x16x1_4b_f32 has a contraction of one: every output
@@ -575,112 +540,10 @@ void router_logits_matrix_kernel(RouterJob job) {
   BIGMAC_WAIT_VMCNT(0);                                    // the requests of nothing write the LDS too
 }
 
-// The k picks of each token in pick order (greater logit first, ties to the lower index) and the softmax over
-// their logits, summed in pick order.  One wavefront per token; a workgroup walks the `tokens` tokens of
-// its share and, if counts is given (up to 128 experts), counts their pairs per expert on the way (the sort's counters,
-// see launch_build_permutation).  PER = logits per lane.  Up to 64 experts: one key per lane, sorted across the wavefront by a
-// bitonic network (the order is strict and total, so the result is the unique sorted sequence);
-// lanes 0 .. k-1 then hold the picks.  Up to 128: two keys per lane, both halves sorted the same way;
-// the first 64 of their union are, lane by lane, the first of (half 0 at lane l, half 1 at lane
-// 63 - l), a bitonic sequence that six more steps sort: k <= 64 picks are all there.  More: every lane
-// ranks its logits against all N by broadcast (rank = how many logits come first); ranks below k
-// are the selection.  That one is bound by its comparisons, which take no branches (1024 tokens, 512 experts: 106 us with, 52 without).
-// The network is a serial chain of 21 (27) exchanges and bound by its latency: keys of 64 bits cost one
-// comparison, partners are read by DPP moves and row swaps instead of through the LDS, and a
-// wavefront takes U tokens at a time: two where the grid follows the sort's chunks (8192 tokens, 64 experts, counting included: 15.0 us by wavefronts
-// that take eight one by one, 6.3 us so).
 template <int PER, int U>
-__global__ __launch_bounds__(1024) void topk_gate_kernel(const float* __restrict__ logits, int T, int N, int k, int tokens,
-                                                         int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int32_t* __restrict__ counts) {
+__global__ __launch_bounds__(1024) void topk_gate_kernel(TopkJob j) {
   __shared__ int hist[128];
-  const int lane = threadIdx.x & 63;
-  if (PER <= 2 && counts) {
-    for (int e = threadIdx.x; e < N; e += blockDim.x) hist[e] = 0;
-    __syncthreads();
-  }
-  auto finish = [&](int t, float logit, int expert) {   // lane j < k holds pick j
-    const float m = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(logit), 0));
-    const float e = lane < k ? expf(logit - m) : 0.0f;
-    float s = 0.0f;
-    for (int j = 0; j < k; ++j) s += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(e), j));
-    if (lane < k) {
-      topk_idx[(size_t)t * k + lane] = expert;
-      topk_w[(size_t)t * k + lane] = e / s;
-      if (PER <= 2 && counts) atomicAdd(&hist[expert], 1);
-    }
-  };
-  const int t_end = min(T, (int)(blockIdx.x + 1) * tokens), step = blockDim.x >> 6;
-  for (int t = blockIdx.x * tokens + (threadIdx.x >> 6); t < t_end; t += U * step) {
-    if constexpr (PER <= 2) {
-      unsigned long long key[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {     // (tokens past the chunk repeat the last one's loads and are not finished)
-        const float* row = logits + (size_t)min(t + u * step, t_end - 1) * N;
-        key[u] = pick_key(row, lane, N);
-      }
-      if constexpr (PER == 1) {
-        sort_keys<64>(key, lane);
-      } else {
-        unsigned long long upper[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const float* row = logits + (size_t)min(t + u * step, t_end - 1) * N;
-          upper[u] = pick_key(row, 64 + lane, N);
-        }
-        sort_keys<64>(key, lane);
-        sort_keys<64>(upper, lane);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const unsigned hi = __shfl((unsigned)(upper[u] >> 32), 63 - lane, 64), lo = __shfl((unsigned)upper[u], 63 - lane, 64);
-          const unsigned long long mirrored = ((unsigned long long)hi << 32) | lo;
-          if (mirrored > key[u]) key[u] = mirrored;
-        }
-        merge_keys<64, 32>(key, lane);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (t + u * step < t_end) finish(t + u * step, key_logit(key[u]), (int)~(unsigned)key[u]);
-    } else {
-      const float* row = logits + (size_t)t * N;
-      float v[PER];
-      int rank[PER];
-#pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const int n = i * 64 + lane;
-        v[i] = n < N ? row[n] : -INFINITY;
-        rank[i] = 0;
-      }
-#pragma unroll
-      for (int io = 0; io < PER; ++io) {
-        const int live = min(64, N - io * 64);        // lanes of this register that hold a logit
-        for (int l = 0; l < live; ++l) {
-          const float o = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[io]), l));
-          const int on = io * 64 + l;
-#pragma unroll
-          for (int i = 0; i < PER; ++i) rank[i] += (int)(o > v[i]) | ((int)(o == v[i]) & (int)(on < i * 64 + lane));   // (no branches)
-        }
-      }
-      // lane j < k collects the j-th pick: its index and logit
-      float selv = 0.0f;
-      int seli = 0;
-      for (int j = 0; j < k; ++j) {
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-          const unsigned long long hit = __ballot(rank[i] == j && i * 64 + lane < N);
-          if (hit) {                                  // wave-uniform: exactly one (i, lane) has rank j
-            const int src = __ffsll((long long)hit) - 1;
-            const float pv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[i]), src));
-            if (lane == j) { selv = pv; seli = i * 64 + src; }
-          }
-        }
-      }
-      finish(t, selv, seli);
-    }
-  }
-  if (PER <= 2 && counts) {
-    __syncthreads();
-    for (int e = threadIdx.x; e < N; e += blockDim.x) counts[(size_t)blockIdx.x * N + e] = hist[e];
-  }
+  topk_gate_block<PER, U>(j.logits, j.T, j.N, j.k, j.tokens, (int)blockIdx.x, j.topk_idx, j.topk_w, j.counts, hist);
 }
 
 __global__ void transpose_f32_kernel(const float* __restrict__ in, float* __restrict__ out, int rows, int cols) {
@@ -1045,12 +908,17 @@ TopkGrid topk_grid(int T, int k, int N, bool counting) {
   return {sc.count * sc.parts, std::min(1024, (sc.tokens + 1) / 2 * 64), sc.tokens};
 }
 
+TopkJob topk_job(const bigmac_dims& D, const float* logits, int32_t* topk_idx, float* topk_w, int32_t* counts) {
+  const TopkGrid G = topk_grid(D.T, D.k, D.N, counts != nullptr);
+  return {logits, topk_idx, topk_w, counts, D.T, D.N, D.k, G.tokens, G.workgroups};
+}
+
 int launch_topk_gate(const bigmac_dims& D, const float* logits, int32_t* topk_idx, float* topk_w, hipStream_t s, int32_t* counts) {
   if (counts && !topk_counts(D.T, D.k, D.N)) return BIGMAC_ERR_INVALID_ARG;
-  const TopkGrid G = topk_grid(D.T, D.k, D.N, counts != nullptr);
-  const dim3 g2(G.workgroups), block(G.threads);
+  const TopkJob job = topk_job(D, logits, topk_idx, topk_w, counts);
+  const dim3 g2(job.workgroups), block(topk_grid(D.T, D.k, D.N, counts != nullptr).threads);
   const int per = (D.N + 63) / 64;
-#define BIGMAC_TOPK(P, U) hipLaunchKernelGGL((topk_gate_kernel<P, U>), g2, block, 0, s, logits, D.T, D.N, D.k, G.tokens, topk_idx, topk_w, counts)
+#define BIGMAC_TOPK(P, U) hipLaunchKernelGGL((topk_gate_kernel<P, U>), g2, block, 0, s, job)
   if (per <= 1 && counts) BIGMAC_TOPK(1, 2);
   else if (per <= 1) BIGMAC_TOPK(1, 1);
   else if (per <= 2 && counts) BIGMAC_TOPK(2, 2);

@@ -108,4 +108,20 @@ __device__ __forceinline__ void gate_backward_row(float w, float g, int e, const
   }
 }
 
+// Work of one wavefront of a SliceSum: four neighbouring elements per lane, eight slices on their way at a time.
+__device__ __forceinline__ void slice_sum_block(const SliceSum& job, int block) {
+  const size_t i = ((size_t)block * SLICE_SUM_LANES + threadIdx.x) * 4;
+  if (threadIdx.x >= SLICE_SUM_LANES || i >= job.n) return;
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int z = 0; z < job.nslices; z += 8) {
+    float4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = *(const float4*)(job.part + (size_t)min(z + u, job.nslices - 1) * job.n + i);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (z + u < job.nslices) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
+  }
+  *(uint2*)((bf16_t*)job.out + i) = make_uint2(f2bf_pair(s.x, s.y), f2bf_pair(s.z, s.w));
+}
+
 }  // namespace bigmac

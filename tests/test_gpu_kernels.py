@@ -329,6 +329,26 @@ def test_picks_beside_the_logits(oracle, T, d, N, k, dtype):
     assert ((idx >= 0) & (idx < N)).all() and (idx.sort(dim=1).values.diff(dim=1) > 0).all()
 
 
+# forward-only calls pick the experts in workgroups beside the descending projection (17 to 128 experts; its K split or not, on either tile; with
+# the sort's counters and without) and sum its slices beside the sort: the y of the training forward, which does neither
+@pytest.mark.parametrize("T,d,r,N,k", [(1, 512, 128, 17, 17), (37, 4096, 64, 65, 3), (130, 2048, 320, 128, 8), (520, 1024, 128, 64, 8), (1025, 2560, 64, 72, 5),
+                                       (700, 64, 64, 20, 2), (2100, 512, 64, 128, 64), (300, 1024, 64, 136, 4)])
+def test_top_k_beside_the_descending_projection(T, d, r, N, k):
+    g = torch.Generator(device=DEV).manual_seed(T + N)
+    bf = lambda *s: (torch.randn(s, generator=g, device=DEV) * 0.1).to(torch.bfloat16)
+    x, w_gate, bias = bf(T, d), torch.randn((d, N), generator=g, device=DEV), torch.randn(N, generator=g, device=DEV)
+    dims = B.make_dims(T, d, r, N, k, 64, B.BF16, capacity=(2 * T * k + N - 1) // N)
+    w = [bf(*n) for n in ((d, r), (r, d), (N, r, 64), (N, 64, r))]
+    params = B.make_params(w[0], w[1], w_gate, bias, w[2], w[3])
+    ys = []
+    for saved in (None, B.alloc_bytes(B.workspace_bytes(dims, B.WS_SAVED))):
+        ws = B.alloc_bytes(B.workspace_bytes(dims, B.WS_LAYER_FORWARD if saved is None else B.WS_LAYER_TRAIN))
+        ws.fill_(255)
+        ys.append(torch.full((T, d), float("nan"), device=DEV))
+        B.bigmac_layer_forward(dims, params, x, ys[-1], saved, ws)
+    assert ys[0].isfinite().all() and torch.equal(ys[0], ys[1])
+
+
 # the summed slices of a dense product, to bf16 as to fp32 (the same sums in the same order): 2, 5 and 10 slices, few elements
 @pytest.mark.parametrize("T,d,r", [(1, 64, 256), (3, 2560, 640), (33, 1280, 1280), (5, 192, 2048)])
 def test_slice_sums_to_bf16(T, d, r):
