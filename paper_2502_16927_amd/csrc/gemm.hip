@@ -365,6 +365,9 @@ void mfma_gemm_kernel(GemmDesc p) {
           else add_bias_plain(acc[i][j], (const bf16_t*)t.bias, t.n0 + wn + j * 32, p.N, lane);
         }
     }
+    // Sub-tiles past the last row of the group are left out (see phased_gemm_kernel).
+    const int first_row = t.m0 + __builtin_amdgcn_readfirstlane(wm);
+    auto no_rows = [&](int i) { return first_row + i * 32 >= t.m_end; };
     // epilogue: lane l of a 32x32 tile holds column l%32, rows 8*(v/4) + 4*(l/32) + v%4
     if (EPI == EPI_ACCUM || OUTF32) {
       // fp32 results: a lane group already writes 128 contiguous bytes per row.  Accumulation into
@@ -373,7 +376,8 @@ void mfma_gemm_kernel(GemmDesc p) {
       const __amdgpu_buffer_rsrc_t rc = rows_of(t, t.C, 4);
       const unsigned row_step = (unsigned)(p.ldc * 4);
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i) {
+        if (no_rows(i)) break;
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
           const int col = t.n0 + wn + j * 32 + (lane & 31);
@@ -395,6 +399,7 @@ void mfma_gemm_kernel(GemmDesc p) {
           for (int v = 0; v < 16; ++v)
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[i][j][v]), rc, off[v >> 2] + (v & 3) * row_step, 0, NON_TEMPORAL);
         }
+      }
     } else {
       // bf16 results.  With the transposed accumulation lane l owns row l%32 of each 32-row sub-tile
       // and, per accumulator quad, 4 consecutive columns: the epilogue math runs on the accumulators,
@@ -450,6 +455,7 @@ void mfma_gemm_kernel(GemmDesc p) {
       };
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
+        if (no_rows(i)) break;
         if (EPI == EPI_GELU && p.aux_out) {   // the pre-activation itself, for the backward pass
 #pragma unroll
           for (int j = 0; j < TN; ++j)

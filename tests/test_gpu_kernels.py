@@ -49,6 +49,27 @@ def test_f32_expert_products(rows, r, h):
     assert rel(o, ref_o) < 1e-5
 
 
+# bf16 row products whose tiles are part full: every number of 32-row sub-tiles that a wavefront stores, after a tile of any other
+# number (more tiles than workgroups, largest and smallest tile), and rows behind the last expert's that have to stay as they are.
+# Inputs are exact; the activation's bf16 rounding is off by 2^-9 / sqrt(3) = 1.1e-3 of a row's norm, the output by that of the hidden
+# values (a sum of roundings that cancel no better than the sum itself) and its own: bounds twice that.
+@pytest.mark.parametrize("flags", [0, B.FLAG_TILES_SMALL, B.FLAG_TILES_LARGE])
+def test_row_tiles_part_full(flags):
+    rows = [1, 256, 32, 224, 33, 193, 0, 255, 64, 161, 65, 129, 96, 192, 97, 128, 160, 225, 257, 31, 200, 40, 300, 63] * 3
+    r, h, n, total, guard = 256, 2048, len(rows), sum(rows), 64
+    g = torch.Generator(device=DEV).manual_seed(3)
+    rand = lambda shape, std: (torch.randn(shape, generator=g, device=DEV) * std).bfloat16()
+    xp, w1, w2 = rand((total, r), 1.0), rand((n, r, h), r ** -0.5), rand((n, h, r), h ** -0.5)
+    dims = B.make_dims(total, 512, r, n, 1, h, B.BF16, flags=flags)
+    act, o = (torch.full((total + guard, w), 7.0, device=DEV, dtype=torch.bfloat16) for w in (h, r))
+    B.bigmac_grouped_ffn(dims, xp, ragged_offsets(rows), w1, w2, act, o, B.alloc_bytes(B.workspace_bytes(dims, B.WS_GROUPED_FFN)))
+    ref_a, ref_o = ffn_reference(xp, rows, w1, w2)
+    row_rel = lambda a, b: float(((a.double() - b).norm(dim=1) / b.norm(dim=1)).max())
+    assert row_rel(act[:total], ref_a) < 2.2e-3
+    assert row_rel(o[:total], ref_o) < 3.2e-3
+    assert bool((act[total:] == 7).all()) and bool((o[total:] == 7).all())
+
+
 # fp32 products from 2048 tiles on in the layouts of the backward pass: both matrices' data gradients (ragged), dx' W_down^T (dense),
 # the experts' weight gradients (ragged K), with an odd token count and an expert without rows
 def test_f32_layer_of_many_tiles():
