@@ -164,6 +164,7 @@ struct GemmDesc {
   int kloop_priority;        // MFMA kernels: raise the wave priority inside the k loop (see the kernel)
   int deep_tile;             // bf16, dense, store or accumulate (K % 64 == 0 with a k-contiguous operand): 128 x 64 outputs, 64-deep k tiles
   int big_tile;              // bf16: 256 x 256 outputs by eight wavefronts, one workgroup per CU (ragged-M: tile map of 256-row tiles)
+  int stream_tile;           // bf16 ragged-M, k-contiguous A, B not, store or GELU: 128 x 256 outputs, for few rows per group (tile map of 128-row tiles)
   const int* gather;         // ragged-M MFMA kernels with a k-contiguous A, GELU epilogue: row m of the product is row gather[m] / gather_div of A (device [max_rows]); NULL: A holds the rows in order
   int gather_rows, gather_div; //   rows of A behind the index; the index is divided by gather_div first (flat (row, pick) pairs)
   const int* scatter;        // dense bf16 products with a k-contiguous A, B not k-contiguous, plain bf16 store: row m of the product is

@@ -79,9 +79,7 @@ void mfma_gemm_kernel(GemmDesc p) {
   // folded into this product's operand loads).  A lane's chunks keep their place in the tile;
   // what changes from tile to tile is the memory row behind each of them: its index is read one
   // tile ahead (gather_request) and turned into the mover's offsets once the k loop of the tile
-  // before is over (gather_apply).  Tile rows past the group's end read row gather[..] = 0 of A
-  // (an index beyond the table's range arrives as zero): finite values that only reach output rows
-  // the epilogue does not store.
+  // before is over (gather_apply).  Tile rows past the group's end are out of range: zeros, no traffic.
   static_assert(!GATHER || AK, "gathered rows are k-contiguous rows of A");
   // SCATTER (dense product, plain bf16 store): row m of the result goes to the rows
   // scatter[m * scatter_k + j] of C instead of row m: the shared descending projection writes
@@ -106,10 +104,11 @@ void mfma_gemm_kernel(GemmDesc p) {
       for (int i = 0; i < MoveA::NCH; ++i) gather_idx[i] = __builtin_amdgcn_raw_buffer_load_b32(rg, (unsigned)(t.m0 + gather_row[i]) * 4u, 0, 0);
     }
   };
-  auto gather_apply = [&]() {
+  auto gather_apply = [&](const TileCoord& t) {
     if (GATHER) {
 #pragma unroll
-      for (int i = 0; i < MoveA::NCH; ++i) ma.voff[i] = (gather_idx[i] / (unsigned)p.gather_div) * (unsigned)(p.lda * 2) + gather_col[i];
+      for (int i = 0; i < MoveA::NCH; ++i)
+        ma.voff[i] = ((gather_idx[i] / (unsigned)p.gather_div) * (unsigned)(p.lda * 2) + gather_col[i]) | ((unsigned)(t.m_end - 1 - t.m0 - gather_row[i]) >> 31) * OUT_OF_RANGE;
     }
   };
   const int wrap_tiles = p.kwrap_b ? p.kwrap_b / BK : 0x7FFFFFFF;
@@ -213,7 +212,7 @@ void mfma_gemm_kernel(GemmDesc p) {
   if (id < 0) return;
   TileOperands cur = operands(id);
   gather_request(cur.t);
-  gather_apply();
+  gather_apply(cur.t);
   prefetch(cur);
   request_aux(cur.t);
   // Tile order (see TileClaim): the first tile is this workgroup's slot, every later one is claimed.
@@ -314,7 +313,7 @@ void mfma_gemm_kernel(GemmDesc p) {
     // last stage (the last k step waited for everything that was requested into it).
     __builtin_amdgcn_s_barrier();
     claim.request();                                     // (everyone has read the box)
-    gather_apply();                                      // the mover's rows are now those of the next tile
+    gather_apply(nxt.t);                                 // the mover's rows are now those of the next tile
     // bf16 epilogue staging, in the ring's last stage: the prefetch below fills stages
     // 0 .. NS - 2, and the last stage is requested again only behind the first barrier of the next
     // k loop.  A staged row is 128 bytes = 8 chunks of 16; chunk c of row r sits at position
@@ -707,6 +706,27 @@ int launch_mfma_deep(const GemmDesc& g, hipStream_t s) {
   return BIGMAC_OK;
 }
 
+// Few rows per expert: the product streams the weights, and how fast the memory delivers them depends on the piece that a
+// request covers.  128 x 256 outputs over 32-deep k tiles read 512 bytes of 32 consecutive weight rows.  Streaming 512 MB alone, by
+// tile: 256 bytes of 32 rows 94 to 98 us, 512 bytes of 32 rows 82 to 87, of 16 rows 86 to 101, of 64 rows (the 256 x 256
+// tile) 84 to 95; in whole rows 84 to 87.  Two workgroups per CU; more bytes in flight brought nothing (64 x 128 outputs, 64-deep k tiles 102 us).
+// 64 experts, 4 rows each, 1024 x 4096: up 100.5 -> 92.3 us, down 98.7 -> 90.4 (5.9 TB/s); a tile of 64 rows was level with this one.
+int launch_mfma_stream(const GemmDesc& g, hipStream_t s) {
+  constexpr int BM = 128, BN = 256, BK = 32;
+  dim3 grid = grid_for<BM, BN>(g, false), block(256);
+  if (grid.x > 512) grid.x = 512;
+#define BIGMAC_MFMA_STREAM(EPI, OUTF32, GATHER) \
+  hipLaunchKernelGGL((mfma_gemm_kernel<BM, BN, BK, 1, 4, true, false, EPI, OUTF32, BIGMAC_TILE_STAGES, GATHER>), grid, block, 0, s, g)
+  if (g.epilogue == EPI_GELU && g.gather) BIGMAC_MFMA_STREAM(EPI_GELU, false, true);
+  else if (g.epilogue == EPI_GELU) BIGMAC_MFMA_STREAM(EPI_GELU, false, false);
+  else if (g.epilogue != EPI_STORE || g.gather) return BIGMAC_ERR_UNSUPPORTED;
+  else if (g.out_f32) BIGMAC_MFMA_STREAM(EPI_STORE, true, false);
+  else BIGMAC_MFMA_STREAM(EPI_STORE, false, false);
+#undef BIGMAC_MFMA_STREAM
+  BIGMAC_CHECK_LAUNCH();
+  return BIGMAC_OK;
+}
+
 }  // namespace
 
 // Matrix-core rate probe: every wavefront issues 32x32x16 bf16 MFMAs back to back on four
@@ -810,10 +830,14 @@ int launch_gemm(const GemmDesc& desc, hipStream_t s) {
   }
   if (g.topk.logits && !gemm_takes_topk(g, g.topk.N)) return BIGMAC_ERR_UNSUPPORTED;
   if (g.big_tile) {
-    if (g.dtype != BIGMAC_BF16 || g.tall_tile || g.wide_k || g.deep_tile || g.touch_bytes || g.ksplit != 1) return BIGMAC_ERR_INVALID_ARG;
+    if (g.dtype != BIGMAC_BF16 || g.tall_tile || g.wide_k || g.deep_tile || g.stream_tile || g.touch_bytes || g.ksplit != 1) return BIGMAC_ERR_INVALID_ARG;
     return launch_gemm_phased(g, s);
   }
   if (g.dtype == BIGMAC_BF16) {
+    if (g.stream_tile) {
+      if (g.mode != GEMM_RAGGED_M || combo != 2 || g.tall_tile || g.wide_k || g.deep_tile) return BIGMAC_ERR_INVALID_ARG;
+      return launch_mfma_stream(g, s);
+    }
     if (g.wide_k) {
       if (g.mode == GEMM_RAGGED_K || g.tall_tile || g.deep_tile || !g.a_kcontig || g.K % 64) return BIGMAC_ERR_INVALID_ARG;
       return g.b_kcontig ? launch_mfma_widek<true, true>(g, s) : launch_mfma_widek<true, false>(g, s);

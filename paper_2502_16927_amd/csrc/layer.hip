@@ -234,6 +234,26 @@ inline bool big_ascend_dgrad(const bigmac_dims& D) {
   if (tiles_forced(D, &large) || big_dense(D, D.T, D.r, D.d)) return big_dense(D, D.T, D.r, D.d);
   return !deep_dense(D, D.T, D.r, D.d) && D.d >= 1024 && (long)((D.T + 255) / 256) * ((D.r + 255) / 256) >= 90;
 }
+// Forward row products on 128 x 256 tiles (launch_mfma_stream), of those that the 256 x 256 tile does not take: experts with so few rows
+// that reading the weights is most of it.  Times of one product, the 128 x 128 tile -> here, by experts x 256-wide column tiles.
+// Up (GELU): 256 tiles 36 -> 33 us, 37 -> 34, 39 -> 35; 384 tiles 36 -> 31, 43 -> 38; 512 to 1024 tiles 70 -> 53, 77 -> 61, 92 -> 83, 94 -> 88,
+// 101 -> 93; 128 and 160 tiles 21 -> 26, 17 -> 19; at K 512 the fewer k tiles want more of them (256 and 384 tiles 18 -> 20, 25 -> 27, 512 and
+// 768 tiles 43 -> 38, 57 -> 57); at K 384 29 -> 28, 21 -> 23 us.
+// Down (store): a round of at least 144 tiles 74 -> 68 (144), 95 -> 83, 82 -> 70, 34 -> 30 (192), 61 -> 55 us (256); 64 to 128 tiles 47 -> 60, 33 -> 40, 62 -> 76.
+// A second round that is nearly empty (288 tiles) 62 -> 66 us, half full (384) 83 -> 75, 63 -> 65.  An eighth of the columns padded 97 -> 118 us.
+// Rows: from 24 on (with a K of 512 from 30, stores of a K under 2048 from 40: 24 rows 24 -> 26 us, 31 rows 35 -> 29; 30 rows 20 ->
+// 25, 40 rows 28 -> 26); fewer where the weights come from memory and not from the memory-side cache (512 MB, 2 rows 93 -> 88 and 87 -> 84 us, 12
+// rows 105 -> 97 and 103 -> 95; 384 MB, 13 rows 84 -> 74 and 101 -> 90, 1 or 2 rows 65 -> 67 and 70 -> 76; 215 MB, 12 rows 52 -> 53 and 57 -> 59; 128 MB 14 -> 19); up to
+// 320 rows 77 -> 68 us (larger counts not measured).
+inline bool stream_rows(const bigmac_dims& D, int cols, int K, GemmEpilogue epilogue) {
+  bool large;
+  if (tiles_forced(D, &large) || big_rows(D, cols, K, epilogue)) return false;
+  const bool gelu = epilogue == EPI_GELU;
+  const long each = (long)D.T * D.k / D.N, gx = (cols + 255) / 256, tiles = D.N * gx;
+  if (K < 512 || cols * 10 < gx * 256 * 9 || (tiles > 256 && tiles < 384) || tiles < (!gelu ? 144 : K < 576 ? 512 : 256)) return false;
+  const size_t weights = (size_t)D.N * K * cols * 2;
+  return each <= 320 && (each >= (gelu ? (K < 576 ? 30 : 24) : K < 2048 ? 40 : 24) || (each >= 8 && weights >= (size_t)384 << 20) || (each >= 2 && weights >= (size_t)480 << 20));
+}
 inline bool any_big_rows(const bigmac_dims& D) {   // a tile map of 256-row tiles is needed
   const Widths W = widths(D);
   return big_rows(D, W.hid, W.win, EPI_GELU) || big_rows(D, W.hid, W.win, EPI_DGELU) || big_rows(D, W.win, W.hid, EPI_STORE) ||
@@ -442,8 +462,9 @@ int run_experts_forward(const bigmac_dims& D, const void* x_perm, const int* off
   // hact = gelu(x_perm W1[e])
   g.epilogue = EPI_GELU;
   g.big_tile = big_rows(D, W.hid, W.win, EPI_GELU);
+  g.stream_tile = stream_rows(D, W.hid, W.win, EPI_GELU);
   g.tile_map = g.big_tile ? tile_map_tall : tile_map;
-  g.wide_k = !g.big_tile && !gather && wide_k_ok(D, W.win, 1);
+  g.wide_k = !g.big_tile && !g.stream_tile && !gather && wide_k_ok(D, W.win, 1);
   g.A = x_perm; g.lda = W.win; g.K = W.win;
   g.gather = gather; g.gather_rows = D.T; g.gather_div = D.k;   // with an index, x_perm is the [T, win] rows before the dispatch
   g.B = w1; g.ldb = W.hid; g.gstride_b = (long)W.win * W.hid; g.N = W.hid;
@@ -467,8 +488,9 @@ int run_experts_forward(const bigmac_dims& D, const void* x_perm, const int* off
   g.C = o_perm; g.ldc = W.win;
   g.bias = b2; g.gstride_bias = W.win;
   g.big_tile = big_rows(D, W.win, W.hid, EPI_STORE);
+  g.stream_tile = stream_rows(D, W.win, W.hid, EPI_STORE);
   g.tile_map = g.big_tile ? tile_map_tall : tile_map;
-  g.wide_k = !g.big_tile && wide_k_ok(D, W.hid, 2);
+  g.wide_k = !g.big_tile && !g.stream_tile && wide_k_ok(D, W.hid, 2);
   g.kloop_priority = 1;
   g.touch = nullptr; g.touch_bytes = 0;
   if (!g.big_tile) touch_weights(D, g, w2, 2);

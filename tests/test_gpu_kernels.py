@@ -1,10 +1,12 @@
 """Kernels and dispatch branches at the sizes where they change: edges of tiles, remainders, the smallest and
 largest of a branch's range, each against a plain torch evaluation of the same step."""
+import numpy as np
 import pytest
 import torch
 
 from paper_2502_16927_amd import binding as B
 from paper_2502_16927_amd import synth
+from gpu_util import DeviceLayer, host
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -68,6 +70,40 @@ def test_row_tiles_part_full(flags):
     assert row_rel(act[:total], ref_a) < 2.2e-3
     assert row_rel(o[:total], ref_o) < 3.2e-3
     assert bool((act[total:] == 7).all()) and bool((o[total:] == 7).all())
+
+
+# The 128 x 256 tile of experts with few rows: both products on it (384 and 192 tiles; widths that end inside a column tile), row counts at
+# its edges, against the square tile (the same sums in the same order) and the oracle's bounds of the test above.
+@pytest.mark.parametrize("r,h", [(768, 1536), (704, 1408)])
+def test_few_rows_per_expert(r, h):
+    rows = ([1, 31, 32, 33, 0, 63, 64, 65, 95, 96, 97, 127, 128, 129, 5, 257] * 4)
+    n, total, guard = len(rows), sum(rows), 64
+    g = torch.Generator(device=DEV).manual_seed(r)
+    rand = lambda shape, std: (torch.randn(shape, generator=g, device=DEV) * std).bfloat16()
+    xp, w1, w2 = rand((total, r), 1.0), rand((n, r, h), r ** -0.5), rand((n, h, r), h ** -0.5)
+    outs = []
+    for flags in (0, B.FLAG_TILES_SMALL):
+        dims = B.make_dims(total, 512, r, n, 1, h, B.BF16, flags=flags)
+        act, o = (torch.full((total + guard, w), 7.0, device=DEV, dtype=torch.bfloat16) for w in (h, r))
+        B.bigmac_grouped_ffn(dims, xp, ragged_offsets(rows), w1, w2, act, o, B.alloc_bytes(B.workspace_bytes(dims, B.WS_GROUPED_FFN)))
+        outs.append((act, o))
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
+    act, o = outs[0]
+    ref_a, ref_o = ffn_reference(xp, rows, w1, w2)
+    row_rel = lambda a, b: float(((a.double() - b).norm(dim=1) / b.norm(dim=1)).max())
+    assert row_rel(act[:total], ref_a) < 2.2e-3 and row_rel(o[:total], ref_o) < 3.2e-3
+    assert bool((act[total:] == 7).all()) and bool((o[total:] == 7).all())
+
+
+# ... with the rows through the index (forward-only) and by copy, results in fp32 and in bf16, even and skewed routing, a capacity
+@pytest.mark.parametrize("flags", [0, B.FLAG_WIRE_BF16, B.FLAG_NO_FUSED_DISPATCH])
+@pytest.mark.parametrize("T,k,capacity,zipf", [(641, 4, 0, 0.0), (700, 6, 40, 1.2)])
+def test_few_rows_per_expert_in_the_layer(T, k, capacity, zipf, flags):
+    wl = synth.small(T=T, d=256, r=768, N=64, k=k, h=1536, zipf_s=zipf)
+    data = synth.generate(wl)
+    for training in (False, True):
+        y = [host(DeviceLayer(wl, data, flags=flags | f, capacity=capacity).forward(training=training)).copy() for f in (0, B.FLAG_TILES_SMALL)]
+        assert np.isfinite(y[0]).all() and np.abs(y[0]).max() > 0 and np.array_equal(y[0], y[1])
 
 
 # fp32 products from 2048 tiles on in the layouts of the backward pass: both matrices' data gradients (ragged), dx' W_down^T (dense),
