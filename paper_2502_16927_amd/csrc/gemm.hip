@@ -6,7 +6,7 @@
 // transposition) with XOR swizzles against bank conflicts; operands whose contraction index is
 // not the fast one in memory are fetched with the gfx950 LDS transpose read (ds_read_b64_tr_b16).
 // Workgroup tiles: 128 x 128; 256 x 128 for weight gradients; 128 x 64 and 128 x 128 with 64-deep k tiles for products
-// with few tiles.  The 256 x 256 tile, which most of the larger products run on, is a kernel of its own (gemm_phased.hip).
+// with few tiles; 128 x 256 for experts with few rows.  The 256 x 256 tile, which most of the larger products run on, is a kernel of its own (gemm_phased.hip).
 // fp32 storage: see gemm_f32.hip.
 #include "gemm_core.hpp"
 #include "topk.hpp"
@@ -20,7 +20,8 @@ namespace bigmac {
 // latency.  Every vector memory instruction is issued unconditionally (accesses that must not
 // happen are pushed out of their buffer's range instead of being branched around): the number of
 // instructions in flight behind any load is then a compile-time constant, which is what the
-// counter waits below and the compiler's own ones are derived from.
+// counter waits below and the compiler's own ones are derived from.  (Only an epilogue's sub-tiles past a group's
+// last row are left out: no wait counts on their stores.)
 // SIDE: the workgroups past the product's own take the top-k and gate of some tokens (see gemm_takes_topk).
 template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, bool AK, bool BKC, int EPI, bool OUTF32, int NS = BIGMAC_TILE_STAGES, bool GATHER = false,
           bool SCATTER = false, bool SIDE = false>
