@@ -828,7 +828,10 @@ __global__ __launch_bounds__(ROUTER_DX_THREADS) void router_dx_kernel(const int3
 
 }  // namespace
 
-static bool router_whole_chunks(const bigmac_dims& D) { return D.N % 4 == 0 && (size_t)D.d * D.N * 4 < (1ull << 30); }   // 16-byte pieces of a router row; 32-bit offsets within a stage
+// 16-byte pieces of a router row; 32-bit byte offsets from a tile's first router row and within its up to 32 token rows
+static bool router_whole_chunks(const bigmac_dims& D) {
+  return D.N % 4 == 0 && (size_t)D.d * D.N * 4 < (1ull << 30) && (size_t)D.d * 32 * esize(D.dtype) < (1ull << 31);
+}
 
 bool router_picks(const bigmac_dims& D) { return D.N <= 16 && router_whole_chunks(D); }
 

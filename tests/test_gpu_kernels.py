@@ -366,6 +366,20 @@ def test_router_logits_on_the_matrix_cores(oracle, T, d, N, dtype):
     assert torch.equal(logits.cpu()[rest].view(torch.int32), ref[rest].view(torch.int32)) and logits[odd].isnan().all()
 
 
+# four experts leave room for token rows so long that 15 of them span 2 GiB: past the 32-bit offsets of a tile's rows
+def test_router_logits_of_very_long_rows(oracle):
+    T, d, N = 16, 64 * 560000, 4
+    g = torch.Generator(device=DEV).manual_seed(9)
+    x, w_gate = torch.randn((T, d), generator=g, device=DEV), torch.randn((d, N), generator=g, device=DEV)
+    dims = B.make_dims(T, d, 64, N, 2, 64, B.F32)
+    idx, w, logits = torch.empty((T, 2), dtype=torch.int32, device=DEV), torch.empty((T, 2), device=DEV), torch.empty((T, N), device=DEV)
+    B.bigmac_route(dims, x, w_gate, None, idx, w, logits)
+    at = [0, T - 1]
+    r_idx, r_gate, r_logits = oracle.route(x[at].cpu().numpy(), w_gate.cpu().numpy(), None, 2)
+    assert (logits[at].cpu().numpy().view("uint32") == r_logits.view("uint32")).all() and (idx[at].cpu().numpy() == r_idx).all()
+    assert abs(w[at].cpu().numpy() - r_gate).max() < 1e-6
+
+
 # up to 16 experts the picks and gates come from the launch that works out the logits: the oracle's, ties to the lower index (columns repeat),
 # and k different experts whatever the logits are; a layer of more than 4096 pairs, which counts them, picks the same
 @pytest.mark.parametrize("dtype", [B.BF16, B.F32])
