@@ -242,17 +242,26 @@ inline bool big_ascend_dgrad(const bigmac_dims& D) {
 // Down (store): a round of at least 144 tiles 74 -> 68 (144), 95 -> 83, 82 -> 70, 34 -> 30 (192), 61 -> 55 us (256); 64 to 128 tiles 47 -> 60, 33 -> 40, 62 -> 76.
 // A second round that is nearly empty (288 tiles) 62 -> 66 us, half full (384) 83 -> 75, 63 -> 65.  An eighth of the columns padded 97 -> 118 us.
 // Rows: from 24 on (with a K of 512 from 30, stores of a K under 2048 from 40: 24 rows 24 -> 26 us, 31 rows 35 -> 29; 30 rows 20 ->
-// 25, 40 rows 28 -> 26); fewer where the weights come from memory and not from the memory-side cache (512 MB, 2 rows 93 -> 88 and 87 -> 84 us, 12
-// rows 105 -> 97 and 103 -> 95; 384 MB, 13 rows 84 -> 74 and 101 -> 90, 1 or 2 rows 65 -> 67 and 70 -> 76; 215 MB, 12 rows 52 -> 53 and 57 -> 59; 128 MB 14 -> 19); up to
-// 320 rows 77 -> 68 us (larger counts not measured).
+// 25, 40 rows 28 -> 26) up to 320 (there level, 0.99 to 1.01; larger counts not measured).  257 to 383 tiles: up level (1.01 / 1.02 / 1.02 times as fast
+// under even routing / Zipf 0.6 / Zipf 1.2), down level where routing is even (1.00 / 1.06 / 1.07).
+// Fewer rows, where next to all of the time is the stream of weights: only widths that are powers of two, whose rows all start on the same
+// few memory channels, gain by the larger piece (means over 8300 shapes of 180 to 512 MB of weights per product, 2 rows and more, k 2, 4 and 8, routing as above).  Up,
+// K 1024: from 448 tiles on 1.06 / 1.06 / 1.03, 384 tiles 0.98 / 0.99 / 0.99; K 512 1.03 / 1.01 / 0.94; other widths 1.00 / 1.00 / 0.98.  Down, 1024
+// columns, from 8 rows on: 224 and 256 tiles 1.07 / 1.11 / 1.08, from 448 on 1.06 / 1.07 / 1.06, 320 and 384 0.99 / 1.02 / 1.07, 192 1.02 / 1.11 / 1.03, up to 160
+// 0.88 / 0.91 / 0.85; 512 columns 1.04 / 1.09 / 0.78; other widths 0.99 / 1.03 / 0.98.  Down, 3 to 7 rows: skewed routing leaves CUs without a
+// tile, so only where that costs nothing (from 448 tiles on 1.05 / 1.04 / 1.05) or where even routing gains most (224 and 256 tiles: K 4096 1.07 / 1.08 / 0.91, shorter
+// 1.03 / 1.06 / 0.93; other widths 0.98 / 0.97 / 0.84); 2 rows 1.04 / 0.99 / 0.84.
 inline bool stream_rows(const bigmac_dims& D, int cols, int K, GemmEpilogue epilogue) {
   bool large;
   if (tiles_forced(D, &large) || big_rows(D, cols, K, epilogue)) return false;
   const bool gelu = epilogue == EPI_GELU;
   const long each = (long)D.T * D.k / D.N, gx = (cols + 255) / 256, tiles = D.N * gx;
-  if (K < 512 || cols * 10 < gx * 256 * 9 || (tiles > 256 && tiles < 384) || tiles < (!gelu ? 144 : K < 576 ? 512 : 256)) return false;
-  const size_t weights = (size_t)D.N * K * cols * 2;
-  return each <= 320 && (each >= (gelu ? (K < 576 ? 30 : 24) : K < 2048 ? 40 : 24) || (each >= 8 && weights >= (size_t)384 << 20) || (each >= 2 && weights >= (size_t)480 << 20));
+  if (K < 512 || each > 320 || cols * 10 < gx * 256 * 9 || (tiles > 256 && tiles < 384) || tiles < (!gelu ? 144 : K < 576 ? 512 : 256)) return false;
+  if (each >= (gelu ? (K < 576 ? 30 : 24) : K < 2048 ? 40 : 24)) return true;
+  if (cols & (cols - 1)) return false;
+  if (gelu) return each >= 2 && K >= 1024 && tiles >= 448;
+  const bool chip_full = tiles >= 448;
+  return K >= 2048 && cols >= 1024 && (chip_full || (tiles >= 224 && tiles <= 256)) && each >= (chip_full || K >= 4096 ? 3 : 8);
 }
 inline bool any_big_rows(const bigmac_dims& D) {   // a tile map of 256-row tiles is needed
   const Widths W = widths(D);
