@@ -233,7 +233,7 @@ struct SliceSum {
   int nslices;
 };
 constexpr int SLICE_SUM_LANES = 64;
-inline unsigned slice_sum_blocks(const SliceSum& j) { return (unsigned)((j.n / 4 + SLICE_SUM_LANES - 1) / SLICE_SUM_LANES); }
+inline unsigned slice_sum_blocks(const SliceSum& j, int threads) { return (unsigned)((j.n / 4 + threads - 1) / threads); }
 int launch_reduce_partials_bf16(const SliceSum& job, hipStream_t s);
 
 // ----------------------------------------------------------------------------- route ----

@@ -570,7 +570,7 @@ __global__ __launch_bounds__(SLICE_SUM_LANES) void reduce_partials_bf16_kernel(S
 
 int launch_reduce_partials_bf16(const SliceSum& job, hipStream_t s) {
   if (job.n % 8) return BIGMAC_ERR_INVALID_ARG;
-  hipLaunchKernelGGL(reduce_partials_bf16_kernel, dim3(slice_sum_blocks(job)), dim3(SLICE_SUM_LANES), 0, s, job);
+  hipLaunchKernelGGL(reduce_partials_bf16_kernel, dim3(slice_sum_blocks(job, SLICE_SUM_LANES)), dim3(SLICE_SUM_LANES), 0, s, job);
   BIGMAC_CHECK_LAUNCH();
   return BIGMAC_OK;
 }

@@ -193,7 +193,7 @@ template <int THREADS>
 __global__ __launch_bounds__(THREADS) void perm_place_kernel(const int32_t* __restrict__ idx, int Tk, int pairs_per_chunk, int nchunks, int parts, int N, int NP, int nbits,
                                                              int capacity, const int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
                                                              int32_t* __restrict__ slot_of, int32_t* __restrict__ src_of, TileMapJobs maps, SliceSum beside, int sorting) {
-  if ((int)blockIdx.x >= sorting) {      // the first wavefront of a workgroup past the sort's own
+  if ((int)blockIdx.x >= sorting) {
     slice_sum_block(beside, (int)blockIdx.x - sorting);
     return;
   }
@@ -653,8 +653,8 @@ int launch_build_permutation(int T, int k, int N, int capacity, const int32_t* t
       BIGMAC_CHECK_LAUNCH();
     }
     const int sorting = sc.count + (maps.map[0] ? 1 : 0);
-    const dim3 grid(sorting + (beside ? slice_sum_blocks(*beside) : 0));
     const SliceSum sum = beside ? *beside : SliceSum{};
+    const dim3 grid(sorting + slice_sum_blocks(sum, sc.threads));
 #define BIGMAC_PLACE(THREADS)                                                                                                        \
   hipLaunchKernelGGL(perm_place_kernel<THREADS>, grid, dim3(THREADS), THREADS / 64 * N * sizeof(int), s, topk_idx, Tk, pairs, \
                      sc.count, sc.parts, N, NP, nbits, capacity, counts, expert_offsets, slot_of, src_of, maps, sum, sorting)

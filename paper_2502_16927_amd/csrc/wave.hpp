@@ -108,10 +108,10 @@ __device__ __forceinline__ void gate_backward_row(float w, float g, int e, const
   }
 }
 
-// Work of one wavefront of a SliceSum: four neighbouring elements per lane, eight slices on their way at a time.
+// A workgroup's piece of a SliceSum: four neighbouring elements per thread, eight slices on their way at a time.
 __device__ __forceinline__ void slice_sum_block(const SliceSum& job, int block) {
-  const size_t i = ((size_t)block * SLICE_SUM_LANES + threadIdx.x) * 4;
-  if (threadIdx.x >= SLICE_SUM_LANES || i >= job.n) return;
+  const size_t i = ((size_t)block * blockDim.x + threadIdx.x) * 4;
+  if (i >= job.n) return;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int z = 0; z < job.nslices; z += 8) {
     float4 v[8];

@@ -103,6 +103,22 @@ def test_few_rows_per_expert(r, h, rows, biases):
     assert bool((act[total:] == 7).all()) and bool((o[total:] == 7).all())
 
 
+def median_stage_us(calls, stages, turns=14, skip=4):
+    """Medians of the stages' times, added up, of each call, the calls in turn."""
+    at = [2 * s for s in range(B.STAGE_COUNT) if B.stage_name(s) in stages]
+    times = [[] for _ in calls]
+    for turn in range(turns):
+        for call, t in zip(calls, times):
+            events = B.StageEvents()
+            events.install()
+            call()
+            events.clear()
+            torch.cuda.synchronize()
+            if turn >= skip:
+                t.append(sum(events.events[s].elapsed_time(events.events[s + 1]) for s in at) * 1e3)
+    return [float(np.median(t)) for t in times]
+
+
 # ... and where the rule must not take it: few rows under skewed routing, all of them on 40 of 128 experts, leave most CUs without a tile of 256
 # columns.  704 of them, no power of two, were 1.3 times slower so; the default stays within 1.12 times of the square tile (medians of
 # two equal runs differ by 1 to 3 percent).
@@ -116,19 +132,12 @@ def test_skewed_few_rows_are_not_on_the_slower_tile():
     xp = torch.randn((total, r), generator=g, device=DEV).bfloat16()
     w1, w2 = (torch.empty(s, device=DEV, dtype=torch.bfloat16).normal_(0.0, 0.02, generator=g) for s in ((n, r, h), (n, h, r)))
     offsets, o = ragged_offsets(rows.tolist()), torch.empty((total, r), device=DEV, dtype=torch.bfloat16)
-    down = 2 * next(s for s in range(B.STAGE_COUNT) if B.stage_name(s) == "expert_down")
-    times = {0: [], B.FLAG_TILES_SMALL: []}
-    for turn in range(14):
-        for flags, t in times.items():
-            dims = B.make_dims(total // 2, 512, r, n, 2, h, B.BF16, flags=flags)
-            ws, events = B.alloc_bytes(B.workspace_bytes(dims, B.WS_GROUPED_FFN)), B.StageEvents()
-            events.install()
-            B.bigmac_grouped_ffn(dims, xp, offsets, w1, w2, None, o, ws)
-            events.clear()
-            torch.cuda.synchronize()
-            if turn >= 4:
-                t.append(events.events[down].elapsed_time(events.events[down + 1]) * 1e3)
-    default, small = (float(np.median(t)) for t in times.values())
+    def call(flags):
+        dims = B.make_dims(total // 2, 512, r, n, 2, h, B.BF16, flags=flags)
+        ws = B.alloc_bytes(B.workspace_bytes(dims, B.WS_GROUPED_FFN))
+        return lambda: B.bigmac_grouped_ffn(dims, xp, offsets, w1, w2, None, o, ws)
+
+    default, small = median_stage_us([call(0), call(B.FLAG_TILES_SMALL)], {"expert_down"})
     print(f"expert_down: default {default:.1f} us, small tiles {small:.1f} us", flush=True)
     assert default < 1.12 * small
 
@@ -456,6 +465,25 @@ def test_top_k_beside_the_descending_projection(T, d, r, N, k):
         ys.append(torch.full((T, d), float("nan"), device=DEV))
         B.bigmac_layer_forward(dims, params, x, ys[-1], saved, ws)
     assert ys[0].isfinite().all() and torch.equal(ys[0], ys[1])
+
+
+# The slices' sum beside the sort must not be slower than the launch of its own that a router on x' leaves it: 256 experts, whose sort
+# has workgroups of 1024 threads (with one of 16 wavefronts summing 1.1 times slower; 1.04 allows for the spread of the medians).
+def test_slice_sums_beside_a_large_sort():
+    T, d, r, N, k, h = 4096, 4096, 1024, 256, 4, 64
+    g = torch.Generator(device=DEV).manual_seed(7)
+    bf = lambda *s: torch.empty(s, device=DEV, dtype=torch.bfloat16).normal_(0.0, 0.05, generator=g)
+    x, y, w = bf(T, d), torch.empty((T, d), device=DEV), [bf(*s) for s in ((d, r), (r, d), (N, r, h), (N, h, r))]
+
+    def call(flags):
+        dims = B.make_dims(T, d, r, N, k, h, B.BF16, flags=flags)
+        params = B.make_params(w[0], w[1], torch.randn((r if flags else d, N), generator=g, device=DEV), None, w[2], w[3])
+        ws = B.alloc_bytes(B.workspace_bytes(dims, B.WS_LAYER_FORWARD))
+        return lambda: B.bigmac_layer_forward(dims, params, x, y, None, ws)
+
+    beside, apart = median_stage_us([call(0), call(B.FLAG_ROUTE_LOW)], {"descend", "permutation"})
+    print(f"descend + permutation: sum beside the sort {beside:.1f} us, in a launch of its own {apart:.1f} us", flush=True)
+    assert beside < 1.04 * apart
 
 
 # the summed slices of a dense product, to bf16 as to fp32 (the same sums in the same order): 2, 5 and 10 slices, few elements
