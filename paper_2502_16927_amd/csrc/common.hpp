@@ -246,7 +246,7 @@ struct TopkGrid {
   int workgroups, threads, tokens;   // tokens per workgroup
 };
 TopkGrid topk_grid(int T, int k, int N, bool counting);
-TopkJob topk_job(const bigmac_dims& D, const float* logits, int32_t* topk_idx, float* topk_w, int32_t* counts);
+TopkJob topk_job_beside(const bigmac_dims& D, const float* logits, int32_t* topk_idx, float* topk_w, int32_t* counts);   // for GemmDesc::topk
 int launch_topk_gate(const bigmac_dims& D, const float* logits, int32_t* topk_idx, float* topk_w, hipStream_t s, int32_t* counts = nullptr);
 // Gate backward (softmax over the k picked logits) and the router's share of dx:
 //   dlogit[t,j] = w[t,j] (dgate[t,j] - sum_m w[t,m] dgate[t,m])

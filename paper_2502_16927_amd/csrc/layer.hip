@@ -799,7 +799,7 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
     }
     // (the loss reads the picks, and 16 experts' are there already)
     if (!low_router && !scatter_descend && !aux && (chunk_counts || !router_picks(*D)) && gemm_takes_topk(down, D->N))
-      down.topk = topk_job(*D, logits, topk_idx, topk_w, chunk_counts);
+      down.topk = topk_job_beside(*D, logits, topk_idx, topk_w, chunk_counts);
   }
   if (!low_router) {   // Section 3.1's default: the router reads the full-width token
     rc = route(x, down.topk.logits != nullptr);

@@ -467,6 +467,25 @@ def test_top_k_beside_the_descending_projection(T, d, r, N, k):
     assert ys[0].isfinite().all() and torch.equal(ys[0], ys[1])
 
 
+# The picks beside the projection must cost less than a launch of their own, 3.5 us here over an empty interval, on top of the projection
+# alone (a router on x' picks behind it): 128 experts, no counting; 4.7 us more when each wavefront sorted its one token twice, 1.8 since.
+def test_top_k_beside_the_descending_projection_pays():
+    T, d, r, N, k, h = 4096, 512, 512, 128, 1, 64
+    g = torch.Generator(device=DEV).manual_seed(7)
+    bf = lambda *s: torch.empty(s, device=DEV, dtype=torch.bfloat16).normal_(0.0, 0.05, generator=g)
+    x, y, w = bf(T, d), torch.empty((T, d), device=DEV), [bf(*s) for s in ((d, r), (r, d), (N, r, h), (N, h, r))]
+
+    def call(flags):
+        dims = B.make_dims(T, d, r, N, k, h, B.BF16, flags=flags)
+        params = B.make_params(w[0], w[1], torch.randn((r if flags else d, N), generator=g, device=DEV), None, w[2], w[3])
+        ws = B.alloc_bytes(B.workspace_bytes(dims, B.WS_LAYER_FORWARD))
+        return lambda: B.bigmac_layer_forward(dims, params, x, y, None, ws)
+
+    with_picks, alone = median_stage_us([call(0), call(B.FLAG_ROUTE_LOW)], {"descend"}, turns=24)
+    print(f"descend: with the picks {with_picks:.1f} us, alone {alone:.1f} us", flush=True)
+    assert with_picks - alone < 3.2
+
+
 # The slices' sum beside the sort must not be slower than the launch of its own that a router on x' leaves it: 256 experts, whose sort
 # has workgroups of 1024 threads (with one of 16 wavefronts summing 1.1 times slower; 1.04 allows for the spread of the medians).
 def test_slice_sums_beside_a_large_sort():
