@@ -828,9 +828,10 @@ __global__ __launch_bounds__(ROUTER_DX_THREADS) void router_dx_kernel(const int3
 
 }  // namespace
 
-// 16-byte pieces of a router row; 32-bit byte offsets from a tile's first router row and within its up to 32 token rows
+// 16-byte pieces of a router row; 32-bit byte offsets within a tile's up to 32 token rows.  (Router rows are addressed stage by stage, by 64-bit
+// bases.  From 2 GiB of them on the kernel with one 64-bit address per load, as ever.)
 static bool router_whole_chunks(const bigmac_dims& D) {
-  return D.N % 4 == 0 && (size_t)D.d * D.N * 4 < (1ull << 30) && (size_t)D.d * 32 * esize(D.dtype) < (1ull << 31);
+  return D.N % 4 == 0 && (size_t)D.d * D.N * 4 < (1ull << 31) && (size_t)D.d * 32 * esize(D.dtype) < (1ull << 31);
 }
 
 bool router_picks(const bigmac_dims& D) { return D.N <= 16 && router_whole_chunks(D); }

@@ -427,6 +427,30 @@ def test_router_logits_of_very_long_rows(oracle):
     assert abs(w[at].cpu().numpy() - r_gate).max() < 1e-6
 
 
+# either side of 1 GiB of router weights: the same kernel, bit for bit, in the same time per row (1.3 allows for what is left over in rounds)
+def test_router_logits_of_large_router_weights(oracle):
+    T, N, times = 48, 1024, []
+    g = torch.Generator(device=DEV).manual_seed(9)
+    for d in (64 * 4095, 64 * 4097):
+        x, w_gate = torch.randn((T, d), generator=g, device=DEV).bfloat16(), torch.randn((d, N), generator=g, device=DEV)
+        dims = B.make_dims(T, d, 64, N, 2, 64, B.BF16)
+        idx, w, logits = torch.empty((T, 2), dtype=torch.int32, device=DEV), torch.empty((T, 2), device=DEV), torch.empty((T, N), device=DEV)
+        us = []
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            B.bigmac_route(dims, x, w_gate, None, idx, w, logits)
+            b.record()
+            torch.cuda.synchronize()
+            us.append(a.elapsed_time(b) * 1e3)
+        times.append(float(np.median(us[1:])))
+        r_logits = oracle.router_logits(x[-1:].float().cpu().numpy(), w_gate.cpu().numpy(), None)
+        assert (logits[-1:].cpu().numpy().view("uint32") == r_logits.view("uint32")).all()
+        del x, w_gate
+    print(f"route: {times[0]:.0f} us under 1 GiB, {times[1]:.0f} us past it", flush=True)
+    assert times[1] < 1.3 * times[0]
+
+
 # up to 16 experts the picks and gates come from the launch that works out the logits: the oracle's, ties to the lower index (columns repeat),
 # and k different experts whatever the logits are; a layer of more than 4096 pairs, which counts them, picks the same
 @pytest.mark.parametrize("dtype", [B.BF16, B.F32])
