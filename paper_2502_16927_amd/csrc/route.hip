@@ -170,8 +170,8 @@ struct RouterJob {
   float* topk_w;
   int k;
 };
-// PICK (one 16-wide tile holds all experts): the tile's top-k and gate behind its logits, as topk_gate_kernel works them out, in 16 lanes
-// per token.
+// PICK (one 16-wide tile holds all experts): the tile's top-k and gate behind its logits, as topk_gate_kernel works them out, in the 16 lanes
+// that hold a token's logits.
 template <typename XT, int TT, int ET, int QQT, bool PICK = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void router_logits_matrix_kernel(RouterJob job) {
@@ -460,17 +460,9 @@ void router_logits_matrix_kernel(RouterJob job) {
           }
           logits[(size_t)t * N + n] = sum[0];
         }
-        if constexpr (PICK) asm volatile("ds_write_b32 %0, %1" ::"v"(lds_at + (unsigned)(C::BIAS_AT + 1024 + threadIdx.x * 4)), "v"(sum[0]) : "memory");
-      }
-      if constexpr (PICK) {
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        if (wave < 4) {                                   // lane l: expert l % 16 of token 4 wave + l / 16
-          const int expert = lane & 15, t = t0 + wave * 4 + (lane >> 4), first = lane & 48;
-          unsigned own[1];
-          lds_read_b32<0>(lds_at + (unsigned)(C::BIAS_AT + 1024 + wave * 256 + lane * 4), own[0]);
-          lds_wait(own);
-          unsigned long long key[1] = {expert < N ? logit_key(__uint_as_float(own[0]), expert) : (unsigned)~expert};
+        if constexpr (PICK) {                             // lane l: expert l % 16 of token 4 wave + l / 16
+          const int expert = lane & 15, first = lane & 48;
+          unsigned long long key[1] = {expert < N ? logit_key(sum[0], expert) : (unsigned)~expert};
           sort_keys<16>(key, expert);
           const float logit = key_logit(key[0]), m = __shfl(logit, first, 64), e = expert < job.k ? expf(logit - m) : 0.0f;
           float all = 0.0f;
