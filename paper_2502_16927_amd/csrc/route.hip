@@ -158,6 +158,155 @@ template <int OFFSET>
 __device__ __forceinline__ void lds_write_b64(unsigned addr, u32x2_t v) {
   asm volatile("ds_write_b64 %0, %1 offset:%2" ::"v"(addr), "v"(v), "n"(OFFSET) : "memory");
 }
+// The same sums for few tokens of few elements (N % 4 == 0; see launch_router_logits), on the vector ALU: TB tokens per wavefront, 16 experts per
+// workgroup of four.  Bound by latency: what counts is the chain from the launch over the first loads to the logits, which is shorter here than
+// in the matrix kernel below (no rounding up to stages of 256 elements, the tree in registers instead of through the LDS).  Tiles of 128 elements of the
+// tokens and of the router's columns travel global -> LDS directly (16 bytes per lane) through a ring of three, two in flight while one is
+// consumed.  Token rows past T and router rows past d lie outside the buffer ranges and arrive as zeros; they are never used anyway.
+template <typename XT, int TB>
+__global__ __launch_bounds__(256) void router_logits_few_kernel(const XT* __restrict__ x, const float* __restrict__ wg, const float* __restrict__ bias,
+                                                                float* __restrict__ logits, int T, int d, int N) {
+  constexpr int S = 3, QQT = 2, TROWS = 64 * QQT;   // ring stages; 64-element blocks of a tile
+  constexpr int ES = (int)sizeof(XT), TOKENS = 4 * TB, ACCS = TB * R_NB;
+  constexpr int XROW = TROWS * ES / 16;             // 16-byte chunks per token row of a tile
+  constexpr int XCH = TOKENS * XROW;                // chunks of a token tile: at most one per thread, or whole passes
+  constexpr int XL = (XCH + 255) / 256, WL = TROWS * 4 / 256, LPT = XL + WL;
+  __shared__ uint4 xring[S * XL * 256], wring[S * WL * 256];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  // The workgroups of a token block lie 8 apart, that is on one XCD: its token rows come from memory once.
+  const int slices = (N + R_NB - 1) / R_NB, lin = (int)(blockIdx.x >> 3);
+  const int tb = ((lin / slices) * 8 + (int)(blockIdx.x & 7)) * TOKENS, n0 = (lin % slices) * R_NB;
+  if (tb >= T) return;
+  const int nq = d / 64, ntiles = (nq + QQT - 1) / QQT;
+  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)(x + (size_t)tb * d), 0, (int)((size_t)min(TOKENS, T - tb) * d * ES), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)(wg + n0), 0, (int)(((size_t)(d - 1) * N + min(R_NB, N - n0)) * 4), 0x00020000);
+  unsigned xoff[XL], woff[WL];
+#pragma unroll
+  for (int i = 0; i < XL; ++i) {
+    const int q = i * 256 + (int)threadIdx.x;
+    xoff[i] = q < XCH ? (unsigned)((q / XROW) * d * ES + (q % XROW) * 16) : 0x80000000u;
+  }
+  // LDS position q holds column chunk (q & 3) ^ ((row >> 2) & 3) of row q >> 2: the 16 rows of one pass of a 16-byte read fall on 16
+  // different bank groups
+#pragma unroll
+  for (int i = 0; i < WL; ++i) {
+    const int q = i * 256 + (int)threadIdx.x, row = q >> 2;
+    woff[i] = (unsigned)((row * N + (((q & 3) ^ ((row >> 2) & 3)) << 2)) * 4);
+  }
+  const int wave_chunk = __builtin_amdgcn_readfirstlane((int)(threadIdx.x & ~63u));
+  auto issue = [&](int tile) {
+    uint4* xs = xring + (tile % S) * (XL * 256) + wave_chunk;
+    uint4* ws = wring + (tile % S) * (WL * 256) + wave_chunk;
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+    for (int i = 0; i < XL; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (__attribute__((address_space(3))) void*)(xs + i * 256), 16, xoff[i] + (unsigned)(tile * TROWS * ES), 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < WL; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (__attribute__((address_space(3))) void*)(ws + i * 256), 16, woff[i] + (unsigned)(tile * TROWS * N * 4), 0, 0, 0);
+#else
+    (void)xs; (void)ws;
+#endif
+  };
+  float acc[ACCS];
+#pragma unroll
+  for (int v = 0; v < ACCS; ++v) acc[v] = 0.0f;
+  // The tile reads are assembly: the compiler would make an LDS access that it can see wait for every direct-to-LDS load in flight, the
+  // next tiles' included.  No branch lies between a read and the wait for it (the compiler may copy a register there).
+  const unsigned xring_at = lds_address(xring) + (unsigned)((wave * TB * TROWS + lane) * ES), wring_at = lds_address(wring) + (unsigned)(lane * 64);
+  unsigned xraw[QQT][TB];                           // (a bf16 element arrives in the upper half; the lower one is zero for good)
+  u32x4_t wraw[QQT][4];
+#pragma unroll
+  for (int i = 0; i < QQT * TB; ++i) xraw[i % QQT][i / QQT] = 0u;
+  auto request = [&](int tile, auto block) {
+    constexpr int QQ = decltype(block)::value;
+    const unsigned stage = (unsigned)(tile % S), xat = xring_at + stage * (XL * 256 * 16), wat = wring_at + stage * (WL * 256 * 16);
+    auto& xs = xraw[QQ];
+    auto& ws = wraw[QQ];
+    static_for<0, TB>([&](auto token) {
+      constexpr int I = decltype(token)::value;
+      if constexpr (ES == 2) lds_read_high_u16<(I * TROWS + QQ * 64) * 2>(xat, xs[I]);
+      else lds_read_b32<(I * TROWS + QQ * 64) * 4>(xat, xs[I]);
+    });
+#pragma unroll
+    for (int c = 0; c < 4; ++c) lds_read_b128<QQ * 64 * 64>(wat + (unsigned)((c ^ ((lane >> 2) & 3)) * 16), ws[c]);
+  };
+  auto arrive = [&](auto block) {
+    constexpr int QQ = decltype(block)::value;
+    auto& xs = xraw[QQ];
+    auto& ws = wraw[QQ];
+    lds_wait(xs);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) asm volatile("" : "+v"(ws[c]));
+  };
+  auto add = [&](auto block) {
+    constexpr int QQ = decltype(block)::value;
+#pragma unroll
+    for (int i = 0; i < TB; ++i)
+#pragma unroll
+      for (int c = 0; c < R_NB; ++c) acc[i * R_NB + c] = fmaf(__uint_as_float(xraw[QQ][i]), __uint_as_float(wraw[QQ][c >> 2][c & 3]), acc[i * R_NB + c]);
+  };
+  constexpr StaticIndex<0> I0{};
+  constexpr StaticIndex<1> I1{};
+  // At tile t a wavefront waits until only the tiles requested after t are in flight; the barrier makes that true for everyone's part of t
+  // and says that everyone has left tile t - 1, whose stage then takes tile t + S - 1.
+  for (int tile = 0; tile < S - 1 && tile < ntiles; ++tile) issue(tile);
+  for (int tile = 0; tile < ntiles; ++tile) {
+    if (tile + 1 < ntiles) BIGMAC_WAIT_VMCNT(LPT);
+    else BIGMAC_WAIT_VMCNT(0);
+    __builtin_amdgcn_s_barrier();
+    if (tile + S - 1 < ntiles) issue(tile + S - 1);
+    if (tile * QQT + 1 < nq) {
+      request(tile, I0);
+      request(tile, I1);
+      arrive(I0);
+      arrive(I1);
+      add(I0);
+      add(I1);
+    } else {
+      request(tile, I0);
+      arrive(I0);
+      add(I0);
+    }
+  }
+  // Halving tree (lane l with lane l ^ off).  While a lane holds two or more sums a step is a reduce-scatter (see router_logits_kernel): at
+  // distances 32 and 16 one swap exchanges the upper half (odd 16-lane rows) of one sum with the lower half (even rows) of another, and
+  // every lane then holds what it keeps and what its partner sent; once a lane is down to one sum both lanes of a pair add the
+  // other's.  The sum of accumulator v ends on the lanes whose top bits spell v.
+  constexpr int SCATTER_STEPS = TB == 2 ? 5 : 4;
+  static_assert(ACCS == 1 << SCATTER_STEPS, "1 or 2 tokens per wavefront");
+  static_for<0, 6>([&](auto n) {
+    constexpr int step = decltype(n)::value, off = 32 >> step, half = ACCS >> (step + 1);
+    if constexpr (off >= 16) {
+#pragma unroll
+      for (int v = 0; v < half; ++v) {
+        const unsigned a = __float_as_uint(acc[v]), b = __float_as_uint(acc[v + half]);
+        if constexpr (off == 32) {
+          const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+          acc[v] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        } else {
+          const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+          acc[v] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        }
+      }
+    } else if constexpr (step < SCATTER_STEPS) {
+      const bool hi = (lane & off) != 0;
+#pragma unroll
+      for (int v = 0; v < half; ++v) {
+        const float send = hi ? acc[v] : acc[v + half], keep = hi ? acc[v + half] : acc[v];
+        acc[v] = keep + __uint_as_float(from_lane_xor<off>(__float_as_uint(send), lane));
+      }
+    } else {
+      acc[0] = acc[0] + __uint_as_float(from_lane_xor<off>(__float_as_uint(acc[0]), lane));
+    }
+  });
+  constexpr int SHARE = 6 - SCATTER_STEPS;          // low lane bits that hold copies of the same sum
+  if ((lane & ((1 << SHARE) - 1)) == 0) {
+    const int v = lane >> SHARE, t = tb + wave * TB + v / R_NB, n = n0 + v % R_NB;
+    if (t < T && n < N) logits[(size_t)t * N + n] = bias ? acc[0] + bias[n] : acc[0];
+  }
+}
+
 struct RouterJob {
   const void* x;
   const float *wg, *bias;
@@ -839,12 +988,30 @@ int launch_router_logits(const bigmac_dims& D, const void* x, const float* w_gat
     BIGMAC_CHECK_LAUNCH();
     return BIGMAC_OK;
   }
+  // Few tokens of few elements: the kernel on the vector ALU (1 token per wavefront up to three workgroups per CU, else 2).  bigmac_route, us, this kernel /
+  // the tiles below: up to 256 workgroups T 32, N 64: d 64 4.9 / 6.2, d 512 6.1 / 6.9, d 1024 7.5 / 7.8, d 1280 8.2 / 8.4 (fp32 8.3 / 8.4; N 20,
+  // T 500 8.9 / 8.8); up to 512 T 500, N 64: d 256 5.8 / 6.4, d 768 7.3 / 7.6, d 1024 8.0 / 8.2 (fp32 8.4 / 8.3); up to 768 T 700, N 64:
+  // d 384 6.7 / 7.2, d 512 7.1 / 7.3, d 768 8.1 / 7.8, T 500, N 96, d 512 8.3 / 8.2; two tokens T 1400, N 64: d 384 7.6 / 8.4, d 512 8.5 / 8.5; up
+  // to 1024 of them T 2000, N 64: d 128 7.0 / 7.4, d 384 8.6 / 8.5; T 1400, N 96 (1050): d 128 8.7 / 8.5.
+  const long slices = (D.N + R_NB - 1) / R_NB, one = ((long)D.T + 3) / 4 * slices, two = ((long)D.T + 7) / 8 * slices;
+  if (!topk_idx && D.d <= (one <= 256 ? 1024 : one <= 512 ? 768 : two <= 768 ? 384 : two <= 1024 ? 128 : 0)) {
+    const int tokens = one <= 768 ? 4 : 8;
+    const dim3 grid((unsigned)(((D.T + tokens - 1) / tokens + 7) / 8 * 8 * slices));
+#define BIGMAC_ROUTER_FEW(XT, TB) hipLaunchKernelGGL((router_logits_few_kernel<XT, TB>), grid, dim3(256), 0, s, (const XT*)x, w_gate, bias, logits, D.T, D.d, D.N)
+    if (D.dtype == BIGMAC_BF16 && tokens == 4) BIGMAC_ROUTER_FEW(bf16_t, 1);
+    else if (D.dtype == BIGMAC_BF16) BIGMAC_ROUTER_FEW(bf16_t, 2);
+    else if (tokens == 4) BIGMAC_ROUTER_FEW(float, 1);
+    else BIGMAC_ROUTER_FEW(float, 2);
+#undef BIGMAC_ROUTER_FEW
+    BIGMAC_CHECK_LAUNCH();
+    return BIGMAC_OK;
+  }
   // Tile of a workgroup: 32 x 32 logits keep the multipliers busiest, smaller ones give more workgroups.  A tile takes a time per 64 rows
   // of d and one of its own (start, reduction), and a CU, which holds one workgroup, its share of the tiles one after the other.
   // Measured, us with the top-k, 32 x 32 / 16 x 32 / 16 x 16: d 4096, N 64: T 32 25.2 / 17.8 / 12.9, T 2048 25.5 / 19.5 / 21.8,
   // T 8192 48.3 / 56.9 / 65.0; d 1024, N 64: T 3001 12.7 / 14.9 / 14.3, T 8192 20.7 / 24.8 / 27.7; T 32768, d 4096, N 128 355 / 415 / 542;
-  // T 30000, d 1280, N 8 45.1 / 52.9 / 36.6.  The kernel of fused multiply-adds on the vector ALU that this one took the place of: 16.1,
-  // 25.5, 67.0; 13.5, 26.3; 504; 37.3 (and 3.4 us where this one takes 4.2 at the smallest fp32 sizes: T 256, d 256, N 8).
+  // T 30000, d 1280, N 8 45.1 / 52.9 / 36.6.  Fused multiply-adds on the vector ALU, up to 8 tokens per wavefront: 16.1, 25.5, 67.0; 13.5,
+  // 26.3; 504; 37.3.
   auto tile_rounds = [&](int tokens, int experts) {   // tiles of an XCD over its 32 CUs
     const long groups = (((long)D.T + tokens - 1) / tokens + 7) / 8 * ((D.N + experts - 1) / experts);
     return (double)((groups + 31) / 32);

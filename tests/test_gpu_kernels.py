@@ -371,11 +371,12 @@ def test_picks_of_non_finite_logits(N, k):
     assert (idx.sort(dim=1).values.diff(dim=1) > 0).all()
 
 
-# router logits, bit for bit: 1, 2, 4 and 8 tokens per wavefront, either side of each line (768 workgroups; 512 and 1024 of eight)
+# router logits of few tokens, bit for bit: 1 and 2 tokens per wavefront, either side of each line (256, 512 and 768 workgroups of one token per
+# wavefront, 768 and 1024 of two; d 128, 384, 768 and 1024), one token, experts that end inside a slice, 1 to 16 blocks of 64 elements
 @pytest.mark.parametrize("dtype", [B.BF16, B.F32])
-@pytest.mark.parametrize("T,N", [(384, 128), (385, 128), (769, 128), (1537, 128), (2049, 128), (4065, 128), (6145, 12), (3073, 40)])
-def test_router_logits_tokens_per_wavefront(oracle, T, N, dtype):
-    d = 192
+@pytest.mark.parametrize("T,d,N", [(384, 192, 128), (385, 192, 128), (768, 384, 128), (769, 384, 128), (1024, 128, 128), (1025, 128, 128), (1000, 192, 128), (2056, 192, 40), (2049, 192, 40), (2049, 64, 20), (1, 64, 20), (1, 1024, 1024),
+                                   (128, 1024, 128), (129, 1024, 128), (128, 1088, 128), (256, 768, 128), (257, 768, 128), (256, 832, 128), (9, 320, 68), (1030, 128, 24)])
+def test_router_logits_tokens_per_wavefront(oracle, T, d, N, dtype):
     g = torch.Generator(device=DEV).manual_seed(T + N)
     x = torch.randn((T, d), generator=g, device=DEV).to(torch.bfloat16 if dtype == B.BF16 else torch.float32)
     w_gate, bias = torch.randn((d, N), generator=g, device=DEV), torch.randn(N, generator=g, device=DEV)
@@ -385,6 +386,34 @@ def test_router_logits_tokens_per_wavefront(oracle, T, N, dtype):
     ref = torch.from_numpy(oracle.router_logits(x.float().cpu().numpy(), w_gate.cpu().numpy(), bias.cpu().numpy()))
     assert torch.equal(logits.cpu().view(torch.int32), ref.view(torch.int32))
     assert (idx[:, 0].cpu().long() == ref.argmax(dim=1)).all()
+
+
+# ... and why they are not on the matrix cores' tiles: bigmac_route for few tokens of few elements takes 1.2 times as long with 64 experts as with 16, whose
+# picks need no second launch (on the tiles 1.5 times; medians of runs of 400 calls)
+def test_router_of_few_tokens_is_not_on_the_slower_kernel():
+    T, d, k = 32, 64, 4
+    x, times, graphs = torch.randn((T, d), device=DEV).bfloat16(), {16: [], 64: []}, {}
+    for N in times:
+        dims = B.make_dims(T, d, 64, N, k, 64, B.BF16)
+        held = torch.randn((d, N), device=DEV), torch.empty((T, k), dtype=torch.int32, device=DEV), torch.empty((T, k), device=DEV), torch.empty((T, N), device=DEV)
+        B.bigmac_route(dims, x, held[0], None, *held[1:])
+        torch.cuda.synchronize()
+        graphs[N] = torch.cuda.CUDAGraph(), held
+        with torch.cuda.graph(graphs[N][0]):
+            for _ in range(20):
+                B.bigmac_route(dims, x, held[0], None, *held[1:])
+    for turn in range(12):
+        for N, t in times.items():
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(20):
+                graphs[N][0].replay()
+            end.record()
+            torch.cuda.synchronize()
+            t.append(start.elapsed_time(end) / 400 * 1e3)
+    few, many = (float(np.median(t[2:])) for t in times.values())
+    print(f"bigmac_route: {few:.2f} us with 16 experts, {many:.2f} us with 64", flush=True)
+    assert many < 1.33 * few
 
 
 # router logits on the matrix cores, bit for bit: each tile (32 x 32: many tokens; 16 x 32; 16 x 16: few), ragged tokens and columns, one
