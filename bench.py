@@ -41,12 +41,13 @@ MEASURED_TRAFFIC = {   # stage -> (MiB read, MiB written) per launch
 }
 
 
-def stage_work(wl, order_cdac: bool, training: bool, wire_bf16: bool = False, paired: bool = False):
+def stage_work(wl, order_cdac: bool, training: bool, wire_bf16: bool = False, paired: bool = False, topk: int = 0):
     """Algorithmic work per stage: (kind, flops, bytes).  Bytes are compulsory traffic: every
     input read once, every output written once, real rows only.  e = bytes per stored element,
     ew = bytes per element of the rows that return through the second All-to-All (expert outputs)
     and of their backward counterpart (fp32 unless the all-bf16 wire format is asked for).  paired: one
-    kernel does both expert products, as the stage of the first; the hidden rows never reach memory."""
+    kernel does both expert products, as the stage of the first; the hidden rows never reach memory.  topk: where the
+    experts are picked (0 a kernel of its own; 1 the logits' kernel, which holds what it picks from; 2 beside the descending projection)."""
     T, d, r, N, k, h = wl.T, wl.d, wl.r, wl.N, wl.k, wl.h
     e = 2 if wl.dtype == 1 else 4
     ew = 2 if (e == 2 and wire_bf16) else 4
@@ -61,6 +62,10 @@ def stage_work(wl, order_cdac: bool, training: bool, wire_bf16: bool = False, pa
     W["dispatch"] = ("hbm", 0.0, (T + Tk) * win * e + 4 * Tk)
     W["expert_up"] = ("mfma", 2.0 * Tk * win * hid, Tk * win * e + N * win * hid * e + Tk * hid * e * (2 if training else 1))
     W["expert_down"] = ("mfma", 2.0 * Tk * hid * win, Tk * hid * e + N * win * hid * e + Tk * win * ew)
+    if topk:
+        into = "router_logits" if topk == 1 else "descend"
+        kind, flops, nbytes = W[into]
+        W[into] = (kind, flops, nbytes + 8 * Tk + (T * N * 4 if topk == 2 else 0))
     if paired:
         W["expert_up"] = ("mfma", 4.0 * Tk * win * hid, Tk * win * e + 2 * N * win * hid * e + Tk * win * ew)
         del W["expert_down"]
@@ -86,9 +91,12 @@ def stage_work(wl, order_cdac: bool, training: bool, wire_bf16: bool = False, pa
     return W
 
 
-def live_stages(order_cdac: bool, training: bool, paired: bool = False) -> set:
-    """Names of the stages that the layer calls record (a dispatch folded into a product excepted).  paired: see stage_work."""
-    live = {"router_logits", "topk_gate", "permutation", "dispatch", "expert_up", "combine"}
+def live_stages(order_cdac: bool, training: bool, paired: bool = False, topk: int = 0, loss: bool = False) -> set:
+    """Names of the stages that the layer calls record (a dispatch folded into a product excepted).  paired, topk: see
+    stage_work; loss: with the load-balance loss, which is part of the top-k's stage wherever the experts are picked."""
+    live = {"router_logits", "permutation", "dispatch", "expert_up", "combine"}
+    if not topk or loss:
+        live.add("topk_gate")
     if not paired:
         live.add("expert_down")
     if training:
@@ -357,11 +365,12 @@ def main():
 
     ms_per_step = elapsed / args.steps * 1e3
     paired = B.expert_pairing(dims, training)
-    work = stage_work(wl, cdac, training, args.wire_bf16, paired)
+    topk = B.topk_folding(dims, training)
+    work = stage_work(wl, cdac, training, args.wire_bf16, paired, topk)
     stage_ms = {}
     if tables:
         names = [B.stage_name(s) for s in range(B.STAGE_COUNT)]
-        live = {names.index(n) for n in live_stages(cdac, training, paired)}
+        live = {names.index(n) for n in live_stages(cdac, training, paired, topk, args.aux_alpha > 0)}
         for tb in tables:
             for s, ms in tb.elapsed_ms(live).items():
                 stage_ms[names[s]] = stage_ms.get(names[s], 0.0) + ms / args.steps
@@ -416,6 +425,7 @@ def main():
         "roofline": roofline,
         "matrix_tflops": fwd_flops * (3 if training else 1) / (elapsed / args.steps) / 1e12,
         "permute_bytes_per_step": B.permute_bytes(dims) * (1.0 if training else 0.5),
+        "topk": {0: "kernel of its own", 1: "in the logits' kernel", 2: "beside the descending projection"}[topk],
         "dispatch": {0: "copy kernel", 1: "folded into the expert-up product (rows read through src_of)",
                      2: "folded into the descending projection (rows written through slot_of)"}[folding],
         **({"experts": "one kernel for both products (expert_up)"} if paired else {}),

@@ -233,9 +233,9 @@ int bigmac_saved_aux_layout(const bigmac_dims *dims, size_t *off_aux_loss, size_
  * it is not thread-safe.  Returns BIGMAC_OK. */
 typedef enum {
   BIGMAC_STAGE_ROUTER_LOGITS = 0, /* F0  x W_g                                   */
-  BIGMAC_STAGE_TOPK_GATE,         /* F1  top-k and gate values                   */
-  BIGMAC_STAGE_DESCEND,           /* F2  x' = x W_down                           */
-  BIGMAC_STAGE_PERMUTATION,       /* F3  counting sort + tile maps               */
+  BIGMAC_STAGE_TOPK_GATE,         /* F1  top-k and gate values, unless F0's or F2's kernel has them (bigmac_topk_folding); load-balance loss */
+  BIGMAC_STAGE_DESCEND,           /* F2  x' = x W_down; with F1 where it is folded in */
+  BIGMAC_STAGE_PERMUTATION,       /* F3  counting sort + tile maps; where F2 is summed from K slices and the router reads x: that sum too */
   BIGMAC_STAGE_DISPATCH,          /* F4  first All-to-All (row scatter)          */
   BIGMAC_STAGE_EXPERT_UP,         /* F5  act(x_perm W1[e]); with . W2[e] where one kernel does both (bigmac_expert_pairing) */
   BIGMAC_STAGE_EXPERT_DOWN,       /* F6  . W2[e], unless F5's kernel has done it */
@@ -291,6 +291,12 @@ int bigmac_dispatch_folding(const bigmac_dims *dims, int training);
  * measurement code, like the call above.  training: 0 = a call with saved == NULL.  Negative: an
  * error code for bad dims. */
 int bigmac_expert_pairing(const bigmac_dims *dims, int training);
+/* Where a layer forward with these dims picks the experts: 0 = a kernel of its own, timed as
+ * BIGMAC_STAGE_TOPK_GATE; 1 = the kernel that works out the logits (up to 16 experts); 2 = workgroups
+ * beside the descending projection.  With 1 and 2 BIGMAC_STAGE_TOPK_GATE records the load-balance loss
+ * only, or nothing.  For measurement code, like the calls above.  training: 0 = a call with saved ==
+ * NULL.  Negative: an error code for bad dims. */
+int bigmac_topk_folding(const bigmac_dims *dims, int training);
 
 #ifdef __cplusplus
 }

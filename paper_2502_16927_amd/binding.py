@@ -76,6 +76,8 @@ def lib() -> ctypes.CDLL:
         L.bigmac_dispatch_folding.argtypes = [dp, ci]
         L.bigmac_expert_pairing.restype = ci
         L.bigmac_expert_pairing.argtypes = [dp, ci]
+        L.bigmac_topk_folding.restype = ci
+        L.bigmac_topk_folding.argtypes = [dp, ci]
         L.bigmac_stage_name.restype = ctypes.c_char_p
         L.bigmac_stage_name.argtypes = [ci]
         L.bigmac_gather_probe.restype = ci
@@ -88,7 +90,7 @@ def lib() -> ctypes.CDLL:
 
 EXPORTS = ("bigmac_workspace_bytes", "bigmac_status_string", "bigmac_forward_matrix_flops", "bigmac_permute_bytes",
            "bigmac_saved_layout", "bigmac_saved_aux_layout", "bigmac_aux_loss", "bigmac_route", "bigmac_dispatch", "bigmac_dispatch_static", "bigmac_grouped_ffn", "bigmac_combine",
-           "bigmac_layer_forward", "bigmac_layer_backward", "bigmac_set_stage_events", "bigmac_stage_name", "bigmac_dispatch_folding", "bigmac_expert_pairing",
+           "bigmac_layer_forward", "bigmac_layer_backward", "bigmac_set_stage_events", "bigmac_stage_name", "bigmac_dispatch_folding", "bigmac_expert_pairing", "bigmac_topk_folding",
            "bigmac_mfma_probe", "bigmac_gather_probe")
 STAGE_COUNT = 22
 
@@ -230,6 +232,14 @@ def expert_pairing(dims, training: bool) -> bool:
     if rc < 0:
         _check(rc, "bigmac_expert_pairing")
     return rc == 1
+
+
+def topk_folding(dims, training: bool) -> int:
+    """0: a kernel of its own; 1: in the logits' kernel; 2: beside the descending projection."""
+    rc = lib().bigmac_topk_folding(ctypes.byref(dims), int(bool(training)))
+    if rc < 0:
+        _check(rc, "bigmac_topk_folding")
+    return rc
 
 
 def stage_name(stage: int) -> str:

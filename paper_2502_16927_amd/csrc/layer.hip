@@ -601,6 +601,24 @@ bool descend_scatters(const bigmac_dims& D) {
   if (forward_ksplit(D, D.T, D.r, D.d) != 1) return false;
   return (size_t)D.T * D.k * (size_t)D.r * 2 < (1ull << 31) && (size_t)D.T * D.k * 4 < (1ull << 31);
 }
+GemmDesc descend_product(const bigmac_dims& D) {   // x' = x W_down, without its pointers
+  GemmDesc g = base_desc(D);
+  g.ksplit = forward_ksplit(D, D.T, D.r, D.d);
+  g.a_kcontig = 1; g.b_kcontig = 0; g.epilogue = EPI_STORE; g.out_f32 = bf(D) && g.ksplit == 1 ? 0 : 1;
+  g.lda = D.d; g.M = D.T; g.K = D.d;
+  g.ldb = D.r; g.N = D.r; g.ldc = D.r;
+  g.big_tile = g.ksplit == 1 && big_dense(D, D.T, D.r, D.d);
+  g.deep_tile = g.ksplit == 1 && !g.big_tile && deep_dense(D, D.T, D.r, D.d);
+  return g;
+}
+// Where a layer forward picks the experts (the values of bigmac_topk_folding).  With the logits: all experts in one tile of them, and no pairs
+// to count for the sort.  Beside the descending projection: neither needs the other (the loss reads the picks in front of it).
+enum TopkPlace { TOPK_OWN_LAUNCH = 0, TOPK_WITH_LOGITS = 1, TOPK_BESIDE_DESCEND = 2 };
+TopkPlace topk_place(const bigmac_dims& D, bool training) {
+  if (!topk_counts(D.T, D.k, D.N) && router_picks(router_dims(D))) return TOPK_WITH_LOGITS;
+  if (D.order != BIGMAC_ORDER_DCCA || route_low(D) || D.aux_alpha > 0.0f || (training && descend_scatters(D))) return TOPK_OWN_LAUNCH;
+  return gemm_takes_topk(descend_product(D), D.N) ? TOPK_BESIDE_DESCEND : TOPK_OWN_LAUNCH;
+}
 // forward-only call: the expert-up product reads its rows through src_of (see bigmac_layer_forward);
 // the rows behind the index must lie within one 32-bit byte offset
 bool expert_up_gathers(const bigmac_dims& D) {
@@ -619,6 +637,11 @@ int bigmac_expert_pairing(const bigmac_dims* D, int training) {
   const int rc = check_dims(D);
   if (rc) return rc;
   return !training && pair_experts(*D, nullptr, nullptr, nullptr) ? 1 : 0;
+}
+
+int bigmac_topk_folding(const bigmac_dims* D, int training) {
+  const int rc = check_dims(D);
+  return rc ? rc : topk_place(*D, training != 0);
 }
 
 const char* bigmac_stage_name(int stage) {
@@ -753,18 +776,17 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
   const bool low_router = route_low(*D);
   // x' is the workspace's piece, or (router on x': the backward pass reads it again) the saved block's
   void* x_low_buf = (low_router && saved) ? (void*)(sv + S.x_low) : (void*)(wsb + F.x_low);
-  // The top-k stands in a launch of its own unless the router's tiles hold all experts or (beside) the descending projection takes it along.
-  auto route = [&](const void* router_in, bool beside) -> int {
-    const bigmac_dims R = router_dims(*D);
-    const bool picks = !chunk_counts && router_picks(R);   // all experts in one tile of the logits, and no pairs to count
+  const TopkPlace place = topk_place(*D, saved != nullptr);
+  auto route = [&](const void* router_in) -> int {
+    const bool picks = place == TOPK_WITH_LOGITS;
     int rr;
     {
       BIGMAC_STAGE(BIGMAC_STAGE_ROUTER_LOGITS);
-      rr = launch_router_logits(R, router_in, P->w_gate, P->gate_bias, logits, s, picks ? topk_idx : nullptr, picks ? topk_w : nullptr);
+      rr = launch_router_logits(router_dims(*D), router_in, P->w_gate, P->gate_bias, logits, s, picks ? topk_idx : nullptr, picks ? topk_w : nullptr);
     }
-    if (rr) return rr;
+    if (rr || (place != TOPK_OWN_LAUNCH && !aux)) return rr;
     BIGMAC_STAGE(BIGMAC_STAGE_TOPK_GATE);
-    if (!picks && !beside) rr = launch_topk_gate(*D, logits, topk_idx, topk_w, s, chunk_counts);
+    if (place == TOPK_OWN_LAUNCH) rr = launch_topk_gate(*D, logits, topk_idx, topk_w, s, chunk_counts);
     if (!rr && aux)
       rr = launch_aux_loss(*D, logits, topk_idx, (float*)(sv + S.aux + 256), (float*)(sv + S.aux), nullptr, wsb + F.aux, s, chunk_counts);
     return rr;
@@ -780,29 +802,19 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
   // narrow row straight into the places of its pairs in the permuted copy (x' itself is not
   // stored: nothing else reads it).  Not where the product is summed from K slices, nor where the
   // copy is too large for one 32-bit byte offset.
-  const int descend_ksplit = dcca ? forward_ksplit(*D, D->T, D->r, D->d) : 1;
-  const bool descend_big = dcca && descend_ksplit == 1 && big_dense(*D, D->T, D->r, D->d);
-  const bool descend_deep = dcca && descend_ksplit == 1 && !descend_big && deep_dense(*D, D->T, D->r, D->d);
   const bool scatter_descend = saved && descend_scatters(*D);
-  GemmDesc down = base_desc(*D);   // x' = x W_down
+  GemmDesc down = {};
   if (dcca) {
-    down.a_kcontig = 1; down.b_kcontig = 0; down.epilogue = EPI_STORE; down.out_f32 = bf(*D) && descend_ksplit == 1 ? 0 : 1;
-    down.A = x; down.lda = D->d; down.M = D->T; down.K = D->d;
-    down.B = P->w_down; down.ldb = D->r; down.N = D->r;
-    down.C = x_low_buf; down.ldc = D->r;
-    down.ksplit = descend_ksplit;
-    down.big_tile = descend_big;
-    down.deep_tile = descend_deep;
+    down = descend_product(*D);
+    down.A = x; down.B = P->w_down; down.C = x_low_buf;
     if (scatter_descend) {
       down.scatter = slot_of; down.scatter_k = D->k; down.scatter_rows = D->T * D->k;
       down.C = x_perm;
     }
-    // (the loss reads the picks, and 16 experts' are there already)
-    if (!low_router && !scatter_descend && !aux && (chunk_counts || !router_picks(*D)) && gemm_takes_topk(down, D->N))
-      down.topk = topk_job_beside(*D, logits, topk_idx, topk_w, chunk_counts);
+    if (place == TOPK_BESIDE_DESCEND) down.topk = topk_job_beside(*D, logits, topk_idx, topk_w, chunk_counts);
   }
   if (!low_router) {   // Section 3.1's default: the router reads the full-width token
-    rc = route(x, down.topk.logits != nullptr);
+    rc = route(x);
     if (rc) return rc;
   }
   if (scatter_descend) {
@@ -834,7 +846,7 @@ int bigmac_layer_forward(const bigmac_dims* D, const bigmac_params* P, const voi
     x_low = x_low_buf;
   }
   if (low_router) {    // the alternative Section 3.1 names: the router reads x' (as stored)
-    rc = route(x_low, false);
+    rc = route(x_low);
     if (rc) return rc;
   }
   if (!scatter_descend) {

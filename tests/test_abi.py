@@ -129,6 +129,33 @@ def test_expert_pairing_and_its_price():
     assert set(apart) - set(one) == {"expert_down"} == bench.live_stages(False, False) - bench.live_stages(False, False, paired=True)
 
 
+def test_where_the_experts_are_picked_and_its_price():
+    """bigmac_topk_folding: host logic only.  Up to 16 experts with the logits unless the sort wants the pairs counted; 17 to 128 beside the
+    descending projection of a bf16 call whose router reads x, unless that writes the dispatched rows or runs on 256 x 256 tiles; else,
+    and with the load-balance loss, a kernel of its own.  The benchmark prices the picks where they are made."""
+    import bench
+    from paper_2502_16927_amd import synth
+    place = lambda training=False, **dims: B.topk_folding(B.make_dims(**dict(dict(T=500, d=1024, r=256, N=64, k=4, h=512), **dims)), training)
+    assert place() == 2 and place(N=128) == 2 and place(N=17) == 2
+    assert place(training=True) == 2                                  # the projection is summed from K slices: no dispatched rows there
+    assert place(T=8192) == 2 and place(T=8192, training=True) == 0   # ... and here its epilogue writes them
+    assert place(N=129) == 0 and place(N=64, dtype=B.F32) == 0 and place(order=B.ORDER_CDAC) == 0
+    assert place(flags=B.FLAG_ROUTE_LOW) == 0 and place(aux_alpha=0.001) == 0
+    assert place(T=32768, d=1024, r=1024, flags=B.FLAG_TILES_LARGE) == 0
+    for extra in (dict(), dict(dtype=B.F32), dict(order=B.ORDER_CDAC), dict(flags=B.FLAG_ROUTE_LOW), dict(aux_alpha=0.001)):
+        assert place(N=16, **extra) == 1 and place(N=16, training=True, **extra) == 1
+        assert place(N=16, T=1024, **extra) == 1 and place(N=16, T=1025, **extra) != 1    # more than 4096 pairs are counted by the top-k
+    assert place(N=14) == 2                                           # not a multiple of 4: the general logits kernel, picks beside the projection
+    with pytest.raises(B.BigmacError):
+        place(T=0)
+    wl = synth.small(T=500, d=1024, r=256, N=64, k=4, h=512)
+    own, logits, descend = (bench.stage_work(wl, False, False, topk=t) for t in (0, 1, 2))
+    assert logits["router_logits"][2] - own["router_logits"][2] == 8 * 500 * 4
+    assert descend["descend"][2] - own["descend"][2] == own["topk_gate"][2]
+    assert bench.live_stages(False, False) - bench.live_stages(False, False, topk=2) == {"topk_gate"}
+    assert "topk_gate" in bench.live_stages(False, True, topk=1, loss=True)
+
+
 def test_which_shapes_have_a_map_of_256_row_tiles():
     """Host logic only: the saved block holds a second tile map exactly where some row product of the step runs on 256 x 256 tiles.
     Shapes whose products had become slower there (padded columns or experts counted as tiles) are back on the smaller

@@ -259,16 +259,19 @@ def test_dispatch_sort_of_few_pairs(oracle, T, k, N, capacity, popular):
 
 
 # bench.py times exactly the stages that the layer calls record: training in both orders, forward-only calls with the
-# expert products apart (width 64) and in one kernel (width 128), and prices exactly those
-@pytest.mark.parametrize("order,training,r", [(B.ORDER_DCCA, True, 64), (B.ORDER_CDAC, True, 64), (B.ORDER_DCCA, False, 64), (B.ORDER_DCCA, False, 128)])
-def test_stages_that_the_benchmark_times(order, training, r):
+# expert products apart (width 64) and in one kernel (width 128), and prices exactly those; the experts picked with the logits (N 8), beside the
+# descending projection (N 32, forward-only) and in a launch of their own, with the load-balance loss and without
+@pytest.mark.parametrize("order,training,r,N,topk,alpha", [(B.ORDER_DCCA, True, 64, 8, 1, 0.0), (B.ORDER_CDAC, True, 64, 8, 1, 0.0), (B.ORDER_DCCA, False, 64, 8, 1, 0.0),
+                                                           (B.ORDER_DCCA, False, 128, 8, 1, 0.0), (B.ORDER_DCCA, True, 64, 8, 1, 0.01), (B.ORDER_DCCA, True, 64, 32, 0, 0.0),
+                                                           (B.ORDER_CDAC, False, 64, 32, 0, 0.0), (B.ORDER_DCCA, False, 64, 32, 2, 0.0), (B.ORDER_DCCA, True, 64, 32, 0, 0.01)])
+def test_stages_that_the_benchmark_times(order, training, r, N, topk, alpha):
     import bench
-    T, d, N, k, h = 200, 128, 8, 2, 128
+    T, d, k, h = 200, 128, 2, 128
     cdac = order == B.ORDER_CDAC
     win, hid = (d, r) if cdac else (r, h)
     bf = lambda *s: torch.randn(s, device=DEV).to(torch.bfloat16)
     f32 = lambda *s: torch.empty(s, device=DEV)
-    dims = B.make_dims(T, d, r, N, k, h, B.BF16, order)
+    dims = B.make_dims(T, d, r, N, k, h, B.BF16, order, aux_alpha=alpha)
     w = [None if cdac else bf(d, r), None if cdac else bf(r, d), torch.randn((d, N), device=DEV), bf(N, win, hid), bf(N, hid, win)]
     params = B.make_params(w[0], w[1], w[2], None, w[3], w[4])
     x, dy, saved = bf(T, d), bf(T, d), B.alloc_bytes(B.workspace_bytes(dims, B.WS_SAVED)) if training else None
@@ -288,9 +291,10 @@ def test_stages_that_the_benchmark_times(order, training, r):
     recorded = {B.stage_name(s) for s in range(B.STAGE_COUNT) if before.elapsed_time(events.events[2 * s]) > 0}
     folded = {"dispatch"} if B.dispatch_folding(dims, training) else set()
     paired = B.expert_pairing(dims, training)
-    assert paired == (not training and r == 128)
-    assert recorded == bench.live_stages(cdac, training, paired) - folded
-    assert recorded <= set(bench.stage_work(synth.small(T=T, d=d, r=r, N=N, k=k, h=h), cdac, training, False, paired))
+    assert paired == (not training and win == 128)
+    assert B.topk_folding(dims, training) == topk
+    assert recorded == bench.live_stages(cdac, training, paired, topk, alpha > 0) - folded
+    assert recorded <= set(bench.stage_work(synth.small(T=T, d=d, r=r, N=N, k=k, h=h), cdac, training, False, paired, topk))
 
 
 # the map of 256-row tiles: written (its tile count, behind the 128-row one in the plan) where a product of the call runs on such
