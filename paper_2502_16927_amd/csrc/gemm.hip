@@ -566,7 +566,7 @@ int launch_build_tile_map(const int* offsets, int groups, const TileMapJobs& map
 // slice, so it is bound by latency: eight loads in flight per thread, four columns per thread and one wavefront per
 // workgroup to reach more CUs (16 slices of 32 x 1024 took 10.1 us with
 // eight columns and one slice at a time; the forward-only call around it, 32 tokens at d 4096, went 248.9 -> 242.9 us).
-__global__ __launch_bounds__(SLICE_SUM_LANES) void reduce_partials_bf16_kernel(SliceSum job) { slice_sum_block(job, (int)blockIdx.x); }
+__global__ __launch_bounds__(SLICE_SUM_LANES) void reduce_partials_bf16_kernel(SliceSum job) { slice_sum_block<SLICE_SUM_LANES>(job, (int)blockIdx.x); }
 
 int launch_reduce_partials_bf16(const SliceSum& job, hipStream_t s) {
   if (job.n % 8) return BIGMAC_ERR_INVALID_ARG;

@@ -189,13 +189,17 @@ __global__ __launch_bounds__(64) void perm_rank_kernel(const int32_t* __restrict
 // 4096 and 128 experts (replayed from a graph).  The line: with k = 1 and every pair on one expert the atomics of a wavefront go
 // one after the other; at 4096 pairs that costs as much as the launch saves (6.9 us), at 6144 it is 8.6 against 7.3 us
 // (spread pairs, k 8: 5.1 against 7.4).
-template <int THREADS>
+// SUM: the workgroups past the sort's own (`sorting` of them) sum slices.  A kernel of its own: these arguments lie in a third
+// 64-byte line, and a sort that looked at them first waited for one more chain of scalar loads (the stage at T 26327, N 16 / 64 / 128: 11.0 / 10.6 / 16.4 -> 10.6 / 10.3 / 16.1 us).
+template <int THREADS, bool SUM>
 __global__ __launch_bounds__(THREADS) void perm_place_kernel(const int32_t* __restrict__ idx, int Tk, int pairs_per_chunk, int nchunks, int parts, int N, int NP, int nbits,
                                                              int capacity, const int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
                                                              int32_t* __restrict__ slot_of, int32_t* __restrict__ src_of, TileMapJobs maps, SliceSum beside, int sorting) {
-  if ((int)blockIdx.x >= sorting) {
-    slice_sum_block(beside, (int)blockIdx.x - sorting);
-    return;
+  if constexpr (SUM) {
+    if ((int)blockIdx.x >= sorting) {
+      slice_sum_block<THREADS>(beside, (int)blockIdx.x - sorting);
+      return;
+    }
   }
   constexpr int WAVES = THREADS / 64;
   extern __shared__ int cnt[];           // [wavefront][expert]
@@ -655,12 +659,16 @@ int launch_build_permutation(int T, int k, int N, int capacity, const int32_t* t
     const int sorting = sc.count + (maps.map[0] ? 1 : 0);
     const SliceSum sum = beside ? *beside : SliceSum{};
     const dim3 grid(sorting + slice_sum_blocks(sum, sc.threads));
-#define BIGMAC_PLACE(THREADS)                                                                                                        \
-  hipLaunchKernelGGL(perm_place_kernel<THREADS>, grid, dim3(THREADS), THREADS / 64 * N * sizeof(int), s, topk_idx, Tk, pairs, \
+#define BIGMAC_PLACE(THREADS, SUM)                                                                                                   \
+  hipLaunchKernelGGL((perm_place_kernel<THREADS, SUM>), grid, dim3(THREADS), THREADS / 64 * N * sizeof(int), s, topk_idx, Tk, pairs, \
                      sc.count, sc.parts, N, NP, nbits, capacity, counts, expert_offsets, slot_of, src_of, maps, sum, sorting)
-    if (sc.threads == 256) BIGMAC_PLACE(256);
-    else if (sc.threads == 512) BIGMAC_PLACE(512);
-    else BIGMAC_PLACE(1024);
+    if (beside) {
+      if (sc.threads == 256) BIGMAC_PLACE(256, true);
+      else if (sc.threads == 512) BIGMAC_PLACE(512, true);
+      else BIGMAC_PLACE(1024, true);
+    } else if (sc.threads == 256) BIGMAC_PLACE(256, false);
+    else if (sc.threads == 512) BIGMAC_PLACE(512, false);
+    else BIGMAC_PLACE(1024, false);
 #undef BIGMAC_PLACE
     BIGMAC_CHECK_LAUNCH();
     return BIGMAC_OK;

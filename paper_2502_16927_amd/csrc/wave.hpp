@@ -109,8 +109,9 @@ __device__ __forceinline__ void gate_backward_row(float w, float g, int e, const
 }
 
 // A workgroup's piece of a SliceSum: four neighbouring elements per thread, eight slices on their way at a time.
+template <int THREADS>
 __device__ __forceinline__ void slice_sum_block(const SliceSum& job, int block) {
-  const size_t i = ((size_t)block * blockDim.x + threadIdx.x) * 4;
+  const size_t i = ((size_t)block * THREADS + threadIdx.x) * 4;
   if (i >= job.n) return;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int z = 0; z < job.nslices; z += 8) {
