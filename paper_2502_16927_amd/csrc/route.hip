@@ -158,8 +158,8 @@ template <int OFFSET>
 __device__ __forceinline__ void lds_write_b64(unsigned addr, u32x2_t v) {
   asm volatile("ds_write_b64 %0, %1 offset:%2" ::"v"(addr), "v"(v), "n"(OFFSET) : "memory");
 }
-// The same sums for few tokens of few elements (N % 4 == 0; see launch_router_logits), on the vector ALU: TB tokens per wavefront, 16 experts per
-// workgroup of four.  Bound by latency: what counts is the chain from the launch over the first loads to the logits, which is shorter here than
+// The same sums for few tokens of few elements, or few experts (N % 4 == 0; see launch_router_logits), on the vector ALU: TB tokens per wavefront, 16 experts
+// per workgroup of four.  Bound by latency: what counts is the chain from the launch over the first loads to the logits, which is shorter here than
 // in the matrix kernel below (no rounding up to stages of 256 elements, the tree in registers instead of through the LDS).  Tiles of 128 elements of the
 // tokens and of the router's columns travel global -> LDS directly (16 bytes per lane) through a ring of three, two in flight while one is
 // consumed.  Token rows past T and router rows past d lie outside the buffer ranges and arrive as zeros; they are never used anyway.
@@ -231,11 +231,13 @@ __global__ __launch_bounds__(256) void router_logits_few_kernel(const XT* __rest
 #pragma unroll
     for (int c = 0; c < 4; ++c) lds_read_b128<QQ * 64 * 64>(wat + (unsigned)((c ^ ((lane >> 2) & 3)) * 16), ws[c]);
   };
-  auto arrive = [&](auto block) {
+  auto arrive = [&](auto block, auto younger) {      // (reads requested behind this block's)
     constexpr int QQ = decltype(block)::value;
+    lds_wait_for<decltype(younger)::value>();
     auto& xs = xraw[QQ];
     auto& ws = wraw[QQ];
-    lds_wait(xs);
+#pragma unroll
+    for (int i = 0; i < TB; ++i) asm volatile("" : "+v"(xs[i]));
 #pragma unroll
     for (int c = 0; c < 4; ++c) asm volatile("" : "+v"(ws[c]));
   };
@@ -259,13 +261,13 @@ __global__ __launch_bounds__(256) void router_logits_few_kernel(const XT* __rest
     if (tile * QQT + 1 < nq) {
       request(tile, I0);
       request(tile, I1);
-      arrive(I0);
-      arrive(I1);
+      arrive(I0, StaticIndex<TB + 4>{});
       add(I0);
+      arrive(I1, I0);
       add(I1);
     } else {
       request(tile, I0);
-      arrive(I0);
+      arrive(I0, I0);
       add(I0);
     }
   }
@@ -273,8 +275,8 @@ __global__ __launch_bounds__(256) void router_logits_few_kernel(const XT* __rest
   // distances 32 and 16 one swap exchanges the upper half (odd 16-lane rows) of one sum with the lower half (even rows) of another, and
   // every lane then holds what it keeps and what its partner sent; once a lane is down to one sum both lanes of a pair add the
   // other's.  The sum of accumulator v ends on the lanes whose top bits spell v.
-  constexpr int SCATTER_STEPS = TB == 2 ? 5 : 4;
-  static_assert(ACCS == 1 << SCATTER_STEPS, "1 or 2 tokens per wavefront");
+  constexpr int SCATTER_STEPS = TB == 1 ? 4 : TB == 2 ? 5 : 6;
+  static_assert(ACCS == 1 << SCATTER_STEPS, "1, 2 or 4 tokens per wavefront");
   static_for<0, 6>([&](auto n) {
     constexpr int step = decltype(n)::value, off = 32 >> step, half = ACCS >> (step + 1);
     if constexpr (off >= 16) {
@@ -681,7 +683,7 @@ void router_logits_matrix_kernel(RouterJob job) {
   BIGMAC_WAIT_VMCNT(0);                                    // the requests of nothing write the LDS too
 }
 
-// (No TopkJob: with its number of workgroups the arguments, the block's size behind them included, pass the first 64-byte line, 0.3 us more.)
+// (No TopkJob: with its number of workgroups the arguments, the block's size behind them included, pass the first 64-byte line, 0.1 to 0.3 us more.)
 template <int PER, int U>
 __global__ __launch_bounds__(1024) void topk_gate_kernel(const float* __restrict__ logits, int T, int N, int k, int tokens,
                                                          int32_t* __restrict__ topk_idx, float* __restrict__ topk_w, int32_t* __restrict__ counts) {
@@ -990,20 +992,30 @@ int launch_router_logits(const bigmac_dims& D, const void* x, const float* w_gat
     BIGMAC_CHECK_LAUNCH();
     return BIGMAC_OK;
   }
-  // Few tokens of few elements: the kernel on the vector ALU (1 token per wavefront up to three workgroups per CU, else 2).  bigmac_route, us, this kernel /
-  // the tiles below: up to 256 workgroups T 32, N 64: d 64 4.9 / 6.2, d 512 6.1 / 6.9, d 1024 7.5 / 7.8, d 1280 8.2 / 8.4 (fp32 8.3 / 8.4; N 20,
-  // T 500 8.9 / 8.8); up to 512 T 500, N 64: d 256 5.8 / 6.4, d 768 7.3 / 7.6, d 1024 8.0 / 8.2 (fp32 8.4 / 8.3); up to 768 T 700, N 64:
-  // d 384 6.7 / 7.2, d 512 7.1 / 7.3, d 768 8.1 / 7.8, T 500, N 96, d 512 8.3 / 8.2; two tokens T 1400, N 64: d 384 7.6 / 8.4, d 512 8.5 / 8.5; up
-  // to 1024 of them T 2000, N 64: d 128 7.0 / 7.4, d 384 8.6 / 8.5; T 1400, N 96 (1050): d 128 8.7 / 8.5.
+  // Few tokens of few elements: the kernel on the vector ALU, with the fewest tokens per wavefront that need at most three workgroups per CU.
+  // bigmac_route, us, this kernel / the tiles below.  One token, up to 256 workgroups T 32, N 64: d 64 4.9 / 6.2, d 512 6.1 / 6.9, d 1024
+  // 7.5 / 7.8, d 1280 8.2 / 8.4 (fp32 8.3 / 8.4; N 20, T 500 8.9 / 8.8); up to 512 T 500, N 64: d 256 5.8 / 6.4, d 768 7.3 / 7.6, d 1024 8.0 / 8.2
+  // (fp32 8.4 / 8.3); up to 768 T 700, N 64: d 384 6.7 / 7.2, d 512 7.1 / 7.3, d 768 8.1 / 7.8, T 500, N 96, d 512 8.3 / 8.2; two tokens
+  // T 1400, N 64: d 384 7.6 / 8.4, d 512 8.5 / 8.5; up to 1024 of them T 2000, N 64: d 128 7.0 / 7.4, d 384 8.6 / 8.5; T 1400, N 96 (1050): d 128 8.7 / 8.5.
+  // Up to 16 experts (that are not picked in the same launch) a tile has one slice only and the tiles gain later.  N 16, bf16 / fp32: T 3000, d 512 7.4 / 7.5
+  // and 7.5 / 7.8, d 768 8.2 / 8.1; two tokens T 4500, d 1536 12.7 / 13.2 and 13.3 / 13.9, d 2048 14.7 / 15.0 and 15.5 / 16.3, d 3072 19.4 / 18.7; T 6000,
+  // d 2048 15.3 / 15.2; four T 13294, d 256 12.2 / 14.1, d 1024 17.7 / 19.2 and 22.0 / 22.9, d 2048 25.2 / 25.8 and 32.3 / 29.4; T 18000, d 1024 22.9 /
+  // 23.4, d 1536 27.8 / 27.5; T 32768, d 512 26.2 / 28.4 and 29.3 / 29.7, d 1024 33.7 / 34.8 and 41.3 / 39.9.
   const long slices = (D.N + R_NB - 1) / R_NB, one = ((long)D.T + 3) / 4 * slices, two = ((long)D.T + 7) / 8 * slices;
-  if (!topk_idx && D.d <= (one <= 256 ? 1024 : one <= 512 ? 768 : two <= 768 ? 384 : two <= 1024 ? 128 : 0)) {
-    const int tokens = one <= 768 ? 4 : 8;
-    const dim3 grid((unsigned)(((D.T + tokens - 1) / tokens + 7) / 8 * 8 * slices));
+  const int most = one <= 256 ? 1024 : one <= 512 ? 768 : slices == 1 ? (one <= 768 ? 512 : two <= 768 ? 1536 : D.T <= 28672 ? 1024 : 512) : two <= 768 ? 384 : two <= 1024 ? 128 : 0;
+  if (!topk_idx && D.d <= most) {
+    const int tokens = one <= 768 ? 1 : two <= 768 || slices > 1 ? 2 : 4;
+    const dim3 grid((unsigned)((((long)D.T + 4 * tokens - 1) / (4 * tokens) + 7) / 8 * 8 * slices));
 #define BIGMAC_ROUTER_FEW(XT, TB) hipLaunchKernelGGL((router_logits_few_kernel<XT, TB>), grid, dim3(256), 0, s, (const XT*)x, w_gate, bias, logits, D.T, D.d, D.N)
-    if (D.dtype == BIGMAC_BF16 && tokens == 4) BIGMAC_ROUTER_FEW(bf16_t, 1);
-    else if (D.dtype == BIGMAC_BF16) BIGMAC_ROUTER_FEW(bf16_t, 2);
-    else if (tokens == 4) BIGMAC_ROUTER_FEW(float, 1);
-    else BIGMAC_ROUTER_FEW(float, 2);
+    if (D.dtype == BIGMAC_BF16) {
+      if (tokens == 1) BIGMAC_ROUTER_FEW(bf16_t, 1);
+      else if (tokens == 2) BIGMAC_ROUTER_FEW(bf16_t, 2);
+      else BIGMAC_ROUTER_FEW(bf16_t, 4);
+    } else {
+      if (tokens == 1) BIGMAC_ROUTER_FEW(float, 1);
+      else if (tokens == 2) BIGMAC_ROUTER_FEW(float, 2);
+      else BIGMAC_ROUTER_FEW(float, 4);
+    }
 #undef BIGMAC_ROUTER_FEW
     BIGMAC_CHECK_LAUNCH();
     return BIGMAC_OK;

@@ -392,7 +392,49 @@ def test_router_logits_tokens_per_wavefront(oracle, T, d, N, dtype):
     assert (idx[:, 0].cpu().long() == ref.argmax(dim=1)).all()
 
 
-# ... and why they are not on the matrix cores' tiles: bigmac_route for few tokens of few elements takes 1.2 times as long with 64 experts as with 16, whose
+# Up to 16 experts in a layer of more than 4096 pairs, where the logits have a kernel of their own: 1, 2 and 4 tokens per wavefront and the tiles, either side of the
+# lines (T 3072, 6144 and 28672; d 512, 1024 and 1536).  Picks and gates are bigmac_route's, whose logits come from the tiles (bit for bit the
+# oracle's: see below), so a logit that differs shows in its token's gates.
+@pytest.mark.parametrize("dtype", [B.BF16, B.F32])
+@pytest.mark.parametrize("T,d,N", [(513, 1024, 16), (1030, 832, 8), (3072, 512, 16), (3072, 576, 12), (3073, 1536, 16), (6144, 64, 4), (6145, 1024, 16), (9001, 192, 8), (6145, 1088, 16),
+                                   (28673, 512, 16), (28673, 576, 16)])
+def test_router_of_few_experts_in_the_layer(T, d, N, dtype):
+    r, k, h = 64, 16 if T < 600 else min(N, 4), 64
+    g = torch.Generator(device=DEV).manual_seed(T + d)
+    rand = lambda *s: (torch.randn(s, generator=g, device=DEV) * s[-2] ** -0.5).to(torch.bfloat16 if dtype == B.BF16 else torch.float32)
+    dims = B.make_dims(T, d, r, N, k, h, dtype)
+    x, w_gate, bias = rand(d, T).t().contiguous(), torch.randn((d, N), generator=g, device=DEV), torch.randn(N, generator=g, device=DEV)
+    w = [rand(*n) for n in ((d, r), (r, d), (N, r, h), (N, h, r))]
+    assert B.topk_folding(dims, training=True) != 1
+    idx, gates = torch.empty((T, k), dtype=torch.int32, device=DEV), torch.empty((T, k), device=DEV)
+    B.bigmac_route(dims, x, w_gate, bias, idx, gates, torch.empty((T, N), device=DEV))
+    saved, ws = (B.alloc_bytes(B.workspace_bytes(dims, n)) for n in (B.WS_SAVED, B.WS_LAYER_TRAIN))
+    ws.fill_(255)
+    B.bigmac_layer_forward(dims, B.make_params(w[0], w[1], w_gate, bias, w[2], w[3]), x, torch.empty((T, d), device=DEV), saved, ws)
+    at = B.saved_layout(dims)
+    assert torch.equal(saved[at["topk_idx"]:at["topk_idx"] + 4 * T * k].view(torch.int32).view(T, k), idx)
+    assert torch.equal(saved[at["topk_w"]:at["topk_w"] + 4 * T * k].view(torch.float32).view(T, k), gates)
+
+
+# ... whose logits take 0.81 times as long as 32 experts' (on the tiles of the matrix cores 0.92 to 0.96 times: a tile then has one slice of experts only)
+def test_router_of_few_experts_is_not_on_the_slower_kernel():
+    T, d, r, k, h = 13294, 512, 128, 4, 64
+    g = torch.Generator(device=DEV).manual_seed(7)
+    bf = lambda *s: torch.empty(s, device=DEV, dtype=torch.bfloat16).normal_(0.0, 0.05, generator=g)
+    x, y = bf(T, d), torch.empty((T, d), device=DEV)
+
+    def call(N):
+        dims = B.make_dims(T, d, r, N, k, h, B.BF16)
+        w = bf(d, r), bf(r, d), torch.randn((d, N), generator=g, device=DEV), None, bf(N, r, h), bf(N, h, r)
+        ws, saved = (B.alloc_bytes(B.workspace_bytes(dims, n)) for n in (B.WS_LAYER_TRAIN, B.WS_SAVED))
+        return lambda: B.bigmac_layer_forward(dims, B.make_params(*w), x, y, saved, ws)
+
+    few_us, many_us = median_stage_us([call(16), call(32)], {"router_logits"}, turns=24)
+    print(f"router logits: {few_us:.1f} us with 16 experts, {many_us:.1f} us with 32", flush=True)
+    assert few_us < 0.9 * many_us
+
+
+# ... and why few tokens are not on the matrix cores' tiles: bigmac_route for few tokens of few elements takes 1.2 times as long with 64 experts as with 16, whose
 # picks need no second launch (on the tiles 1.5 times; medians of runs of 400 calls)
 def test_router_of_few_tokens_is_not_on_the_slower_kernel():
     T, d, k = 32, 64, 4
@@ -557,9 +599,9 @@ def test_top_k_beside_the_descending_projection_pays():
 
     def call(flags):
         dims = B.make_dims(T, d, r, N, k, h, B.BF16, flags=flags)
-        params = B.make_params(w[0], w[1], torch.randn((r if flags else d, N), generator=g, device=DEV), None, w[2], w[3])
+        w_gate = torch.randn((r if flags else d, N), generator=g, device=DEV)
         ws = B.alloc_bytes(B.workspace_bytes(dims, B.WS_LAYER_FORWARD))
-        return lambda: B.bigmac_layer_forward(dims, params, x, y, None, ws)
+        return lambda: B.bigmac_layer_forward(dims, B.make_params(w[0], w[1], w_gate, None, w[2], w[3]), x, y, None, ws)
 
     with_picks, alone = median_stage_us([call(0), call(B.FLAG_ROUTE_LOW)], {"descend"}, turns=24)
     print(f"descend: with the picks {with_picks:.1f} us, alone {alone:.1f} us", flush=True)
@@ -576,9 +618,9 @@ def test_slice_sums_beside_a_large_sort():
 
     def call(flags):
         dims = B.make_dims(T, d, r, N, k, h, B.BF16, flags=flags)
-        params = B.make_params(w[0], w[1], torch.randn((r if flags else d, N), generator=g, device=DEV), None, w[2], w[3])
+        w_gate = torch.randn((r if flags else d, N), generator=g, device=DEV)
         ws = B.alloc_bytes(B.workspace_bytes(dims, B.WS_LAYER_FORWARD))
-        return lambda: B.bigmac_layer_forward(dims, params, x, y, None, ws)
+        return lambda: B.bigmac_layer_forward(dims, B.make_params(w[0], w[1], w_gate, None, w[2], w[3]), x, y, None, ws)
 
     beside, apart = median_stage_us([call(0), call(B.FLAG_ROUTE_LOW)], {"descend", "permutation"})
     print(f"descend + permutation: sum beside the sort {beside:.1f} us, in a launch of its own {apart:.1f} us", flush=True)
