@@ -612,12 +612,19 @@ GemmDesc descend_product(const bigmac_dims& D) {   // x' = x W_down, without its
   return g;
 }
 // Where a layer forward picks the experts (the values of bigmac_topk_folding).  With the logits: all experts in one tile of them, and no pairs
-// to count for the sort.  Beside the descending projection: neither needs the other (the loss reads the picks in front of it).
+// to count for the sort.  Beside the descending projection: neither needs the other (the loss reads the picks in front of it).  A workgroup there is four
+// wavefronts, which take eight tokens in 1.3 us; where the sort wants large parts counted that chain outlasts the projection, and a launch
+// of its own has up to 16 wavefronts for a part.  Forward-only calls (h 64, k 1 to 8), own launch -> beside: parts of up to 32 tokens 0 to 6.8 us less; 64
+// tokens (T 9000 / 13000) d 512 4 to 7 us more, d 1024 2.7 less to 1.8 more / 5 to 12 more, d 2048 6 to 11 / 4 to 8 less, d 4096 7 to 13 / 7 to
+// 11 less; 128 tokens (T 20000 / 32000) d 512 9 to 17 / 16 to 29 more, d 1024 4 to 9 / 4 to 13 more, d 2048 and 4096 21 more to 2 less.
 enum TopkPlace { TOPK_OWN_LAUNCH = 0, TOPK_WITH_LOGITS = 1, TOPK_BESIDE_DESCEND = 2 };
 TopkPlace topk_place(const bigmac_dims& D, bool training) {
-  if (!topk_counts(D.T, D.k, D.N) && router_picks(router_dims(D))) return TOPK_WITH_LOGITS;
+  const bool counted = topk_counts(D.T, D.k, D.N);
+  if (!counted && router_picks(router_dims(D))) return TOPK_WITH_LOGITS;
   if (D.order != BIGMAC_ORDER_DCCA || route_low(D) || D.aux_alpha > 0.0f || (training && descend_scatters(D))) return TOPK_OWN_LAUNCH;
-  return gemm_takes_topk(descend_product(D), D.N) ? TOPK_BESIDE_DESCEND : TOPK_OWN_LAUNCH;
+  const GemmDesc g = descend_product(D);
+  const int part = counted ? topk_grid(D.T, D.k, D.N, true).tokens : 0;
+  return gemm_takes_topk(g, D.N) && (part <= 32 || (part <= 64 && g.K / g.ksplit >= 2048)) ? TOPK_BESIDE_DESCEND : TOPK_OWN_LAUNCH;
 }
 // forward-only call: the expert-up product reads its rows through src_of (see bigmac_layer_forward);
 // the rows behind the index must lie within one 32-bit byte offset

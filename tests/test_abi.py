@@ -131,14 +131,16 @@ def test_expert_pairing_and_its_price():
 
 def test_where_the_experts_are_picked_and_its_price():
     """bigmac_topk_folding: host logic only.  Up to 16 experts with the logits unless the sort wants the pairs counted; 17 to 128 beside the
-    descending projection of a bf16 call whose router reads x, unless that writes the dispatched rows or runs on 256 x 256 tiles; else,
-    and with the load-balance loss, a kernel of its own.  The benchmark prices the picks where they are made."""
+    descending projection of a bf16 call whose router reads x, unless that writes the dispatched rows, runs on 256 x 256 tiles or is over before
+    the large parts that the sort wants counted (32 tokens, 64 with a K of 2048); else, and with the load-balance loss, a kernel of its own.  The benchmark prices the picks where they are made."""
     import bench
     from paper_2502_16927_amd import synth
     place = lambda training=False, **dims: B.topk_folding(B.make_dims(**dict(dict(T=500, d=1024, r=256, N=64, k=4, h=512), **dims)), training)
     assert place() == 2 and place(N=128) == 2 and place(N=17) == 2
     assert place(training=True) == 2                                  # the projection is summed from K slices: no dispatched rows there
     assert place(T=8192) == 2 and place(T=8192, training=True) == 0   # ... and here its epilogue writes them
+    assert place(T=9000) == 0 and place(T=9000, d=2048, r=512) == 2 and place(T=20000, d=2048, r=512) == 0
+    assert place(T=32000, d=512, r=128, N=128, k=8) == 0 and place(T=6000, d=512, r=128, N=128, k=8) == 2
     assert place(N=129) == 0 and place(N=64, dtype=B.F32) == 0 and place(order=B.ORDER_CDAC) == 0
     assert place(flags=B.FLAG_ROUTE_LOW) == 0 and place(aux_alpha=0.001) == 0
     assert place(T=32768, d=1024, r=1024, flags=B.FLAG_TILES_LARGE) == 0

@@ -608,6 +608,25 @@ def test_top_k_beside_the_descending_projection_pays():
     assert with_picks - alone < 3.2
 
 
+# ... and with counting, in the large parts of a large batch: no slower than a launch of its own, 44 us with the projection (72 beside it, where
+# four wavefronts took 128 tokens; 1.15 allows for the spread of the medians and for an empty interval)
+def test_large_parts_are_not_picked_beside_the_projection():
+    T, d, r, N, k, h = 32000, 512, 128, 128, 8, 64
+    g = torch.Generator(device=DEV).manual_seed(7)
+    bf = lambda *s: torch.empty(s, device=DEV, dtype=torch.bfloat16).normal_(0.0, 0.05, generator=g)
+    x, y, w = bf(T, d), torch.empty((T, d), device=DEV), [bf(*s) for s in ((d, r), (r, d), (N, r, h), (N, h, r))]
+
+    def call(flags):
+        dims = B.make_dims(T, d, r, N, k, h, B.BF16, flags=flags)
+        w_gate = torch.randn((r if flags else d, N), generator=g, device=DEV)
+        ws = B.alloc_bytes(B.workspace_bytes(dims, B.WS_LAYER_FORWARD))
+        return lambda: B.bigmac_layer_forward(dims, B.make_params(w[0], w[1], w_gate, None, w[2], w[3]), x, y, None, ws)
+
+    ours, apart = median_stage_us([call(0), call(B.FLAG_ROUTE_LOW)], {"descend", "topk_gate"}, turns=24)
+    print(f"descend + top-k: {ours:.1f} us, with a router on x' {apart:.1f} us", flush=True)
+    assert ours < 1.15 * apart
+
+
 # The slices' sum beside the sort must not be slower than the launch of its own that a router on x' leaves it: 256 experts, whose sort
 # has workgroups of 1024 threads (with one of 16 wavefronts summing 1.1 times slower; 1.04 allows for the spread of the medians).
 def test_slice_sums_beside_a_large_sort():
